@@ -2,180 +2,200 @@
 // (App. "Salient Weight Protection": per-channel activation scale from a calibration
 // forward pass).  s_absmean[c] = mean_t |x_tc|, s_rms[c] = sqrt(mean_t x_tc^2).
 //
-// Pure streaming reduction over the token axis, bound by HBM.  A workgroup owns a strip
-// of 512 channels and a slab of 32 tokens: each lane reads 8 consecutive channels of a
-// token with 128-bit loads (64 lanes = 1 KB contiguous for bf16), the four wavefronts
-// take every fourth token.  fp64 sums, combined in a fixed order: wavefronts through
-// LDS, slabs by the finalize kernel.
+// Pure streaming reduction over the token axis, bound by HBM.  A workgroup owns a strip of
+// 8 L channels (L lanes side by side, 8 channels = 16 or 32 bytes each) and a slab of tokens;
+// its 256 / L lane groups take every (256 / L)-th token, eight loads in flight per lane.
+// fp64 sums, combined in a fixed order: lane groups through LDS, slabs by the finalize kernel.
 //
-// Few tokens (the calibration sets of the paper's configs: 512 per input) are a few MB, and
-// two dependent launches cost more than the data: then ONE kernel does it all.  A workgroup
-// owns a strip of 64 channels (8 lanes x 8) over all tokens, its 32 lane groups take every
-// 32nd token, and the 32 partial sums are added in order through LDS.
+// How a matrix is cut (calib_cut):
+//   few tokens (the calibration sets of the benchmark configurations: 512): ONE slab and narrow
+//     strips (L = 8, 64 channels), so that the workgroup writes the result itself: two dependent
+//     launches cost more than a few MB do.  Up to 1024 tokens (1024 x 4096: 6.8 us against 9.9 in
+//     slabs), up to 2048 where 4096 channels give at least 64 strips (2048 x 4096: 10.3 against
+//     12.2 us; 2048 x 1024: 9.6 against 8.5, so not there).
+//   more: L = 64 (512 channels, a wavefront reads 1 KB of a token; less for narrow matrices) and
+//     as many slabs as give the chip about 1024 workgroups, four for each of its 256 CUs (what
+//     the 33 KB of LDS allow; 2048 measured 14 % slower): more slabs only mean more partial sums
+//     to write and read back.  16384 x 4096 bf16, both statistics: 33 us = 4.0 TB/s (162 us with
+//     32-token slabs, whose 33 MB of partial sums one thread per channel then added in a chain);
+//     a large copy moves 5.1 TB/s.
+// All matrices of a batch share the launch (and the finalize launch, where any needs it).
 #include "windq_common.hpp"
 #include "windq_ws.hpp"
 
 namespace windq {
 
 constexpr int CALIB_THREADS = 256;
-constexpr int CALIB_WAVES = CALIB_THREADS / 64;
-constexpr int CALIB_COLS_PER_LANE = 8;
-constexpr int CALIB_STRIP = 64 * CALIB_COLS_PER_LANE;
-
-template <int DT>
-__global__ __launch_bounds__(CALIB_THREADS) void calib_partial_kernel(const void* __restrict__ X, int64_t rows,
-                                                                      int64_t cols, int64_t ld,
-                                                                      double* __restrict__ partial) {
-    __shared__ double red[CALIB_WAVES][2 * CALIB_COLS_PER_LANE][64];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int64_t c0 = (int64_t)blockIdx.x * CALIB_STRIP + (int64_t)lane * CALIB_COLS_PER_LANE;
-    const int64_t slab = blockIdx.y;
-    const int64_t r_begin = slab * CALIB_SLAB_ROWS;
-    const int64_t r_end = r_begin + CALIB_SLAB_ROWS < rows ? r_begin + CALIB_SLAB_ROWS : rows;
-    double sa[CALIB_COLS_PER_LANE], sq[CALIB_COLS_PER_LANE];
-#pragma unroll
-    for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) sa[j] = sq[j] = 0.0;
-    if (c0 < cols) {
-        for (int64_t r = r_begin + wave; r < r_end; r += CALIB_WAVES) {
-            float v[CALIB_COLS_PER_LANE];
-            const int64_t off = r * ld + c0;
-            if (DT == WINDQ_BF16) {
-                const uint4 raw = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(X) + off);
-                v[0] = bf16_bits_to_f32(raw.x & 0xffffu); v[1] = __uint_as_float(raw.x & 0xffff0000u);
-                v[2] = bf16_bits_to_f32(raw.y & 0xffffu); v[3] = __uint_as_float(raw.y & 0xffff0000u);
-                v[4] = bf16_bits_to_f32(raw.z & 0xffffu); v[5] = __uint_as_float(raw.z & 0xffff0000u);
-                v[6] = bf16_bits_to_f32(raw.w & 0xffffu); v[7] = __uint_as_float(raw.w & 0xffff0000u);
-            } else {
-                const float4* src = reinterpret_cast<const float4*>(static_cast<const float*>(X) + off);
-                const float4 a = src[0], b = src[1];
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-                v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-            }
-#pragma unroll
-            for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) {
-                const double x = (double)v[j];
-                sa[j] += fabs(x);
-                sq[j] = fma(x, x, sq[j]);
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) {
-        red[wave][j][lane] = sa[j];
-        red[wave][CALIB_COLS_PER_LANE + j][lane] = sq[j];
-    }
-    __syncthreads();
-    if (wave == 0 && c0 < cols) {
-#pragma unroll
-        for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) {
-            double a = 0.0, q = 0.0;
-#pragma unroll
-            for (int w = 0; w < CALIB_WAVES; ++w) {
-                a += red[w][j][lane];
-                q += red[w][CALIB_COLS_PER_LANE + j][lane];
-            }
-            double* dst = partial + ((size_t)slab * (size_t)cols + (size_t)(c0 + j)) * 2;
-            dst[0] = a;
-            dst[1] = q;
-        }
-    }
-}
-
-constexpr int CALIB_DIRECT_LANES = 8;                                   // lanes across a strip
-constexpr int CALIB_DIRECT_STRIP = CALIB_DIRECT_LANES * CALIB_COLS_PER_LANE;
-constexpr int CALIB_DIRECT_GROUPS = CALIB_THREADS / CALIB_DIRECT_LANES;   // token groups
-constexpr int64_t CALIB_DIRECT_MAX_ROWS = 4096;
+constexpr int CALIB_CPL = 8;                        // channels per lane
+constexpr int CALIB_INFLIGHT = 8;                   // loads in flight per lane
+constexpr int64_t CALIB_DIRECT_ROWS = 1024, CALIB_DIRECT_ROWS_WIDE = 2048, CALIB_DIRECT_WIDE_COLS = 4096;
+constexpr int64_t CALIB_TARGET_WGS = 1024;
+constexpr int64_t CALIB_SLAB_LIMIT_ROWS = 4096;     // above this many tokens the number of 32-token slabs is limited
 
 // One activation matrix of a launch; a launch covers up to WINDQ_MAX_BATCH of them, their
-// column strips numbered one matrix after the other.
+// workgroups (and the finalize kernel's) numbered one matrix after the other.
 struct CalibMat {
     const void* X;
     int64_t rows, cols, ld;
     float* s_absmean;
     float* s_rms;
+    double* partial;        // [slabs][2][cols]: sum |x|, sum x^2
+    int64_t slab_rows;
+    int32_t slabs, strips;
+    int32_t lane_shift;     // L = 1 << lane_shift
+    int32_t reserved;
 };
 struct CalibBatch {
     int32_t n;
-    int64_t strip_start[WINDQ_MAX_BATCH + 1];
+    int64_t wg_start[WINDQ_MAX_BATCH + 1];
     CalibMat m[WINDQ_MAX_BATCH];
 };
 
+// Eight consecutive activations as they lie in memory.
 template <int DT>
-__global__ __launch_bounds__(CALIB_THREADS) void calib_direct_kernel(const CalibBatch B) {
-    __shared__ double red[CALIB_DIRECT_GROUPS][2][CALIB_DIRECT_STRIP + 1];
-    const int mi = batch_index(B.strip_start, B.n, blockIdx.x);
-    const void* __restrict__ X = B.m[mi].X;
-    const int64_t rows = B.m[mi].rows, cols = B.m[mi].cols, ld = B.m[mi].ld;
-    float* __restrict__ s_absmean = B.m[mi].s_absmean;
-    float* __restrict__ s_rms = B.m[mi].s_rms;
-    const int64_t strip = (int64_t)blockIdx.x - B.strip_start[mi];
-    const int cl = threadIdx.x % CALIB_DIRECT_LANES;
-    const int tg = threadIdx.x / CALIB_DIRECT_LANES;
-    const int64_t c0 = strip * CALIB_DIRECT_STRIP + (int64_t)cl * CALIB_COLS_PER_LANE;
-    double sa[CALIB_COLS_PER_LANE], sq[CALIB_COLS_PER_LANE];
+struct Raw8 {
+    uint4 q[DT == WINDQ_BF16 ? 1 : 2];
+    __device__ __forceinline__ void load(const char* __restrict__ p) {
 #pragma unroll
-    for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) sa[j] = sq[j] = 0.0;
+        for (int h = 0; h < (DT == WINDQ_BF16 ? 1 : 2); ++h) q[h] = reinterpret_cast<const uint4*>(p)[h];
+    }
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int h = 0; h < (DT == WINDQ_BF16 ? 1 : 2); ++h) q[h] = make_uint4(0u, 0u, 0u, 0u);
+    }
+};
+
+template <int DT, bool RMS>
+__device__ __forceinline__ void calib_add(const Raw8<DT>& raw, double (&sa)[CALIB_CPL], double (&sq)[CALIB_CPL]) {
+    float v[CALIB_CPL];
+    const uint4 a = raw.q[0];
+    if (DT == WINDQ_BF16) {
+        v[0] = bf16_bits_to_f32(a.x & 0xffffu); v[1] = __uint_as_float(a.x & 0xffff0000u);
+        v[2] = bf16_bits_to_f32(a.y & 0xffffu); v[3] = __uint_as_float(a.y & 0xffff0000u);
+        v[4] = bf16_bits_to_f32(a.z & 0xffffu); v[5] = __uint_as_float(a.z & 0xffff0000u);
+        v[6] = bf16_bits_to_f32(a.w & 0xffffu); v[7] = __uint_as_float(a.w & 0xffff0000u);
+    } else {
+        const uint4 b = raw.q[DT == WINDQ_BF16 ? 0 : 1];
+        v[0] = __uint_as_float(a.x); v[1] = __uint_as_float(a.y); v[2] = __uint_as_float(a.z); v[3] = __uint_as_float(a.w);
+        v[4] = __uint_as_float(b.x); v[5] = __uint_as_float(b.y); v[6] = __uint_as_float(b.z); v[7] = __uint_as_float(b.w);
+    }
+#pragma unroll
+    for (int j = 0; j < CALIB_CPL; ++j) {
+        const double x = (double)v[j];
+        sa[j] += fabs(x);
+        if (RMS) sq[j] = fma(x, x, sq[j]);
+    }
+}
+
+template <int DT, bool RMS>
+__global__ __launch_bounds__(CALIB_THREADS) void calib_sum_kernel(const CalibBatch B) {
+    constexpr int NV = RMS ? 2 * CALIB_CPL : CALIB_CPL;
+    // [value][thread]; the odd row length spreads the eight values of a lane over the banks
+    __shared__ double red[NV][CALIB_THREADS + 1];
+    const int mi = batch_index(B.wg_start, B.n, blockIdx.x);
+    const CalibMat& M = B.m[mi];
+    const uint32_t at = (uint32_t)((int64_t)blockIdx.x - B.wg_start[mi]);
+    const uint32_t slab = at / (uint32_t)M.strips;
+    const uint32_t strip = at - slab * (uint32_t)M.strips;
+    const int L = 1 << M.lane_shift;
+    const int groups = CALIB_THREADS >> M.lane_shift;
+    const int cl = threadIdx.x & (L - 1);
+    const int tg = threadIdx.x >> M.lane_shift;
+    const int64_t cols = M.cols;
+    const int64_t strip0 = (int64_t)strip * (int64_t)(L * CALIB_CPL);
+    const int64_t c0 = strip0 + cl * CALIB_CPL;
+    const int64_t r_end = (int64_t)(slab + 1) * M.slab_rows < M.rows ? (int64_t)(slab + 1) * M.slab_rows : M.rows;
+    double sa[CALIB_CPL], sq[CALIB_CPL];
+#pragma unroll
+    for (int j = 0; j < CALIB_CPL; ++j) sa[j] = sq[j] = 0.0;
     if (c0 < cols) {
-#pragma unroll 4
-        for (int64_t r = tg; r < rows; r += CALIB_DIRECT_GROUPS) {
-            float v[CALIB_COLS_PER_LANE];
-            const int64_t off = r * ld + c0;
-            if (DT == WINDQ_BF16) {
-                const uint4 raw = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(X) + off);
-                v[0] = bf16_bits_to_f32(raw.x & 0xffffu); v[1] = __uint_as_float(raw.x & 0xffff0000u);
-                v[2] = bf16_bits_to_f32(raw.y & 0xffffu); v[3] = __uint_as_float(raw.y & 0xffff0000u);
-                v[4] = bf16_bits_to_f32(raw.z & 0xffffu); v[5] = __uint_as_float(raw.z & 0xffff0000u);
-                v[6] = bf16_bits_to_f32(raw.w & 0xffffu); v[7] = __uint_as_float(raw.w & 0xffff0000u);
-            } else {
-                const float4* src = reinterpret_cast<const float4*>(static_cast<const float*>(X) + off);
-                const float4 a = src[0], b = src[1];
-                v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-                v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        constexpr int EB = Elem<DT>::bytes;
+        const char* __restrict__ src = static_cast<const char*>(M.X) + c0 * EB;
+        const int64_t step = M.ld * EB;
+        int64_t r = (int64_t)slab * M.slab_rows + tg;
+        // whole batches of loads without a bounds check between them; then the rest, four at a time: a token past
+        // the end is read from the slab's last one and added as zeros
+        for (; r + (int64_t)groups * (CALIB_INFLIGHT - 1) < r_end; r += (int64_t)groups * CALIB_INFLIGHT) {
+            Raw8<DT> raw[CALIB_INFLIGHT];
+#pragma unroll
+            for (int k = 0; k < CALIB_INFLIGHT; ++k) raw[k].load(src + (r + (int64_t)k * groups) * step);
+#pragma unroll
+            for (int k = 0; k < CALIB_INFLIGHT; ++k) calib_add<DT, RMS>(raw[k], sa, sq);
+        }
+        for (; r < r_end; r += (int64_t)groups * 4) {
+            Raw8<DT> raw[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int64_t rr = r + (int64_t)k * groups;
+                raw[k].load(src + (rr < r_end ? rr : r_end - 1) * step);
             }
 #pragma unroll
-            for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) {
-                const double x = (double)v[j];
-                sa[j] += fabs(x);
-                sq[j] = fma(x, x, sq[j]);
+            for (int k = 0; k < 4; ++k) {
+                if (r + (int64_t)k * groups >= r_end) raw[k].clear();
+                calib_add<DT, RMS>(raw[k], sa, sq);
             }
         }
     }
 #pragma unroll
-    for (int j = 0; j < CALIB_COLS_PER_LANE; ++j) {
-        red[tg][0][cl * CALIB_COLS_PER_LANE + j] = sa[j];
-        red[tg][1][cl * CALIB_COLS_PER_LANE + j] = sq[j];
+    for (int j = 0; j < CALIB_CPL; ++j) {
+        red[j][threadIdx.x] = sa[j];
+        if (RMS) red[CALIB_CPL + j][threadIdx.x] = sq[j];
     }
     __syncthreads();
-    if (threadIdx.x < CALIB_DIRECT_STRIP) {
-        const int64_t c = strip * CALIB_DIRECT_STRIP + threadIdx.x;
-        if (c < cols) {
-            double a = 0.0, q = 0.0;
-#pragma unroll
-            for (int g = 0; g < CALIB_DIRECT_GROUPS; ++g) {
-                a += red[g][0][threadIdx.x];
-                q += red[g][1][threadIdx.x];
-            }
-            s_absmean[c] = (float)(a / (double)rows);
-            if (s_rms != nullptr) s_rms[c] = (float)sqrt(q / (double)rows);
+    // channel by channel, lane groups in order
+    for (int q = threadIdx.x; q < L * NV; q += CALIB_THREADS) {
+        const int which = q >> (M.lane_shift + 3);                            // 0: sum |x|, 1: sum x^2
+        const int col = q & (L * CALIB_CPL - 1);
+        const double* __restrict__ row = red[which * CALIB_CPL + (col & (CALIB_CPL - 1))] + (col >> 3);
+        double t = 0.0;
+        for (int g = 0; g < groups; g += 4) {                                 // four reads in flight, added in order
+            const double t0 = row[g << M.lane_shift], t1 = row[(g + 1) << M.lane_shift];
+            const double t2 = row[(g + 2) << M.lane_shift], t3 = row[(g + 3) << M.lane_shift];
+            t = (((t + t0) + t1) + t2) + t3;
+        }
+        const int64_t c = strip0 + col;
+        if (c >= cols) continue;
+        if (M.slabs > 1) {
+            M.partial[((size_t)slab * 2 + (size_t)which) * (size_t)cols + (size_t)c] = t;
+        } else if (which == 0) {
+            M.s_absmean[c] = (float)(t / (double)M.rows);
+        } else if (M.s_rms != nullptr) {
+            M.s_rms[c] = (float)sqrt(t / (double)M.rows);
         }
     }
 }
 
-__global__ __launch_bounds__(256) void calib_finalize_kernel(const double* __restrict__ partial, int64_t n_slabs,
-                                                              int64_t rows, int64_t cols,
-                                                              float* __restrict__ s_absmean,
-                                                              float* __restrict__ s_rms) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
+// The slabs of 16 channels by a workgroup: 16 phases, phase p adds slabs p, p + 16, ..., the phases in order.
+constexpr int CALIB_FIN_COLS = 16;
+template <bool RMS>
+__global__ __launch_bounds__(256) void calib_finalize_kernel(const CalibBatch B) {
+    constexpr int PH = 256 / CALIB_FIN_COLS;
+    __shared__ double red[2][PH][CALIB_FIN_COLS + 1];
+    const int mi = batch_index(B.wg_start, B.n, blockIdx.x);
+    const CalibMat& M = B.m[mi];
+    const int cl = threadIdx.x & (CALIB_FIN_COLS - 1);
+    const int ph = threadIdx.x / CALIB_FIN_COLS;
+    const int64_t c = ((int64_t)blockIdx.x - B.wg_start[mi]) * CALIB_FIN_COLS + cl;
     double a = 0.0, q = 0.0;
-    for (int64_t sl = 0; sl < n_slabs; ++sl) {
-        const double* src = partial + ((size_t)sl * (size_t)cols + (size_t)c) * 2;
-        a += src[0];
-        q += src[1];
+    if (c < M.cols) {
+        const double* __restrict__ src = M.partial + c;
+#pragma unroll 4
+        for (int32_t s = ph; s < M.slabs; s += PH) {
+            a += src[(size_t)s * 2 * (size_t)M.cols];
+            if (RMS) q += src[((size_t)s * 2 + 1) * (size_t)M.cols];
+        }
     }
-    s_absmean[c] = (float)(a / (double)rows);
-    if (s_rms != nullptr) s_rms[c] = (float)sqrt(q / (double)rows);
+    red[0][ph][cl] = a;
+    red[1][ph][cl] = q;
+    __syncthreads();
+    if (threadIdx.x >= 2 * CALIB_FIN_COLS) return;
+    const int which = threadIdx.x / CALIB_FIN_COLS;
+    if (c >= M.cols) return;
+    double t = 0.0;
+#pragma unroll
+    for (int p = 0; p < PH; ++p) t += red[which][p][cl];
+    if (which == 0) M.s_absmean[c] = (float)(t / (double)M.rows);
+    else if (RMS && M.s_rms != nullptr) M.s_rms[c] = (float)sqrt(t / (double)M.rows);
 }
 
 }  // namespace windq
@@ -188,69 +208,78 @@ static int calib_check(const windq_mat* X, const float* s_absmean, const void* w
     if (s_absmean == nullptr) return WINDQ_EINVAL;
     const size_t need = calib_ws_bytes(X->rows, X->cols);
     if (ws == nullptr || ws_bytes < need || !aligned(ws, 256)) return WINDQ_EWORKSPACE;
-    if (X->rows > CALIB_DIRECT_MAX_ROWS && calib_slabs(X->rows) > 65535) return WINDQ_ESHAPE;
+    if (X->rows > CALIB_SLAB_LIMIT_ROWS && calib_slabs(X->rows) > 65535) return WINDQ_ESHAPE;
     return WINDQ_OK;
 }
 
-// The matrices of a launch that the direct kernel takes (few tokens), all of one element type.
-static int calib_direct_launch(const windq_calib_item* items, int32_t n, hipStream_t hs) {
-    CalibBatch B;
-    B.n = n;
-    int64_t strips = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        const windq_mat* X = items[i].X;
-        B.m[i] = {X->data, X->rows, X->cols, X->ld, items[i].s_absmean, items[i].s_rms};
-        B.strip_start[i] = strips;
-        strips += (X->cols + CALIB_DIRECT_STRIP - 1) / CALIB_DIRECT_STRIP;
+// How a matrix is cut into strips and slabs (the rule and its reasons: top of the file).  A slab has
+// at least 32 tokens: the workspace holds one pair of sums per channel and 32 tokens.
+static void calib_cut(CalibMat* M) {
+    const bool direct = M->rows <= CALIB_DIRECT_ROWS || (M->rows <= CALIB_DIRECT_ROWS_WIDE && M->cols >= CALIB_DIRECT_WIDE_COLS);
+    M->lane_shift = direct ? 3 : 6;
+    while (M->lane_shift > 3 && (int64_t)(CALIB_CPL << (M->lane_shift - 1)) >= M->cols) --M->lane_shift;
+    const int64_t strip = (int64_t)CALIB_CPL << M->lane_shift;
+    M->strips = (int32_t)((M->cols + strip - 1) / strip);
+    int64_t slabs = 1;
+    if (!direct) {
+        slabs = (CALIB_TARGET_WGS + M->strips - 1) / M->strips;
+        if (slabs > calib_slabs(M->rows)) slabs = calib_slabs(M->rows);
     }
-    for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) B.strip_start[i] = strips;
-    for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (strips > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
-    if (items[0].X->dtype == WINDQ_BF16)
-        hipLaunchKernelGGL(calib_direct_kernel<WINDQ_BF16>, dim3((unsigned)strips), dim3(CALIB_THREADS), 0, hs, B);
-    else
-        hipLaunchKernelGGL(calib_direct_kernel<WINDQ_F32>, dim3((unsigned)strips), dim3(CALIB_THREADS), 0, hs, B);
-    return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
-}
-
-static int calib_slab_launch(const windq_calib_item& it, hipStream_t hs) {
-    const windq_mat* X = it.X;
-    const int64_t n_slabs = calib_slabs(X->rows);
-    double* partial = static_cast<double*>(it.ws);
-    const dim3 grid((unsigned)((X->cols + CALIB_STRIP - 1) / CALIB_STRIP), (unsigned)n_slabs);
-    if (X->dtype == WINDQ_BF16)
-        hipLaunchKernelGGL(calib_partial_kernel<WINDQ_BF16>, grid, dim3(CALIB_THREADS), 0, hs, X->data, X->rows,
-                           X->cols, X->ld, partial);
-    else
-        hipLaunchKernelGGL(calib_partial_kernel<WINDQ_F32>, grid, dim3(CALIB_THREADS), 0, hs, X->data, X->rows,
-                           X->cols, X->ld, partial);
-    if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
-    hipLaunchKernelGGL(calib_finalize_kernel, dim3((unsigned)((X->cols + 255) / 256)), dim3(256), 0, hs, partial,
-                       n_slabs, X->rows, X->cols, it.s_absmean, it.s_rms);
-    return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
+    M->slab_rows = ((M->rows + slabs - 1) / slabs + CALIB_SLAB_ROWS - 1) / CALIB_SLAB_ROWS * CALIB_SLAB_ROWS;
+    M->slabs = (int32_t)((M->rows + M->slab_rows - 1) / M->slab_rows);
 }
 
 extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n, void* stream) {
     if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
+    CalibBatch B, F;            // all matrices; those whose slabs are still to be added
+    B.n = n;
+    F.n = 0;
+    int64_t wgs = 0, fin = 0;
+    bool rms = false;
     for (int32_t i = 0; i < n; ++i) {
-        if (items[i].X == nullptr) return WINDQ_EINVAL;
-        const int st = calib_check(items[i].X, items[i].s_absmean, items[i].ws, items[i].ws_bytes);
+        const windq_mat* X = items[i].X;
+        if (X == nullptr) return WINDQ_EINVAL;
+        const int st = calib_check(X, items[i].s_absmean, items[i].ws, items[i].ws_bytes);
         if (st != WINDQ_OK) return st;
-        if (items[i].X->dtype != items[0].X->dtype) return WINDQ_EINVAL;      // one kernel per launch
-    }
-    hipStream_t hs = static_cast<hipStream_t>(stream);
-    // matrices of few tokens share one launch; the others take their two launches each
-    windq_calib_item direct[WINDQ_MAX_BATCH];
-    int32_t nd = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        if (items[i].X->rows <= CALIB_DIRECT_MAX_ROWS) {
-            direct[nd++] = items[i];
-        } else {
-            const int st = calib_slab_launch(items[i], hs);
-            if (st != WINDQ_OK) return st;
+        if (X->dtype != items[0].X->dtype) return WINDQ_EINVAL;      // one kernel per launch
+        CalibMat& M = B.m[i];
+        M.X = X->data;
+        M.rows = X->rows;
+        M.cols = X->cols;
+        M.ld = X->ld;
+        M.s_absmean = items[i].s_absmean;
+        M.s_rms = items[i].s_rms;
+        M.partial = static_cast<double*>(items[i].ws);
+        M.reserved = 0;
+        calib_cut(&M);
+        rms = rms || M.s_rms != nullptr;
+        B.wg_start[i] = wgs;
+        wgs += (int64_t)M.strips * M.slabs;
+        if (M.slabs > 1) {
+            F.wg_start[F.n] = fin;
+            fin += (M.cols + CALIB_FIN_COLS - 1) / CALIB_FIN_COLS;
+            F.m[F.n++] = M;
         }
     }
-    return nd > 0 ? calib_direct_launch(direct, nd, hs) : WINDQ_OK;
+    if (wgs > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) B.wg_start[i] = wgs;
+    for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    const dim3 grid((unsigned)wgs), block(CALIB_THREADS);
+    if (items[0].X->dtype == WINDQ_BF16) {
+        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, true>), grid, block, 0, hs, B);
+        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, false>), grid, block, 0, hs, B);
+    } else {
+        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, true>), grid, block, 0, hs, B);
+        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, false>), grid, block, 0, hs, B);
+    }
+    if (F.n > 0) {
+        for (int32_t i = F.n; i <= WINDQ_MAX_BATCH; ++i) F.wg_start[i] = fin;
+        for (int32_t i = F.n; i < WINDQ_MAX_BATCH; ++i) F.m[i] = F.m[0];
+        if (rms) hipLaunchKernelGGL(calib_finalize_kernel<true>, dim3((unsigned)fin), dim3(256), 0, hs, F);
+        else hipLaunchKernelGGL(calib_finalize_kernel<false>, dim3((unsigned)fin), dim3(256), 0, hs, F);
+    }
+    return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 
 extern "C" int windq_calib_stats(const windq_mat* X, float* s_absmean, float* s_rms, void* ws, size_t ws_bytes,

@@ -86,6 +86,23 @@ def test_calib_stats(windq, T, C, dtype):
     assert_close(to_np(s_rms), o_rms, what="s_rms")
 
 
+@pytest.mark.parametrize("T,C,ld,dtype", [(1024, 72, 80, torch.bfloat16), (1025, 72, 72, torch.bfloat16), (1025, 8, 8, torch.float32),
+                                          (2048, 4096, 4096, torch.bfloat16), (2049, 4104, 4112, torch.bfloat16),
+                                          (1055, 520, 520, torch.float32), (1100, 512, 640, torch.bfloat16),
+                                          (255, 136, 136, torch.float32), (257, 64, 64, torch.bfloat16)])
+def test_calib_stats_at_the_edges_of_its_cuts(windq, T, C, ld, dtype):
+    """One slab or many, whole and partial load batches, narrow and partial strips; fp64 sums, so what is left is the
+    rounding of the fp32 output: 2^-24 and a little."""
+    X = synth.activations_llm(T, ld, seed=T + C, device=DEV, dtype=dtype)[:, ld - C:]
+    s_abs, s_rms = windq.windq_calib_stats(X)
+    s_only, _ = windq.windq_calib_stats(X, want_rms=False)
+    both = windq.windq_calib_stats_batch([X, X[:40]])
+    x = X.double()
+    assert torch.equal(s_abs, s_only) and torch.equal(s_abs, both[0][0]) and torch.equal(s_rms, both[0][1])
+    for got, want in ((s_abs, x.abs().mean(0)), (s_rms, x.square().mean(0).sqrt())):
+        assert float(((got.double() - want).abs() / want).max()) <= 1e-7
+
+
 def test_calib_stats_strided_rows(windq):
     big = synth.activations_llm(64, 1024, seed=3, device=DEV)
     X = big[:, 256:768]                                   # ld = 1024, cols = 512, 16-byte aligned start
