@@ -526,12 +526,15 @@ int windq_dequant_plan_batch(const windq_dequant_item* items /*HOST [n]*/, int32
 /*
  * The product of the reconstruction with a vector, from the packed artefact alone (the first piece of
  * a path that serves the quantized weights): for every row r
- *   y[r] = sum_c w_hat[r][c] * x[c],   w_hat as windq_dequant_plan reconstructs it (fp32, one fused
- *          multiply-add per weight; skip units keep their weights: W is read for them only;
- *          protected weights of a mask count as 0: their values live in the INT8 side stream).
- * Eight columns at a time are multiplied and summed in fp32 (fused multiply-adds in column order), those
- * runs in fp64 (a row's runs of one chunk, then the chunks in order), and y is rounded once: results are
- * bit-reproducible and differ from the exact product by at most ~1e-6 of sum_c |w_hat x|.
+ *   y[r] = sum_c w_hat[r][c] * x[c],   w_hat as windq_dequant_plan reconstructs it (skip units keep their
+ *          weights: W is read for them only; protected weights of a mask count as 0: their values live in
+ *          the INT8 side stream).
+ * Units at 1, 1.58 and 2 bits are summed in fp64 as scale * sum_c (code - centre) x[c] (at 2 bits plus
+ * (offset + 1.5 scale) * sum_c x[c]: w_hat before its rounding to fp32); the others, units
+ * under a mask, and chunks of x that hold infinities, NaN or values above 2^96, weight by weight: eight columns at a time
+ * in fp32 (one fused multiply-add per weight for w_hat, one for the product), those runs in fp64.  A row's chunks are
+ * added in fp64 in a fixed order and y is rounded once: results are bit-reproducible and differ from the exact product
+ * by at most ~1e-6 of sum_c |w_hat x|.
  *   x [cols] f32, y [rows] f32 (every element written).  Workspace: WINDQ_CALL_DEQUANT_GEMV.
  * Plan entries are checked as in windq_dequant_plan (a malformed one counts as skip).  The batch form
  * takes up to WINDQ_MAX_BATCH matrices (one chunk width, unit_rows, element type) in one launch plus

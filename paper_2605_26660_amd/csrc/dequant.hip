@@ -64,10 +64,7 @@ __device__ __forceinline__ int64_t dq_bytes_per_group(int a, int G) {
     }
 }
 
-// GEMV: instead of the error and the reconstruction, the product of the reconstruction with x:
-// per row and chunk, eight columns at a time in fp32 (fused multiply-adds in column order), those
-// runs summed in fp64.
-template <int DT, bool GEMV>
+template <int DT>
 __global__ __launch_bounds__(64) void dequant_tile_kernel(const DequantBatch B) {
     extern __shared__ char smem[];
     const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
@@ -79,7 +76,7 @@ __global__ __launch_bounds__(64) void dequant_tile_kernel(const DequantBatch B) 
     float* scol = reinterpret_cast<float*>(smem + TILE_ROWS * row_bytes);
     const int lane = threadIdx.x;
     load_tile_raw<DT>(A.W, A.g.ld, tc, G, smem);
-    for (int32_t c = lane; c < G; c += 64) scol[c] = GEMV ? A.x[tc.col0 + c] : A.s[tc.col0 + c];
+    for (int32_t c = lane; c < G; c += 64) scol[c] = A.s[tc.col0 + c];
     __syncthreads();
 
     int a = A.action[tc.u];
@@ -97,7 +94,7 @@ __global__ __launch_bounds__(64) void dequant_tile_kernel(const DequantBatch B) 
         const float of = a != 0 ? A.offset[gidx] : 0.0f;
         const uint8_t* __restrict__ src = A.codes + base + (tc.lrow0 + lane) * bpg;
         const uint8_t* __restrict__ mrow = A.mask != nullptr ? A.mask + row * A.mask_ld + (tc.col0 >> 3) : nullptr;
-        float* __restrict__ orow = !GEMV && A.what != nullptr ? A.what + row * A.what_ld + tc.col0 : nullptr;
+        float* __restrict__ orow = A.what != nullptr ? A.what + row * A.what_ld + tc.col0 : nullptr;
         const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : (a == 4 ? 2 : 1)));
         for (int32_t c = 0; c < G; c += 8) {
             float w[8];
@@ -120,7 +117,6 @@ __global__ __launch_bounds__(64) void dequant_tile_kernel(const DequantBatch B) 
 #pragma unroll
                 for (int j = 0; j < 8; ++j) stored[j] = (uint32_t)(v >> (j * bits)) & ((1u << bits) - 1u);
             }
-            float run = 0.0f;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const bool prot = ((m >> j) & 1u) != 0u;
@@ -139,20 +135,16 @@ __global__ __launch_bounds__(64) void dequant_tile_kernel(const DequantBatch B) 
                     }
                     if (prot) {
                         wh = 0.0f;                                    // lives in the INT8 side stream
-                    } else if (!GEMV) {
+                    } else {
                         const double d = (double)w[j] - whd;
                         const double ac = (double)scol[c + j] * (double)scol[c + j];
                         acc = fma(ac * d, d, acc);
                     }
                 }
-                if (GEMV) run = fmaf(wh, scol[c + j], run);
-                else if (orow != nullptr) orow[c + j] = wh;
+                if (orow != nullptr) orow[c + j] = wh;
             }
-            if (GEMV) acc += (double)run;
         }
-        if (GEMV) A.gpart[(tc.col0 / G) * A.g.rows + row] = acc;
     }
-    if (GEMV) return;
     acc = wave_sum(acc);
     if (lane == 0) A.part[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t] = acc;      // one partial per tile
 }
@@ -174,17 +166,27 @@ __device__ __forceinline__ void load8_global(const void* __restrict__ p, float (
     }
 }
 
+// Entry threadIdx.x of the table that turns a byte into its five trits, as five 2-bit fields.
+__device__ __forceinline__ void fill_trits(uint16_t* __restrict__ trits_of) {
+    uint32_t b = threadIdx.x, t = 0;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        t |= (b % 3u) << (2 * i);
+        b /= 3u;
+    }
+    trits_of[threadIdx.x] = (uint16_t)t;
+}
+
 // Lanes-per-row kernel: chunk_w = 8 << lpr_shift columns.  A workgroup takes one pass of a
 // 64-row tile, the 256 >> lpr_shift rows its threads cover at once: no loop over rows, so all
 // of a workgroup's loads are in flight together.
 constexpr int DQ_THREADS = 256;
-template <int DT, bool GEMV>
+template <int DT>
 __global__ __launch_bounds__(DQ_THREADS) void dequant_split_kernel(const DequantBatch B, const int lpr_shift) {
     __shared__ double red[DQ_THREADS / 64];
     const int32_t passes = dequant_passes(8 << lpr_shift);
-    // (the product: a workgroup takes all passes of its tile, one after the other, and keeps its x)
-    const int64_t tile_b = GEMV ? (int64_t)blockIdx.x : blockIdx.x / passes;                 // tile of the launch
-    const int32_t pass0 = GEMV ? 0 : (int32_t)(blockIdx.x - tile_b * passes);
+    const int64_t tile_b = blockIdx.x / passes;                 // tile of the launch
+    const int32_t pass = (int32_t)(blockIdx.x - tile_b * passes);
     const int mi = batch_index(B.tile_start, B.n, tile_b);
     const DequantArgs& A = B.m[mi];
     const TileCoord tc = tile_coord(A.g, tile_b - B.tile_start[mi]);
@@ -205,39 +207,26 @@ __global__ __launch_bounds__(DQ_THREADS) void dequant_split_kernel(const Dequant
     double ac[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const double sv = GEMV ? 0.0 : (double)A.s[tc.col0 + c + j];
+        const double sv = (double)A.s[tc.col0 + c + j];
         ac[j] = sv * sv;
     }
     // ternary: a byte's five trits as five 2-bit fields, from a table the workgroup fills once
     __shared__ uint16_t trits_of[256];
     if (a == 5) {
-        uint32_t b = threadIdx.x, t = 0;
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            t |= (b % 3u) << (2 * i);
-            b /= 3u;
-        }
-        trits_of[threadIdx.x] = (uint16_t)t;
+        fill_trits(trits_of);
         __syncthreads();
     }
 
-    float xv[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if (GEMV) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) xv[j] = A.x[tc.col0 + c + j];
-    }
     double acc = 0.0;
-    for (int32_t pass = pass0; pass < (GEMV ? passes : pass0 + 1); ++pass) {
-        float dot = 0.0f;           // GEMV: this thread's eight columns of the row times x
+    {
         const int32_t r = pass * rows_per_pass + rsub;
         if (r < tc.nrows && r < TILE_ROWS) {
             const int64_t row = tc.row0 + r;
             const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + r;
             float w[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            if (!GEMV || a == 0)        // the product reads W only for skip units
-                load8_global<DT>(static_cast<const char*>(A.W) + (row * A.g.ld + tc.col0 + c) * EB, w);
+            load8_global<DT>(static_cast<const char*>(A.W) + (row * A.g.ld + tc.col0 + c) * EB, w);
             const uint32_t m = A.mask != nullptr ? A.mask[row * A.mask_ld + (tc.col0 >> 3) + sub] : 0u;
-            float* __restrict__ orow = !GEMV && A.what != nullptr ? A.what + row * A.what_ld + tc.col0 + c : nullptr;
+            float* __restrict__ orow = A.what != nullptr ? A.what + row * A.what_ld + tc.col0 + c : nullptr;
             float wh[8];
             if (a == 0) {
 #pragma unroll
@@ -297,30 +286,17 @@ __global__ __launch_bounds__(DQ_THREADS) void dequant_split_kernel(const Dequant
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const bool prot = ((m >> j) & 1u) != 0u;              // lives in the INT8 side stream
-                    if (!GEMV) {
-                        const double d = (double)w[j] - whd[j];
-                        acc = fma(prot ? 0.0 : ac[j] * d, d, acc);
-                    }
+                    const double d = (double)w[j] - whd[j];
+                    acc = fma(prot ? 0.0 : ac[j] * d, d, acc);
                     wh[j] = prot ? 0.0f : wh[j];
                 }
             }
-            if (GEMV) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) dot = fmaf(wh[j], xv[j], dot);
-            } else if (orow != nullptr) {
+            if (orow != nullptr) {
                 reinterpret_cast<float4*>(orow)[0] = make_float4(wh[0], wh[1], wh[2], wh[3]);
                 reinterpret_cast<float4*>(orow)[1] = make_float4(wh[4], wh[5], wh[6], wh[7]);
             }
         }
-        if (GEMV) {
-            // the row's 8-column runs, held by neighbouring lanes, summed in fp64
-            double d = (double)dot;
-            for (int mk = 1; mk < (1 << lpr_shift); mk <<= 1) d += __shfl_xor(d, mk, 64);
-            if (sub == 0 && r < tc.nrows && r < TILE_ROWS) A.gpart[(tc.col0 / G) * A.g.rows + tc.row0 + r] = d;
-        }
     }
-    if (GEMV) return;
-    const int32_t pass = pass0;
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
@@ -343,21 +319,418 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
     if (threadIdx.x == 0) A.err[u] = (float)t;
 }
 
-// y[row] = the row's chunk partials in chunk order, fp64, rounded once; one thread per row.
-__global__ __launch_bounds__(256) void dequant_gemv_finalize_kernel(const DequantBatch B) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= B.row_start[B.n]) return;
-    const int mi = batch_index(B.row_start, B.n, i);
-    const DequantArgs& A = B.m[mi];
-    const int64_t row = i - B.row_start[mi];
-    double t = 0.0;
-    for (int64_t j0 = 0; j0 < A.g.n_chunks; j0 += 8) {       // eight loads in flight, added in chunk order
-        double v[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = j0 + k < A.g.n_chunks ? A.gpart[(j0 + k) * A.g.rows + row] : 0.0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) t += v[k];
+// ------------------------------------------------------------- the product from the artefact
+// y = W_hat x for one vector.  The codes are a few bits a weight, so what bounds a straightforward kernel
+// is not HBM (63 MB for a 7B-shaped block at 2 bits: 12 us) but taking codes apart: extract, convert, two
+// multiply-adds per weight.  Units at 1, 1.58 and 2 bits - nearly all of a plan - are looked up instead, several
+// weights at a time: for the workgroup's chunk of x a table holds, for every value that a piece of the stream can take,
+//     sum_j (code_j - centre) x_j      (centre: 1/2 of a bit's two signs, trit 1, code 1.5)
+// The centre keeps the entries as small as the products they stand for; what it leaves out is
+// (offset + centre * scale) * sum_c x_c, added once per row in fp64.  Pieces are small on purpose: a nibble
+// (four 1-bit or two 2-bit weights; 16 entries), and of a byte of trits the lower three (27 entries) and the upper two (10).
+// A wavefront's 64 look-ups into up to 32 consecutive words meet no bank conflict; tables of whole bytes (256
+// entries, half the look-ups) do, and take 16 times as long to make: four 4096 x 11008 matrices took 26.0 / 34.5 /
+// 36.3 us at 1 / 1.58 / 2 bits with them, 21.3 / 28.3 / 30.1 with the small ones (92 to 98 us with one lane per eight weights).
+//   A lane owns a row (its bytes are contiguous, and so are its neighbours': a unit's rows lie one after the
+// other).  Tables and sums are fp64: what the centre leaves to (offset + centre * scale) may cancel.
+//   The other routes, one weight at a time, same results to rounding: 3, 4 and 8 bits (little to
+// share), units under a protection mask, and chunks of x that hold a value no
+// fp32 sum of a few columns may meet (infinite, NaN or above 2^96).  Skip units read W, G/8 lanes a row.
+//   7B-shaped block at a 2-bit plan: 40 us (109 before), of which the sums over chunks take 5.  The six wavefronts per
+// SIMD that 84 registers allow are worth 5 to 10 % over the four that the skip route's loads would take.
+constexpr int GEMV_THREADS = 256;
+constexpr int GEMV_TRIT_WORDS = 48;                 // of a byte of trits: 27 entries at 0, 10 at 32
+// LDS of the largest table, trits of whole dwords (2 bits: 8 entries a column, 1 bit: 4), after the chunk's x.
+static size_t gemv_lds(int32_t chunk_w) {
+    return (size_t)WINDQ_MAX_CHUNK * sizeof(float) + (size_t)(((chunk_w + 4) / 5 + 3) & ~3) * GEMV_TRIT_WORDS * sizeof(double);
+}
+
+// n (1..16) bytes of a row's codes, n the same for all lanes; the rest zero.  Rows start at any byte.
+__device__ __forceinline__ void load_code_bytes(const uint8_t* __restrict__ p, int n, uint32_t (&d)[4]) {
+    if (n == 16) {
+        __builtin_memcpy(d, p, 16);
+        return;
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        d[i] = 0u;
+        if (4 * i + 4 <= n) {
+            __builtin_memcpy(&d[i], p + 4 * i, 4);
+        } else {
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                if (4 * i + b < n) d[i] |= (uint32_t)p[4 * i + b] << (8 * b);
+        }
+    }
+}
+
+// The tables of a chunk, nb bytes a row; pieces up to the end of the row's last dword are cleared.
+//   1 bit   nibble n covers columns 4n ..    2 bits   nibble n covers columns 2n, 2n + 1
+//   trits   byte k covers columns 5k .. ; columns past the chunk (the last byte) count as zero
+__device__ __forceinline__ void gemv_tables(int a, const float* __restrict__ x, int32_t G, int32_t nb, double* __restrict__ tab) {
+    const int32_t nb4 = (nb + 3) & ~3;
+    if (a == 5) {
+        for (int32_t i = threadIdx.x; i < nb4 * GEMV_TRIT_WORDS; i += GEMV_THREADS) {
+            const uint32_t k = (uint32_t)i / GEMV_TRIT_WORDS, e = (uint32_t)i - k * GEMV_TRIT_WORDS;
+            const uint32_t v = e < 32u ? e : e - 32u;
+            const int32_t c = (int32_t)k * 5 + (e < 32u ? 0 : 3);
+            double t = 0.0;
+            if (c < G) t = ((double)(v % 3u) - 1.0) * (double)x[c];
+            if (c + 1 < G) t = fma((double)((v / 3u) % 3u) - 1.0, (double)x[c + 1], t);
+            if (e < 32u && c + 2 < G) t = fma((double)((v / 9u) % 3u) - 1.0, (double)x[c + 2], t);
+            tab[i] = (int32_t)k < nb ? t : 0.0;
+        }
+        return;
+    }
+    for (int32_t i = threadIdx.x; i < nb4 * 32; i += GEMV_THREADS) {
+        const int32_t n = i >> 4;
+        const uint32_t v = (uint32_t)i & 15u;
+        double t = 0.0;
+        if (n < 2 * nb) {
+            if (a == 6) {
+                const float4 q = *reinterpret_cast<const float4*>(x + 4 * n);
+                t = ((v & 1u) != 0u ? (double)q.x : -(double)q.x) + ((v & 2u) != 0u ? (double)q.y : -(double)q.y);
+                t += ((v & 4u) != 0u ? (double)q.z : -(double)q.z) + ((v & 8u) != 0u ? (double)q.w : -(double)q.w);
+            } else {
+                t = fma((double)(v & 3u) - 1.5, (double)x[2 * n], ((double)(v >> 2) - 1.5) * (double)x[2 * n + 1]);
+            }
+        }
+        tab[i] = t;
+    }
+}
+
+// The sum of the entries that up to sixteen bytes select, whose first piece's table is at tab.
+__device__ __forceinline__ double gemv_lookup_nibbles(const uint32_t (&d)[4], int n, const double* __restrict__ tab) {
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (4 * i < n) {                                            // the same for all lanes
+            const char* __restrict__ t = reinterpret_cast<const char*>(tab + i * 128);
+            double e[8];
+            e[0] = *reinterpret_cast<const double*>(t + ((d[i] << 3) & 0x78u));
+#pragma unroll
+            for (int k = 1; k < 8; ++k) e[k] = *reinterpret_cast<const double*>(t + 128 * k + ((d[i] >> (4 * k - 3)) & 0x78u));
+            acc += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+        }
+    }
+    return acc;
+}
+__device__ __forceinline__ double gemv_lookup_trits(const uint32_t (&d)[4], int n, const double* __restrict__ tab) {
+    double acc = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (4 * i < n) {
+            const char* __restrict__ t = reinterpret_cast<const char*>(tab + i * 4 * GEMV_TRIT_WORDS);
+            double e[8];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t v = (d[i] >> (8 * k)) & 0xffu;
+                const uint32_t q = (v * 607u) >> 14;                // v / 27 for v < 256
+                const uint32_t r = v - q * 27u;
+                e[2 * k] = *reinterpret_cast<const double*>(t + 8 * GEMV_TRIT_WORDS * k + 8 * r);
+                e[2 * k + 1] = *reinterpret_cast<const double*>(t + 8 * GEMV_TRIT_WORDS * k + 256 + 8 * q);
+            }
+            acc += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+        }
+    }
+    return acc;
+}
+
+// The reconstruction of eight columns from c (a multiple of 8) of a row: `bits` bytes of its codes at any
+// alignment, or the two or three bytes that hold eight trits.
+__device__ __forceinline__ void decode8(int a, int bits, const uint8_t* __restrict__ src, int32_t c, int32_t bpg, float sc,
+                                        float of, const uint16_t* __restrict__ trits_of, float (&wh)[8]) {
+    if (a == 5) {
+        const int32_t b0 = c / 5, last = bpg - 1;
+        const uint32_t y0 = src[b0];
+        const uint32_t y1 = src[b0 + 1 <= last ? b0 + 1 : last];
+        const uint32_t y2 = src[b0 + 2 <= last ? b0 + 2 : last];
+        const uint32_t v = ((uint32_t)trits_of[y0] | ((uint32_t)trits_of[y1] << 10) | ((uint32_t)trits_of[y2] << 20)) >> (2 * (c - 5 * b0));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) wh[j] = sc * ((float)((v >> (2 * j)) & 3u) - 1.0f);
+        return;
+    }
+    uint64_t v = 0;
+    const uint8_t* p = src + (c >> 3) * bits;
+    for (int b = 0; b < bits; ++b) v |= (uint64_t)p[b] << (8 * b);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t code = (uint32_t)(v >> (j * bits)) & ((1u << bits) - 1u);
+        wh[j] = a == 6 ? (code != 0u ? sc : -sc) : fmaf((float)code, sc, of);
+    }
+}
+
+// The products of N rows with the chunk of x one weight at a time: the values windq_dequant_plan reconstructs, eight
+// columns in fp32 in column order, those runs in fp64.  32 columns (4 BITS bytes of codes, 4 of the mask) of every
+// row per step, the next step's on their way meanwhile.
+template <int BITS, bool MASKED, int N>
+__device__ __forceinline__ void gemv_rows(const uint8_t* const (&src)[N], const uint8_t* const (&mrow)[N], bool mask4, int32_t G,
+                                          const float (&sc)[N], const float (&of)[N], const float* __restrict__ xs, double (&acc)[N]) {
+    const int32_t G32 = G & ~31;
+    uint32_t d[N][BITS], m[N];
+    auto fetch = [&](int32_t c, uint32_t (&dd)[N][BITS], uint32_t (&mm)[N]) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            __builtin_memcpy(dd[k], src[k] + (c >> 3) * BITS, 4 * BITS);
+            mm[k] = 0u;
+            if (MASKED) {
+                const uint8_t* q = mrow[k] + (c >> 3);
+                if (mask4) mm[k] = *reinterpret_cast<const uint32_t*>(q);
+                else mm[k] = (uint32_t)q[0] | ((uint32_t)q[1] << 8) | ((uint32_t)q[2] << 16) | ((uint32_t)q[3] << 24);
+            }
+        }
+    };
+    if (G32 > 0) fetch(0, d, m);
+#pragma unroll 1
+    for (int32_t c = 0; c < G32; c += 32) {
+        uint32_t dn[N][BITS], mn[N];
+        fetch(c + 32 < G32 ? c + 32 : c, dn, mn);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = xs[c + 8 * q + j];
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                float dot = 0.0f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int bit = (8 * q + j) * BITS, w = bit >> 5, sft = bit & 31;
+                    uint32_t code = d[k][w] >> sft;
+                    if (sft + BITS > 32) code |= d[k][w + 1 < BITS ? w + 1 : w] << (32 - sft);
+                    code &= (1u << BITS) - 1u;
+                    float wh = BITS == 1 ? (code != 0u ? sc[k] : -sc[k]) : fmaf((float)code, sc[k], of[k]);
+                    if (MASKED) wh = ((m[k] >> (8 * q + j)) & 1u) != 0u ? 0.0f : wh;
+                    dot = fmaf(wh, x[j], dot);
+                }
+                acc[k] += (double)dot;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+#pragma unroll
+            for (int i = 0; i < BITS; ++i) d[k][i] = dn[k][i];
+            m[k] = mn[k];
+        }
+    }
+    for (int32_t c = G32; c < G; c += 8) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            float wh[8], dot = 0.0f;
+            decode8(BITS == 1 ? 6 : 1, BITS, src[k], c, 0, sc[k], of[k], nullptr, wh);
+            const uint32_t mb = MASKED ? mrow[k][c >> 3] : 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) dot = fmaf(((mb >> j) & 1u) != 0u ? 0.0f : wh[j], xs[c + j], dot);
+            acc[k] += (double)dot;
+        }
+    }
+}
+
+template <bool MASKED, int N>
+__device__ __forceinline__ void gemv_rows_of(int a, const uint8_t* const (&src)[N], const uint8_t* const (&mrow)[N], bool mask4,
+                                             int32_t G, int32_t bpg, const float (&sc)[N], const float (&of)[N],
+                                             const float* __restrict__ xs, const uint16_t* __restrict__ trits_of, double (&acc)[N]) {
+    switch (a) {
+        case 1: return gemv_rows<8, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
+        case 2: return gemv_rows<4, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
+        case 3: return gemv_rows<3, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
+        case 4: return gemv_rows<2, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
+        case 6: return gemv_rows<1, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
+        default: break;                                                // trits
+    }
+#pragma unroll 2
+    for (int32_t c = 0; c < G; c += 8) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            float wh[8], dot = 0.0f;
+            decode8(5, 0, src[k], c, bpg, sc[k], of[k], trits_of, wh);
+            const uint32_t m = MASKED ? mrow[k][c >> 3] : 0u;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) dot = fmaf(((m >> i) & 1u) != 0u ? 0.0f : wh[i], xs[c + i], dot);
+            acc[k] += (double)dot;
+        }
+    }
+}
+
+// RPT rows per thread: a workgroup takes RPT * 256 rows of a unit.
+template <int DT, int RPT>
+__global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatch B) {
+    extern __shared__ __align__(16) char gemv_smem[];
+    float* xs = reinterpret_cast<float*>(gemv_smem);
+    double* tab = reinterpret_cast<double*>(gemv_smem + WINDQ_MAX_CHUNK * sizeof(float));
+    __shared__ double red[GEMV_THREADS / 64];
+    constexpr int nt = RPT * GEMV_THREADS;         // rows
+    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
+    const DequantArgs& A = B.m[mi];
+    // workgroups of one matrix: chunks side by side, then row ranges, then row blocks
+    const uint32_t at = (uint32_t)((int64_t)blockIdx.x - B.tile_start[mi]);
+    const uint32_t nc = (uint32_t)A.g.n_chunks;
+    const uint32_t nr = (uint32_t)((A.g.R_u + nt - 1) / nt);
+    const uint32_t band = at / nc, j = at - band * nc;
+    const uint32_t rb = band / nr, rr = band - rb * nr;
+    const int64_t u = (int64_t)rb * nc + j;
+    const int64_t lrow0 = (int64_t)rr * nt;                            // first row, local to the unit
+    const int64_t row0 = (int64_t)rb * A.g.R_u + lrow0;
+    const int64_t left = A.g.R_u - lrow0;
+    const int32_t nrows = left < nt ? (int32_t)left : nt;
+    const int32_t G = A.g.chunk_w;
+    const int64_t col0 = (int64_t)j * G;
+    const int tid = threadIdx.x;
+
+    int a = A.action[u];                           // on their way while x is looked over
+    const int64_t base = A.code_off[u];
+    bool odd = false;
+    double xsum = 0.0;
+    for (int32_t c = tid; c < G; c += GEMV_THREADS) {
+        const float v = A.x[col0 + c];
+        xs[c] = v;
+        xsum += (double)v;
+        odd = odd || !(fabsf(v) <= 0x1p96f);
+    }
+    xsum = wave_sum(xsum);
+    if ((tid & 63) == 0) red[tid >> 6] = xsum;
+    const bool direct = __syncthreads_or(odd ? 1 : 0) != 0 || A.mask != nullptr;
+    if (a >= WINDQ_N_ACTIONS) a = 0;
+    const int64_t bpg = dq_bytes_per_group(a, G);
+    if (base < 0 || (base & 15) != 0 || base + bpg * A.g.R_u > A.codes_bytes) a = 0;   // a malformed entry reads nothing
+    double* __restrict__ out = A.gpart + (int64_t)j * A.g.rows + row0;
+
+    if (a == 0) {
+        constexpr int EB = Elem<DT>::bytes;
+        const char* __restrict__ w0 = static_cast<const char*>(A.W) + (row0 * A.g.ld + col0) * EB;
+        const int32_t lpr = G >> 3;
+        if ((lpr & (lpr - 1)) == 0) {                      // G/8 lanes side by side share a row
+            const int sub = tid & (lpr - 1);
+            const int step = GEMV_THREADS / lpr;
+            float xv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) xv[i] = A.x[col0 + sub * 8 + i];
+            constexpr int NR = DT == WINDQ_BF16 ? 8 : 4;
+            for (int32_t r0 = tid / lpr; r0 < nrows; r0 += NR * step) {        // NR rows in flight; lpr lanes keep together
+                uint4 raw[NR][EB / 2];
+#pragma unroll
+                for (int k = 0; k < NR; ++k) {
+                    const int32_t r = r0 + k * step;
+                    __builtin_memcpy(raw[k], w0 + ((int64_t)(r < nrows ? r : nrows - 1) * A.g.ld + sub * 8) * EB, 8 * EB);
+                }
+#pragma unroll
+                for (int k = 0; k < NR; ++k) {
+                    float w[8], dot = 0.0f;
+                    load8_global<DT>(raw[k], w);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) dot = fmaf(w[i], xv[i], dot);
+                    double d = (double)dot;
+                    for (int mk = 1; mk < lpr; mk <<= 1) d += __shfl_xor(d, mk, 64);
+                    if (sub == 0 && r0 + k * step < nrows) out[r0 + k * step] = d;
+                }
+            }
+        } else {
+            for (int32_t r = tid; r < nrows; r += GEMV_THREADS) {
+                double acc = 0.0;
+                for (int32_t c = 0; c < G; c += 8) {
+                    float w[8], dot = 0.0f;
+                    load8_global<DT>(w0 + ((int64_t)r * A.g.ld + c) * EB, w);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) dot = fmaf(w[i], xs[c + i], dot);
+                    acc += (double)dot;
+                }
+                out[r] = acc;
+            }
+        }
+        return;
+    }
+
+    const int64_t g0 = u * A.g.R_u + lrow0;
+    const uint8_t* __restrict__ src0 = A.codes + base + lrow0 * bpg;
+    if (a >= 4 && !direct) {
+        // the rows' loads are on their way while the tables are made, the next bytes while these are looked up; a thread
+        // past the last row reads the last row's data again and writes nothing
+        uint32_t d[RPT][4];
+        float sc[RPT], of[RPT];
+        double acc[RPT];
+        const int32_t nb = (int32_t)bpg;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const int32_t r = k * GEMV_THREADS + tid, row = r < nrows ? r : nrows - 1;
+            load_code_bytes(src0 + (int64_t)row * bpg, nb < 16 ? nb : 16, d[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const int32_t r = k * GEMV_THREADS + tid, row = r < nrows ? r : nrows - 1;
+            sc[k] = A.scale[g0 + row];
+            of[k] = a == 4 ? A.offset[g0 + row] : 0.0f;
+            acc[k] = 0.0;
+        }
+        gemv_tables(a, xs, G, nb, tab);
+        __syncthreads();
+        const double* __restrict__ t = tab;
+        for (int32_t b0 = 0; b0 < nb; b0 += 16, t += a == 5 ? 16 * GEMV_TRIT_WORDS : 16 * 32) {
+            const int n = nb - b0 < 16 ? nb - b0 : 16;
+            const int32_t b1 = b0 + 16;
+#pragma unroll
+            for (int k = 0; k < RPT; ++k) {
+                const uint32_t now[4] = {d[k][0], d[k][1], d[k][2], d[k][3]};
+                const int32_t r = k * GEMV_THREADS + tid, row = r < nrows ? r : nrows - 1;
+                if (b1 < nb) load_code_bytes(src0 + (int64_t)row * bpg + b1, nb - b1 < 16 ? nb - b1 : 16, d[k]);
+                acc[k] += a == 5 ? gemv_lookup_trits(now, n, t) : gemv_lookup_nibbles(now, n, t);
+            }
+        }
+        const double xt = ((red[0] + red[1]) + red[2]) + red[3];
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            const int32_t r = k * GEMV_THREADS + tid;
+            if (r < nrows) {
+                const double scd = (double)sc[k];
+                out[r] = a == 4 ? fma(fma(1.5, scd, (double)of[k]), xt, scd * acc[k]) : scd * acc[k];
+            }
+        }
+        return;
+    }
+
+    uint16_t* trits_of = reinterpret_cast<uint16_t*>(tab);
+    if (a == 5) {
+        fill_trits(trits_of);
+        __syncthreads();
+    }
+    const bool mask4 = A.mask != nullptr && (A.mask_ld & 3) == 0 && ((reinterpret_cast<uintptr_t>(A.mask) + (uintptr_t)(col0 >> 3)) & 3) == 0;
+    const uint8_t *src[RPT], *mrow[RPT];
+    float sc[RPT], of[RPT];
+    double acc[RPT];
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        const int32_t r = k * GEMV_THREADS + tid, row = r < nrows ? r : nrows - 1;
+        src[k] = src0 + (int64_t)row * bpg;
+        mrow[k] = A.mask != nullptr ? A.mask + (row0 + row) * A.mask_ld + (col0 >> 3) : nullptr;
+        sc[k] = A.scale[g0 + row];
+        of[k] = A.offset[g0 + row];
+        acc[k] = 0.0;
+    }
+    if (A.mask != nullptr) gemv_rows_of<true>(a, src, mrow, mask4, G, (int32_t)bpg, sc, of, xs, trits_of, acc);
+    else gemv_rows_of<false>(a, src, mrow, mask4, G, (int32_t)bpg, sc, of, xs, trits_of, acc);
+#pragma unroll
+    for (int k = 0; k < RPT; ++k)
+        if (k * GEMV_THREADS + tid < nrows) out[k * GEMV_THREADS + tid] = acc[k];
+}
+
+// y[row] = the row's chunk partials: 8 phases, phase p adds chunks p, p + 8, ..., the phases in order; fp64,
+// rounded once.  32 rows to a workgroup, so that the short sums of a block's rows fill the chip.
+constexpr int GEMV_FIN_ROWS = 32;
+__global__ __launch_bounds__(256) void gemv_finalize_kernel(const DequantBatch B) {
+    __shared__ double red[8][GEMV_FIN_ROWS];
+    const int mi = batch_index(B.row_start, B.n, blockIdx.x);
+    const DequantArgs& A = B.m[mi];
+    const int rl = threadIdx.x & (GEMV_FIN_ROWS - 1), ph = threadIdx.x / GEMV_FIN_ROWS;
+    const int64_t row = ((int64_t)blockIdx.x - B.row_start[mi]) * GEMV_FIN_ROWS + rl;
+    double t = 0.0;
+    if (row < A.g.rows) {
+#pragma unroll 4
+        for (int64_t c = ph; c < A.g.n_chunks; c += 8) t += A.gpart[c * A.g.rows + row];
+    }
+    red[ph][rl] = t;
+    __syncthreads();
+    if (threadIdx.x >= GEMV_FIN_ROWS || row >= A.g.rows) return;
+#pragma unroll
+    for (int p = 1; p < 8; ++p) t += red[p][rl];
     A.y[row] = (float)t;
 }
 
@@ -404,9 +777,29 @@ struct DequantItem {
     size_t ws_bytes;
 };
 
+static void dequant_args(const DequantItem& it, DequantArgs* A) {
+    A->W = it.W->data;
+    A->s = it.s;
+    A->mask = it.mask;
+    A->mask_ld = it.W->cols / 8;
+    A->action = it.action;
+    A->code_off = it.code_off;
+    A->codes = it.codes;
+    A->codes_bytes = (int64_t)it.codes_bytes;
+    A->scale = it.scale;
+    A->offset = it.offset;
+    A->what = nullptr;
+    A->what_ld = it.W->cols;
+    A->part = static_cast<double*>(it.ws);
+    A->err = nullptr;
+    A->per_unit = 0;
+    A->x = it.x;
+    A->y = it.y;
+    A->gpart = static_cast<double*>(it.ws);
+}
+
 // Matrices whose layout allows it go through the lanes-per-row kernel, the others through the
 // tile kernel, exactly as each would alone: at most two sub-batches per call.
-template <bool GEMV>
 static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int64_t unit_rows, void* stream) {
     if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
     // lanes-per-row kernel: 8 x 2^k columns, 16-byte pieces of W and of w_hat aligned
@@ -425,33 +818,14 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
         if (st != WINDQ_OK) return st;
         if (it.action == nullptr || it.code_off == nullptr || it.scale == nullptr || it.offset == nullptr) return WINDQ_EINVAL;
         if (it.codes == nullptr && it.codes_bytes != 0) return WINDQ_EINVAL;
-        if (GEMV) {
-            if (it.x == nullptr || it.y == nullptr) return WINDQ_EINVAL;
-        } else {
-            if (it.s == nullptr || (it.err == nullptr && it.w_hat == nullptr)) return WINDQ_EINVAL;
-            if (it.w_hat != nullptr && !aligned(it.w_hat, 4)) return WINDQ_EINVAL;
-        }
+        if (it.s == nullptr || (it.err == nullptr && it.w_hat == nullptr)) return WINDQ_EINVAL;
+        if (it.w_hat != nullptr && !aligned(it.w_hat, 4)) return WINDQ_EINVAL;
         if (!aligned(it.code_off, 8)) return WINDQ_EINVAL;
         if (it.W->dtype != items[0].W->dtype) return WINDQ_EINVAL;      // one kernel per launch
-        const size_t need = GEMV ? dequant_gemv_ws_bytes(A.g) : dequant_ws_bytes(A.g);
-        if (it.ws == nullptr || it.ws_bytes < need || !aligned(it.ws, 256)) return WINDQ_EWORKSPACE;
-        A.W = it.W->data;
-        A.s = it.s;
-        A.mask = it.mask;
-        A.mask_ld = it.W->cols / 8;
-        A.action = it.action;
-        A.code_off = it.code_off;
-        A.codes = it.codes;
-        A.codes_bytes = (int64_t)it.codes_bytes;
-        A.scale = it.scale;
-        A.offset = it.offset;
-        A.what = GEMV ? nullptr : it.w_hat;
-        A.what_ld = it.W->cols;
-        A.part = static_cast<double*>(it.ws);
-        A.err = GEMV ? nullptr : it.err;
-        A.x = it.x;
-        A.y = it.y;
-        A.gpart = static_cast<double*>(it.ws);
+        if (it.ws == nullptr || it.ws_bytes < dequant_ws_bytes(A.g) || !aligned(it.ws, 256)) return WINDQ_EWORKSPACE;
+        dequant_args(it, &A);
+        A.what = it.w_hat;
+        A.err = it.err;
         const size_t eb = it.W->dtype == WINDQ_BF16 ? 2 : 4;
         const bool split = lpr_shift >= 0 && aligned(it.W->data, 16) && ((size_t)it.W->ld * eb) % 16 == 0 &&
                            (A.what == nullptr || aligned(A.what, 16)) && aligned(it.codes, 8);
@@ -469,11 +843,10 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
     if (S.n > 0) {
         const int64_t tiles = dequant_number(&S);
         if (tiles * passes > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
-        const dim3 grid((unsigned)(GEMV ? tiles : tiles * passes));
-        if (dtype == WINDQ_BF16) hipLaunchKernelGGL((dequant_split_kernel<WINDQ_BF16, GEMV>), grid, dim3(DQ_THREADS), 0, hs, S, lpr_shift);
-        else hipLaunchKernelGGL((dequant_split_kernel<WINDQ_F32, GEMV>), grid, dim3(DQ_THREADS), 0, hs, S, lpr_shift);
-        if (GEMV) hipLaunchKernelGGL(dequant_gemv_finalize_kernel, dim3((unsigned)((S.row_start[S.n] + 255) / 256)), dim3(256), 0, hs, S);
-        else if (any_err_s) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)S.unit_start[S.n]), dim3(256), 0, hs, S);
+        const dim3 grid((unsigned)(tiles * passes));
+        if (dtype == WINDQ_BF16) hipLaunchKernelGGL(dequant_split_kernel<WINDQ_BF16>, grid, dim3(DQ_THREADS), 0, hs, S, lpr_shift);
+        else hipLaunchKernelGGL(dequant_split_kernel<WINDQ_F32>, grid, dim3(DQ_THREADS), 0, hs, S, lpr_shift);
+        if (any_err_s) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)S.unit_start[S.n]), dim3(256), 0, hs, S);
     }
     if (T.n > 0) {
         const int64_t tiles = dequant_number(&T);
@@ -481,17 +854,73 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
         const size_t lds = raw_tile_lds_bytes(dtype, chunk_w) + (size_t)chunk_w * sizeof(float);
         const dim3 grid((unsigned)tiles);
         if (dtype == WINDQ_BF16) {
-            const int st = ensure_lds(reinterpret_cast<const void*>(&dequant_tile_kernel<WINDQ_BF16, GEMV>), lds);
+            const int st = ensure_lds(reinterpret_cast<const void*>(&dequant_tile_kernel<WINDQ_BF16>), lds);
             if (st != WINDQ_OK) return st;
-            hipLaunchKernelGGL((dequant_tile_kernel<WINDQ_BF16, GEMV>), grid, dim3(64), lds, hs, T);
+            hipLaunchKernelGGL(dequant_tile_kernel<WINDQ_BF16>, grid, dim3(64), lds, hs, T);
         } else {
-            const int st = ensure_lds(reinterpret_cast<const void*>(&dequant_tile_kernel<WINDQ_F32, GEMV>), lds);
+            const int st = ensure_lds(reinterpret_cast<const void*>(&dequant_tile_kernel<WINDQ_F32>), lds);
             if (st != WINDQ_OK) return st;
-            hipLaunchKernelGGL((dequant_tile_kernel<WINDQ_F32, GEMV>), grid, dim3(64), lds, hs, T);
+            hipLaunchKernelGGL(dequant_tile_kernel<WINDQ_F32>, grid, dim3(64), lds, hs, T);
         }
-        if (GEMV) hipLaunchKernelGGL(dequant_gemv_finalize_kernel, dim3((unsigned)((T.row_start[T.n] + 255) / 256)), dim3(256), 0, hs, T);
-        else if (any_err_t) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)T.unit_start[T.n]), dim3(256), 0, hs, T);
+        if (any_err_t) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)T.unit_start[T.n]), dim3(256), 0, hs, T);
     }
+    return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
+}
+
+// The product.  A workgroup takes 512 rows of a unit (two per thread, their loads in flight together) where that still
+// makes four workgroups per CU, else 256.  1024 rows are as fast when all units have one bit-width, but the few units at
+// 8 bits or skipped then outlast the others: 4096 x 11008 x 4 at a mixed plan 45 us against 35.
+constexpr int64_t GEMV_MIN_WGS = 1024;
+static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int64_t unit_rows, void* stream) {
+    if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
+    DequantBatch B;
+    B.n = n;
+    for (int32_t i = 0; i < n; ++i) {
+        const DequantItem& it = items[i];
+        DequantArgs& A = B.m[i];
+        if (it.W == nullptr) return WINDQ_EINVAL;
+        const int st = make_geometry(it.W, chunk_w, unit_rows, &A.g);
+        if (st != WINDQ_OK) return st;
+        if (it.action == nullptr || it.code_off == nullptr || it.scale == nullptr || it.offset == nullptr) return WINDQ_EINVAL;
+        if (it.codes == nullptr && it.codes_bytes != 0) return WINDQ_EINVAL;
+        if (it.x == nullptr || it.y == nullptr || !aligned(it.code_off, 8)) return WINDQ_EINVAL;
+        if (it.W->dtype != items[0].W->dtype) return WINDQ_EINVAL;      // one kernel per launch
+        if (it.ws == nullptr || it.ws_bytes < dequant_gemv_ws_bytes(A.g) || !aligned(it.ws, 256)) return WINDQ_EWORKSPACE;
+        dequant_args(it, &A);
+    }
+    int rpt = 4;
+    int64_t wgs;
+    do {                        // row_start: the finalize kernel's workgroups
+        rpt >>= 1;
+        wgs = 0;
+        int64_t fin = 0;
+        for (int32_t i = 0; i < n; ++i) {
+            const Geometry& g = B.m[i].g;
+            B.tile_start[i] = wgs;
+            B.row_start[i] = fin;
+            wgs += g.U * ((g.R_u + rpt * GEMV_THREADS - 1) / (rpt * GEMV_THREADS));
+            fin += (g.rows + GEMV_FIN_ROWS - 1) / GEMV_FIN_ROWS;
+        }
+        for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) {
+            B.tile_start[i] = wgs;
+            B.row_start[i] = fin;
+        }
+    } while (rpt > 1 && wgs < GEMV_MIN_WGS);
+    for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) B.unit_start[i] = 0;
+    for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
+    if (wgs > (int64_t)0x7fffffff || B.row_start[n] > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    hipStream_t hs = static_cast<hipStream_t>(stream);
+    const dim3 grid((unsigned)wgs), block(GEMV_THREADS);
+    const bool bf = items[0].W->dtype == WINDQ_BF16;
+    const size_t lds = gemv_lds(chunk_w);         // at most 41 KB
+    if (rpt == 2) {
+        if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, 2>), grid, block, lds, hs, B);
+        else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, 2>), grid, block, lds, hs, B);
+    } else {
+        if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, 1>), grid, block, lds, hs, B);
+        else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, 1>), grid, block, lds, hs, B);
+    }
+    hipLaunchKernelGGL(gemv_finalize_kernel, dim3((unsigned)B.row_start[n]), dim3(256), 0, hs, B);
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 
@@ -500,7 +929,7 @@ extern "C" int windq_dequant_plan(const windq_mat* W, const float* s, int32_t ch
                                   const uint8_t* codes, size_t codes_bytes, const float* scale, const float* offset,
                                   float* err, float* w_hat, void* ws, size_t ws_bytes, void* stream) {
     const DequantItem it = {W, s, mask, action, code_off, codes, codes_bytes, scale, offset, err, w_hat, nullptr, nullptr, ws, ws_bytes};
-    return dequant_launch<false>(&it, 1, chunk_w, unit_rows, stream);
+    return dequant_launch(&it, 1, chunk_w, unit_rows, stream);
 }
 
 extern "C" int windq_dequant_plan_batch(const windq_dequant_item* items, int32_t n, int32_t chunk_w, int64_t unit_rows,
@@ -510,7 +939,7 @@ extern "C" int windq_dequant_plan_batch(const windq_dequant_item* items, int32_t
     for (int32_t i = 0; i < n; ++i)
         its[i] = {items[i].W, items[i].s, items[i].mask, items[i].action, items[i].code_off, items[i].codes, items[i].codes_bytes,
                   items[i].scale, items[i].offset, items[i].err, items[i].w_hat, nullptr, nullptr, items[i].ws, items[i].ws_bytes};
-    return dequant_launch<false>(its, n, chunk_w, unit_rows, stream);
+    return dequant_launch(its, n, chunk_w, unit_rows, stream);
 }
 
 extern "C" int windq_dequant_gemv(const windq_mat* W, int32_t chunk_w, int64_t unit_rows, const uint8_t* mask,
@@ -518,7 +947,7 @@ extern "C" int windq_dequant_gemv(const windq_mat* W, int32_t chunk_w, int64_t u
                                   const float* scale, const float* offset, const float* x, float* y, void* ws,
                                   size_t ws_bytes, void* stream) {
     const DequantItem it = {W, nullptr, mask, action, code_off, codes, codes_bytes, scale, offset, nullptr, nullptr, x, y, ws, ws_bytes};
-    return dequant_launch<true>(&it, 1, chunk_w, unit_rows, stream);
+    return gemv_launch(&it, 1, chunk_w, unit_rows, stream);
 }
 
 extern "C" int windq_dequant_gemv_batch(const windq_gemv_item* items, int32_t n, int32_t chunk_w, int64_t unit_rows,
@@ -528,5 +957,5 @@ extern "C" int windq_dequant_gemv_batch(const windq_gemv_item* items, int32_t n,
     for (int32_t i = 0; i < n; ++i)
         its[i] = {items[i].W, nullptr, items[i].mask, items[i].action, items[i].code_off, items[i].codes, items[i].codes_bytes,
                   items[i].scale, items[i].offset, nullptr, nullptr, items[i].x, items[i].y, items[i].ws, items[i].ws_bytes};
-    return dequant_launch<true>(its, n, chunk_w, unit_rows, stream);
+    return gemv_launch(its, n, chunk_w, unit_rows, stream);
 }

@@ -134,6 +134,38 @@ def test_gemv_from_the_artefact(windq, R, C, G, unit_rows, K, dtype):
     gemv_case(windq, W, s, G, unit_rows, K)
 
 
+@pytest.mark.parametrize("R,C,G,unit_rows,dtype", [
+    (257, 128, 128, 0, torch.bfloat16),                 # one row more than a workgroup, one chunk
+    (513, 7 * 8, 8, 0, torch.bfloat16), (300, 7 * 24, 24, 0, torch.float32),      # rows of 1 to 24 bytes, pieces cleared to whole dwords
+    (260, 3 * 512, 512, 0, torch.bfloat16),             # the widest chunk: four to seven 16-byte steps per row
+    (512, 7 * 96, 96, 256, torch.bfloat16)])
+def test_gemv_at_the_edges_of_its_tables(windq, R, C, G, unit_rows, dtype):
+    W = synth.weights_llm(R, C, seed=121, device=DEV, dtype=dtype)
+    s = torch.ones(C, device=DEV)
+    gemv_case(windq, W, s, G, unit_rows, 4)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), 2.0 ** 120])
+def test_gemv_with_values_no_table_may_hold(windq, bad):
+    """A chunk of x with an infinity or a huge value is summed weight by weight: what the reconstruction times x gives in
+    fp32, signs and NaN included, and the other chunks as ever."""
+    W = synth.weights_llm(96, 6 * 64, seed=122, device=DEV)
+    action = torch.tensor([6, 5, 4, 6, 5, 4], dtype=torch.uint8)
+    off = windq.windq_plan_layout(action, 96, 64)
+    codes, scale, offset = windq.windq_apply_plan(W, 64, 0, action.to(DEV), None, None, off.to(DEV))
+    x = torch.randn(6 * 64, generator=torch.Generator().manual_seed(3)).to(DEV)
+    _, w_hat = windq.windq_dequant_plan(W, torch.ones(384, device=DEV), 64, 0, action.to(DEV), off.to(DEV), codes, scale, offset)
+    for u in range(3):
+        xb = x.clone()
+        xb[64 * u + 5] = bad
+        y = windq.windq_dequant_gemv(W, 64, 0, action.to(DEV), off.to(DEV), codes, scale, offset, xb).double()
+        want = (w_hat.double() * xb.double()).sum(1)
+        assert torch.equal(torch.isnan(y), torch.isnan(want)) and torch.equal(torch.isinf(y), torch.isinf(want))
+        ok = torch.isfinite(want)
+        assert bool(((y - want)[ok].abs() <= 1e-6 * (w_hat.double() * xb.double()).abs().sum(1)[ok]).all())
+        assert torch.equal(torch.sign(y[torch.isinf(want)]), torch.sign(want[torch.isinf(want)]))
+
+
 @pytest.mark.parametrize("R,C,G,unit_rows,ppm", [(256, 512, 128, 0, 30000), (70, 96, 32, 0, 300000), (24, 80, 40, 3, 100000)])
 def test_gemv_under_a_protection_mask(windq, R, C, G, unit_rows, ppm):
     W = synth.weights_llm(R, C, seed=113, device=DEV)
