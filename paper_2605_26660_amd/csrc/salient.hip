@@ -3,25 +3,29 @@
 // low-bit quantizer and stored in INT8; Eq. 5 then charges them 8 bits each.
 //
 // windq_salient_select  finds the protected set EXACTLY: the saliency threshold T of a
-//   unit is the n_p-th largest key, located by most-significant-digit radix selection on
-//   the bit pattern of the fp32 saliency (digits of 11 + 11 + 9 bits).  The first digit
-//   takes one histogram pass over W (LDS histograms flushed by integer atomics).  Its bin
-//   e0 holds well under 1 % of a unit's keys, so a second pass over W writes every mask bit
-//   that e0 decides and lists the keys of that bin with their positions; the remaining
-//   digits, the ties (weights equal to T are taken in the order of their flat index inside
-//   the unit: the first n_p - #above of them) and the listed weights' mask bits are then
-//   settled per unit from the list alone.  Units whose bin outgrows the list (a thirty-
-//   second of the unit: constant weights, say) take the remaining digits by histogram
-//   passes over W instead, count their ties per tile where they are split between kept and
+//   unit is the n_p-th largest key (the bit pattern of the fp32 saliency).  A sample of the
+//   unit's rows brackets T between two keys lo <= T < hi; ONE pass over W then writes every
+//   mask bit that the bracket decides (key >= hi: protected, key < lo: not), counts the
+//   first kind and lists the keys in between, about 1 % of the unit, with their positions.
+//   The counts prove the bracket: T lies in it if and only if n_p lies between the number
+//   above it and that plus the number in it.  The rest is settled per unit from the list alone:
+//   T by radix selection over the bracket, the ties (weights equal to T are taken in
+//   the order of their flat index inside the unit) by the same over their positions.
+//   Units whose sample misled, or whose bracket outgrows the list (a thirty-second of the
+//   unit: constant weights, say), are selected by digit passes over W instead (11 + 11 + 9
+//   bits of the key), count their ties per tile where they are split between kept and
 //   protected, and rank them in a last pass.  The result is a bit mask in the layout of W:
 //   one byte per 8 columns.
 // windq_salient_encode  stores the protected weights: per unit one symmetric scale
 //   sigma = fp32(max|w_p| / 127), codes clamp(rne(w * fp32(1/sigma)), -127, 127) in
 //   flat-index order, and the activation-weighted error of that INT8 part.
-// Everything is integer or fixed-order fp64: bit-reproducible.  Select streams W twice (the
-// units that fall back: four times, and a fifth for the tiles of those whose ties are split);
-// encode reads the mask twice and of W only the protected elements.  Every kernel takes a
-// batch of matrices, so a decoder block costs twelve launches for select and four for encode.
+// Everything is integer or fixed-order fp64: bit-reproducible.  Select streams W once and a
+// sixteenth (the units that fall back: four times more, and a fifth for the tiles of those whose
+// ties are split); encode reads of W only the pieces that hold protected weights, once.  Every kernel
+// takes a batch of matrices, so a decoder block costs eight launches for select and four for encode.
+// 7B-shaped block at 3 %: select and encode 307 us (586 with two passes over W, a histogram atomic per weight in the
+// first, and two gathers): sample 17, the pass over W 113 (3.6 TB/s; a plain copy moves 5.1), lists 26, five passes that
+// find nothing flagged 23, collect 107, codes 30.
 // None of this is on the per-step hot path (the mask of a matrix is computed once per
 // protection rate).
 #include <float.h>
@@ -40,17 +44,16 @@ struct SalArgs {
     uint8_t* mask;          // [rows][mask_ld] bytes
     int64_t mask_ld;
     Geometry g;
-    uint32_t* hist;         // [3][U][FEAT_BINS]
-    uint32_t* prefix;       // [U]  key prefix found so far; after the last digit: the threshold T
-    uint32_t* rank;         // [U]  1-based ascending rank still to find under the prefix
-    uint32_t* cnt;          // [n_tiles][2]  keys above T, keys equal to T
-    uint32_t* eq_before;    // [n_tiles]     ties in earlier tiles of the unit
-    uint32_t* need;         // [U]  ties to protect
+    uint32_t* hist;         // [3][U][FEAT_BINS]  digit histograms of flagged units
+    uint32_t* lo;           // [U]  the bracket: lo <= T < hi
+    uint32_t* hi;           // [U]
+    uint32_t* mid;          // [U]  where the sample puts T: what the pass over W takes for it inside the bracket
+    uint64_t* count;        // [U]  upper half: keys >= hi; lower half: keys in the bracket
+    uint32_t* cnt;          // [n_tiles]  select: keys equal to T; encode: protected weights, then those of earlier tiles
     uint32_t* flag;         // [U]  1: selected by digit passes over W; 0: from the unit's candidate list
     uint32_t* n_flagged;    // how many units are flagged, and ...
     uint32_t* flagged;      // [U]  ... which, in no particular order
-    uint32_t* cand_count;   // [U]  candidates listed
-    uint2* cand;            // [U][cap]  (key, flat position in the unit) of the keys in the threshold's first-digit bin
+    uint2* cand;            // [U][cap]  (key, flat position in the unit) of the keys in the bracket
     uint32_t cap;
     uint32_t use_list;      // 0: every unit takes the digit passes (mask not addressable in whole dwords)
     uint32_t n_p;           // protected weights per unit
@@ -60,17 +63,17 @@ struct SalArgs {
     float* prot_scale;      // [U]
     float* err_prot;        // [U]
     float* tile_max;        // [n_tiles]
-    uint32_t* row_off;      // [U * R_u]  protected weights in earlier rows of the unit
     double* err_part;       // [n_tiles]
 };
 
 // A launch covers up to WINDQ_MAX_BATCH matrices (one chunk width, one element type): tiles,
-// units and the workgroups that clear the histograms are numbered one matrix after the other.
+// and units are numbered one matrix after the other.
 struct SalBatch {
     int32_t n;
+    uint32_t* any_flagged;      // flagged units of all matrices
     int64_t tile_start[WINDQ_MAX_BATCH + 1];
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
-    int64_t fill_start[WINDQ_MAX_BATCH + 1];     // in workgroups of 256 counters
+    int64_t band_start[WINDQ_MAX_BATCH + 1];     // workgroups of the candidate pass
     SalArgs m[WINDQ_MAX_BATCH];
 };
 
@@ -145,22 +148,6 @@ __device__ __forceinline__ float raw_elem(const Raw8<DT>& r, int j) {
     }
 }
 
-// One element of W.
-template <int DT>
-__device__ __forceinline__ float load1g(const void* __restrict__ data, int64_t off) {
-    if (DT == WINDQ_BF16) return bf16_bits_to_f32(static_cast<const uint16_t*>(data)[off]);
-    return static_cast<const float*>(data)[off];
-}
-
-// Zeroes the digit histograms of every matrix of the launch.
-__global__ __launch_bounds__(256) void sal_clear_hist_kernel(const SalBatch B) {
-    const int mi = batch_index(B.fill_start, B.n, blockIdx.x);
-    const SalArgs& A = B.m[mi];
-    const int64_t i = ((int64_t)blockIdx.x - B.fill_start[mi]) * 256 + threadIdx.x;
-    if (i < (int64_t)3 * A.g.U * FEAT_BINS) A.hist[i] = 0u;
-    if (i == 0) *A.n_flagged = 0u;
-}
-
 // Clears the mask of a matrix (rows x mask_ld bytes, dense).
 __global__ __launch_bounds__(256) void sal_clear_mask_kernel(uint8_t* __restrict__ mask, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -179,15 +166,38 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* sh) {
     return t;
 }
 
+// ------------------------------------------------------- selection by digit passes over W
+// What the histograms of the first `levels` digits say about a flagged unit: the threshold's digits so far, and the
+// 1-based ascending rank still to find among the keys that carry them.  After the last digit the prefix is the
+// threshold T, every key of the bin equals T, and the rank left over, r, says that the wanted key is
+// the r-th of those e ties in ascending order: r - 1 of them count among the kept weights and
+// e - r + 1 among the protected ones.  Every workgroup of a pass works this out for itself.
+struct SalFound {
+    uint32_t prefix, rank, in_bin;
+};
+__device__ __forceinline__ SalFound sal_find(const SalArgs& A, int64_t u, int levels, uint32_t* sh_part, uint32_t* sh_out) {
+    SalFound f = {0u, A.rank0, 0u};
+    for (int level = 0; level < levels; ++level) {
+        const uint32_t* h = A.hist + ((size_t)level * (size_t)A.g.U + (size_t)u) * FEAT_BINS;
+        uint32_t bin;
+        uint64_t below;
+        __syncthreads();
+        select_bin<SAL_THREADS>(h, 1 << sal_bits(level), f.rank, sh_part, sh_out, &bin, &below);
+        f.rank -= (uint32_t)below;
+        f.prefix = (f.prefix << sal_bits(level)) | bin;
+        f.in_bin = h[bin];
+    }
+    return f;
+}
+
 // Histogram of digit `level` of the keys of one tile that carry the unit's prefix.
 template <int DT>
-__device__ __forceinline__ void sal_hist_tile(const SalArgs& A, const TileCoord& tc, const int level, uint32_t* lhist,
-                                              float* scol) {
+__device__ __forceinline__ void sal_hist_tile(const SalArgs& A, const TileCoord& tc, const int level, const uint32_t prefix,
+                                              uint32_t* lhist, float* scol) {
     const int32_t G = A.g.chunk_w;
     const int32_t nbins = 1 << sal_bits(level);
     for (int32_t b = threadIdx.x; b < nbins; b += SAL_THREADS) lhist[b] = 0;
     for (int32_t c = threadIdx.x; c < G; c += SAL_THREADS) scol[c] = A.s[tc.col0 + c];
-    const uint32_t prefix = level == 0 ? 0u : A.prefix[tc.u];
     __syncthreads();
     const int32_t shift = sal_shift(level), bits = sal_bits(level);
     const uint32_t dmask = (1u << bits) - 1u;
@@ -212,59 +222,14 @@ __device__ __forceinline__ void sal_hist_tile(const SalArgs& A, const TileCoord&
     }
 }
 
-// The first digit: every tile of the launch.
+// Per tile of a unit whose ties are split (some protected, some not: only then does their order
+// matter): how many keys equal the threshold.
 template <int DT>
-__global__ __launch_bounds__(SAL_THREADS) void sal_hist_kernel(const SalBatch B) {
-    __shared__ uint32_t lhist[FEAT_BINS];
-    __shared__ float scol[WINDQ_MAX_CHUNK];
-    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
-    const SalArgs& A = B.m[mi];
-    sal_hist_tile<DT>(A, tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]), 0, lhist, scol);
-}
-
-// Per unit: the bin of digit `level` that holds the wanted rank; extends the prefix.  After the
-// last digit the prefix is the threshold T, every key of the bin equals T, and the rank left
-// over, r, says that the wanted key is the r-th of those e ties in ascending order: r - 1 of
-// them count among the kept weights and need = e - r + 1 among the protected ones.
-__global__ __launch_bounds__(SAL_THREADS) void sal_prefix_kernel(const SalBatch B, const int level) {
-    __shared__ uint32_t sh_part[SAL_THREADS];
-    __shared__ uint32_t sh_out[4];
-    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
-    const SalArgs& A = B.m[mi];
-    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
-    if (level > 0 && A.flag[u] == 0u) return;
-    const uint32_t rank = level == 0 ? A.rank0 : A.rank[u];
-    const uint32_t prefix = level == 0 ? 0u : A.prefix[u];
-    const uint32_t* h = A.hist + ((size_t)level * (size_t)A.g.U + (size_t)u) * FEAT_BINS;
-    uint32_t bin;
-    uint64_t below;
-    select_bin<SAL_THREADS>(h, 1 << sal_bits(level), rank, sh_part, sh_out, &bin, &below);
-    if (threadIdx.x == 0) {
-        const uint32_t left = rank - (uint32_t)below;
-        A.prefix[u] = (prefix << sal_bits(level)) | bin;
-        A.rank[u] = left;
-        if (level == 2) A.need[u] = h[bin] - left + 1u;
-        if (level == 0) {
-            // the keys of this bin decide the rest: few enough for the unit's list?
-            const bool listed = A.use_list != 0u && h[bin] <= A.cap;
-            A.flag[u] = listed ? 0u : 1u;
-            A.cand_count[u] = 0u;
-            if (!listed) A.flagged[atomicAdd(A.n_flagged, 1u)] = (uint32_t)u;
-        }
-    }
-}
-
-// Which of a unit's ties are protected depends on their order only when some of them are not
-// (rank left over above 1); otherwise all are, and nothing has to be counted.
-__device__ __forceinline__ bool ties_split(const SalArgs& A, int64_t u) { return A.rank[u] > 1u; }
-
-// Per tile of a unit whose ties are split: how many keys equal the threshold.
-template <int DT>
-__device__ __forceinline__ void sal_count_tile(const SalArgs& A, const TileCoord& tc, float* scol, uint32_t* sh) {
-    if (!ties_split(A, tc.u)) return;
+__device__ __forceinline__ void sal_count_tile(const SalArgs& A, const TileCoord& tc, const SalFound& f, float* scol, uint32_t* sh) {
+    if (f.rank <= 1u) return;
     const int32_t G = A.g.chunk_w;
     for (int32_t c = threadIdx.x; c < G; c += SAL_THREADS) scol[c] = A.s[tc.col0 + c];
-    const uint32_t T = A.prefix[tc.u];
+    const uint32_t T = f.prefix;
     __syncthreads();
     const int32_t pieces = G >> 3;
     const int32_t total = tc.nrows * pieces;
@@ -282,19 +247,20 @@ __device__ __forceinline__ void sal_count_tile(const SalArgs& A, const TileCoord
 }
 
 // Exclusive prefix sum over a workgroup, in thread order (all SAL_THREADS threads call it);
-// *total receives the sum.
-__device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t v, uint32_t* sh, uint32_t* total) {
+// *total receives the sum.  T: u32 or u64 (two or four counts side by side).
+template <typename T>
+__device__ __forceinline__ T block_exclusive_scan(T v, T* sh, T* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = v;
+    T inc = v;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(inc, d, 64);
+        const T t = __shfl_up(inc, d, 64);
         if (lane >= d) inc += t;
     }
     __syncthreads();
     if (lane == 63) sh[wave] = inc;
     __syncthreads();
-    uint32_t excl = inc - v, tot = 0;
+    T excl = inc - v, tot = 0;
     for (int w = 0; w < SAL_THREADS / 64; ++w) {
         if (w < wave) excl += sh[w];
         tot += sh[w];
@@ -303,40 +269,23 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t v, uint32_
     return excl;
 }
 
-// Per unit: ties in earlier tiles (tile order = row order); zeros where the ties are not split.
-__global__ __launch_bounds__(SAL_THREADS) void sal_scan_kernel(const SalBatch B) {
-    __shared__ uint32_t sh[SAL_THREADS / 64];
-    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
-    const SalArgs& A = B.m[mi];
-    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
-    if (A.flag[u] == 0u) return;
-    const int64_t T = A.g.tiles_per_unit;
-    const size_t base = (size_t)u * (size_t)T;
-    const bool split = ties_split(A, u);
-    uint32_t carry = 0;
-    for (int64_t t0 = 0; t0 < T; t0 += SAL_THREADS) {
-        const int64_t t = t0 + threadIdx.x;
-        const uint32_t eq = split && t < T ? A.cnt[base + t] : 0u;
-        uint32_t tot;
-        const uint32_t excl = block_exclusive_scan_u32(eq, sh, &tot);
-        if (t < T) A.eq_before[base + t] = carry + excl;
-        carry += tot;
-    }
-}
-
 // Per tile: the protection bits.  A thread takes eight consecutive columns of a row, i.e. one
 // byte of the mask, straight from HBM; threads walk the tile in flat-index order.  Where the
 // unit's ties are split, a tie is protected when its rank among the unit's ties, in flat-index
 // order, is below `need`: ties in earlier tiles, plus a scan over the workgroup's threads, plus
 // the thread's own eight in order.  Elsewhere every tie is protected and nothing is ranked.
 template <int DT>
-__device__ __forceinline__ void sal_mask_tile(const SalArgs& A, const TileCoord& tc, float* scol, uint32_t* sh) {
+__device__ __forceinline__ void sal_mask_tile(const SalArgs& A, const TileCoord& tc, const SalFound& f, float* scol, uint32_t* sh) {
     const int32_t G = A.g.chunk_w;
     for (int32_t c = threadIdx.x; c < G; c += SAL_THREADS) scol[c] = A.s[tc.col0 + c];
-    const uint32_t T = A.prefix[tc.u];
-    const uint32_t need = A.need[tc.u];
-    const bool split = ties_split(A, tc.u);
-    uint32_t carry = split ? A.eq_before[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t] : 0u;
+    const uint32_t T = f.prefix;
+    const uint32_t need = f.in_bin - f.rank + 1u;
+    const bool split = f.rank > 1u;
+    uint32_t carry = 0;
+    if (split) {
+        for (int64_t i = threadIdx.x; i < tc.t; i += SAL_THREADS) carry += A.cnt[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)i];
+        carry = block_sum_u32(carry, sh);
+    }
     __syncthreads();
     const int32_t pieces = G >> 3;
     const int32_t total = tc.nrows * pieces;
@@ -359,7 +308,7 @@ __device__ __forceinline__ void sal_mask_tile(const SalArgs& A, const TileCoord&
         uint32_t byte = 0;
         if (split) {                                   // uniform over the workgroup
             uint32_t tot;
-            uint32_t tie_rank = carry + block_exclusive_scan_u32(eq, sh, &tot);
+            uint32_t tie_rank = carry + block_exclusive_scan(eq, sh, &tot);
             carry += tot;
             if (valid) {
 #pragma unroll
@@ -380,345 +329,593 @@ __device__ __forceinline__ void sal_mask_tile(const SalArgs& A, const TileCoord&
     }
 }
 
-// The later digits, the tie counts and the masks of the units that do not select from a list: a
+// The digits, the tie counts and the masks of the units that do not select from a list: a
 // fixed grid walks the tiles of the listed ("flagged") units of every matrix of the launch; with
 // none flagged it returns at once.
-constexpr int SAL_FLAGGED_GRID = 1024;
+constexpr int SAL_FLAGGED_GRID = 512;
 constexpr int SAL_WHAT_HIST = 0, SAL_WHAT_COUNT = 1, SAL_WHAT_MASK = 2;
 template <int DT, int WHAT>
 __global__ __launch_bounds__(SAL_THREADS) void sal_flagged_kernel(const SalBatch B, const int level) {
+    if (*B.any_flagged == 0u) return;
     __shared__ uint32_t lhist[WHAT == SAL_WHAT_HIST ? FEAT_BINS : 1];
     __shared__ float scol[WINDQ_MAX_CHUNK];
-    __shared__ uint32_t sh[SAL_THREADS / 64];
+    __shared__ uint32_t sh[SAL_THREADS / 64], sh_part[SAL_THREADS / 64], sh_out[2];
     for (int mi = 0; mi < B.n; ++mi) {
         const SalArgs& A = B.m[mi];
         const int64_t items = (int64_t)*A.n_flagged * A.g.tiles_per_unit;
         for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
             const int64_t f = it / A.g.tiles_per_unit;
             const TileCoord tc = tile_coord_of_unit(A.g, (int64_t)A.flagged[f], it - f * A.g.tiles_per_unit);
+            const SalFound found = sal_find(A, tc.u, WHAT == SAL_WHAT_HIST ? level : 3, sh_part, sh_out);
             __syncthreads();        // the previous tile's shared state is no longer read
-            if (WHAT == SAL_WHAT_HIST) sal_hist_tile<DT>(A, tc, level, lhist, scol);
-            else if (WHAT == SAL_WHAT_COUNT) sal_count_tile<DT>(A, tc, scol, sh);
-            else sal_mask_tile<DT>(A, tc, scol, sh);
+            if (WHAT == SAL_WHAT_HIST) sal_hist_tile<DT>(A, tc, level, found.prefix, lhist, scol);
+            else if (WHAT == SAL_WHAT_COUNT) sal_count_tile<DT>(A, tc, found, scol, sh);
+            else sal_mask_tile<DT>(A, tc, found, scol, sh);
         }
     }
 }
 
 // ------------------------------------------------- selection from the unit's candidate list
-// Units whose threshold bin (first digit e0) is small enough -- all but degenerate ones -- need no
-// further digit pass over W.  One pass writes the mask bits that e0 already decides (first digit
-// above e0: protected; below: not) and lists the keys whose first digit IS e0 with their flat
-// position; one workgroup per unit then finds the threshold, and the ties to take, in the list and
-// sets the remaining bits.  Two reads of W in all.
-constexpr int SAL_CAND_ITERS = 4;       // 16-byte pieces a thread holds at once
+// The bin (of nbins, a multiple of 64 up to FEAT_BINS) of a histogram in LDS that holds the 1-based ascending rank, and
+// the count below it, by one wavefront: a lane adds a run of bins (starting each at its own bank), the lanes of the
+// run that holds the rank then take a bin each.
+__device__ __forceinline__ void wave_select_bin(const uint32_t* __restrict__ h, int nbins, uint32_t rank, uint32_t* bin, uint32_t* below) {
+    const int lane = threadIdx.x & 63, run = nbins >> 6;
+    uint32_t sum = 0u;
+    for (int j = 0; j < run; ++j) sum += h[lane * run + ((j + lane) % run)];
+    uint32_t inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t v = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += v;
+    }
+    const uint64_t reached = __ballot(inc >= rank);
+    const int at = reached != 0ull ? __ffsll((unsigned long long)reached) - 1 : 63;
+    uint32_t base = __shfl(inc - sum, at, 64);
+    const uint32_t own = lane < run ? h[at * run + lane] : 0u;
+    uint32_t in = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t v = __shfl_up(in, d, 64);
+        if (lane >= d) in += v;
+    }
+    const uint64_t hit = __ballot(lane < run && base + in >= rank);
+    const int b = hit != 0ull ? __ffsll((unsigned long long)hit) - 1 : run - 1;
+    *bin = (uint32_t)(at * run + b);
+    *below = base + __shfl(in - own, b, 64);
+}
+
+// The bracket, from a sample of whole rows evenly spread over the unit: up to 32768 weights, at least
+// 4096, and half the unit between (so that small units are read one and a half times, not twice).  With p_s
+// protected weights expected in the sample the bracket reaches from rank p_s + d to p_s - d,
+//     d = 5 standard deviations of a random sample's count + 4 % of p_s + 8,
+// to a 128th of an octave: 1 % of a 524288-weight unit at a 3 % rate.  The margin decides nothing but how often a
+// unit has to be selected the long way; whether the bracket holds is counted.
+constexpr int SAL_BIG = 1024;               // threads of the per-unit kernels
+constexpr int SAL_SAMPLE_PIECES = 4096;     // most 8-weight pieces a unit's sample holds
 template <int DT>
-__global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B) {
+__global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
+    __shared__ uint32_t lh[FEAT_BINS];
+    __shared__ uint32_t sh_bin[3], sh_below[3];
     __shared__ float scol[WINDQ_MAX_CHUNK];
-    __shared__ uint32_t sh[SAL_THREADS / 64];
-    __shared__ uint32_t sh_base;
-    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
+    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
     const SalArgs& A = B.m[mi];
-    const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]);
-    if (A.flag[tc.u] != 0u) return;
+    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    if (threadIdx.x == 0) {
+        A.count[u] = 0ull;
+        A.flag[u] = A.use_list != 0u ? 0u : 1u;
+        if (u == 0) *A.n_flagged = 0u;
+        if (u == 0 && mi == 0) *B.any_flagged = 0u;
+    }
+    if (A.use_list == 0u) return;
     const int32_t G = A.g.chunk_w;
-    for (int32_t c = threadIdx.x; c < G; c += SAL_THREADS) scol[c] = A.s[tc.col0 + c];
-    const uint32_t e0 = A.prefix[tc.u];
-    uint2* __restrict__ list = A.cand + (size_t)tc.u * (size_t)A.cap;
-    __syncthreads();
     const int32_t pieces = G >> 3;
-    const int32_t total = tc.nrows * pieces;
-    PieceWalk walk((int32_t)threadIdx.x, SAL_THREADS, pieces);
-    for (int32_t i0 = 0; i0 < total; i0 += SAL_CAND_ITERS * SAL_THREADS) {
-        Raw8<DT> raw[SAL_CAND_ITERS];           // kept as loaded: the keys of a candidate piece are formed again
-        uint32_t cm[SAL_CAND_ITERS];            // which of a piece's eight keys are candidates
-        int32_t rk[SAL_CAND_ITERS], pk[SAL_CAND_ITERS];      // row and piece of each
-        uint32_t n_mine = 0;
+    const int64_t rb = u / A.g.n_chunks;
+    const int64_t col0 = (u - rb * A.g.n_chunks) * G;
+    // rows of the sample
+    int64_t want = A.g.R_u * pieces / 2;
+    if (want < SAL_SAMPLE_PIECES / 8) want = SAL_SAMPLE_PIECES / 8;
+    if (want > SAL_SAMPLE_PIECES) want = SAL_SAMPLE_PIECES;
+    int64_t rows = want / pieces;
+    if (rows > A.g.R_u) rows = A.g.R_u;                    // at least 8 for the widest chunk (64 pieces)
+    const int64_t stride = A.g.R_u / rows;
+    const int32_t total = (int32_t)rows * pieces;
+    for (int32_t b = threadIdx.x; b < FEAT_BINS; b += SAL_BIG) lh[b] = 0u;
+    for (int32_t c = threadIdx.x; c < G; c += SAL_BIG) scol[c] = A.s[col0 + c];
+    __syncthreads();
+    constexpr int PER = SAL_SAMPLE_PIECES / SAL_BIG;
+    uint32_t key[PER][8];
+    Raw8<DT> raw[PER];
 #pragma unroll
-        for (int k = 0; k < SAL_CAND_ITERS; ++k) {
-            const int32_t i = i0 + k * SAL_THREADS + (int32_t)threadIdx.x;
-            rk[k] = walk.r;
-            pk[k] = walk.pc;
-            walk.next();
-            if (i < total) raw[k] = load8raw<DT>(A.W, (tc.row0 + rk[k]) * A.g.ld + tc.col0 + pk[k] * 8);
+    for (int k = 0; k < PER; ++k) {
+        const int32_t i = k * SAL_BIG + (int32_t)threadIdx.x;
+        if (i < total) {
+            const int32_t r = (int32_t)((uint32_t)i / (uint32_t)pieces), pc = i - r * pieces;
+            raw[k] = load8raw<DT>(A.W, (rb * A.g.R_u + r * stride + stride / 2) * A.g.ld + col0 + pc * 8);
         }
+    }
 #pragma unroll
-        for (int k = 0; k < SAL_CAND_ITERS; ++k) {
-            const int32_t i = i0 + k * SAL_THREADS + (int32_t)threadIdx.x;
-            cm[k] = 0u;
+    for (int k = 0; k < PER; ++k) {
+        const int32_t i = k * SAL_BIG + (int32_t)threadIdx.x;
+        if (i < total) {
+            const int32_t pc = (int32_t)((uint32_t)i % (uint32_t)pieces);
+            float w[8];
+            unpack8raw<DT>(raw[k], w);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                key[k][j] = sal_key(w[j], scol[pc * 8 + j]);
+                atomicAdd(&lh[key[k][j] >> 20], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    // ranks from the top, 1-based, of the bracket's ends
+    const double n_s = (double)total * 8.0, n = (double)A.g.R_u * (double)G;
+    const double f = n_s / n, p_s = (double)A.n_p * f;
+    const double d = 5.0 * sqrt(p_s * (1.0 - f)) + 0.04 * p_s + 8.0;
+    const uint32_t ns = (uint32_t)total * 8u;
+    // (the first three wavefronts look for one of them each)
+    const int wave = threadIdx.x >> 6;
+    const bool open = wave == 0 ? p_s + d >= n_s : (wave == 1 && p_s - d < 1.0);
+    const double place = wave == 0 ? p_s + d : (wave == 1 ? p_s - d : (p_s < 1.0 ? 1.0 : p_s));
+    const uint32_t rank = open ? (wave == 0 ? 1u : ns) : ns - (uint32_t)place + 1u;      // ascending
+    uint32_t bin = 0, below = 0;
+    if (wave < 3) {
+        wave_select_bin(lh, FEAT_BINS, rank, &bin, &below);
+        if ((threadIdx.x & 63) == 0) {
+            sh_bin[wave] = bin;
+            sh_below[wave] = below;
+        }
+    }
+    __syncthreads();
+    // the next four bits of the keys from the lowest of the three bins to the highest
+    const uint32_t first = sh_bin[0], below0 = sh_below[0];
+    const uint32_t span = (sh_bin[1] - first + 1u) * 16u;
+    const bool narrow = span <= FEAT_BINS;                                                // else: sixteen octaves wide
+    for (int32_t b = threadIdx.x; b < FEAT_BINS; b += SAL_BIG) lh[b] = 0u;
+    __syncthreads();
+    if (narrow) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int32_t i = k * SAL_BIG + (int32_t)threadIdx.x;
             if (i < total) {
-                const int32_t r = rk[k], pc = pk[k];
-                float w[8];
-                unpack8raw<DT>(raw[k], w);
-                uint32_t byte = 0;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const uint32_t d0 = sal_key(w[j], scol[pc * 8 + j]) >> sal_shift(0);
-                    byte |= (d0 > e0 ? 1u : 0u) << j;
-                    cm[k] |= (d0 == e0 ? 1u : 0u) << j;
-                }
-                A.mask[(tc.row0 + r) * A.mask_ld + (tc.col0 >> 3) + pc] = (uint8_t)byte;
-                n_mine += (uint32_t)__builtin_popcount(cm[k]);
-            }
-        }
-        // one place in the unit's list for the workgroup's candidates, then each thread's share of it
-        // (one atomic per tile: four per tile, one a wavefront, took 2.5 times as long - the answers to
-        // atomics on one counter come back one after the other)
-        uint32_t tot;
-        uint32_t at = block_exclusive_scan_u32(n_mine, sh, &tot);
-        if (threadIdx.x == 0) sh_base = tot != 0u ? atomicAdd(&A.cand_count[tc.u], tot) : 0u;
-        __syncthreads();
-        at += sh_base;
-#pragma unroll
-        for (int k = 0; k < SAL_CAND_ITERS; ++k) {
-            if (cm[k] != 0u) {
-                const int32_t r = rk[k], pc = pk[k];
-                const uint32_t pos0 = (uint32_t)(tc.lrow0 + r) * (uint32_t)G + (uint32_t)pc * 8u;
-                for (uint32_t m = cm[k]; m != 0u; m &= m - 1u) {        // usually one bit
-                    const int j = __ffs(m) - 1;
-                    if (at < A.cap) list[at] = make_uint2(sal_key(raw_elem<DT>(raw[k], j), scol[pc * 8 + j]), pos0 + (uint32_t)j);
-                    ++at;
+                    const uint32_t q = (key[k][j] >> 16) - (first << 4);
+                    if (q < span) atomicAdd(&lh[q], 1u);
                 }
             }
         }
-        __syncthreads();        // sh_base is read before the next round overwrites it
+    }
+    __syncthreads();
+    if (wave < 3) {
+        uint32_t q = (bin - first) << 4, lower;
+        if (narrow) wave_select_bin(lh, FEAT_BINS, rank - below0, &q, &lower);
+        const uint32_t start = ((first << 4) + q) << 16;                                  // of the 128th of an octave that holds the rank
+        if ((threadIdx.x & 63) == 0) {
+            if (wave == 0) A.lo[u] = open ? 0u : start;
+            else if (wave == 1) A.hi[u] = open ? 0x80000000u : start + (narrow ? 0x10000u : 0x100000u);      // above every key where open
+            else A.mid[u] = start;
+        }
     }
 }
 
-// Histogram of `bits` bits at `shift` of field x (0: key, 1: position) of the list's entries that
-// satisfy pred, then the bin of 1-based ascending rank `rank`; returns the bin, the count below it
-// and the bin's own count.  All SAL_THREADS threads call it.
-template <typename Pred>
-__device__ __forceinline__ void list_digit(const uint2* __restrict__ list, uint32_t n, int field, int shift, int bits,
-                                           uint32_t rank, Pred pred, uint32_t* lh, uint32_t* sh_part, uint32_t* sh_out,
-                                           uint32_t* bin, uint32_t* below, uint32_t* in_bin) {
+// bits = 2 bits + (key >= limit): a compare into the carry and an add with carry, where the compiler makes a
+// compare, a select, a shift and an or of the same in C.
+__device__ __forceinline__ void push_ge(uint32_t& bits, uint32_t key, uint32_t limit) {
+    asm("v_cmp_le_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(key), "s"(limit) : "vcc");
+}
+
+// The pass over W: the mask (inside the bracket as if T were `mid`), the counts, the list.  Bound by HBM: per weight one multiply and two
+// pushes of a bit.  A workgroup takes 256 rows of a unit and no wavefront waits for another in its loop: candidates go
+// into the workgroup's LDS in any order (the list has none), and are moved to the unit's list with ONE global atomic at
+// the end.  (With a scan, a global atomic and two barriers per 64-row tile the pass took 157 us per 7B-shaped block.)
+constexpr int SAL_CAND_ITERS = 4;       // pieces of 8 weights that a thread has in flight: more take registers from the other wavefronts
+constexpr int SAL_CAND_TILES = 4;       // tiles per workgroup
+constexpr uint32_t SAL_CAND_BUF = 2048; // candidates the LDS holds; beyond that they go straight to the list
+// FIXED: a thread's pieces all lie in the same columns (the pieces of a row divide the workgroup), its scales stay in registers
+template <int DT, bool FIXED>
+__global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B) {
+    __shared__ __align__(16) float scol[WINDQ_MAX_CHUNK];
+    __shared__ uint2 buf[SAL_CAND_BUF];
+    __shared__ uint32_t sh[SAL_THREADS / 64];
+    __shared__ uint32_t n_buf, base;
+    const int mi = batch_index(B.band_start, B.n, blockIdx.x);
+    const SalArgs& A = B.m[mi];
+    // chunks side by side, then row ranges, then row blocks
+    const uint32_t idx = (uint32_t)((int64_t)blockIdx.x - B.band_start[mi]), nc = (uint32_t)A.g.n_chunks;
+    const uint32_t ranges = (uint32_t)((A.g.tiles_per_unit + SAL_CAND_TILES - 1) / SAL_CAND_TILES);
+    const uint32_t band = idx / nc, j0 = idx - band * nc;
+    const uint32_t rb = band / ranges, rr = band - rb * ranges;
+    const int64_t u = (int64_t)rb * nc + j0;
+    if (A.flag[u] != 0u) return;
+    const int64_t lrow0 = (int64_t)rr * (SAL_CAND_TILES * TILE_ROWS), row0 = (int64_t)rb * A.g.R_u + lrow0;
+    const int64_t left = A.g.R_u - lrow0;
+    const int32_t nrows = left < SAL_CAND_TILES * TILE_ROWS ? (int32_t)left : SAL_CAND_TILES * TILE_ROWS;
+    const int32_t G = A.g.chunk_w;
+    const int64_t col0 = (int64_t)j0 * G;
+    const int32_t pieces = G >> 3;
+    for (int32_t c = threadIdx.x; c < G; c += SAL_THREADS) scol[c] = A.s[col0 + c];
+    if (threadIdx.x == 0) n_buf = 0u;
+    const uint32_t lo = A.lo[u], hi = A.hi[u], mid = A.mid[u];
+    uint2* __restrict__ list = A.cand + (size_t)u * (size_t)A.cap;
+    const int32_t total = nrows * pieces;
+    PieceWalk walk((int32_t)threadIdx.x, SAL_THREADS, pieces);
+    __syncthreads();
+    float sc[8];
+    if (FIXED) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sc[j] = scol[walk.pc * 8 + j];
+    }
+    constexpr int NB = SAL_CAND_ITERS;
+    uint32_t n_above = 0u;
+    for (int32_t i0 = threadIdx.x; i0 < total; i0 += NB * SAL_THREADS) {
+        Raw8<DT> raw[NB];                       // kept as loaded: the keys of a candidate piece are formed again
+        int32_t rk[NB], pk[NB];                 // row and piece of each
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            rk[k] = walk.r;
+            pk[k] = walk.pc;
+            walk.next();
+            if (i0 + k * SAL_THREADS < total) raw[k] = load8raw<DT>(A.W, (row0 + rk[k]) * A.g.ld + col0 + pk[k] * 8);
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (i0 + k * SAL_THREADS >= total) break;
+            float w[8];
+            unpack8raw<DT>(raw[k], w);
+            if (!FIXED) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) sc[j] = scol[pk[k] * 8 + j];
+            }
+            uint32_t above = 0u, in = 0u;
+#pragma unroll
+            for (int j = 7; j >= 0; --j) {
+                const uint32_t key = sal_key(w[j], sc[j]);
+                push_ge(above, key, hi);
+                push_ge(in, key, lo);
+            }
+            n_above += (uint32_t)__builtin_popcount(above);
+            in ^= above;
+            if (in != 0u) {
+                const uint32_t pos0 = (uint32_t)(lrow0 + rk[k]) * (uint32_t)G + (uint32_t)pk[k] * 8u;
+                uint32_t at = atomicAdd(&n_buf, (uint32_t)__builtin_popcount(in));
+                for (uint32_t m = in; m != 0u; m &= m - 1u, ++at) {        // usually one bit
+                    const int j = __ffs(m) - 1;
+                    const uint2 e = make_uint2(sal_key(raw_elem<DT>(raw[k], j), scol[pk[k] * 8 + j]), pos0 + (uint32_t)j);
+                    above |= (e.x >= mid ? 1u : 0u) << j;
+                    if (at < SAL_CAND_BUF) {
+                        buf[at] = e;
+                    } else {
+                        const uint32_t g = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&A.count[u]), 1ull);
+                        if (g < A.cap) list[g] = e;
+                    }
+                }
+            }
+            A.mask[(row0 + rk[k]) * A.mask_ld + (col0 >> 3) + pk[k]] = (uint8_t)above;
+        }
+    }
+    n_above = block_sum_u32(n_above, sh);       // (and a barrier: the buffer is complete)
+    const uint32_t n = min(n_buf, SAL_CAND_BUF);
+    if (threadIdx.x == 0 && (n | n_above) != 0u)
+        base = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&A.count[u]), ((unsigned long long)n_above << 32) | n);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += SAL_THREADS)
+        if (base + i < A.cap) list[base + i] = buf[i];
+}
+
+// The bin of 1-based ascending rank `rank` among the list's entries that satisfy pred, by `value`; returns the bin,
+// the count below it and the bin's own count.  All SAL_BIG threads call it.
+template <typename Value, typename Pred>
+__device__ __forceinline__ void list_digit(const uint2* __restrict__ list, uint32_t n, int bits, uint32_t rank, Value value, Pred pred,
+                                           uint32_t* lh, uint32_t* sh_part, uint32_t* sh_out, uint32_t* bin, uint32_t* below,
+                                           uint32_t* in_bin) {
     const int32_t nbins = 1 << bits;
     __syncthreads();
-    for (int32_t b = threadIdx.x; b < nbins; b += SAL_THREADS) lh[b] = 0u;
+    for (int32_t b = threadIdx.x; b < nbins; b += SAL_BIG) lh[b] = 0u;
     __syncthreads();
-    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * SAL_THREADS) {       // four loads in flight per thread
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * SAL_BIG) {       // four loads in flight per thread
         uint2 e[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (i0 + k * SAL_THREADS < n) e[k] = list[i0 + k * SAL_THREADS];
+            if (i0 + k * SAL_BIG < n) e[k] = list[i0 + k * SAL_BIG];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (i0 + k * SAL_THREADS < n && pred(e[k]))
-                atomicAdd(&lh[((field == 0 ? e[k].x : e[k].y) >> shift) & (uint32_t)(nbins - 1)], 1u);
+            if (i0 + k * SAL_BIG < n && pred(e[k])) atomicAdd(&lh[value(e[k]) & (uint32_t)(nbins - 1)], 1u);
     }
     __syncthreads();
     uint64_t bl;
-    select_bin<SAL_THREADS>(lh, nbins, rank, sh_part, sh_out, bin, &bl);
+    select_bin<SAL_BIG>(lh, nbins, rank, sh_part, sh_out, bin, &bl);
     *below = (uint32_t)bl;
     *in_bin = lh[*bin];
 }
 
-// Per unit: the threshold among the listed keys (their first digit is e0; digits of 11 and 9 bits
-// remain), the ties to take (by smallest flat position: three digits of the position), and the
-// mask bits of every listed weight that is protected.
-__global__ __launch_bounds__(SAL_THREADS) void sal_list_kernel(const SalBatch B) {
+// Corrects the mask bit of a listed weight where the pass over W guessed it wrong.  (Setting the bit of every protected
+// weight on the list, half of them, took 35 us per 7B-shaped block: scattered atomics run at about 34 a nanosecond.)
+__device__ __forceinline__ void settle(const SalArgs& A, int64_t rb, int64_t col0, uint32_t mid, const uint2& e, bool prot) {
+    if (prot == (e.x >= mid)) return;
+    const uint32_t G = (uint32_t)A.g.chunk_w;
+    const uint32_t r = e.y / G, c = e.y - r * G;
+    const int64_t byte = (rb * A.g.R_u + (int64_t)r) * A.mask_ld + ((col0 + (int64_t)c) >> 3);
+    atomicXor(reinterpret_cast<uint32_t*>(A.mask + (byte & ~(int64_t)3)), 1u << (8u * (uint32_t)(byte & 3) + (c & 7u)));
+}
+
+// Per unit: does the bracket hold the threshold, and the list the bracket?  If not, the unit is flagged.  If so: the
+// threshold's bin among 2048 over the bracket's width, by one pass over the list; a second settles the mask bits of the
+// weights outside that bin and gathers the bin's own, a handful, which are ranked one against another (key, then flat
+// position).  A bin of more than SAL_BIN weights (ties) is resolved digit by digit instead: the threshold, then, where
+// ties are split, the last position taken, by three digits of the position.
+constexpr uint32_t SAL_BIN = 1024;
+__global__ __launch_bounds__(SAL_BIG) void sal_list_kernel(const SalBatch B) {
     __shared__ uint32_t lh[FEAT_BINS];
-    __shared__ uint32_t sh_part[SAL_THREADS];
-    __shared__ uint32_t sh_out[4];
+    __shared__ uint2 own[SAL_BIN];
+    __shared__ uint32_t n_own;
+    __shared__ uint32_t sh_part[SAL_BIG / 64];
+    __shared__ uint32_t sh_out[2];
     const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
     const SalArgs& A = B.m[mi];
     const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
-    if (A.flag[u] != 0u) return;
+    const uint64_t count = A.count[u];
+    const uint32_t n = (uint32_t)count, above = (uint32_t)(count >> 32);
+    if (A.flag[u] != 0u || n > A.cap || above > A.n_p || A.n_p - above > n) {
+        for (int32_t i = threadIdx.x; i < 3 * FEAT_BINS; i += SAL_BIG)
+            A.hist[((size_t)(i / FEAT_BINS) * (size_t)A.g.U + (size_t)u) * FEAT_BINS + (size_t)(i % FEAT_BINS)] = 0u;
+        if (threadIdx.x == 0) {
+            A.flagged[atomicAdd(A.n_flagged, 1u)] = (uint32_t)u;
+            atomicAdd(B.any_flagged, 1u);
+        }
+        return;
+    }
+    const uint32_t take = A.n_p - above;                  // of the listed weights
     const uint2* __restrict__ list = A.cand + (size_t)u * (size_t)A.cap;
-    const uint32_t n = min(A.cand_count[u], A.cap);
-    uint32_t b1, b2, below, in_bin;
-    list_digit(list, n, 0, sal_shift(1), sal_bits(1), A.rank[u], [](const uint2&) { return true; }, lh, sh_part, sh_out,
-               &b1, &below, &in_bin);
-    const uint32_t r1 = A.rank[u] - below;
-    list_digit(list, n, 0, sal_shift(2), sal_bits(2), r1,
-               [=](const uint2& e) { return ((e.x >> sal_shift(1)) & ((1u << sal_bits(1)) - 1u)) == b1; }, lh, sh_part,
-               sh_out, &b2, &below, &in_bin);
-    const uint32_t T = (A.prefix[u] << (sal_bits(1) + sal_bits(2))) | (b1 << sal_bits(2)) | b2;
-    const uint32_t ties = in_bin;
-    const uint32_t need = ties - (r1 - below) + 1u;      // the rank left over counts the ties that stay unprotected, plus one
+    const uint32_t lo = A.lo[u], width = A.hi[u] - 1u - lo, mid = A.mid[u];
+    const int64_t rb = u / A.g.n_chunks;
+    const int64_t col0 = (u - rb * A.g.n_chunks) * A.g.chunk_w;
+    if (take == 0u) {
+        for (uint32_t i = threadIdx.x; i < n; i += SAL_BIG) settle(A, rb, col0, mid, list[i], false);
+        return;
+    }
+    uint32_t left = n - take + 1u, prefix = 0u, ties = n, below, bin;
+    if (threadIdx.x == 0) n_own = 0u;
+    for (int rem = width == 0u ? 0 : 32 - __builtin_clz(width); rem > 0;) {
+        const int bits = rem < FEAT_DIGIT_BITS ? rem : FEAT_DIGIT_BITS, shift = rem - bits;
+        list_digit(list, n, bits, left, [=](const uint2& e) { return (e.x - lo) >> shift; },
+                   [=](const uint2& e) { return rem == 32 || ((e.x - lo) >> rem) == prefix; }, lh, sh_part, sh_out, &bin, &below, &ties);
+        prefix = (prefix << bits) | bin;
+        left -= below;
+        rem = shift;
+        if (ties > SAL_BIN) continue;
+        // `ties` weights share the digits found so far; the last ties - left + 1 of them are protected, and so is all above
+        for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * SAL_BIG) {
+            uint2 e[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (i0 + k * SAL_BIG < n) e[k] = list[i0 + k * SAL_BIG];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (i0 + k * SAL_BIG >= n) continue;
+                const uint32_t d = (e[k].x - lo) >> shift;
+                if (d == prefix) own[atomicAdd(&n_own, 1u)] = e[k];
+                else settle(A, rb, col0, mid, e[k], d > prefix);
+            }
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < ties; i += SAL_BIG) {
+            uint32_t ahead = 0u;
+            for (uint32_t q = 0; q < ties; ++q) ahead += own[q].x > own[i].x || (own[q].x == own[i].x && own[q].y < own[i].y) ? 1u : 0u;
+            settle(A, rb, col0, mid, own[i], ahead < ties - left + 1u);
+        }
+        return;
+    }
+    const uint32_t T = lo + prefix;
+    const uint32_t need = ties - left + 1u;              // the rank left over counts the ties that stay unprotected, plus one
     uint32_t pos_max = 0xffffffffu;                        // ties up to this position are protected
     if (need < ties) {
         // the need-th smallest position among the ties (positions are distinct): digits of 11, 11, 10 bits
-        uint32_t p1, p2, p3, bl;
-        list_digit(list, n, 1, 21, 11, need, [=](const uint2& e) { return e.x == T; }, lh, sh_part, sh_out, &p1, &bl, &in_bin);
+        uint32_t p1, p2, p3, bl, in_bin;
+        list_digit(list, n, 11, need, [](const uint2& e) { return e.y >> 21; }, [=](const uint2& e) { return e.x == T; }, lh, sh_part,
+                   sh_out, &p1, &bl, &in_bin);
         const uint32_t n1 = need - bl;
-        list_digit(list, n, 1, 10, 11, n1, [=](const uint2& e) { return e.x == T && (e.y >> 21) == p1; }, lh, sh_part, sh_out,
-                   &p2, &bl, &in_bin);
+        list_digit(list, n, 11, n1, [](const uint2& e) { return e.y >> 10; }, [=](const uint2& e) { return e.x == T && (e.y >> 21) == p1; },
+                   lh, sh_part, sh_out, &p2, &bl, &in_bin);
         const uint32_t n2 = n1 - bl;
-        list_digit(list, n, 1, 0, 10, n2, [=](const uint2& e) { return e.x == T && (e.y >> 10) == ((p1 << 11) | p2); }, lh,
-                   sh_part, sh_out, &p3, &bl, &in_bin);
+        list_digit(list, n, 10, n2, [](const uint2& e) { return e.y; },
+                   [=](const uint2& e) { return e.x == T && (e.y >> 10) == ((p1 << 11) | p2); }, lh, sh_part, sh_out, &p3, &bl, &in_bin);
         pos_max = (p1 << 21) | (p2 << 10) | p3;
     }
-    const int64_t rb = u / A.g.n_chunks;
-    const int64_t col0 = (u - rb * A.g.n_chunks) * A.g.chunk_w;
-    const uint32_t G = (uint32_t)A.g.chunk_w;
-    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * SAL_THREADS) {
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 4 * SAL_BIG) {
         uint2 e[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            if (i0 + k * SAL_THREADS < n) e[k] = list[i0 + k * SAL_THREADS];
+            if (i0 + k * SAL_BIG < n) e[k] = list[i0 + k * SAL_BIG];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (i0 + k * SAL_THREADS < n && (e[k].x > T || (e[k].x == T && e[k].y <= pos_max))) {
-                const uint32_t r = e[k].y / G, c = e[k].y - r * G;
-                const int64_t byte = (rb * A.g.R_u + (int64_t)r) * A.mask_ld + ((col0 + (int64_t)c) >> 3);
-                atomicOr(reinterpret_cast<uint32_t*>(A.mask + (byte & ~(int64_t)3)),
-                         1u << (8u * (uint32_t)(byte & 3) + (c & 7u)));
-            }
-        }
+        for (int k = 0; k < 4; ++k)
+            if (i0 + k * SAL_BIG < n) settle(A, rb, col0, mid, e[k], e[k].x > T || (e[k].x == T && e[k].y <= pos_max));
     }
 }
 
 // ---------------------------------------------------------------------------- encode
-// The encode kernels stage only the tile's mask bytes (a sixteenth of the weights' bytes at
-// bf16) and fetch the few protected weights straight from HBM, one element at a time but
-// SAL_GATHER of them in flight per lane: a lane first notes the columns of its next protected
-// weights (in LDS: a register array indexed by a running count would live in scratch memory),
-// then requests them together, then works through them in column order.
-// LDS: [mask tile][s_c of the chunk][SAL_GATHER x 64 column slots].
-constexpr int SAL_GATHER = 8;
-static size_t sal_gather_lds(int32_t chunk_w);
-
-// Calls f(column, weight) for the protected weights of the lane's row, in column order.
-template <int DT, typename F>
-__device__ __forceinline__ void for_protected(const void* __restrict__ W, int64_t woff, const uint8_t* __restrict__ mrow,
-                                              int32_t G, uint16_t* __restrict__ slots, F f) {
-    int32_t c = 0;          // first column of the next mask byte
-    uint32_t m = 0;         // bits of the current byte still to take (it covers columns c - 8 .. c - 1)
-    for (;;) {
-        int n = 0;
-        while (n < SAL_GATHER) {
-            if (m == 0u) {
-                if (c >= G) break;
-                m = mrow[c >> 3];
-                c += 8;
-                continue;
-            }
-            const int j = __ffs(m) - 1;
-            m &= m - 1u;
-            slots[n * 64] = (uint16_t)(c - 8 + j);
-            ++n;
-        }
-        if (n == 0) break;
-        float w[SAL_GATHER];
-        uint32_t col[SAL_GATHER];
-#pragma unroll
-        for (int k = 0; k < SAL_GATHER; ++k) {
-            if (k < n) {
-                col[k] = slots[k * 64];
-                w[k] = load1g<DT>(W, woff + col[k]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < SAL_GATHER; ++k)
-            if (k < n) f((int32_t)col[k], w[k]);
-        if (n < SAL_GATHER) break;       // the row is exhausted
-    }
+// INT8 codes need the unit's largest protected weight first.  The first kernel therefore collects a tile's
+// protected weights (value and column, in flat-index order) in the tile's part of the candidate area, so that the
+// second, which knows the scale, need not fetch them from W again: at 3 % they touch most of W's 64-byte
+// sectors.  A tile with more of them than its part holds is collected from W a second time, as is every tile
+// of a mask that was not made by select at a rate the area is for.
+template <int DT>
+struct SalPart {                // of one tile
+    uint16_t* col;
+    uint16_t* w16;              // bf16
+    float* w32;                 // fp32
+    uint32_t cap;
+};
+template <int DT>
+__device__ __forceinline__ SalPart<DT> sal_part(const SalArgs& A, const TileCoord& tc) {
+    const uint64_t bytes = ((uint64_t)A.cap * sizeof(uint2) / (uint64_t)A.g.tiles_per_unit) & ~(uint64_t)15;
+    char* p = reinterpret_cast<char*>(A.cand + (size_t)tc.u * (size_t)A.cap) + (uint64_t)tc.t * bytes;
+    SalPart<DT> s;
+    s.cap = (uint32_t)(bytes / (2 + Elem<DT>::bytes)) & ~1u;
+    s.w32 = reinterpret_cast<float*>(p);
+    s.w16 = reinterpret_cast<uint16_t*>(p);
+    s.col = reinterpret_cast<uint16_t*>(p + (uint64_t)s.cap * Elem<DT>::bytes);
+    return s;
 }
 
-// Per tile, one lane per row: protected weights in the row, largest protected magnitude.
-template <int DT>
-__global__ __launch_bounds__(64) void sal_rows_kernel(const SalBatch B) {
-    extern __shared__ char smem[];
-    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
-    const SalArgs& A = B.m[mi];
-    const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]);
-    const int32_t G = A.g.chunk_w;
-    const int lane = threadIdx.x;
-    uint8_t* mtile = reinterpret_cast<uint8_t*>(smem);
-    uint16_t* slots = reinterpret_cast<uint16_t*>(smem + TILE_ROWS * mask_row_stride(G) + G * sizeof(float)) + lane;
-    load_mask_tile(A.mask, A.mask_ld, tc, G, mtile);
-    __syncthreads();
-    const bool valid = lane < tc.nrows;
-    uint32_t n = 0;
-    float mx = 0.0f;
-    if (valid) {
-        const int64_t woff = (tc.row0 + lane) * A.g.ld + tc.col0;
-        const uint8_t* mrow = mtile + lane * mask_row_stride(G);
-        for_protected<DT>(A.W, woff, mrow, G, slots, [&](int32_t, float w) {
-            ++n;
-            mx = fmaxf(mx, fabsf(w));
-        });
-        A.row_off[tc.u * A.g.R_u + tc.lrow0 + lane] = n;
+// The tile of a wavefront: a workgroup's four take four neighbouring tiles, each by itself.
+__device__ __forceinline__ bool sal_wave_tile(const SalBatch& B, int* mi, int64_t* tile) {
+    const int64_t t = (int64_t)blockIdx.x * (SAL_THREADS / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (t >= B.tile_start[B.n]) return false;
+    *mi = batch_index(B.tile_start, B.n, t);
+    *tile = t - B.tile_start[*mi];
+    return true;
+}
+
+// Calls f(index, column, weight) for the protected weights of a wavefront's tile; index counts them in flat order.  A lane
+// takes 8 columns at a time, four such pieces in flight, and reads of W only the pieces that hold one.  Returns their number.
+constexpr int SAL_ENC_ITERS = 4;
+template <int DT, typename F>
+__device__ __forceinline__ uint32_t for_protected(const SalArgs& A, const TileCoord& tc, F f) {
+    const int lane = threadIdx.x & 63;
+    const int32_t pieces = A.g.chunk_w >> 3;
+    const int32_t total = tc.nrows * pieces;
+    const uint8_t* __restrict__ mask = A.mask + tc.row0 * A.mask_ld + (tc.col0 >> 3);
+    PieceWalk walk(lane, 64, pieces);
+    uint32_t before = 0;
+    for (int32_t i0 = 0; i0 < total; i0 += SAL_ENC_ITERS * 64) {
+        uint32_t m[SAL_ENC_ITERS];
+        int32_t rk[SAL_ENC_ITERS], pk[SAL_ENC_ITERS];
+        Raw8<DT> raw[SAL_ENC_ITERS];
+#pragma unroll
+        for (int k = 0; k < SAL_ENC_ITERS; ++k) {
+            rk[k] = walk.r;
+            pk[k] = walk.pc;
+            walk.next();
+            m[k] = i0 + k * 64 + lane < total ? mask[rk[k] * A.mask_ld + pk[k]] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < SAL_ENC_ITERS; ++k)
+            if (m[k] != 0u) raw[k] = load8raw<DT>(A.W, (tc.row0 + rk[k]) * A.g.ld + tc.col0 + pk[k] * 8);
+#pragma unroll
+        for (int h = 0; h < SAL_ENC_ITERS; h += 4) {
+            uint64_t mine = 0;                  // 16 bits per round of four: at most 512 weights each
+#pragma unroll
+            for (int k = 0; k < 4; ++k) mine |= (uint64_t)__builtin_popcount(m[h + k]) << (16 * k);
+            uint64_t inc = mine;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint64_t v = __shfl_up(inc, d, 64);
+                if (lane >= d) inc += v;
+            }
+            const uint64_t tot = __shfl(inc, 63, 64);
+            const uint64_t excl = inc - mine;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                uint32_t at = before + (uint32_t)((excl >> (16 * k)) & 0xffffu);
+                for (uint32_t b = m[h + k]; b != 0u; b &= b - 1u) {
+                    const int j = __ffs(b) - 1;
+                    f(at++, pk[h + k] * 8 + j, raw_elem<DT>(raw[h + k], j));
+                }
+                before += (uint32_t)((tot >> (16 * k)) & 0xffffu);
+            }
+        }
     }
+    return before;
+}
+
+// Per tile: its protected weights collected, their number, the largest magnitude.
+template <int DT>
+__global__ __launch_bounds__(SAL_THREADS) void sal_collect_kernel(const SalBatch B) {
+    int mi;
+    int64_t tile;
+    if (!sal_wave_tile(B, &mi, &tile)) return;
+    const SalArgs& A = B.m[mi];
+    const TileCoord tc = tile_coord(A.g, tile);
+    const SalPart<DT> part = sal_part<DT>(A, tc);
+    float mx = 0.0f;
+    const uint32_t n = for_protected<DT>(A, tc, [&](uint32_t at, int32_t c, float w) {
+        mx = fmaxf(mx, fabsf(w));
+        if (at < part.cap) {
+            part.col[at] = (uint16_t)c;
+            if (DT == WINDQ_BF16) part.w16[at] = (uint16_t)(__float_as_uint(w) >> 16);
+            else part.w32[at] = w;
+        }
+    });
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-    if (lane == 0) A.tile_max[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t] = mx;
+    if ((threadIdx.x & 63) == 0) {
+        const size_t at = (size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t;
+        A.tile_max[at] = mx;
+        A.cnt[at] = n;
+    }
 }
 
-// Per unit: the INT8 scale, and the row counts turned into offsets (exclusive prefix in row order).
+// Per unit: the INT8 scale, and the tiles' counts turned into those of all earlier tiles.
 __global__ __launch_bounds__(SAL_THREADS) void sal_unit_kernel(const SalBatch B) {
     __shared__ uint32_t sh[SAL_THREADS / 64];
     __shared__ float shm[SAL_THREADS / 64];
     const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
     const SalArgs& A = B.m[mi];
     const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    const int64_t T = A.g.tiles_per_unit;
+    const size_t base = (size_t)u * (size_t)T;
     float mx = 0.0f;
-    for (int64_t t = threadIdx.x; t < A.g.tiles_per_unit; t += SAL_THREADS)
-        mx = fmaxf(mx, A.tile_max[(size_t)u * (size_t)A.g.tiles_per_unit + (size_t)t]);
+    uint32_t carry = 0;
+    for (int64_t t0 = 0; t0 < T; t0 += SAL_THREADS) {
+        const int64_t t = t0 + threadIdx.x;
+        if (t < T) mx = fmaxf(mx, A.tile_max[base + (size_t)t]);
+        const uint32_t n = t < T ? A.cnt[base + (size_t)t] : 0u;
+        uint32_t tot;
+        const uint32_t excl = block_exclusive_scan(n, sh, &tot);
+        if (t < T) A.cnt[base + (size_t)t] = carry + excl;
+        carry += tot;
+    }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
     if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = mx;
     __syncthreads();
     if (threadIdx.x == 0) {
-        float m = shm[0];
-        for (int w = 1; w < SAL_THREADS / 64; ++w) m = fmaxf(m, shm[w]);
-        float sg = m / 127.0f;
+        for (int w = 1; w < SAL_THREADS / 64; ++w) mx = fmaxf(mx, shm[w]);
+        float sg = mx / 127.0f;
         if (!(sg >= FLT_MIN)) sg = 0.0f;
         A.prot_scale[u] = sg;
-    }
-    // each thread owns a run of consecutive rows: its sum, one scan over the threads, then the
-    // run again to write the offsets (one scan per unit instead of one per 256 rows)
-    uint32_t* __restrict__ ro = A.row_off + u * A.g.R_u;
-    const int64_t run = (A.g.R_u + SAL_THREADS - 1) / SAL_THREADS;
-    const int64_t r_lo = (int64_t)threadIdx.x * run;
-    const int64_t r_hi = r_lo + run < A.g.R_u ? r_lo + run : A.g.R_u;
-    uint32_t mine = 0;
-    for (int64_t r = r_lo; r < r_hi; ++r) mine += ro[r];
-    uint32_t tot;
-    uint32_t pos = block_exclusive_scan_u32(mine, sh, &tot);
-    for (int64_t r = r_lo; r < r_hi; ++r) {
-        const uint32_t n = ro[r];
-        ro[r] = pos;
-        pos += n;
+        A.count[u] = carry;                    // the unit's protected weights
     }
 }
 
-// Per tile, one lane per row: INT8 codes of the row's protected weights at their place in
-// the unit's stream, and the activation-weighted error of the tile's INT8 part.
+// Per tile: INT8 codes of the protected weights at their place in the unit's stream, and the
+// activation-weighted error of the tile's INT8 part.
 template <int DT>
-__global__ __launch_bounds__(64) void sal_encode_kernel(const SalBatch B) {
-    extern __shared__ char smem[];
-    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
+__global__ __launch_bounds__(SAL_THREADS) void sal_encode_kernel(const SalBatch B) {
+    int mi;
+    int64_t tile;
+    if (!sal_wave_tile(B, &mi, &tile)) return;
     const SalArgs& A = B.m[mi];
-    const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]);
-    const int32_t G = A.g.chunk_w;
-    const int lane = threadIdx.x;
-    uint8_t* mtile = reinterpret_cast<uint8_t*>(smem);
-    float* scol = reinterpret_cast<float*>(smem + TILE_ROWS * mask_row_stride(G));
-    uint16_t* slots = reinterpret_cast<uint16_t*>(scol + G) + lane;
-    load_mask_tile(A.mask, A.mask_ld, tc, G, mtile);
-    for (int32_t c = lane; c < G; c += 64) scol[c] = A.s[tc.col0 + c];
-    __syncthreads();
+    const TileCoord tc = tile_coord(A.g, tile);
+    const size_t slot = (size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t;
+    const uint32_t first = A.cnt[slot];
+    const uint32_t end = tc.t + 1 < A.g.tiles_per_unit ? A.cnt[slot + 1] : (uint32_t)A.count[tc.u];
     const float sg = A.prot_scale[tc.u];
     const float inv = sg > 0.0f ? 1.0f / sg : 0.0f;
+    const float* __restrict__ s = A.s + tc.col0;
+    int8_t* __restrict__ dst = A.prot_codes + (size_t)tc.u * (size_t)A.n_p;
+    const SalPart<DT> part = sal_part<DT>(A, tc);
     double err = 0.0;
-    if (lane < tc.nrows) {
-        const int64_t woff = (tc.row0 + lane) * A.g.ld + tc.col0;
-        const uint8_t* mrow = mtile + lane * mask_row_stride(G);
-        uint32_t pos = A.row_off[tc.u * A.g.R_u + tc.lrow0 + lane];
-        int8_t* __restrict__ dst = A.prot_codes + (size_t)tc.u * (size_t)A.n_p;
-        for_protected<DT>(A.W, woff, mrow, G, slots, [&](int32_t c, float w) {
-            const float t = w * inv;
-            const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(t), -127.0f, 127.0f);
-            if (pos < A.n_p) dst[pos] = (int8_t)(int32_t)q;     // a mask with more bits than n_p writes nothing past the unit
-            ++pos;
-            const double d = (double)w - (double)q * (double)sg;
-            const double a = (double)scol[c] * (double)scol[c];
-            err = fma(a * d, d, err);
-        });
+    auto encode = [&](uint32_t at, int32_t c, float w) {
+        const float t = w * inv;
+        const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(t), -127.0f, 127.0f);
+        if (first + at < A.n_p) dst[first + at] = (int8_t)(int32_t)q;     // a mask with more bits than n_p writes nothing past the unit
+        const double d = (double)w - (double)q * (double)sg;
+        const double a = (double)s[c] * (double)s[c];
+        err = fma(a * d, d, err);
+    };
+    const uint32_t n = end - first;
+    if (n <= part.cap) {
+#pragma unroll 4
+        for (uint32_t at = threadIdx.x & 63; at < n; at += 64)
+            encode(at, part.col[at], DT == WINDQ_BF16 ? bf16_bits_to_f32(part.w16[at]) : part.w32[at]);
+    } else {
+        for_protected<DT>(A, tc, encode);
     }
     err = wave_sum(err);
-    if (lane == 0) A.err_part[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t] = err;
+    if ((threadIdx.x & 63) == 0) A.err_part[slot] = err;
 }
 
 __global__ __launch_bounds__(256) void sal_err_kernel(const SalBatch B) {
@@ -771,60 +968,46 @@ __global__ __launch_bounds__(256) void unit_saliency_finalize_kernel(const doubl
     if (threadIdx.x == 0) sal[u] = (float)(t / ((double)g.R_u * (double)g.chunk_w));
 }
 
-// encode's kernels: the tile's mask bytes, s_c of the chunk, the lanes' column slots
-static size_t sal_gather_lds(int32_t chunk_w) {
-    return mask_tile_lds_bytes(chunk_w) + (size_t)chunk_w * sizeof(float) + (size_t)SAL_GATHER * 64 * sizeof(uint16_t);
-}
-
 static void carve(SalArgs& A, void* ws, const SalientLayout& L) {
     char* base = static_cast<char*>(ws);
     A.hist = reinterpret_cast<uint32_t*>(base + L.hist);
-    A.prefix = reinterpret_cast<uint32_t*>(base + L.prefix);
-    A.rank = reinterpret_cast<uint32_t*>(base + L.rank);
+    A.lo = reinterpret_cast<uint32_t*>(base + L.lo);
+    A.hi = reinterpret_cast<uint32_t*>(base + L.hi);
+    A.mid = reinterpret_cast<uint32_t*>(base + L.mid);
+    A.count = reinterpret_cast<uint64_t*>(base + L.count);
     A.cnt = reinterpret_cast<uint32_t*>(base + L.cnt);
-    A.eq_before = reinterpret_cast<uint32_t*>(base + L.eq_before);
-    A.need = reinterpret_cast<uint32_t*>(base + L.need);
     A.flag = reinterpret_cast<uint32_t*>(base + L.flag);
     A.n_flagged = reinterpret_cast<uint32_t*>(base + L.n_flagged);
     A.flagged = reinterpret_cast<uint32_t*>(base + L.flagged);
-    A.cand_count = reinterpret_cast<uint32_t*>(base + L.cand_count);
     A.cand = reinterpret_cast<uint2*>(base + L.cand);
     A.cap = L.cap;
     A.tile_max = reinterpret_cast<float*>(base + L.tile_max);
-    A.row_off = reinterpret_cast<uint32_t*>(base + L.row_off);
     A.err_part = reinterpret_cast<double*>(base + L.err_part);
 }
 
 template <int DT>
 static int launch_select(const SalBatch& B, hipStream_t hs) {
-    const dim3 tiles((unsigned)B.tile_start[B.n]), units((unsigned)B.unit_start[B.n]), some(SAL_FLAGGED_GRID);
-    hipLaunchKernelGGL(sal_clear_hist_kernel, dim3((unsigned)B.fill_start[B.n]), dim3(256), 0, hs, B);
-    hipLaunchKernelGGL(sal_hist_kernel<DT>, tiles, dim3(SAL_THREADS), 0, hs, B);
-    hipLaunchKernelGGL(sal_prefix_kernel, units, dim3(SAL_THREADS), 0, hs, B, 0);
+    const dim3 units((unsigned)B.unit_start[B.n]), some(SAL_FLAGGED_GRID);
     // units that select from their candidate list ...
-    hipLaunchKernelGGL(sal_cand_kernel<DT>, tiles, dim3(SAL_THREADS), 0, hs, B);
-    hipLaunchKernelGGL(sal_list_kernel, units, dim3(SAL_THREADS), 0, hs, B);
+    hipLaunchKernelGGL(sal_sample_kernel<DT>, units, dim3(SAL_BIG), 0, hs, B);
+    const dim3 bands((unsigned)B.band_start[B.n]);
+    if (SAL_THREADS % (B.m[0].g.chunk_w >> 3) == 0) hipLaunchKernelGGL((sal_cand_kernel<DT, true>), bands, dim3(SAL_THREADS), 0, hs, B);
+    else hipLaunchKernelGGL((sal_cand_kernel<DT, false>), bands, dim3(SAL_THREADS), 0, hs, B);
+    hipLaunchKernelGGL(sal_list_kernel, units, dim3(SAL_BIG), 0, hs, B);
     // ... and the others
-    for (int level = 1; level < 3; ++level) {
+    for (int level = 0; level < 3; ++level)
         hipLaunchKernelGGL((sal_flagged_kernel<DT, SAL_WHAT_HIST>), some, dim3(SAL_THREADS), 0, hs, B, level);
-        hipLaunchKernelGGL(sal_prefix_kernel, units, dim3(SAL_THREADS), 0, hs, B, level);
-    }
     hipLaunchKernelGGL((sal_flagged_kernel<DT, SAL_WHAT_COUNT>), some, dim3(SAL_THREADS), 0, hs, B, 0);
-    hipLaunchKernelGGL(sal_scan_kernel, units, dim3(SAL_THREADS), 0, hs, B);
     hipLaunchKernelGGL((sal_flagged_kernel<DT, SAL_WHAT_MASK>), some, dim3(SAL_THREADS), 0, hs, B, 0);
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 
 template <int DT>
-static int launch_encode(const SalBatch& B, hipStream_t hs, size_t lds) {
-    const dim3 tiles((unsigned)B.tile_start[B.n]), units((unsigned)B.unit_start[B.n]);
-    int st = ensure_lds(reinterpret_cast<const void*>(&sal_rows_kernel<DT>), lds);
-    if (st != WINDQ_OK) return st;
-    st = ensure_lds(reinterpret_cast<const void*>(&sal_encode_kernel<DT>), lds);
-    if (st != WINDQ_OK) return st;
-    hipLaunchKernelGGL(sal_rows_kernel<DT>, tiles, dim3(64), lds, hs, B);
+static int launch_encode(const SalBatch& B, hipStream_t hs) {
+    const dim3 tiles((unsigned)((B.tile_start[B.n] + SAL_THREADS / 64 - 1) / (SAL_THREADS / 64))), units((unsigned)B.unit_start[B.n]);
+    hipLaunchKernelGGL(sal_collect_kernel<DT>, tiles, dim3(SAL_THREADS), 0, hs, B);
     hipLaunchKernelGGL(sal_unit_kernel, units, dim3(SAL_THREADS), 0, hs, B);
-    hipLaunchKernelGGL(sal_encode_kernel<DT>, tiles, dim3(64), lds, hs, B);
+    hipLaunchKernelGGL(sal_encode_kernel<DT>, tiles, dim3(SAL_THREADS), 0, hs, B);
     hipLaunchKernelGGL(sal_err_kernel, units, dim3(256), 0, hs, B);
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
@@ -864,24 +1047,25 @@ static int salient_common(const windq_mat* W, const float* s, int32_t chunk_w, i
     return WINDQ_OK;
 }
 
-// Numbers the tiles, units and histogram-clearing workgroups of the first B->n matrices.
+// Numbers the tiles and units of the first B->n matrices.
 static int salient_number(SalBatch* B) {
-    int64_t tiles = 0, units = 0, fill = 0;
+    int64_t tiles = 0, units = 0, bands = 0;
     for (int32_t i = 0; i < B->n; ++i) {
         B->tile_start[i] = tiles;
         B->unit_start[i] = units;
-        B->fill_start[i] = fill;
+        B->band_start[i] = bands;
+        bands += B->m[i].g.U * ((B->m[i].g.tiles_per_unit + SAL_CAND_TILES - 1) / SAL_CAND_TILES);
         tiles += B->m[i].g.n_tiles;
         units += B->m[i].g.U;
-        fill += ((int64_t)3 * B->m[i].g.U * FEAT_BINS + 255) / 256;
     }
     for (int32_t i = B->n; i <= WINDQ_MAX_BATCH; ++i) {
         B->tile_start[i] = tiles;
         B->unit_start[i] = units;
-        B->fill_start[i] = fill;
+        B->band_start[i] = bands;
     }
     for (int32_t i = B->n; i < WINDQ_MAX_BATCH; ++i) B->m[i] = B->m[0];
-    return tiles > (int64_t)0x7fffffff || fill > (int64_t)0x7fffffff ? WINDQ_ESHAPE : WINDQ_OK;
+    B->any_flagged = B->m[0].n_flagged + 1;       // in the 256 bytes of the first matrix's own count
+    return tiles > (int64_t)0x7fffffff ? WINDQ_ESHAPE : WINDQ_OK;
 }
 
 static int salient_select_launch(const windq_salient_item* items, int32_t n, int32_t chunk_w, int64_t unit_rows,
@@ -937,8 +1121,7 @@ static int salient_encode_launch(const windq_salient_item* items, int32_t n, int
     if (st != WINDQ_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
-    const size_t lds = sal_gather_lds(chunk_w);
-    return dtype == WINDQ_BF16 ? launch_encode<WINDQ_BF16>(B, hs, lds) : launch_encode<WINDQ_F32>(B, hs, lds);
+    return dtype == WINDQ_BF16 ? launch_encode<WINDQ_BF16>(B, hs) : launch_encode<WINDQ_F32>(B, hs);
 }
 
 extern "C" int windq_salient_select(const windq_mat* W, const float* s, int32_t chunk_w, int64_t unit_rows,

@@ -70,6 +70,31 @@ def test_ties_are_taken_in_flat_index_order(windq):
         check_encode(windq, Wc, s[:128], 64, 96, ppm, mask, keep)
 
 
+@pytest.mark.parametrize("R,C,G,unit_rows,ppm,dtype", [
+    (1, 64, 8, 0, 250000, torch.float32), (3, 1024, 512, 0, 50000, torch.bfloat16), (2048, 512, 512, 0, 30000, torch.bfloat16),
+    (1030, 256, 128, 0, 1000, torch.bfloat16), (2304, 96, 96, 1152, 50000, torch.float32), (4100, 8, 8, 0, 30000, torch.bfloat16)])
+def test_select_over_the_sizes_of_its_sample(windq, R, C, G, unit_rows, ppm, dtype):
+    """Units smaller than the sample's least, read half, and sampled thinly; a mask of several rounds per tile."""
+    W = synth.weights_llm(R, C, seed=78, device=DEV, dtype=dtype)
+    s = torch.exp(torch.randn(C, generator=torch.Generator().manual_seed(5))).to(DEV)
+    mask, keep = check_select(windq, W, s, G, unit_rows, ppm)
+    check_encode(windq, W, s, G, unit_rows, ppm, mask, keep)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_select_and_encode_where_the_sample_misleads(windq, dtype):
+    """The protected weights in rows that no evenly spread sample of that size meets, in every second chunk: the count of the
+    pass over W refutes the bracket and those units are selected the long way (their ties too), the others from
+    their lists; one tile then holds more protected weights than its part of the collection area."""
+    R, C, G, ppm = 4096, 512, 128, 15000
+    W = synth.weights_llm(R, C, seed=79, device=DEV, dtype=dtype)
+    W[129:200, :128] *= 64                        # a solid run of rows: at most 5 of the sample's 256
+    W[1000:1064, 256:384] = 3.0                   # and one of equal weights
+    s = torch.ones(C, device=DEV)
+    mask, keep = check_select(windq, W, s, G, 0, ppm)
+    check_encode(windq, W, s, G, 0, ppm, mask, keep)
+
+
 def test_select_routes_agree(windq):
     """Selection from the units' candidate lists (the usual route) and by digit passes over W (taken when the
     mask cannot be addressed in whole dwords, or a unit's threshold bin outgrows its list) give the same mask."""
