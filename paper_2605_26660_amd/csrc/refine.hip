@@ -11,9 +11,14 @@
 // with contraction off), the parameters are rounded to fp32 after every solve: the results
 // are defined to the bit, so codes and stored parameters can be checked exactly.
 //
-// One wavefront per 64-row tile, one lane per group, tile in LDS (as the general apply-plan
-// kernel): a group's refinement is a lane-private sequence.  fp64 arithmetic at ~15 operations
-// per weight and round: bound by the fp64 ALU, not by HBM; it runs once per chosen plan.
+// One wavefront per 64-row tile, one lane per group: a group's refinement is a lane-private sequence of
+// passes over its row, fp64 arithmetic at 7 to 10 operations per weight and round: bound by the fp64
+// ALU, not by HBM; it runs once per chosen plan.  A lane's row lies in registers (64 for 128 bf16 weights, up to
+// 128), read eight weights at a time by register indexing: a tile staged in LDS (17 KB) leaves room for two wavefronts
+// per SIMD, too few to fill the ALU.  LDS only turns the tile round on its way in, 128 bytes of every row at a
+// time, and the packed codes on their way out.  Wider rows stay in LDS.  Refining a 7B-shaped block at 2 bits, three rounds:
+// 303 us (610 with the tile in LDS, a select per weight for a mask that is not there, and passes of their own for error
+// and codes); five wavefronts per SIMD would spill (1.4 ms), an unrolled pair of blocks is 7 % slower.
 #include <float.h>
 
 #include "windq_common.hpp"
@@ -51,163 +56,315 @@ struct RefineBatch {
     ClipGrid grid;
 };
 
-__device__ __forceinline__ bool kept_bit(uint32_t m, int j) { return ((m >> j) & 1u) == 0u; }
-
-// The sums of one round of the uniform refinement over a group.  S0 = sum a and T0 = sum a w do
-// not depend on the codes: the first round computes them (FIRST), later rounds reuse them; the
-// order of every sum is the column order either way.
-template <int DT, bool FIRST>
-__device__ __forceinline__ void uniform_sums(const char* wrow, const uint8_t* mrow, const double* acol, int32_t G,
-                                             float lo, float inv, float qmax, double* S0_io, double* T0_io,
-                                             double* S1_o, double* S2_o, double* T1_o) {
-    double S0 = 0.0, S1 = 0.0, S2 = 0.0, T0 = 0.0, T1 = 0.0;
-    for (int32_t c = 0; c < G; c += 8) {
-        float w[8];
-        read8<DT>(wrow, c, w);
-        const uint32_t m = mrow != nullptr ? mrow[c >> 3] : 0u;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const float u = w[j] - lo;
-            const float t = u * inv;
-            const double q = (double)__builtin_amdgcn_fmed3f(__builtin_rintf(t), 0.0f, qmax);
-            const double a = kept_bit(m, j) ? acol[c + j] : 0.0;      // a masked weight adds zeros
-            const double wd = (double)w[j];
-            const double aq = a * q;
-            if (FIRST) {
-                S0 = S0 + a;
-                T0 = T0 + a * wd;
-            }
-            S1 = S1 + aq;
-            S2 = S2 + aq * q;
-            T1 = T1 + aq * wd;
-        }
-    }
-    if (FIRST) {
-        *S0_io = S0;
-        *T0_io = T0;
-    }
-    *S1_o = S1;
-    *S2_o = S2;
-    *T1_o = T1;
-}
-
+// A lane's row of G weights in LDS, element type of the input.
 template <int DT>
-__device__ __forceinline__ void refine_uniform(const char* wrow, const uint8_t* mrow, const double* acol,
-                                               int32_t G, float qmax, int n_iter, float* lo_io, float* d_io) {
-    float lo = *lo_io, d = *d_io;
-    double S0 = 0.0, T0 = 0.0;
-    for (int it = 0; it < n_iter; ++it) {
-        if (!(d >= FLT_MIN)) break;
-        const float inv = 1.0f / d;
-        double S1, S2, T1;
-        if (it == 0) uniform_sums<DT, true>(wrow, mrow, acol, G, lo, inv, qmax, &S0, &T0, &S1, &S2, &T1);
-        else uniform_sums<DT, false>(wrow, mrow, acol, G, lo, inv, qmax, &S0, &T0, &S1, &S2, &T1);
-        const double det = S0 * S2 - S1 * S1;
-        if (!(det > 0.0)) break;
-        const double d_new = (S0 * T1 - S1 * T0) / det;
-        const double lo_new = (T0 - S1 * d_new) / S0;
-        const float d32 = (float)d_new, lo32 = (float)lo_new;
-        if (!(d32 >= FLT_MIN)) break;
-        lo = lo32;
-        d = d32;
-    }
-    *lo_io = lo;
-    *d_io = d;
-}
-
-template <int DT>
-__device__ __forceinline__ float refine_ternary(const char* wrow, const uint8_t* mrow, const double* acol,
-                                                int32_t G, int n_iter, float gamma) {
-    for (int it = 0; it < n_iter; ++it) {
-        if (!(gamma >= FLT_MIN)) break;
-        const float inv = 1.0f / gamma;
-        double N1 = 0.0, D1 = 0.0;
+struct LdsRow {
+    const char* p;
+    // f(c, w): eight weights from column c, in column order
+    template <typename F>
+    __device__ __forceinline__ void blocks(int32_t G, F f) const {
         for (int32_t c = 0; c < G; c += 8) {
             float w[8];
-            read8<DT>(wrow, c, w);
-            const uint32_t m = mrow != nullptr ? mrow[c >> 3] : 0u;
+            read8<DT>(p, c, w);
+            f(c, w);
+        }
+    }
+};
+
+// A lane's row in NV x 32 registers (128 bytes each).
+typedef uint32_t Regs32 __attribute__((ext_vector_type(32)));
+template <int DT, int NV>
+struct RegRow {
+    Regs32 r[NV];
+    template <typename F>
+    __device__ __forceinline__ void blocks(int32_t G, F f) const {
+        constexpr int PER = DT == WINDQ_BF16 ? 8 : 4;           // blocks of eight weights in 32 registers
+        constexpr int DW = 32 / PER;
+        const int nb = G >> 3;
+#pragma unroll
+        for (int h = 0; h < NV; ++h) {
+            const int n = nb - h * PER < PER ? nb - h * PER : PER;
+#pragma unroll 1
+            for (int i = 0; i < n; ++i) {
+                uint32_t d[DW];
+#pragma unroll
+                for (int k = 0; k < DW; ++k) d[k] = r[h][i * DW + k];
+                float w[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    if (DT == WINDQ_BF16) w[j] = __uint_as_float((j & 1) != 0 ? d[j >> 1] & 0xffff0000u : d[j >> 1] << 16);
+                    else w[j] = __uint_as_float(d[j < DW ? j : 0]);
+                }
+                f((h * PER + i) * 8, w);
+            }
+        }
+    }
+};
+
+// The tile into its lanes' rows: 128 bytes of every row at a time through LDS (buf: 64 rows of 144 bytes).
+constexpr int RF_THREADS = 64;
+constexpr int RF_SLAB = 128, RF_SLAB_STRIDE = RF_SLAB + 16;
+template <int DT, int NV>
+__device__ __forceinline__ void load_rows(const RefineArgs& A, const TileCoord& tc, char* buf, RegRow<DT, NV>& row) {
+    const int lane = threadIdx.x;
+    const int32_t row_bytes = A.g.chunk_w * Elem<DT>::bytes;
+    const char* __restrict__ src = static_cast<const char*>(A.W) + (tc.row0 * A.g.ld + tc.col0) * Elem<DT>::bytes;
+    const int64_t ld = A.g.ld * Elem<DT>::bytes;
+    uint4 raw[NV][8];
+#pragma unroll
+    for (int h = 0; h < NV; ++h) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int r = 8 * k + (lane >> 3), at = h * RF_SLAB + (lane & 7) * 16;
+            raw[h][k] = make_uint4(0u, 0u, 0u, 0u);
+            if (r < tc.nrows && at < row_bytes) raw[h][k] = *reinterpret_cast<const uint4*>(src + r * ld + at);
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < NV; ++h) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) *reinterpret_cast<uint4*>(buf + (8 * k + (lane >> 3)) * RF_SLAB_STRIDE + (lane & 7) * 16) = raw[h][k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint4 q = *reinterpret_cast<const uint4*>(buf + lane * RF_SLAB_STRIDE + k * 16);
+            row.r[h][4 * k] = q.x;
+            row.r[h][4 * k + 1] = q.y;
+            row.r[h][4 * k + 2] = q.z;
+            row.r[h][4 * k + 3] = q.w;
+        }
+    }
+    __syncthreads();
+}
+
+// One group: its row, its protection bits (masked calls), s_c^2 of the columns.
+template <int DT, bool MASKED, typename Row>
+struct RefineGroup {
+    Row row;
+    const uint8_t* mrow;
+    const double* acol;
+    int32_t G;
+
+    __device__ __forceinline__ uint32_t bits(int32_t c) const { return MASKED ? mrow[c >> 3] : 0u; }
+    __device__ __forceinline__ bool kept(uint32_t m, int j) const { return !MASKED || ((m >> j) & 1u) == 0u; }
+    // s_c^2 of column c + j, zero for a protected weight
+    __device__ __forceinline__ double weight(uint32_t m, int32_t c, int j) const { return kept(m, j) ? acol[c + j] : 0.0; }
+
+    // min and max of the kept weights (0, 0 when none is kept)
+    __device__ __forceinline__ void min_max(float* mn_out, float* mx_out) const {
+        float mn = INFINITY, mx = -INFINITY;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+            if (!MASKED && c == 0) mn = mx = w[0];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float t = w[j] * inv;
-                const double q = (double)__builtin_amdgcn_fmed3f(__builtin_rintf(t), -1.0f, 1.0f);
-                const double a = kept_bit(m, j) ? acol[c + j] : 0.0;
+                mn = fminf(mn, kept(m, j) ? w[j] : INFINITY);
+                mx = fmaxf(mx, kept(m, j) ? w[j] : -INFINITY);
+            }
+        });
+        if (MASKED && mn > mx) mn = mx = 0.0f;
+        *mn_out = mn;
+        *mx_out = mx;
+    }
+
+    // mean |w| as stored: the fp64 sum in column order over the kept weights, rounded to fp32; 0 when none is kept
+    __device__ __forceinline__ float abs_mean() const {
+        double S1 = 0.0;
+        int32_t n = G;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+            n -= __builtin_popcount(m);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) S1 += kept(m, j) ? (double)fabsf(w[j]) : 0.0;
+        });
+        return n > 0 ? (float)(S1 / (double)n) : 0.0f;
+    }
+
+    // The sums of one round of the uniform refinement.  S0 = sum a and T0 = sum a w do not depend on the
+    // codes: the first round computes them (FIRST), later rounds reuse them; the
+    // order of every sum is the column order either way.
+    template <bool FIRST>
+    __device__ __forceinline__ void uniform_sums(float lo, float inv, float qmax, double& S0, double& T0, double& S1, double& S2,
+                                                 double& T1) const {
+        if (FIRST) S0 = T0 = 0.0;
+        S1 = S2 = T1 = 0.0;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float u = w[j] - lo;
+                const float t = u * inv;
+                const double q = (double)__builtin_amdgcn_fmed3f(__builtin_rintf(t), 0.0f, qmax);
+                const double a = weight(m, c, j);             // a masked weight adds zeros
+                const double wd = (double)w[j];
                 const double aq = a * q;
-                N1 = N1 + aq * (double)w[j];
-                D1 = D1 + aq * q;
+                if (FIRST) {
+                    S0 = S0 + a;
+                    T0 = T0 + a * wd;
+                }
+                S1 = S1 + aq;
+                S2 = S2 + aq * q;
+                T1 = T1 + aq * wd;
             }
-        }
-        if (!(D1 > 0.0)) break;
-        const float g = (float)(N1 / D1);
-        if (!(g >= FLT_MIN)) break;
-        gamma = g;
+        });
     }
-    return gamma;
-}
 
-template <int DT>
-__device__ __forceinline__ float refine_binary(const char* wrow, const uint8_t* mrow, const double* acol,
-                                               int32_t G, float alpha) {
-    double N1 = 0.0, D1 = 0.0;
-    for (int32_t c = 0; c < G; c += 8) {
-        float w[8];
-        read8<DT>(wrow, c, w);
-        const uint32_t m = mrow != nullptr ? mrow[c >> 3] : 0u;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const double a = kept_bit(m, j) ? acol[c + j] : 0.0;
-            N1 = N1 + a * (double)fabsf(w[j]);
-            D1 = D1 + a;
+    __device__ __forceinline__ void uniform(float qmax, int n_iter, float* lo_io, float* d_io) const {
+        float lo = *lo_io, d = *d_io;
+        double S0 = 0.0, T0 = 0.0;
+        for (int it = 0; it < n_iter; ++it) {
+            if (!(d >= FLT_MIN)) break;
+            const float inv = 1.0f / d;
+            double S1, S2, T1;
+            if (it == 0) uniform_sums<true>(lo, inv, qmax, S0, T0, S1, S2, T1);
+            else uniform_sums<false>(lo, inv, qmax, S0, T0, S1, S2, T1);
+            const double det = S0 * S2 - S1 * S1;
+            if (!(det > 0.0)) break;
+            const double d_new = (S0 * T1 - S1 * T0) / det;
+            const double lo_new = (T0 - S1 * d_new) / S0;
+            const float d32 = (float)d_new, lo32 = (float)lo_new;
+            if (!(d32 >= FLT_MIN)) break;
+            lo = lo32;
+            d = d32;
         }
+        *lo_io = lo;
+        *d_io = d;
     }
-    return D1 > 0.0 ? (float)(N1 / D1) : alpha;
-}
 
-// Activation-weighted error of a group under its final parameters (fp64; w_hat from the
-// stored fp32 numbers, as everywhere).
-template <int DT>
-__device__ __forceinline__ double group_error(const char* wrow, const uint8_t* mrow, const double* acol,
-                                              int32_t G, int a, float sc, float of) {
-    const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : 2));
-    const float qmax = (float)((1 << bits) - 1);
-    const float inv = sc >= FLT_MIN ? 1.0f / sc : 0.0f;
-    double e = 0.0;
-    for (int32_t c = 0; c < G; c += 8) {
-        float w[8];
-        read8<DT>(wrow, c, w);
-        const uint32_t m = mrow != nullptr ? mrow[c >> 3] : 0u;
+    __device__ __forceinline__ float ternary(int n_iter, float gamma) const {
+        for (int it = 0; it < n_iter; ++it) {
+            if (!(gamma >= FLT_MIN)) break;
+            const float inv = 1.0f / gamma;
+            double N1 = 0.0, D1 = 0.0;
+            row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+                const uint32_t m = bits(c);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            double what;
-            if (a <= 4) {
+                for (int j = 0; j < 8; ++j) {
+                    const float t = w[j] * inv;
+                    const double q = (double)__builtin_amdgcn_fmed3f(__builtin_rintf(t), -1.0f, 1.0f);
+                    const double aq = weight(m, c, j) * q;
+                    N1 = N1 + aq * (double)w[j];
+                    D1 = D1 + fabs(aq);                       // a q^2: q is -1, 0 or 1
+                }
+            });
+            if (!(D1 > 0.0)) break;
+            const float g = (float)(N1 / D1);
+            if (!(g >= FLT_MIN)) break;
+            gamma = g;
+        }
+        return gamma;
+    }
+
+    // The seed (mean |w|) matters only where nothing is weighted.
+    __device__ __forceinline__ float binary(int n_iter) const {
+        if (n_iter <= 0) return abs_mean();
+        double N1 = 0.0, D1 = 0.0;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const double a = weight(m, c, j);
+                N1 = N1 + a * (double)fabsf(w[j]);
+                D1 = D1 + a;
+            }
+        });
+        if (D1 > 0.0) return (float)(N1 / D1);
+        return abs_mean();
+    }
+
+    // Codes under the final parameters, packed at dst (which may be the row's own LDS storage: behind the read position),
+    // and the activation-weighted error (fp64; w_hat from the stored fp32 numbers, as everywhere).
+    template <int BITS>
+    __device__ __forceinline__ double uniform_finish(float sc, float of, uint8_t* dst) const {
+        const float qmax = (float)((1 << BITS) - 1);
+        const float inv = sc >= FLT_MIN ? 1.0f / sc : 0.0f;
+        double e = 0.0;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+            uint32_t code[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
                 const float t = (w[j] - of) * inv;
-                what = (double)of + (double)__builtin_amdgcn_fmed3f(__builtin_rintf(t), 0.0f, qmax) * (double)sc;
-            } else if (a == 5) {
-                what = (double)sc * (double)__builtin_amdgcn_fmed3f(__builtin_rintf(w[j] * inv), -1.0f, 1.0f);
-            } else {
-                what = w[j] >= 0.0f ? (double)sc : -(double)sc;
+                const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(t), 0.0f, qmax);
+                const double what = (double)of + (double)q * (double)sc;
+                const double d = (double)w[j] - what;
+                e = e + weight(m, c, j) * d * d;
+                code[j] = kept(m, j) ? (uint32_t)q : 0u;
             }
-            const double d = (double)w[j] - what;
-            const double ac = kept_bit(m, j) ? acol[c + j] : 0.0;
-            e = e + ac * d * d;
-        }
+            store_codes8<BITS>(dst + (c >> 3) * BITS, code);
+        });
+        return e;
     }
-    return e;
+
+    __device__ __forceinline__ double ternary_finish(float sc, uint8_t* dst) const {
+        const float inv = sc >= FLT_MIN ? 1.0f / sc : 0.0f;
+        double e = 0.0;
+        uint32_t byte = 0, mul = 1;
+        int32_t nb = 0;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(w[j] * inv), -1.0f, 1.0f);
+                const double d = (double)w[j] - (double)sc * (double)q;
+                e = e + weight(m, c, j) * d * d;
+                byte += (kept(m, j) ? (uint32_t)((int32_t)q + 1) : 0u) * mul;
+                mul *= 3;
+                if (mul == 243) {
+                    dst[nb++] = (uint8_t)byte;
+                    byte = 0;
+                    mul = 1;
+                }
+            }
+        });
+        if (mul != 1) dst[nb] = (uint8_t)byte;
+        return e;
+    }
+
+    __device__ __forceinline__ double binary_finish(float sc, uint8_t* dst) const {
+        double e = 0.0;
+        row.blocks(G, [&](int32_t c, const float (&w)[8]) {
+            const uint32_t m = bits(c);
+            uint32_t byte = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool plus = w[j] >= 0.0f;
+                const double d = (double)w[j] - (plus ? (double)sc : -(double)sc);
+                e = e + weight(m, c, j) * d * d;
+                byte |= (plus && kept(m, j) ? 1u : 0u) << j;
+            }
+            dst[c >> 3] = (uint8_t)byte;
+        });
+        return e;
+    }
+};
+
+// LDS of a tile: its rows (NV = 0), or what turns them round and stages the codes; s_c^2 of the columns; the mask bytes.
+__host__ __device__ inline int32_t refine_pack_stride(int32_t G) { return G + 16; }       // 8-bit codes of a row
+static size_t refine_lds(int32_t dtype, int32_t G, int nv, bool masked) {
+    const size_t turn = (size_t)TILE_ROWS * RF_SLAB_STRIDE, pack = (size_t)TILE_ROWS * (size_t)refine_pack_stride(G);
+    return (nv == 0 ? raw_tile_lds_bytes(dtype, G) : (turn > pack ? turn : pack)) + (size_t)G * sizeof(double) +
+           (masked ? mask_tile_lds_bytes(G) : 0);
 }
 
-constexpr int RF_THREADS = 64;
-
+template <int DT, int NV>
+struct RefineRowOf {
+    using type = RegRow<DT, NV>;
+};
 template <int DT>
-__global__ __launch_bounds__(RF_THREADS) void refine_plan_kernel(const RefineBatch B) {
-    extern __shared__ char smem[];
+struct RefineRowOf<DT, 0> {
+    using type = LdsRow<DT>;
+};
+
+// NV: registers of a row / 32; 0: the row in LDS.  128 VGPRs (four wavefronts per SIMD) for NV = 2.
+template <int DT, int NV, bool MASKED>
+__global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kernel(const RefineBatch B) {
+    extern __shared__ __align__(16) char smem[];
     const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
     const RefineArgs& A = B.m[mi];
     const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]);
     const int32_t G = A.g.chunk_w;
-    const int32_t row_bytes = G * Elem<DT>::bytes + 16;
-    char* tile = smem;
-    double* acol = reinterpret_cast<double*>(smem + TILE_ROWS * row_bytes);     // s_c^2 of the chunk's columns
-    const int32_t mstride = mask_row_stride(G);
-    uint8_t* mtile = reinterpret_cast<uint8_t*>(acol + G);                       // the tile's mask bytes (masked calls)
     const int lane = threadIdx.x;
     const bool valid = lane < tc.nrows;
     const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + lane;
@@ -229,19 +386,37 @@ __global__ __launch_bounds__(RF_THREADS) void refine_plan_kernel(const RefineBat
         return;
     }
 
-    load_tile_raw<DT>(A.W, A.g.ld, tc, G, tile);
+    double* acol = reinterpret_cast<double*>(smem);                              // s_c^2 of the chunk's columns
+    char* tile = smem + (size_t)G * sizeof(double);
+    const int32_t stride = NV == 0 ? G * Elem<DT>::bytes + 16 : refine_pack_stride(G);
+    const int32_t turn = TILE_ROWS * (NV == 0 || stride > RF_SLAB_STRIDE ? stride : RF_SLAB_STRIDE);
+    uint8_t* mtile = reinterpret_cast<uint8_t*>(tile + turn);                    // the tile's mask bytes (masked calls)
+    RefineGroup<DT, MASKED, typename RefineRowOf<DT, NV>::type> g;
     for (int32_t c = lane; c < G; c += RF_THREADS) {
         const double sv = (double)A.s[tc.col0 + c];
         acol[c] = sv * sv;
     }
-    if (A.mask != nullptr) load_mask_tile(A.mask, A.mask_ld, tc, G, mtile);
-    __syncthreads();
+    if (MASKED) {
+        if (A.mask != nullptr) {
+            load_mask_tile(A.mask, A.mask_ld, tc, G, mtile);
+        } else {                                                                 // an item without one in a masked launch
+            for (int32_t i = lane; i < TILE_ROWS * mask_row_stride(G); i += RF_THREADS) mtile[i] = 0;
+        }
+    }
+    if constexpr (NV == 0) {
+        load_tile_raw<DT>(A.W, A.g.ld, tc, G, tile);
+        g.row.p = tile + lane * stride;
+        __syncthreads();
+    } else {
+        load_rows<DT, NV>(A, tc, tile, g.row);
+    }
+    g.mrow = MASKED ? mtile + lane * mask_row_stride(G) : nullptr;
+    g.acol = acol;
+    g.G = G;
 
-    char* wrow = tile + lane * row_bytes;
     double err = 0.0;
     if (valid) {
-        const uint8_t* mrow = A.mask != nullptr ? mtile + lane * mstride : nullptr;
-        uint8_t* dst = reinterpret_cast<uint8_t*>(wrow);
+        uint8_t* dst = reinterpret_cast<uint8_t*>(tile + lane * stride);
         float sc = 0.0f, of = 0.0f;
         if (a <= 4) {
             float p = 1.0f;
@@ -253,27 +428,23 @@ __global__ __launch_bounds__(RF_THREADS) void refine_plan_kernel(const RefineBat
             const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : 2));
             const float qmax = (float)((1 << bits) - 1);
             float mn, mx;
-            group_min_max<DT>(wrow, mrow, G, &mn, &mx);
+            g.min_max(&mn, &mx);
             uniform_params(mn, mx, p, qmax, &of, &sc);
-            refine_uniform<DT>(wrow, mrow, acol, G, qmax, B.n_iter, &of, &sc);
-            err = group_error<DT>(wrow, mrow, acol, G, a, sc, of);
+            g.uniform(qmax, B.n_iter, &of, &sc);
             switch (a) {
-                case 1: uniform_pack<DT, 8>(wrow, mrow, G, of, sc, dst); break;
-                case 2: uniform_pack<DT, 4>(wrow, mrow, G, of, sc, dst); break;
-                case 3: uniform_pack<DT, 3>(wrow, mrow, G, of, sc, dst); break;
-                default: uniform_pack<DT, 2>(wrow, mrow, G, of, sc, dst); break;
+                case 1: err = g.template uniform_finish<8>(sc, of, dst); break;
+                case 2: err = g.template uniform_finish<4>(sc, of, dst); break;
+                case 3: err = g.template uniform_finish<3>(sc, of, dst); break;
+                default: err = g.template uniform_finish<2>(sc, of, dst); break;
             }
         } else if (a == 5) {
-            sc = group_abs_mean<DT>(wrow, mrow, G);
+            sc = g.abs_mean();
             sc = sc >= FLT_MIN ? sc : 0.0f;
-            sc = refine_ternary<DT>(wrow, mrow, acol, G, B.n_iter, sc);
-            err = group_error<DT>(wrow, mrow, acol, G, a, sc, 0.0f);
-            ternary_pack<DT>(wrow, mrow, G, sc, dst);
+            sc = g.ternary(B.n_iter, sc);
+            err = g.ternary_finish(sc, dst);
         } else {
-            sc = group_abs_mean<DT>(wrow, mrow, G);
-            if (B.n_iter > 0) sc = refine_binary<DT>(wrow, mrow, acol, G, sc);
-            err = group_error<DT>(wrow, mrow, acol, G, a, sc, 0.0f);
-            binary_pack<DT>(wrow, mrow, G, dst);
+            sc = g.binary(B.n_iter);
+            err = g.binary_finish(sc, dst);
         }
         A.scale[gidx] = sc;
         A.offset[gidx] = of;
@@ -282,7 +453,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_plan_kernel(const RefineBat
     err = wave_sum(err);
     if (lane == 0) A.part[tile_idx] = err;
     __syncthreads();
-    copy_out_rows(tile, row_bytes, (int32_t)bpg, tc.nrows, A.codes + base + tc.lrow0 * bpg, lane, RF_THREADS);
+    copy_out_rows(tile, stride, (int32_t)bpg, tc.nrows, A.codes + base + tc.lrow0 * bpg, lane, RF_THREADS);
     if (padded != payload && tc.t == A.g.tiles_per_unit - 1 && lane < padded - payload)
         A.codes[base + payload + lane] = 0;
 }
@@ -300,6 +471,26 @@ __global__ __launch_bounds__(256) void refine_finalize_kernel(const RefineBatch 
 }  // namespace windq
 
 using namespace windq;
+
+template <int DT, int NV, bool MASKED>
+static int refine_launch_kernel(const RefineBatch& B, int32_t chunk_w, dim3 grid, hipStream_t hs) {
+    const size_t lds = refine_lds(DT, chunk_w, NV, MASKED);
+    const int st = ensure_lds(reinterpret_cast<const void*>(&refine_plan_kernel<DT, NV, MASKED>), lds);
+    if (st != WINDQ_OK) return st;
+    hipLaunchKernelGGL((refine_plan_kernel<DT, NV, MASKED>), grid, dim3(RF_THREADS), lds, hs, B);
+    return WINDQ_OK;
+}
+
+// Rows of up to 256 bytes in 64 registers, up to 512 bytes in 128, wider ones in LDS.
+template <int DT>
+static int refine_launch_rows(const RefineBatch& B, int32_t chunk_w, bool masked, dim3 grid, hipStream_t hs) {
+    const int32_t row_bytes = chunk_w * Elem<DT>::bytes;
+    if (row_bytes <= 2 * RF_SLAB)
+        return masked ? refine_launch_kernel<DT, 2, true>(B, chunk_w, grid, hs) : refine_launch_kernel<DT, 2, false>(B, chunk_w, grid, hs);
+    if (row_bytes <= 4 * RF_SLAB)
+        return masked ? refine_launch_kernel<DT, 4, true>(B, chunk_w, grid, hs) : refine_launch_kernel<DT, 4, false>(B, chunk_w, grid, hs);
+    return masked ? refine_launch_kernel<DT, 0, true>(B, chunk_w, grid, hs) : refine_launch_kernel<DT, 0, false>(B, chunk_w, grid, hs);
+}
 
 static int refine_launch(const windq_refine_item* items, int32_t n, int32_t chunk_w, int64_t unit_rows,
                          const float* clip_grid, int32_t K, int32_t n_iter, void* stream) {
@@ -363,18 +554,9 @@ static int refine_launch(const windq_refine_item* items, int32_t n, int32_t chun
     if (tiles > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
-    const size_t lds = raw_tile_lds_bytes(dtype, chunk_w) + (size_t)chunk_w * sizeof(double) +
-                       (any_mask ? mask_tile_lds_bytes(chunk_w) : 0);
     const dim3 grid((unsigned)tiles);
-    if (dtype == WINDQ_BF16) {
-        st = ensure_lds(reinterpret_cast<const void*>(&refine_plan_kernel<WINDQ_BF16>), lds);
-        if (st != WINDQ_OK) return st;
-        hipLaunchKernelGGL(refine_plan_kernel<WINDQ_BF16>, grid, dim3(RF_THREADS), lds, hs, B);
-    } else {
-        st = ensure_lds(reinterpret_cast<const void*>(&refine_plan_kernel<WINDQ_F32>), lds);
-        if (st != WINDQ_OK) return st;
-        hipLaunchKernelGGL(refine_plan_kernel<WINDQ_F32>, grid, dim3(RF_THREADS), lds, hs, B);
-    }
+    st = dtype == WINDQ_BF16 ? refine_launch_rows<WINDQ_BF16>(B, chunk_w, any_mask, grid, hs) : refine_launch_rows<WINDQ_F32>(B, chunk_w, any_mask, grid, hs);
+    if (st != WINDQ_OK) return st;
     hipLaunchKernelGGL(refine_finalize_kernel, dim3((unsigned)units), dim3(256), 0, hs, B);
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }

@@ -66,6 +66,34 @@ def test_refine_plan(windq, R, C, G, unit_rows, K, n_iter, dtype):
     run_case(windq, W, s, G, unit_rows, K, n_iter)
 
 
+@pytest.mark.parametrize("R,C,G,dtype,ppm", [
+    (65, 7 * 128, 128, torch.bfloat16, 0),          # 64 registers a row, whole; a tile of one row
+    (40, 7 * 72, 72, torch.float32, 0), (70, 7 * 136, 136, torch.bfloat16, 50000),     # 128 registers, partly filled
+    (33, 7 * 128, 128, torch.float32, 50000),       # 128 registers, whole
+    (30, 7 * 136, 136, torch.float32, 0), (20, 7 * 264, 264, torch.bfloat16, 50000)])  # just too wide for registers
+def test_refine_at_the_edges_of_its_row_storage(windq, R, C, G, dtype, ppm):
+    W = synth.weights_llm(R, C, seed=117, device=DEV, dtype=dtype)
+    s = torch.exp(torch.randn(C, generator=torch.Generator().manual_seed(6))).to(DEV)
+    run_case(windq, W, s, G, 0, 5, 2, ppm=ppm)
+
+
+def test_refine_batch_with_and_without_masks(windq):
+    """Items with a mask and items without in one launch: each as it would be alone."""
+    Ws = [synth.weights_llm(96, 256, seed=118 + i, device=DEV) for i in range(2)]
+    s = torch.rand(256, device=DEV) + 0.1
+    mask = windq.windq_salient_select(Ws[0], s, 128, 0, 50000)
+    action = torch.tensor([4, 5], dtype=torch.uint8)
+    off = windq.windq_plan_layout(action, 96, 128).to(DEV)
+    args = (action.to(DEV), None, None, off)
+    alone = [windq.windq_refine_plan(W, s, 128, 0, *args, 3, mask=m) for W, m in zip(Ws, (mask, None))]
+    codes = [torch.zeros_like(alone[0][0]) for _ in range(2)]
+    both = windq.windq_refine_plan_batch(Ws, [s, s], 128, 0, [args[0]] * 2, [None] * 2, None, [off] * 2, 3, codes, masks=[mask, None])
+    torch.cuda.synchronize()
+    for a, b in zip(alone, both):
+        for x, y in zip(a, b):
+            assert torch.equal(x, y)
+
+
 def test_refine_plan_under_a_protection_mask(windq):
     W = synth.weights_llm(128, 256, seed=113, device=DEV)
     X = synth.activations_llm(64, 256, seed=114, device=DEV)
