@@ -27,7 +27,8 @@
 //           and the workgroup that finishes it goes on to select P99 by two digit passes over the
 //           unit's weights and to count in a third.  W is read only for such units.
 // fp32 (31-bit keys, digits 11 + 11 + 9): one pass per further digit plus a counting pass
-// (2|w| > P99, exact in fp32), each re-deriving the prefix from the finished histograms.
+// (2|w| > P99, exact in fp32), each re-deriving the prefix from the finished histograms; units
+// of up to 98304 weights do all of that in one launch, from registers (feat_small_f32_kernel).
 // Passes after the first re-read a matrix that was just streamed; up to the 256 MB
 // last-level cache they are served on chip.  Integer atomics only, fixed-order fp64
 // sums: results are bit-reproducible.
@@ -98,11 +99,12 @@ __global__ __launch_bounds__(256) void feat_init_kernel(const FeatBatch B) {
     if (DT == WINDQ_BF16 && i == 0) *A.list_count = 0u;
 }
 
-// Block-wide sum of a per-thread double in a fixed order (lanes by butterfly, wavefronts in order).
+// Block-wide sum of a per-thread double in a fixed order (lanes by butterfly, wavefronts in order).  In a workgroup of more
+// than FT_THREADS only the first FT_THREADS count: the same order, the same bits.
 __device__ __forceinline__ double block_sum(double v, double* red) {
     v = wave_sum(v);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < FT_THREADS) red[threadIdx.x >> 6] = v;
     __syncthreads();
     double t = 0.0;
 #pragma unroll
@@ -241,7 +243,7 @@ __device__ __forceinline__ void block_sum_n(double (&v)[N], double* red) {
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j] = wave_sum(v[j]);
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 0 && threadIdx.x < FT_THREADS) {
 #pragma unroll
         for (int j = 0; j < N; ++j) red[j * FT_WAVES + (threadIdx.x >> 6)] = v[j];
     }
@@ -318,6 +320,71 @@ __device__ __forceinline__ void feat_exact_bf16_unit(const FeatArgs& A, int64_t 
     }
 }
 
+// The last step of a unit: moments and the chunk's activation scales to features, by the first FT_THREADS threads of a
+// workgroup (all call it).  `above`: this thread's share of the number of |w| > 0.5 P99.
+struct FeatTailIn {
+    double mv[4];
+    float sv0, sv1;
+};
+__device__ __forceinline__ FeatTailIn feat_tail_load(const FeatArgs& A, int64_t u) {
+    static_assert(WINDQ_MAX_CHUNK <= 2 * FT_THREADS, "two activation scales per thread cover a chunk");
+    const int tid = threadIdx.x;
+    const float* __restrict__ sc = A.s + (u % A.g.n_chunks) * A.g.chunk_w;
+    FeatTailIn in = {{0.0, 0.0, 0.0, 0.0}, 0.0f, 0.0f};
+    if (tid < FT_THREADS && tid < A.mparts) {
+        const double* src = A.moments + ((size_t)u * (size_t)A.mparts + (size_t)tid) * 4;
+        in.mv[0] = src[0]; in.mv[1] = src[1]; in.mv[2] = src[2]; in.mv[3] = src[3];
+    }
+    if (tid < FT_THREADS && tid < A.g.chunk_w) in.sv0 = sc[tid];
+    if (tid < FT_THREADS && tid + FT_THREADS < A.g.chunk_w) in.sv1 = sc[tid + FT_THREADS];
+    return in;
+}
+__device__ __forceinline__ void feat_tail(const FeatArgs& A, int64_t u, const FeatTailIn& in, double above, bool above_known, double* red,
+                                          float* smax_sh) {
+    const int tid = threadIdx.x;
+    const int32_t G = A.g.chunk_w;
+    const bool mine = tid < FT_THREADS;
+    const bool has0 = mine && tid < G, has1 = mine && tid + FT_THREADS < G;
+    double m[4] = {in.mv[0], in.mv[1], in.mv[2], in.mv[3]};
+    if (mine) {
+        for (int64_t b = tid + FT_THREADS; b < A.mparts; b += FT_THREADS) {
+            const double* src = A.moments + ((size_t)u * (size_t)A.mparts + (size_t)b) * 4;
+            m[0] += src[0]; m[1] += src[1]; m[2] += src[2]; m[3] += src[3];
+        }
+    }
+    double ssum = 0.0;
+    float smax = A.s[(u % A.g.n_chunks) * G];
+    if (has0) { ssum += (double)in.sv0; smax = fmaxf(smax, in.sv0); }
+    if (has1) { ssum += (double)in.sv1; smax = fmaxf(smax, in.sv1); }
+    double r6[6] = {above, m[0], m[1], m[2], m[3], ssum};
+    block_sum_n<6>(r6, red);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) smax = fmaxf(smax, __shfl_xor(smax, d, 64));
+    if ((tid & 63) == 0 && mine) smax_sh[tid >> 6] = smax;
+    const double smean = r6[5] / (double)G;
+    double sdev = 0.0;
+    if (has0) { const double d = (double)in.sv0 - smean; sdev = fma(d, d, sdev); }
+    if (has1) { const double d = (double)in.sv1 - smean; sdev = fma(d, d, sdev); }
+    sdev = block_sum(sdev, red);   // its barriers also publish smax_sh
+    if (tid == 0) {
+        float mx = smax_sh[0];
+        for (int w = 1; w < FT_WAVES; ++w) mx = fmaxf(mx, smax_sh[w]);
+        const double n = (double)A.g.R_u * (double)G;
+        const double mean = r6[1] / n;
+        double var = r6[2] / n - mean * mean;
+        var = var > 0.0 ? var : 0.0;
+        float* f = A.feat + u * WINDQ_N_FEAT;
+        f[0] = (float)mean;
+        f[1] = (float)sqrt(var);
+        f[2] = (float)(r6[3] / n);
+        f[3] = (float)(r6[4] / n);
+        if (above_known) f[4] = (float)(r6[0] / n);
+        f[5] = (float)smean;
+        f[6] = (float)sqrt(sdev / (double)G);
+        f[7] = mx;
+    }
+}
+
 // Per unit: P99's key from the finished histograms, the count above half of it, the
 // moments in block order, the statistics of s over the chunk; writes the eight features.
 // The kernel is a chain of memory latencies (32-86 workgroups, nothing to overlap them
@@ -329,23 +396,12 @@ __global__ __launch_bounds__(FT_THREADS) void feat_finish_kernel(const FeatBatch
     __shared__ double red[6 * FT_WAVES];
     __shared__ uint32_t sh_part[FT_THREADS];
     __shared__ uint32_t sh_out[4];
-    __shared__ float smax_sh[FT_THREADS];
+    __shared__ float smax_sh[FT_WAVES];
     const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
     const FeatArgs& A = B.m[mi];
     const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
-    const int32_t G = A.g.chunk_w;
-    const float* __restrict__ sc = A.s + (u % A.g.n_chunks) * G;
     const int tid = threadIdx.x;
-    // requested now, used after the selection
-    static_assert(WINDQ_MAX_CHUNK <= 2 * FT_THREADS, "two activation scales per thread cover a chunk");
-    double mv[4] = {0.0, 0.0, 0.0, 0.0};
-    if (tid < A.mparts) {
-        const double* src = A.moments + ((size_t)u * (size_t)A.mparts + (size_t)tid) * 4;
-        mv[0] = src[0]; mv[1] = src[1]; mv[2] = src[2]; mv[3] = src[3];
-    }
-    const bool has0 = tid < G, has1 = tid + FT_THREADS < G;
-    const float sv0 = has0 ? sc[tid] : 0.0f;
-    const float sv1 = has1 ? sc[tid + FT_THREADS] : 0.0f;
+    const FeatTailIn in = feat_tail_load(A, u);      // requested now, used after the selection
     const uint32_t* h0 = A.hist + (size_t)u * FEAT_BINS;
 
     double above = 0.0;
@@ -423,40 +479,7 @@ __global__ __launch_bounds__(FT_THREADS) void feat_finish_kernel(const FeatBatch
         for (int64_t b = tid; b < A.bpu; b += FT_THREADS) above += (double)A.above[(size_t)u * A.bpu + b];
     }
 
-    double m[4] = {mv[0], mv[1], mv[2], mv[3]};
-    for (int64_t b = tid + FT_THREADS; b < A.mparts; b += FT_THREADS) {
-        const double* src = A.moments + ((size_t)u * (size_t)A.mparts + (size_t)b) * 4;
-        m[0] += src[0]; m[1] += src[1]; m[2] += src[2]; m[3] += src[3];
-    }
-    double ssum = 0.0;
-    float smax = sc[0];
-    if (has0) { ssum += (double)sv0; smax = fmaxf(smax, sv0); }
-    if (has1) { ssum += (double)sv1; smax = fmaxf(smax, sv1); }
-    double r6[6] = {above, m[0], m[1], m[2], m[3], ssum};
-    block_sum_n<6>(r6, red);
-    smax_sh[tid] = smax;
-    const double smean = r6[5] / (double)G;
-    double sdev = 0.0;
-    if (has0) { const double d = (double)sv0 - smean; sdev = fma(d, d, sdev); }
-    if (has1) { const double d = (double)sv1 - smean; sdev = fma(d, d, sdev); }
-    sdev = block_sum(sdev, red);   // its barriers also publish smax_sh
-    if (tid == 0) {
-        float mx = smax_sh[0];
-        for (int i = 1; i < FT_THREADS; ++i) mx = fmaxf(mx, smax_sh[i]);
-        const double n = (double)A.g.R_u * (double)G;
-        const double mean = r6[1] / n;
-        double var = r6[2] / n - mean * mean;
-        var = var > 0.0 ? var : 0.0;
-        float* f = A.feat + u * WINDQ_N_FEAT;
-        f[0] = (float)mean;
-        f[1] = (float)sqrt(var);
-        f[2] = (float)(r6[3] / n);
-        f[3] = (float)(r6[4] / n);
-        if (!listed) f[4] = (float)(r6[0] / n);
-        f[5] = (float)smean;
-        f[6] = (float)sqrt(sdev / (double)G);
-        f[7] = mx;
-    }
+    feat_tail(A, u, in, above, !listed, red, smax_sh);
     if (DT == WINDQ_BF16 && listed) {          // (the same decision in every thread)
         __shared__ uint32_t xh[256];
         __shared__ uint32_t xsum[FT_WAVES];
@@ -464,10 +487,107 @@ __global__ __launch_bounds__(FT_THREADS) void feat_finish_kernel(const FeatBatch
     }
 }
 
+// fp32 units of up to FEAT_SMALL weights: everything after the first pass by ONE workgroup per unit that keeps the unit's
+// weights in registers (PER pieces of eight per thread) and takes both later digits, the count and the last step in turn.
+// Larger units take a launch per pass, which costs a small call more than the pass does.  What bounds this kernel is a chain
+// of waits on one CU (load, three selections, two sweeps with atomics in LDS, the last sums).  512 x 512 at chunk 64: 15 us
+// for the three passes' and the finish kernel's 29, and three launches less (features + fit 60 -> 47 us);
+// 1000 x 1056 at chunk 96: 25 us for 35.  Listing the keys that share the first digit, so as to sweep them alone for the
+// last one, gains nothing (its counter is one more wait).  The limit is what 1024 threads hold at 128 registers each; with
+// units that large, and few of them, the passes' many workgroups are about to catch up anyway.
+constexpr int64_t FEAT_SMALL = 98304;
+template <int NT, int PER>
+__global__ __launch_bounds__(NT) void feat_small_f32_kernel(const FeatBatch B) {
+    __shared__ uint32_t lhist[FEAT_BINS];
+    __shared__ double red[6 * FT_WAVES];
+    __shared__ uint32_t sh_part[NT / 64];
+    __shared__ uint32_t sh_out[2];
+    __shared__ float smax_sh[FT_WAVES];
+    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
+    const FeatArgs& A = B.m[mi];
+    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    const int32_t G = A.g.chunk_w;
+    const int32_t pieces = G >> 3;
+    const int32_t total = (int32_t)(A.g.R_u * pieces);
+    const int64_t rb = u / A.g.n_chunks;
+    const float* __restrict__ W = static_cast<const float*>(A.W) + rb * A.g.R_u * A.g.ld + (u - rb * A.g.n_chunks) * G;
+    uint32_t key[PER][8];                // pieces past the unit's end: its last piece again, left out below.  No load waits behind a branch
+    PieceWalk at((int32_t)threadIdx.x, NT, pieces);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const bool in_unit = k * NT + (int32_t)threadIdx.x < total;
+        const int64_t r = in_unit ? at.r : (int32_t)A.g.R_u - 1;
+        const int32_t pc = in_unit ? at.pc : pieces - 1;
+        const uint4* src = reinterpret_cast<const uint4*>(W + r * A.g.ld + pc * 8);
+        const uint4 a = src[0], b = src[1];
+        key[k][0] = a.x; key[k][1] = a.y; key[k][2] = a.z; key[k][3] = a.w;
+        key[k][4] = b.x; key[k][5] = b.y; key[k][6] = b.z; key[k][7] = b.w;
+        at.next();
+    }
+    FeatTailIn in;
+    if (PER <= 8) in = feat_tail_load(A, u);       // where registers are left: requested before the selection
+    uint32_t prefix = 0;
+    uint64_t rank = A.rank;
+#pragma unroll
+    for (int level = 0; level < 3; ++level) {
+        const int shift = level_shift<WINDQ_F32>(level), bits = level_bits<WINDQ_F32>(level);
+        uint32_t bin;
+        uint64_t below;
+        if (level == 0) {
+            select_bin<NT>(A.hist + (size_t)u * FEAT_BINS, FEAT_BINS, rank, sh_part, sh_out, &bin, &below);
+        } else {
+            __syncthreads();
+            for (int32_t b = threadIdx.x; b < FEAT_BINS; b += NT) lhist[b] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < PER; ++k) {
+                if (k * NT + (int32_t)threadIdx.x < total) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t q = key[k][j] & 0x7fffffffu;
+                        if ((q >> (shift + bits)) == prefix) atomicAdd(&lhist[(q >> shift) & ((1u << bits) - 1u)], 1u);
+                    }
+                }
+            }
+            __syncthreads();
+            select_bin<NT>(lhist, 1 << bits, rank, sh_part, sh_out, &bin, &below);
+        }
+        prefix = (prefix << bits) | bin;
+        rank -= below;
+    }
+    const float p99 = __uint_as_float(prefix);
+    uint32_t cnt = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (k * NT + (int32_t)threadIdx.x < total) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) cnt += 2.0f * fabsf(__uint_as_float(key[k][j])) > p99 ? 1u : 0u;
+        }
+    }
+    // the counts of all wavefronts to the first threads, which take part in the last step
+    if (NT > FT_THREADS) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0) sh_part[threadIdx.x >> 6] = cnt;
+        __syncthreads();
+        cnt = threadIdx.x < NT / 64 ? sh_part[threadIdx.x] : 0u;
+    }
+    if (PER > 8) in = feat_tail_load(A, u);
+    feat_tail(A, u, in, (double)cnt, true, red, smax_sh);
+}
+
 template <int DT>
 static int launch_rest(const FeatBatch& B, hipStream_t hs) {
     if (DT == WINDQ_BF16) {
         hipLaunchKernelGGL((feat_finish_kernel<DT>), dim3((unsigned)B.units_total), dim3(FT_THREADS), 0, hs, B);
+    } else if (B.largest_unit <= FEAT_SMALL) {
+        // threads for about 64 weights each; 96 between 64 K and the limit (1024 threads have 128 registers each)
+        const dim3 units((unsigned)B.units_total);
+        if (B.largest_unit <= 16384) hipLaunchKernelGGL((feat_small_f32_kernel<256, 8>), units, dim3(256), 0, hs, B);
+        else if (B.largest_unit <= 32768) hipLaunchKernelGGL((feat_small_f32_kernel<1024, 4>), units, dim3(1024), 0, hs, B);
+        else if (B.largest_unit <= 65536) hipLaunchKernelGGL((feat_small_f32_kernel<1024, 8>), units, dim3(1024), 0, hs, B);
+        else hipLaunchKernelGGL((feat_small_f32_kernel<1024, 12>), units, dim3(1024), 0, hs, B);
     } else {
         const dim3 blocks((unsigned)B.blocks_total);
         hipLaunchKernelGGL((feat_pass_kernel<DT, 1>), blocks, dim3(FT_THREADS), 0, hs, B, 1);
@@ -492,7 +612,7 @@ int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t uni
     if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
     FeatBatch& B = *Bp;
     B.n = n;
-    int64_t blocks = 0, units = 0, inits = 0;
+    int64_t blocks = 0, units = 0, inits = 0, largest = 0;
     float thr = (float)1e-6;
     if ((double)thr < 1e-6) thr = nextafterf(thr, INFINITY);
     // bf16 keys order like their values: the smallest key whose value reaches the threshold
@@ -528,6 +648,7 @@ int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t uni
         A.sparse_thr = thr;
         const uint64_t nw = (uint64_t)A.g.R_u * (uint64_t)chunk_w;
         A.rank = (99 * nw + 99) / 100;
+        if ((int64_t)nw > largest) largest = (int64_t)nw;
         B.block_start[i] = blocks;
         B.unit_start[i] = units;
         B.init_start[i] = inits;
@@ -546,6 +667,7 @@ int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t uni
     B.blocks_total = blocks;
     B.units_total = units;
     B.init_total = inits;
+    B.largest_unit = largest;
     return WINDQ_OK;
 }
 

@@ -36,6 +36,7 @@ struct FeatBatch {
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     int64_t init_start[WINDQ_MAX_BATCH + 1];     // in workgroups of 256 counters
     int64_t blocks_total, units_total, init_total;
+    int64_t largest_unit;                        // weights
     FeatArgs m[WINDQ_MAX_BATCH];
 };
 

@@ -144,6 +144,22 @@ def test_features_bf16(windq, R, C, G, unit_rows):
     check_features(windq, W, s, G, unit_rows)
 
 
+@pytest.mark.parametrize("R,C,G,unit_rows", [
+    (3, 48, 24, 1),                       # units smaller than a wavefront's pieces
+    (512, 64, 32, 0), (2048, 16, 8, 0),   # 16384 weights: the last of the smallest size
+    (513, 64, 32, 0),                     # one row more
+    (1024, 64, 32, 0), (1025, 32, 32, 0), (2048, 32, 32, 0), (2049, 32, 32, 0),
+    (1024, 192, 96, 0), (1025, 192, 96, 0),          # 98304, and the first that takes a launch per pass
+])
+def test_features_fp32_at_the_edges_of_unit_sizes(windq, R, C, G, unit_rows):
+    W = synth.weights_llm(R, C, seed=R + C, dtype=torch.float32).to(DEV)
+    s = torch.rand(C, generator=torch.Generator().manual_seed(R)).add(0.1).to(DEV)
+    check_features(windq, W, s, G, unit_rows)
+    W[:, :G] = 0.25                       # one unit all of one digit: every weight is a candidate to the last
+    W[0, 0] = -0.5
+    check_features(windq, W, s, G, unit_rows)
+
+
 def test_features_exact_zeros_ties_and_tiny_values(windq):
     W = torch.zeros(128, 128, dtype=torch.float32, device=DEV)
     W[:, 64:] = 0.5                       # every |w| in chunk 1 equal: P99 = 0.5, none above 0.25? all are
