@@ -11,9 +11,8 @@
 // 16-byte piece of W, one mask byte, `bits` bytes of codes (ternary: the two or three bytes
 // its eight trits sit in), and G/8 neighbouring lanes cover a row with contiguous loads
 // straight from HBM; a workgroup walks the 64 rows of a tile, each lane keeping the fp64
-// weights s_c^2 of its columns.  ~6 fp64 operations per weight: the fp64 ALU and HBM are
-// both a few times under their limits.  Other widths: one wavefront per tile, one lane per
-// row over a tile staged in LDS (a lane walks its row's byte stream).
+// weights s_c^2 of its columns.  Other widths, and buffers off those alignments: the same
+// pieces, numbered through the tile, a thread's columns found per piece.
 #include "windq_common.hpp"
 #include "windq_ws.hpp"
 
@@ -62,91 +61,6 @@ __device__ __forceinline__ int64_t dq_bytes_per_group(int a, int G) {
         case 6: return G >> 3;
         default: return 0;
     }
-}
-
-template <int DT>
-__global__ __launch_bounds__(64) void dequant_tile_kernel(const DequantBatch B) {
-    extern __shared__ char smem[];
-    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
-    const DequantArgs& A = B.m[mi];
-    const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]);
-    const int32_t G = A.g.chunk_w;
-    constexpr int EB = Elem<DT>::bytes;
-    const int32_t row_bytes = G * EB + 16;
-    float* scol = reinterpret_cast<float*>(smem + TILE_ROWS * row_bytes);
-    const int lane = threadIdx.x;
-    load_tile_raw<DT>(A.W, A.g.ld, tc, G, smem);
-    for (int32_t c = lane; c < G; c += 64) scol[c] = A.s[tc.col0 + c];
-    __syncthreads();
-
-    int a = A.action[tc.u];
-    if (a >= WINDQ_N_ACTIONS) a = 0;
-    const int64_t bpg = dq_bytes_per_group(a, G);
-    const int64_t base = A.code_off[tc.u];
-    if (base < 0 || (base & 15) != 0 || base + bpg * A.g.R_u > A.codes_bytes) a = 0;   // a malformed entry reads nothing
-
-    double acc = 0.0;
-    if (lane < tc.nrows) {
-        const char* wrow = smem + lane * row_bytes;
-        const int64_t row = tc.row0 + lane;
-        const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + lane;
-        const float sc = a != 0 ? A.scale[gidx] : 0.0f;
-        const float of = a != 0 ? A.offset[gidx] : 0.0f;
-        const uint8_t* __restrict__ src = A.codes + base + (tc.lrow0 + lane) * bpg;
-        const uint8_t* __restrict__ mrow = A.mask != nullptr ? A.mask + row * A.mask_ld + (tc.col0 >> 3) : nullptr;
-        float* __restrict__ orow = A.what != nullptr ? A.what + row * A.what_ld + tc.col0 : nullptr;
-        const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : (a == 4 ? 2 : 1)));
-        for (int32_t c = 0; c < G; c += 8) {
-            float w[8];
-            read8<DT>(wrow, c, w);
-            const uint32_t m = mrow != nullptr ? mrow[c >> 3] : 0u;
-            uint32_t stored[8];
-            if (a == 5) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int32_t i = c + j;
-                    const uint32_t byte = src[i / 5];
-                    const int pos = i % 5;
-                    const uint32_t div = pos == 0 ? 1u : (pos == 1 ? 3u : (pos == 2 ? 9u : (pos == 3 ? 27u : 81u)));
-                    stored[j] = (byte / div) % 3u;
-                }
-            } else if (a != 0) {
-                uint64_t v = 0;
-                const uint8_t* p = src + (c >> 3) * bits;          // eight codes = `bits` bytes
-                for (int b = 0; b < bits; ++b) v |= (uint64_t)p[b] << (8 * b);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) stored[j] = (uint32_t)(v >> (j * bits)) & ((1u << bits) - 1u);
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool prot = ((m >> j) & 1u) != 0u;
-                float wh = w[j];                                      // a skip unit keeps its weights
-                if (a != 0) {
-                    double whd;
-                    if (a <= 4) {
-                        wh = fmaf((float)stored[j], sc, of);
-                        whd = (double)of + (double)stored[j] * (double)sc;
-                    } else if (a == 5) {
-                        wh = sc * ((float)stored[j] - 1.0f);
-                        whd = (double)wh;
-                    } else {
-                        wh = stored[j] != 0u ? sc : -sc;
-                        whd = (double)wh;
-                    }
-                    if (prot) {
-                        wh = 0.0f;                                    // lives in the INT8 side stream
-                    } else {
-                        const double d = (double)w[j] - whd;
-                        const double ac = (double)scol[c + j] * (double)scol[c + j];
-                        acc = fma(ac * d, d, acc);
-                    }
-                }
-                if (orow != nullptr) orow[c + j] = wh;
-            }
-        }
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) A.part[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t] = acc;      // one partial per tile
 }
 
 // Eight consecutive weights of a row, straight from global memory.
@@ -296,6 +210,151 @@ __global__ __launch_bounds__(DQ_THREADS) void dequant_split_kernel(const Dequant
                 reinterpret_cast<float4*>(orow)[1] = make_float4(wh[4], wh[5], wh[6], wh[7]);
             }
         }
+    }
+    acc = wave_sum(acc);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < DQ_THREADS / 64; ++i) t += red[i];
+        A.part[((size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t) * (size_t)passes + (size_t)pass] = t;
+    }
+}
+
+// Eight columns of row r of a tile: unpacked, reconstructed, written, and their error added to acc.
+template <int DT, bool ALIGNED>
+__device__ __forceinline__ void dequant_piece(const DequantArgs& A, const TileCoord& tc, int a, int64_t bpg, int64_t base, int32_t r, int32_t sub,
+                                              const double (&ac)[8], const uint16_t* __restrict__ trits_of, double* acc) {
+    constexpr int EB = Elem<DT>::bytes;
+    const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : (a == 4 ? 2 : 1)));
+    const int32_t c = sub * 8;
+    const int64_t row = tc.row0 + r;
+    const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + r;
+    float w[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    load8_global<DT>(static_cast<const char*>(A.W) + (row * A.g.ld + tc.col0 + c) * EB, w);
+    const uint32_t m = A.mask != nullptr ? A.mask[row * A.mask_ld + (tc.col0 >> 3) + sub] : 0u;
+    float* __restrict__ orow = A.what != nullptr ? A.what + row * A.what_ld + tc.col0 + c : nullptr;
+    float wh[8];
+    if (a == 0) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) wh[j] = w[j];                     // a skip unit keeps its weights
+    } else {
+        const float sc = A.scale[gidx];
+        const float of = A.offset[gidx];
+        const uint8_t* __restrict__ src = A.codes + base + (tc.lrow0 + r) * bpg;
+        double whd[8];
+        if (a == 5) {
+            // eight trits, five to a byte: they sit in two or three neighbouring bytes
+            const int32_t b0 = c / 5;
+            const int32_t last = (int32_t)bpg - 1;
+            const uint32_t y0 = src[b0];
+            const uint32_t y1 = src[b0 + 1 <= last ? b0 + 1 : last];
+            const uint32_t y2 = src[b0 + 2 <= last ? b0 + 2 : last];
+            const uint32_t v = ((uint32_t)trits_of[y0] | ((uint32_t)trits_of[y1] << 10) | ((uint32_t)trits_of[y2] << 20)) >>
+                               (2 * (c - 5 * b0));
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                wh[j] = sc * ((float)((v >> (2 * j)) & 3u) - 1.0f);
+                whd[j] = (double)wh[j];
+            }
+        } else {
+            // eight codes = `bits` bytes, aligned to their own size (units start on 16 bytes)
+            const uint8_t* p = src + sub * bits;
+            uint64_t v;
+            if (!ALIGNED) {
+                v = 0;
+                for (int b = 0; b < bits; ++b) v |= (uint64_t)p[b] << (8 * b);
+            } else if (bits == 8) {
+                const uint2 t = *reinterpret_cast<const uint2*>(p);
+                v = (uint64_t)t.x | ((uint64_t)t.y << 32);
+            } else if (bits == 4) {
+                v = *reinterpret_cast<const uint32_t*>(p);
+            } else if (bits == 3) {
+                const uint32_t t0 = p[0], t1 = p[1], t2 = p[2];
+                v = t0 | (t1 << 8) | (t2 << 16);
+            } else if (bits == 2) {
+                v = *reinterpret_cast<const uint16_t*>(p);
+            } else {
+                v = p[0];
+            }
+            if (a == 6) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    wh[j] = ((v >> j) & 1u) != 0u ? sc : -sc;
+                    whd[j] = (double)wh[j];
+                }
+            } else {
+                const double scd = (double)sc, ofd = (double)of;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t code = (uint32_t)(v >> (j * bits)) & ((1u << bits) - 1u);
+                    wh[j] = fmaf((float)code, sc, of);
+                    whd[j] = ofd + (double)code * scd;
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool prot = ((m >> j) & 1u) != 0u;              // lives in the INT8 side stream
+            const double d = (double)w[j] - whd[j];
+            *acc = fma(prot ? 0.0 : ac[j] * d, d, *acc);
+            wh[j] = prot ? 0.0f : wh[j];
+        }
+    }
+    if (orow != nullptr) {
+        if (ALIGNED) {
+            reinterpret_cast<float4*>(orow)[0] = make_float4(wh[0], wh[1], wh[2], wh[3]);
+            reinterpret_cast<float4*>(orow)[1] = make_float4(wh[4], wh[5], wh[6], wh[7]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) orow[j] = wh[j];
+        }
+    }
+}
+
+// Every other case: widths that are not 8 x 2^k columns, w_hat off 16 bytes, codes off 8 (the last two: ALIGNED false).
+// A pass is 256 pieces (eight columns of a row each, rows one after the other), one per thread; widths that are no multiple
+// of 32 have a last pass of more (dequant_passes rounds down), whose threads take several.  Bound by the chain of waits
+// from the unit's action to its codes.  1000 x 1056 fp32 at chunk 96: 6.4 us; a lane per row over a tile in LDS took 41
+// (a division per trit, single words stored 96 apart).  Two or four passes per workgroup, with their loads in
+// flight together, take 8.1 and 8.8: fewer workgroups.  The kernel above stays for its widths: finding a piece's row and
+// columns here costs 10 % there, and even its own body in this function 5 % (7B-shaped block: 308 us against 325 to 341).
+template <int DT, bool ALIGNED>
+__global__ __launch_bounds__(DQ_THREADS) void dequant_any_kernel(const DequantBatch B, const int32_t chunk_w) {
+    __shared__ double red[DQ_THREADS / 64];
+    __shared__ uint16_t trits_of[256];
+    const int32_t passes = dequant_passes(chunk_w);
+    const uint32_t tile_b = blockIdx.x / (uint32_t)passes;      // tile of the launch
+    const int32_t pass = (int32_t)(blockIdx.x - tile_b * (uint32_t)passes);
+    const int mi = batch_index(B.tile_start, B.n, tile_b);
+    const DequantArgs& A = B.m[mi];
+    const TileCoord tc = tile_coord(A.g, (int64_t)tile_b - B.tile_start[mi]);
+    const int32_t G = chunk_w;
+    const int32_t pieces = G >> 3;
+    const int32_t total = tc.nrows * pieces;
+    const uint32_t inv = ((1u << 20) + (uint32_t)pieces - 1u) / (uint32_t)pieces;     // i / pieces = i * inv >> 20 for i < 64 * pieces
+
+    int a = A.action[tc.u];
+    if (a >= WINDQ_N_ACTIONS) a = 0;
+    const int64_t bpg = dq_bytes_per_group(a, G);
+    const int64_t base = A.code_off[tc.u];
+    if (base < 0 || (base & 15) != 0 || base + bpg * A.g.R_u > A.codes_bytes) a = 0;   // a malformed entry reads nothing
+    if (a == 5) {
+        fill_trits(trits_of);
+        __syncthreads();
+    }
+    double acc = 0.0;
+    for (int32_t i = pass * DQ_THREADS + (int32_t)threadIdx.x; i < total; i += passes * DQ_THREADS) {
+        const int32_t r = (int32_t)(((uint32_t)i * inv) >> 20);
+        const int32_t sub = i - r * pieces;
+        double ac[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const double sv = (double)A.s[tc.col0 + sub * 8 + j];
+            ac[j] = sv * sv;
+        }
+        dequant_piece<DT, ALIGNED>(A, tc, a, bpg, base, r, sub, ac, trits_of, &acc);
     }
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -798,18 +857,13 @@ static void dequant_args(const DequantItem& it, DequantArgs* A) {
     A->gpart = static_cast<double*>(it.ws);
 }
 
-// Matrices whose layout allows it go through the lanes-per-row kernel, the others through the
-// tile kernel, exactly as each would alone: at most two sub-batches per call.
+// Matrices whose buffers are aligned go in one launch, the others in one of their own, exactly as each would alone.
 static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int64_t unit_rows, void* stream) {
     if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
-    // lanes-per-row kernel: 8 x 2^k columns, 16-byte pieces of W and of w_hat aligned
-    int lpr_shift = -1;
-    for (int k = 0; k <= 6; ++k)
-        if (chunk_w == (8 << k)) lpr_shift = k;
     const int32_t passes = dequant_passes(chunk_w);
-    DequantBatch S, T;          // lanes-per-row, tile
-    S.n = T.n = 0;
-    bool any_err_s = false, any_err_t = false;
+    DequantBatch L[2];          // aligned, not
+    L[0].n = L[1].n = 0;
+    bool any_err[2] = {false, false};
     for (int32_t i = 0; i < n; ++i) {
         const DequantItem& it = items[i];
         DequantArgs A;
@@ -826,43 +880,33 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
         dequant_args(it, &A);
         A.what = it.w_hat;
         A.err = it.err;
-        const size_t eb = it.W->dtype == WINDQ_BF16 ? 2 : 4;
-        const bool split = lpr_shift >= 0 && aligned(it.W->data, 16) && ((size_t)it.W->ld * eb) % 16 == 0 &&
-                           (A.what == nullptr || aligned(A.what, 16)) && aligned(it.codes, 8);
-        A.per_unit = split ? A.g.tiles_per_unit * passes : A.g.tiles_per_unit;
-        if (split) {
-            S.m[S.n++] = A;
-            any_err_s = any_err_s || A.err != nullptr;
-        } else {
-            T.m[T.n++] = A;
-            any_err_t = any_err_t || A.err != nullptr;
-        }
+        A.per_unit = A.g.tiles_per_unit * passes;
+        const int un = (A.what == nullptr || aligned(A.what, 16)) && aligned(it.codes, 8) ? 0 : 1;
+        L[un].m[L[un].n++] = A;
+        any_err[un] = any_err[un] || A.err != nullptr;
     }
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
-    if (S.n > 0) {
-        const int64_t tiles = dequant_number(&S);
+    int lpr_shift = -1;         // chunk_w = 8 << lpr_shift
+    for (int k = 0; k <= 6; ++k)
+        if (chunk_w == (8 << k)) lpr_shift = k;
+    for (int un = 0; un < 2; ++un) {
+        DequantBatch& B = L[un];
+        if (B.n == 0) continue;
+        const int64_t tiles = dequant_number(&B);
         if (tiles * passes > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
         const dim3 grid((unsigned)(tiles * passes));
-        if (dtype == WINDQ_BF16) hipLaunchKernelGGL(dequant_split_kernel<WINDQ_BF16>, grid, dim3(DQ_THREADS), 0, hs, S, lpr_shift);
-        else hipLaunchKernelGGL(dequant_split_kernel<WINDQ_F32>, grid, dim3(DQ_THREADS), 0, hs, S, lpr_shift);
-        if (any_err_s) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)S.unit_start[S.n]), dim3(256), 0, hs, S);
-    }
-    if (T.n > 0) {
-        const int64_t tiles = dequant_number(&T);
-        if (tiles > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
-        const size_t lds = raw_tile_lds_bytes(dtype, chunk_w) + (size_t)chunk_w * sizeof(float);
-        const dim3 grid((unsigned)tiles);
-        if (dtype == WINDQ_BF16) {
-            const int st = ensure_lds(reinterpret_cast<const void*>(&dequant_tile_kernel<WINDQ_BF16>), lds);
-            if (st != WINDQ_OK) return st;
-            hipLaunchKernelGGL(dequant_tile_kernel<WINDQ_BF16>, grid, dim3(64), lds, hs, T);
+        if (un == 1) {
+            if (dtype == WINDQ_BF16) hipLaunchKernelGGL((dequant_any_kernel<WINDQ_BF16, false>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);
+            else hipLaunchKernelGGL((dequant_any_kernel<WINDQ_F32, false>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);
+        } else if (lpr_shift >= 0) {
+            if (dtype == WINDQ_BF16) hipLaunchKernelGGL(dequant_split_kernel<WINDQ_BF16>, grid, dim3(DQ_THREADS), 0, hs, B, lpr_shift);
+            else hipLaunchKernelGGL(dequant_split_kernel<WINDQ_F32>, grid, dim3(DQ_THREADS), 0, hs, B, lpr_shift);
         } else {
-            const int st = ensure_lds(reinterpret_cast<const void*>(&dequant_tile_kernel<WINDQ_F32>), lds);
-            if (st != WINDQ_OK) return st;
-            hipLaunchKernelGGL(dequant_tile_kernel<WINDQ_F32>, grid, dim3(64), lds, hs, T);
+            if (dtype == WINDQ_BF16) hipLaunchKernelGGL((dequant_any_kernel<WINDQ_BF16, true>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);
+            else hipLaunchKernelGGL((dequant_any_kernel<WINDQ_F32, true>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);
         }
-        if (any_err_t) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)T.unit_start[T.n]), dim3(256), 0, hs, T);
+        if (any_err[un]) hipLaunchKernelGGL(dequant_finalize_kernel, dim3((unsigned)B.unit_start[B.n]), dim3(256), 0, hs, B);
     }
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }

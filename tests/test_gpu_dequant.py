@@ -60,6 +60,53 @@ def test_dequant_closes_the_loop(windq, R, C, G, unit_rows, K, dtype):
     run_case(windq, W, s, G, unit_rows, K)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("R,C,G,unit_rows", [
+    (65, 168, 24, 0),           # less than a pass of 256 pieces to a tile; trits that end within a byte
+    (64, 280, 40, 0),           # a little more than one: some threads take two
+    (63, 168, 56, 21),
+    (130, 192, 96, 0),          # whole passes; the last tile has two rows
+    (129, 672, 168, 43), (66, 1512, 504, 0),       # 504: the widest
+])
+def test_dequant_at_odd_widths(windq, R, C, G, unit_rows, dtype):
+    W = synth.weights_llm(R, C, seed=R + C, device=DEV, dtype=dtype)
+    X = synth.activations_llm(64, C, seed=107, device=DEV)
+    s, _ = windq.windq_calib_stats(X)
+    run_case(windq, W, s, G, unit_rows, 5)
+    run_case(windq, W, s, G, unit_rows, 5, ppm=50000)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("G", [8, 64, 96, 512])
+@pytest.mark.parametrize("what_off,codes_off", [(1, 0), (0, 1), (3, 5)])
+def test_dequant_with_buffers_off_the_wide_alignments(windq, G, dtype, what_off, codes_off):
+    """w_hat on 4 bytes only, codes on any byte: the same numbers as from aligned buffers, also in one batch with them."""
+    R, C = 70, 7 * G
+    W = synth.weights_llm(R, C, seed=G, device=DEV, dtype=dtype)
+    s = torch.rand(C, generator=torch.Generator().manual_seed(G)).add(0.1).to(DEV)
+    cg = synth.clip_grid(4)
+    _, clip_idx, _ = windq.windq_fit_score_all_bits(W, s, G, 0, cg)
+    action = torch.arange(7, dtype=torch.uint8)
+    off = windq.windq_plan_layout(action, R, G)
+    a_dev, off_dev = action.to(DEV), off.to(DEV)
+    codes, scale, offset = windq.windq_apply_plan(W, G, 0, a_dev, clip_idx, cg, off_dev)
+    err, w_hat = windq.windq_dequant_plan(W, s, G, 0, a_dev, off_dev, codes, scale, offset)
+    odd_codes = torch.empty(codes.numel() + 16, dtype=torch.uint8, device=DEV)[codes_off:codes_off + codes.numel()].copy_(codes)
+    odd_what = torch.zeros(R * C + 4, dtype=torch.float32, device=DEV)[what_off:what_off + R * C].view(R, C)
+    odd_err = torch.empty_like(err)
+    for batch in (1, 2):
+        odd_what.zero_()
+        two = [W, W][:batch]
+        outs = [(odd_err, odd_what), (torch.empty_like(err), torch.empty_like(w_hat))][:batch]
+        windq.windq_dequant_plan_batch(two, [s] * batch, G, 0, [a_dev] * batch, [off_dev] * batch, [odd_codes, codes][:batch],
+                                       [scale] * batch, [offset] * batch, outs=outs)
+        torch.cuda.synchronize()
+        assert torch.equal(odd_what, w_hat)
+        # fp64 sums of the same terms, in another order
+        assert torch.all((odd_err - err).abs() <= 2.4e-7 * err)
+    assert torch.equal(outs[1][0], err) and torch.equal(outs[1][1], w_hat)
+
+
 @pytest.mark.parametrize("R,C,G,unit_rows,ppm", [(256, 512, 128, 0, 30000), (200, 256, 64, 100, 50000), (70, 96, 32, 0, 300000)])
 def test_dequant_under_a_protection_mask(windq, R, C, G, unit_rows, ppm):
     W = synth.weights_llm(R, C, seed=103, device=DEV)
