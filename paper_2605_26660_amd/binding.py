@@ -209,8 +209,9 @@ def _require_cuda(*tensors):
 
 
 def as_mat(t: torch.Tensor) -> windq_mat:
-    assert t.dim() == 2 and t.stride(1) == 1, "row-major 2-D tensor expected"
-    return windq_mat(t.data_ptr(), _dtype_code(t), 0, t.shape[0], t.shape[1], t.stride(0))
+    shape, strides = t.shape, t.stride()
+    assert len(shape) == 2 and strides[1] == 1, "row-major 2-D tensor expected"
+    return windq_mat(t.data_ptr(), _dtype_code(t), 0, shape[0], shape[1], strides[0])
 
 
 def _stream() -> int:
@@ -226,10 +227,12 @@ def workspace_bytes(call: int, dtype: int, rows: int, cols: int, chunk_w: int = 
 
 
 def _workspace(call, t, chunk_w, unit_rows, K, ws):
+    # a given workspace's size is checked by the call itself: asking the library for it here as well cost a batch of
+    # four small matrices a third of its time
+    if ws is not None:
+        return ws
     need = workspace_bytes(call, _dtype_code(t), t.shape[0], t.shape[1], chunk_w, unit_rows, K)
-    if ws is None:
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=t.device)
-    return ws
+    return torch.empty(max(need, 256), dtype=torch.uint8, device=t.device)
 
 
 def n_units(rows: int, cols: int, chunk_w: int, unit_rows: int = 0):
