@@ -1106,58 +1106,11 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
     fit_score_tile<DT, MASKED, MODE>(B, A, tc, blockIdx.x & (FS_WAVES - 1), smem);
 }
 
-constexpr int FIN_THREADS = 1024;
-constexpr int FIN_PHASES = FIN_THREADS / 64;
-
-// Number of a listed unit's tiles done again: a word of its first tile's partials that nothing reads once the unit is
-// finalized (its last quarter of the reference energy); the finalize kernel sets it to zero when it lists the unit.
-__device__ __forceinline__ uint32_t* redo_done(const FitScoreMat& A, int32_t K, int64_t u) {
-    return reinterpret_cast<uint32_t*>(A.partial + (size_t)u * (size_t)A.g.tiles_per_unit * (size_t)fit_score_ncand(K) + 4 * K + 11);
-}
-
-// The 8-bit clip index and error of a listed unit, by one wavefront: the sums in the finalize kernel's order (phase p
-// adds tiles p, p + 16, ...; then the phases in order), lane = candidate.
-__device__ __forceinline__ void redo_finalize(const FitScoreMat& A, int32_t K, int64_t u) {
-    static_assert(WINDQ_MAX_CLIP <= 64, "a lane per clip value");
-    const int lane = threadIdx.x & 63;
-    const int32_t ncand = fit_score_ncand(K);
-    const int64_t tpu = A.g.tiles_per_unit;
-    const double* base = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand + (lane < K ? lane : 0);
-    double ph[FIN_PHASES];
-#pragma unroll
-    for (int p = 0; p < FIN_PHASES; ++p) ph[p] = 0.0;
-    for (int64_t t = 0; t < tpu; t += FIN_PHASES) {
-#pragma unroll
-        for (int p = 0; p < FIN_PHASES; ++p) {
-            if (t + p < tpu) ph[p] += base[(size_t)(t + p) * ncand];
-        }
-    }
-    double e = 0.0;
-#pragma unroll
-    for (int p = 0; p < FIN_PHASES; ++p) e += ph[p];
-    double best = __shfl(e, 0, 64);
-    int bk = 0;
-    for (int k = 1; k < K; ++k) {
-        const double ek = __shfl(e, k, 64);
-        if (ek <= best) {
-            best = ek;
-            bk = k;
-        }
-    }
-    if (lane == 0) {
-        A.err[u * WINDQ_N_ERR] = (float)best;
-        A.clip_idx[u * 4] = (uint8_t)bk;
-    }
-}
-
 // The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
-// walks the list; with nothing listed every workgroup ends after reading the counters.  The workgroup
-// that does a unit's last tile finalizes it: a launch of its own for that, which mostly finds nothing listed,
-// costs 1.5 us of 47 (512 x 512, with features), 3 of 272 (a 1024 x 8192 pair, 40 clip values) and 7 of 1470 (7B-shaped block).
+// walks the list; with nothing listed every workgroup ends after reading the counters.
 template <int DT, bool MASKED>
 __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const FitScoreArgs B) {
     extern __shared__ char smem[];
-    __shared__ uint32_t done_sh;
     // (no table of the matrices' first tiles: indexed by a run-time value it would live in scratch memory)
     auto listed_tiles = [&](int i) -> int64_t {
         int64_t cnt = (int64_t)*B.m[i].redo_count;
@@ -1180,27 +1133,28 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const int64_t u = A.redo_list[li];
         const TileCoord tc = tile_coord_of_unit(A.g, u, local - li * A.g.tiles_per_unit);
         fit_score_tile<DT, MASKED, FS_ONLY8>(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
-        __threadfence();      // the partials are visible on every XCD before the tile counts as done
-        __syncthreads();      // (the next tile also overwrites this one's LDS)
-        if (threadIdx.x == 0) done_sh = atomicAdd(redo_done(A, B.K, u), 1u);
-        __syncthreads();
-        if ((int64_t)done_sh + 1 == A.g.tiles_per_unit && threadIdx.x < 64) {
-            __threadfence();
-            redo_finalize(A, B.K, u);
-        }
+        __syncthreads();      // the next tile overwrites this one's LDS
     }
 }
 
 // Per unit: add the tiles' partial errors in a fixed order, pick the clip index with the
 // least error for each uniform bit-width (ties to the largest index), emit fp32.
-// A unit whose 8-bit error may hold too much of the short route's rounding noise (see NOISE_MAX)
-// is put on the list.
+// REDO = false: every unit; a unit whose 8-bit error may hold too much of the short route's
+// rounding noise (see NOISE_MAX) is put on the list.  REDO = true: the listed units only,
+// after their 8-bit partials have been replaced.
+constexpr int FIN_THREADS = 1024;
+constexpr int FIN_PHASES = FIN_THREADS / 64;
+template <bool REDO>
 __global__ __launch_bounds__(FIN_THREADS) void fit_score_finalize_kernel(const FitScoreArgs B) {
     __shared__ double part[FIN_PHASES][5 * WINDQ_MAX_CLIP + 12];
     __shared__ double E[5 * WINDQ_MAX_CLIP + 12];
     const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
-    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    if (REDO) {
+        if (u >= (int64_t)*A.redo_count) return;
+        u = A.redo_list[u];
+    }
     const int32_t K = B.K;
     const int64_t tiles_per_unit = A.g.tiles_per_unit;
     float* __restrict__ err = A.err;
@@ -1237,8 +1191,7 @@ __global__ __launch_bounds__(FIN_THREADS) void fit_score_finalize_kernel(const F
         }
         err[u * WINDQ_N_ERR + tid] = (float)best;
         clip_idx[u * 4 + tid] = (uint8_t)bk;
-        if (tid == 0 && E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best) {
-            *redo_done(A, K, u) = 0u;
+        if (!REDO && tid == 0 && E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best) {
             const uint32_t pos = atomicAdd(A.redo_count, 1u);
             A.redo_list[pos] = (uint32_t)u;
         }
@@ -1401,9 +1354,9 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         st = launch_tiles<FS_SCORE>(A, dtype, masked, lds, grid, hs);
     }
     if (st != WINDQ_OK) return st;
-    hipLaunchKernelGGL(fit_score_finalize_kernel, dim3((unsigned)units), dim3(FIN_THREADS), 0, hs, A);
+    hipLaunchKernelGGL(fit_score_finalize_kernel<false>, dim3((unsigned)units), dim3(FIN_THREADS), 0, hs, A);
     if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
-    // the units the finalize kernel listed: their 8-bit candidates on the exact route, finalized by their last workgroup
+    // the units the finalize kernel listed: their 8-bit candidates on the exact route, finalized again
     const dim3 redo_grid((unsigned)(tiles < FS_REDO_GRID ? tiles : FS_REDO_GRID));
     auto launch_redo = [&](auto kernel) -> int {
         const int e = ensure_lds(reinterpret_cast<const void*>(kernel), lds);
@@ -1414,6 +1367,8 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     if (dtype == WINDQ_BF16) st = masked ? launch_redo(&fit_score_redo_kernel<WINDQ_BF16, true>) : launch_redo(&fit_score_redo_kernel<WINDQ_BF16, false>);
     else st = masked ? launch_redo(&fit_score_redo_kernel<WINDQ_F32, true>) : launch_redo(&fit_score_redo_kernel<WINDQ_F32, false>);
     if (st != WINDQ_OK) return st;
+    hipLaunchKernelGGL(fit_score_finalize_kernel<true>, dim3((unsigned)units), dim3(FIN_THREADS), 0, hs, A);
+    if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
     if (feat != nullptr) return features_launch_rest(*feat, hs);
     return WINDQ_OK;
 }

@@ -404,35 +404,6 @@ def test_fit_score_rows_that_carry_the_error(windq, R, unit_rows):
         assert rescored_any >= 1
 
 
-@pytest.mark.parametrize("R,unit_rows,K", [(128, 0, 20), (1000, 0, 5), (1088, 0, 1), (2112, 1056, 64)])
-def test_fit_score_rescored_units_of_ragged_heights(windq, R, unit_rows, K):
-    """A listed unit is finalized by whoever does its last tile: 2, 16 (the last ragged), 17 and 16.5 tiles of 64 rows, the
-    shortest and the longest clip grid, listed units of two row blocks at once.  Four rows hold all of a listed unit's error,
-    so that its noise is 1.05e-4 sqrt(sum s^4) / (2 sum s^2) of it, ~4.6e-6: over the bar of 3e-6."""
-    G, C = 128, 256
-    U, R_u = windq.n_units(R, C, G, unit_rows)
-    W = 1e-4 * synth.weights_llm(R, C, seed=91, dtype=torch.float32, heavy_frac=0.0).clamp(-0.05, 0.05)
-    heavy = [rb * R_u + 5 * i for rb in range(R // R_u) for i in range(4)]
-    W[heavy, :G] = torch.rand(len(heavy), G, generator=torch.Generator().manual_seed(92)) - 0.5
-    W[heavy, 0], W[heavy, 1] = 0.5, -0.5
-    W = W.to(torch.bfloat16).to(DEV)
-    s = torch.ones(C)
-    cg = grid(K)
-    ws = torch.empty(windq.workspace_bytes(windq.CALL_FIT_SCORE, windq.WINDQ_BF16, R, C, G, unit_rows, K),
-                     dtype=torch.uint8, device=DEV)
-    o_err, o_idx, _, table = O.fit_score_all_bits(to_np(W), s.numpy(), G, unit_rows, cg.numpy())
-    for _ in range(2):
-        err, clip_idx, _ = windq.windq_fit_score_all_bits(W, s.to(DEV), G, unit_rows, cg, ws=ws)
-        torch.cuda.synchronize()
-        if R_u > 128:                     # (smaller units have every column on the exact route at once)
-            assert windq.windq_fit_score_rescored_units(ws, W, G, unit_rows, K) >= R // R_u
-        g_idx = clip_idx.cpu().numpy()
-        for u, b in zip(*np.nonzero(g_idx != o_idx)):
-            assert table[u, b, g_idx[u, b]] <= table[u, b].min() * (1 + 1e-9)
-        rel = np.abs(to_np(err) - o_err) / o_err
-        assert rel.max() <= REL, rel.max()
-
-
 def test_fit_score_rescoring_leaves_other_candidates_alone(windq):
     """A unit scored a second time keeps every result but the 8-bit one, and the second pass is
     reproducible: two calls give the same bits."""
