@@ -100,9 +100,10 @@ int windq_calib_stats(const windq_mat* X, float* s_absmean /*[cols]*/, float* s_
 
 /*
  * windq_calib_stats for up to WINDQ_MAX_BATCH activation matrices (a decoder block has four
- * distinct inputs) of one element type; those of at most 4096 tokens share ONE launch.  Item i
- * is one per-matrix call; results are the same bit for bit.  `items` is a HOST array read
- * during the call.
+ * distinct inputs) of one element type, in one launch, or two where any has enough tokens to be
+ * summed in pieces.  Item i is one per-matrix call; results are the same bit for bit.  Items may
+ * name one workspace: those summed in pieces then take launches of their own, one after the
+ * other.  `items` is a HOST array read during the call.
  */
 typedef struct windq_calib_item {
     const windq_mat* X;     /* HOST descriptor of a device matrix [tokens][channels] */

@@ -19,7 +19,8 @@
 //     to write and read back.  16384 x 4096 bf16, both statistics: 33 us = 4.0 TB/s (162 us with
 //     32-token slabs, whose 33 MB of partial sums one thread per channel then added in a chain);
 //     a large copy moves 5.1 TB/s.
-// All matrices of a batch share the launch (and the finalize launch, where any needs it).
+// All matrices of a batch share the launch (and the finalize launch, where any needs it) but those whose slab sums would
+// lie in the same memory.
 #include "windq_common.hpp"
 #include "windq_ws.hpp"
 
@@ -229,29 +230,16 @@ static void calib_cut(CalibMat* M) {
     M->slabs = (int32_t)((M->rows + M->slab_rows - 1) / M->slab_rows);
 }
 
-extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n, void* stream) {
-    if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
+// The matrices of one launch (two, where slabs are to be added).
+static int calib_launch(const CalibMat* mats, int32_t n, int32_t dtype, hipStream_t hs) {
     CalibBatch B, F;            // all matrices; those whose slabs are still to be added
     B.n = n;
     F.n = 0;
     int64_t wgs = 0, fin = 0;
     bool rms = false;
     for (int32_t i = 0; i < n; ++i) {
-        const windq_mat* X = items[i].X;
-        if (X == nullptr) return WINDQ_EINVAL;
-        const int st = calib_check(X, items[i].s_absmean, items[i].ws, items[i].ws_bytes);
-        if (st != WINDQ_OK) return st;
-        if (X->dtype != items[0].X->dtype) return WINDQ_EINVAL;      // one kernel per launch
-        CalibMat& M = B.m[i];
-        M.X = X->data;
-        M.rows = X->rows;
-        M.cols = X->cols;
-        M.ld = X->ld;
-        M.s_absmean = items[i].s_absmean;
-        M.s_rms = items[i].s_rms;
-        M.partial = static_cast<double*>(items[i].ws);
-        M.reserved = 0;
-        calib_cut(&M);
+        const CalibMat& M = mats[i];
+        B.m[i] = M;
         rms = rms || M.s_rms != nullptr;
         B.wg_start[i] = wgs;
         wgs += (int64_t)M.strips * M.slabs;
@@ -261,12 +249,10 @@ extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n,
             F.m[F.n++] = M;
         }
     }
-    if (wgs > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) B.wg_start[i] = wgs;
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    hipStream_t hs = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)wgs), block(CALIB_THREADS);
-    if (items[0].X->dtype == WINDQ_BF16) {
+    if (dtype == WINDQ_BF16) {
         if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, true>), grid, block, 0, hs, B);
         else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, false>), grid, block, 0, hs, B);
     } else {
@@ -280,6 +266,57 @@ extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n,
         else hipLaunchKernelGGL(calib_finalize_kernel<false>, dim3((unsigned)fin), dim3(256), 0, hs, F);
     }
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
+}
+
+// Do two matrices write slab sums to the same memory?
+static bool calib_share(const CalibMat& a, const CalibMat& b) {
+    if (a.slabs == 1 || b.slabs == 1) return false;
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a.partial), b0 = reinterpret_cast<uintptr_t>(b.partial);
+    const uintptr_t a1 = a0 + (uintptr_t)a.slabs * 2 * (uintptr_t)a.cols * sizeof(double);
+    const uintptr_t b1 = b0 + (uintptr_t)b.slabs * 2 * (uintptr_t)b.cols * sizeof(double);
+    return a0 < b1 && b0 < a1;
+}
+
+// One launch for all matrices whose slab sums do not meet; an item is a call of its own, so that several may name one
+// workspace: those wait for a later launch.
+extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n, void* stream) {
+    if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
+    CalibMat mats[WINDQ_MAX_BATCH];
+    int64_t wgs = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const windq_mat* X = items[i].X;
+        if (X == nullptr) return WINDQ_EINVAL;
+        const int st = calib_check(X, items[i].s_absmean, items[i].ws, items[i].ws_bytes);
+        if (st != WINDQ_OK) return st;
+        if (X->dtype != items[0].X->dtype) return WINDQ_EINVAL;      // one kernel per launch
+        CalibMat& M = mats[i];
+        M.X = X->data;
+        M.rows = X->rows;
+        M.cols = X->cols;
+        M.ld = X->ld;
+        M.s_absmean = items[i].s_absmean;
+        M.s_rms = items[i].s_rms;
+        M.partial = static_cast<double*>(items[i].ws);
+        M.reserved = 0;
+        calib_cut(&M);
+        wgs += (int64_t)M.strips * M.slabs;
+    }
+    if (wgs > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    int32_t left = n;
+    while (left > 0) {
+        CalibMat now[WINDQ_MAX_BATCH];
+        int32_t n_now = 0, n_later = 0;
+        for (int32_t i = 0; i < left; ++i) {
+            bool meets = false;
+            for (int32_t k = 0; k < n_now; ++k) meets = meets || calib_share(now[k], mats[i]);
+            if (meets) mats[n_later++] = mats[i];
+            else now[n_now++] = mats[i];
+        }
+        left = n_later;
+        const int st = calib_launch(now, n_now, items[0].X->dtype, static_cast<hipStream_t>(stream));
+        if (st != WINDQ_OK) return st;
+    }
+    return WINDQ_OK;
 }
 
 extern "C" int windq_calib_stats(const windq_mat* X, float* s_absmean, float* s_rms, void* ws, size_t ws_bytes,

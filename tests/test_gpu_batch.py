@@ -152,6 +152,24 @@ def test_calib_stats_batch_equals_single_calls(windq, dtype):
     assert e.value.status == windq.WINDQ_EINVAL
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_calib_stats_batch_with_one_workspace_for_all(windq, dtype):
+    """Every item is a call of its own: one workspace named by all, or workspaces that overlap in part, change no bit."""
+    shapes = [(1100, 512), (5000, 512), (5000, 1032), (300, 512), (2100, 512)]
+    Xs = [synth.activations_llm(t, c, seed=191 + i, device=DEV).to(dtype) for i, (t, c) in enumerate(shapes)]
+    singles = [windq.windq_calib_stats(X) for X in Xs]
+    code = windq.WINDQ_BF16 if dtype == torch.bfloat16 else windq.WINDQ_F32
+    need = [windq.workspace_bytes(windq.CALL_CALIB_STATS, code, t, c) for t, c in shapes]
+    ws = torch.empty(2 * max(need), dtype=torch.uint8, device=DEV)
+    steps = [0, need[1] // 2, max(need) // 3]
+    for step in steps:
+        at = [min(i * (step // 256 * 256), ws.numel() - n) // 256 * 256 for i, n in enumerate(need)]
+        batch = windq.windq_calib_stats_batch(Xs, wss=[ws[a:] for a in at])
+        torch.cuda.synchronize()
+        for one, got in zip(singles, batch):
+            assert same_bits(one[0], got[0]) and same_bits(one[1], got[1])
+
+
 def _block_step(windq, Ws, ss, G, cg, plan, bufs):
     """features -> fit+score -> apply-plan over a block through the batch calls, into caller-owned buffers."""
     windq.windq_unit_features_batch(Ws, ss, G, 0, wss=bufs["ws"], outs=bufs["feat"])
