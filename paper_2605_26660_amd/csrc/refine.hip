@@ -145,25 +145,27 @@ struct RefineGroup {
     const uint8_t* mrow;
     const double* acol;
     int32_t G;
+    bool protects;              // MASKED: the item has a mask (else its mask bytes are zeros)
 
     __device__ __forceinline__ uint32_t bits(int32_t c) const { return MASKED ? mrow[c >> 3] : 0u; }
     __device__ __forceinline__ bool kept(uint32_t m, int j) const { return !MASKED || ((m >> j) & 1u) == 0u; }
     // s_c^2 of column c + j, zero for a protected weight
     __device__ __forceinline__ double weight(uint32_t m, int32_t c, int j) const { return kept(m, j) ? acol[c + j] : 0.0; }
 
-    // min and max of the kept weights (0, 0 when none is kept)
+    // min and max of the kept weights.  Under a mask 0, 0 when none is kept (or all that are kept are NaN); an item without
+    // one gives NaN for a group of NaN, also in a masked launch
     __device__ __forceinline__ void min_max(float* mn_out, float* mx_out) const {
         float mn = INFINITY, mx = -INFINITY;
         row.blocks(G, [&](int32_t c, const float (&w)[8]) {
             const uint32_t m = bits(c);
-            if (!MASKED && c == 0) mn = mx = w[0];
+            if (!(MASKED && protects) && c == 0) mn = mx = w[0];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 mn = fminf(mn, kept(m, j) ? w[j] : INFINITY);
                 mx = fmaxf(mx, kept(m, j) ? w[j] : -INFINITY);
             }
         });
-        if (MASKED && mn > mx) mn = mx = 0.0f;
+        if (MASKED && protects && mn > mx) mn = mx = 0.0f;
         *mn_out = mn;
         *mx_out = mx;
     }
@@ -413,6 +415,7 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
     g.mrow = MASKED ? mtile + lane * mask_row_stride(G) : nullptr;
     g.acol = acol;
     g.G = G;
+    g.protects = MASKED && A.mask != nullptr;
 
     double err = 0.0;
     if (valid) {

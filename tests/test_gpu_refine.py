@@ -78,9 +78,12 @@ def test_refine_at_the_edges_of_its_row_storage(windq, R, C, G, dtype, ppm):
 
 
 def test_refine_batch_with_and_without_masks(windq):
-    """Items with a mask and items without in one launch: each as it would be alone."""
+    """Items with a mask and items without in one launch: each as it would be alone, groups of NaN included."""
     Ws = [synth.weights_llm(96, 256, seed=118 + i, device=DEV) for i in range(2)]
     s = torch.rand(256, device=DEV) + 0.1
+    for W in Ws:
+        W[3, :128] = float("nan")
+        W[5, 7] = float("nan")
     mask = windq.windq_salient_select(Ws[0], s, 128, 0, 50000)
     action = torch.tensor([4, 5], dtype=torch.uint8)
     off = windq.windq_plan_layout(action, 96, 128).to(DEV)
@@ -91,7 +94,8 @@ def test_refine_batch_with_and_without_masks(windq):
     torch.cuda.synchronize()
     for a, b in zip(alone, both):
         for x, y in zip(a, b):
-            assert torch.equal(x, y)
+            assert torch.equal(torch.isnan(x), torch.isnan(y)) and torch.equal(torch.nan_to_num(x), torch.nan_to_num(y))
+    assert bool(torch.isnan(both[1][2][3]))          # the offset of the unmasked item's group of NaN
 
 
 def test_refine_plan_under_a_protection_mask(windq):
