@@ -531,11 +531,11 @@ int windq_dequant_plan_batch(const windq_dequant_item* items /*HOST [n]*/, int32
  *          weights: W is read for them only; protected weights of a mask count as 0: their values live in
  *          the INT8 side stream).
  * Units at 1, 1.58 and 2 bits are summed in fp64 as scale * sum_c (code - centre) x[c] (at 2 bits plus
- * (offset + 1.5 scale) * sum_c x[c]: w_hat before its rounding to fp32); the others, units
- * under a mask, and chunks of x that hold infinities, NaN or values above 2^96, weight by weight: eight columns at a time
- * in fp32 (one fused multiply-add per weight for w_hat, one for the product), those runs in fp64.  A row's chunks are
- * added in fp64 in a fixed order and y is rounded once: results are bit-reproducible and differ from the exact product
- * by at most ~1e-6 of sum_c |w_hat x|.
+ * (offset + 1.5 scale) * sum_c x[c]: w_hat before its rounding to fp32).  Weight by weight, eight columns at a time in
+ * fp32 (one fused multiply-add per weight for w_hat, one for the product) and those runs in fp64: the other bit-widths,
+ * units under a mask, chunks of x that hold infinities, NaN or values above 2^96, and groups whose scale or offset is such
+ * a value.  A row's chunks are added in fp64 in a fixed order and y is rounded once: results are bit-reproducible and
+ * differ from the exact product by at most ~1e-6 of sum_c |w_hat x|.
  *   x [cols] f32, y [rows] f32 (every element written).  Workspace: WINDQ_CALL_DEQUANT_GEMV.
  * Plan entries are checked as in windq_dequant_plan (a malformed one counts as skip).  The batch form
  * takes up to WINDQ_MAX_BATCH matrices (one chunk width, unit_rows, element type) in one launch plus

@@ -393,8 +393,9 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
 //   A lane owns a row (its bytes are contiguous, and so are its neighbours': a unit's rows lie one after the
 // other).  Tables and sums are fp64: what the centre leaves to (offset + centre * scale) may cancel.
 //   The other routes, one weight at a time, same results to rounding: 3, 4 and 8 bits (little to
-// share), units under a protection mask, and chunks of x that hold a value no
-// fp32 sum of a few columns may meet (infinite, NaN or above 2^96).  Skip units read W, G/8 lanes a row.
+// share), units under a protection mask, and what infinite or NaN weights would show in: chunks of x that hold a value no
+// fp32 sum of a few columns may meet (infinite, NaN or above 2^96), rows whose scale or offset is such a value.  Skip
+// units read W, G/8 lanes a row.
 //   7B-shaped block at a 2-bit plan: 40 us (109 before), of which the sums over chunks take 5.  The six wavefronts per
 // SIMD that 84 registers allow are worth 5 to 10 % over the four that the skip route's loads would take.
 constexpr int GEMV_THREADS = 256;
@@ -517,6 +518,32 @@ __device__ __forceinline__ void decode8(int a, int bits, const uint8_t* __restri
         const uint32_t code = (uint32_t)(v >> (j * bits)) & ((1u << bits) - 1u);
         wh[j] = a == 6 ? (code != 0u ? sc : -sc) : fmaf((float)code, sc, of);
     }
+}
+
+// The product of a row at 2 bits, 1.58 or 1 bit with the chunk of x, weight by weight, without tables.
+__device__ __forceinline__ double gemv_row_plain(int a, const uint8_t* __restrict__ src, int32_t G, float sc, float of,
+                                                 const float* __restrict__ xs) {
+    double acc = 0.0;
+#pragma unroll 1
+    for (int32_t c = 0; c < G; c += 8) {
+        float dot = 0.0f;
+#pragma unroll 1
+        for (int32_t i = c; i < c + 8; ++i) {
+            float wh;
+            if (a == 5) {
+                uint32_t v = src[i / 5];
+                for (int k = i % 5; k > 0; --k) v /= 3u;
+                wh = sc * ((float)(v % 3u) - 1.0f);
+            } else if (a == 4) {
+                wh = fmaf((float)((src[i >> 2] >> (2 * (i & 3))) & 3), sc, of);
+            } else {
+                wh = ((src[i >> 3] >> (i & 7)) & 1) != 0 ? sc : -sc;
+            }
+            dot = fmaf(wh, xs[i], dot);
+        }
+        acc += (double)dot;
+    }
+    return acc;
 }
 
 // The products of N rows with the chunk of x one weight at a time: the values windq_dequant_plan reconstructs, eight
@@ -740,7 +767,9 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
             const int32_t r = k * GEMV_THREADS + tid;
             if (r < nrows) {
                 const double scd = (double)sc[k];
-                out[r] = a == 4 ? fma(fma(1.5, scd, (double)of[k]), xt, scd * acc[k]) : scd * acc[k];
+                double t = a == 4 ? fma(fma(1.5, scd, (double)of[k]), xt, scd * acc[k]) : scd * acc[k];
+                if (!(fabsf(sc[k]) <= 0x1p96f && fabsf(of[k]) <= 0x1p96f)) t = gemv_row_plain(a, src0 + (int64_t)r * bpg, G, sc[k], of[k], xs);
+                out[r] = t;
             }
         }
         return;

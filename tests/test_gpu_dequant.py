@@ -213,6 +213,36 @@ def test_gemv_with_values_no_table_may_hold(windq, bad):
         assert torch.equal(torch.sign(y[torch.isinf(want)]), torch.sign(want[torch.isinf(want)]))
 
 
+@pytest.mark.parametrize("G", [64, 40])
+@pytest.mark.parametrize("positive", [True, False])
+def test_gemv_with_scales_that_are_not_finite(windq, G, positive):
+    """Rows whose stored scale or offset is infinite, NaN or huge: what the reconstruction times x gives, signs and NaN
+    included, and the other rows as ever."""
+    R, C = 300, 6 * G
+    W = synth.weights_llm(R, C, seed=123, device=DEV)
+    W[:8, :G] = W[:8, :G].abs() + 0.01                 # signs all alike: a product of one sign
+    action = torch.tensor([6, 5, 4, 6, 5, 4], dtype=torch.uint8)
+    off = windq.windq_plan_layout(action, R, G)
+    codes, scale, offset = windq.windq_apply_plan(W, G, 0, action.to(DEV), None, None, off.to(DEV))
+    bad = [float("inf"), float("-inf"), float("nan"), 2.0 ** 120, -2.0 ** 120]
+    sc, of = scale.view(6, R), offset.view(6, R)
+    for i, v in enumerate(bad):
+        for u in range(3):
+            sc[u, 3 * i + u] = v
+        of[2, 40 + i] = v
+        sc[5, 280 + i] = v
+    x = torch.randn(C, generator=torch.Generator().manual_seed(4)).to(DEV)
+    x = x.abs() if positive else x
+    _, w_hat = windq.windq_dequant_plan(W, torch.ones(C, device=DEV), G, 0, action.to(DEV), off.to(DEV), codes, scale, offset)
+    y = windq.windq_dequant_gemv(W, G, 0, action.to(DEV), off.to(DEV), codes, scale, offset, x).double()
+    want, mag = (w_hat.double() * x.double()).sum(1), (w_hat.double() * x.double()).abs().sum(1)
+    assert bool(torch.isnan(want).any()) and (not positive or bool(torch.isinf(want).any()))
+    assert torch.equal(torch.isnan(y), torch.isnan(want)) and torch.equal(torch.isinf(y), torch.isinf(want))
+    inf, ok = torch.isinf(want), torch.isfinite(want)
+    assert torch.equal(torch.sign(y[inf]), torch.sign(want[inf]))
+    assert bool(((y - want)[ok].abs() <= 1e-6 * mag[ok]).all())
+
+
 @pytest.mark.parametrize("R,C,G,unit_rows,ppm", [(256, 512, 128, 0, 30000), (70, 96, 32, 0, 300000), (24, 80, 40, 3, 100000)])
 def test_gemv_under_a_protection_mask(windq, R, C, G, unit_rows, ppm):
     W = synth.weights_llm(R, C, seed=113, device=DEV)
