@@ -396,8 +396,9 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
 // share), units under a protection mask, and what infinite or NaN weights would show in: chunks of x that hold a value no
 // fp32 sum of a few columns may meet (infinite, NaN or above 2^96), rows whose scale or offset is such a value.  Skip
 // units read W, G/8 lanes a row.
-//   7B-shaped block at a 2-bit plan: 40 us (109 before), of which the sums over chunks take 5.  The six wavefronts per
-// SIMD that 84 registers allow are worth 5 to 10 % over the four that the skip route's loads would take.
+//   7B-shaped block at a 2-bit plan: 38 us (109 with G/8 lanes a row), of which the sums over chunks take 5; with 3 % of the
+// weights protected 65 (115).  The six wavefronts per SIMD that 84 registers allow are worth 5 to 10 % over the four
+// that the skip route's loads would take.
 constexpr int GEMV_THREADS = 256;
 constexpr int GEMV_TRIT_WORDS = 48;                 // of a byte of trits: 27 entries at 0, 10 at 32
 // LDS of the largest table, trits of whole dwords (2 bits: 8 entries a column, 1 bit: 4), after the chunk's x.
@@ -497,7 +498,7 @@ __device__ __forceinline__ double gemv_lookup_trits(const uint32_t (&d)[4], int 
 }
 
 // The reconstruction of eight columns from c (a multiple of 8) of a row: `bits` bytes of its codes at any
-// alignment, or the two or three bytes that hold eight trits.
+// alignment, or the two or three bytes that hold eight trits (trits_of: fill_trits' table).
 __device__ __forceinline__ void decode8(int a, int bits, const uint8_t* __restrict__ src, int32_t c, int32_t bpg, float sc,
                                         float of, const uint16_t* __restrict__ trits_of, float (&wh)[8]) {
     if (a == 5) {
@@ -512,7 +513,17 @@ __device__ __forceinline__ void decode8(int a, int bits, const uint8_t* __restri
     }
     uint64_t v = 0;
     const uint8_t* p = src + (c >> 3) * bits;
-    for (int b = 0; b < bits; ++b) v |= (uint64_t)p[b] << (8 * b);
+    if (bits == 8) {
+        __builtin_memcpy(&v, p, 8);
+    } else if (bits == 4) {
+        __builtin_memcpy(&v, p, 4);
+    } else if (bits == 3) {
+        v = (uint64_t)((uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16));
+    } else if (bits == 2) {
+        __builtin_memcpy(&v, p, 2);
+    } else {
+        v = p[0];
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const uint32_t code = (uint32_t)(v >> (j * bits)) & ((1u << bits) - 1u);
@@ -547,30 +558,33 @@ __device__ __forceinline__ double gemv_row_plain(int a, const uint8_t* __restric
 }
 
 // The products of N rows with the chunk of x one weight at a time: the values windq_dequant_plan reconstructs, eight
-// columns in fp32 in column order, those runs in fp64.  32 columns (4 BITS bytes of codes, 4 of the mask) of every
-// row per step, the next step's on their way meanwhile.
+// columns in fp32 in column order, those runs in fp64.  32 columns (4 BITS bytes of codes) of every
+// row per step, the next step's on their way meanwhile; the mask 128 columns at a time: a lane's row of it is a line of the
+// cache of its own, gone before four narrower loads have met it (7B-shaped block, mixed plan: 74 us, 138 in dwords).
 template <int BITS, bool MASKED, int N>
-__device__ __forceinline__ void gemv_rows(const uint8_t* const (&src)[N], const uint8_t* const (&mrow)[N], bool mask4, int32_t G,
+__device__ __forceinline__ void gemv_rows(const uint8_t* const (&src)[N], const uint8_t* const (&mrow)[N], int32_t G,
                                           const float (&sc)[N], const float (&of)[N], const float* __restrict__ xs, double (&acc)[N]) {
     const int32_t G32 = G & ~31;
-    uint32_t d[N][BITS], m[N];
-    auto fetch = [&](int32_t c, uint32_t (&dd)[N][BITS], uint32_t (&mm)[N]) {
+    uint32_t d[N][BITS], m[N][4];
+    auto fetch = [&](int32_t c, uint32_t (&dd)[N][BITS]) {
 #pragma unroll
-        for (int k = 0; k < N; ++k) {
-            __builtin_memcpy(dd[k], src[k] + (c >> 3) * BITS, 4 * BITS);
-            mm[k] = 0u;
-            if (MASKED) {
-                const uint8_t* q = mrow[k] + (c >> 3);
-                if (mask4) mm[k] = *reinterpret_cast<const uint32_t*>(q);
-                else mm[k] = (uint32_t)q[0] | ((uint32_t)q[1] << 8) | ((uint32_t)q[2] << 16) | ((uint32_t)q[3] << 24);
-            }
-        }
+        for (int k = 0; k < N; ++k) __builtin_memcpy(dd[k], src[k] + (c >> 3) * BITS, 4 * BITS);
     };
-    if (G32 > 0) fetch(0, d, m);
+    if (G32 > 0) fetch(0, d);
 #pragma unroll 1
     for (int32_t c = 0; c < G32; c += 32) {
-        uint32_t dn[N][BITS], mn[N];
-        fetch(c + 32 < G32 ? c + 32 : c, dn, mn);
+        if (MASKED) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                if ((c & 127) == 0) {
+                    load_code_bytes(mrow[k] + (c >> 3), (G - c) >> 3 < 16 ? (G - c) >> 3 : 16, m[k]);
+                } else {
+                    m[k][0] = m[k][1]; m[k][1] = m[k][2]; m[k][2] = m[k][3];
+                }
+            }
+        }
+        uint32_t dn[N][BITS];
+        fetch(c + 32 < G32 ? c + 32 : c, dn);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             float x[8];
@@ -586,7 +600,7 @@ __device__ __forceinline__ void gemv_rows(const uint8_t* const (&src)[N], const 
                     if (sft + BITS > 32) code |= d[k][w + 1 < BITS ? w + 1 : w] << (32 - sft);
                     code &= (1u << BITS) - 1u;
                     float wh = BITS == 1 ? (code != 0u ? sc[k] : -sc[k]) : fmaf((float)code, sc[k], of[k]);
-                    if (MASKED) wh = ((m[k] >> (8 * q + j)) & 1u) != 0u ? 0.0f : wh;
+                    if (MASKED) wh = ((m[k][0] >> (8 * q + j)) & 1u) != 0u ? 0.0f : wh;
                     dot = fmaf(wh, x[j], dot);
                 }
                 acc[k] += (double)dot;
@@ -596,7 +610,6 @@ __device__ __forceinline__ void gemv_rows(const uint8_t* const (&src)[N], const 
         for (int k = 0; k < N; ++k) {
 #pragma unroll
             for (int i = 0; i < BITS; ++i) d[k][i] = dn[k][i];
-            m[k] = mn[k];
         }
     }
     for (int32_t c = G32; c < G; c += 8) {
@@ -613,43 +626,60 @@ __device__ __forceinline__ void gemv_rows(const uint8_t* const (&src)[N], const 
 }
 
 template <bool MASKED, int N>
-__device__ __forceinline__ void gemv_rows_of(int a, const uint8_t* const (&src)[N], const uint8_t* const (&mrow)[N], bool mask4,
+__device__ __forceinline__ void gemv_rows_of(int a, const uint8_t* const (&src)[N], const uint8_t* const (&mrow)[N],
                                              int32_t G, int32_t bpg, const float (&sc)[N], const float (&of)[N],
                                              const float* __restrict__ xs, const uint16_t* __restrict__ trits_of, double (&acc)[N]) {
     switch (a) {
-        case 1: return gemv_rows<8, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
-        case 2: return gemv_rows<4, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
-        case 3: return gemv_rows<3, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
-        case 4: return gemv_rows<2, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
-        case 6: return gemv_rows<1, MASKED>(src, mrow, mask4, G, sc, of, xs, acc);
+        case 1: return gemv_rows<8, MASKED>(src, mrow, G, sc, of, xs, acc);
+        case 2: return gemv_rows<4, MASKED>(src, mrow, G, sc, of, xs, acc);
+        case 3: return gemv_rows<3, MASKED>(src, mrow, G, sc, of, xs, acc);
+        case 4: return gemv_rows<2, MASKED>(src, mrow, G, sc, of, xs, acc);
+        case 6: return gemv_rows<1, MASKED>(src, mrow, G, sc, of, xs, acc);
         default: break;                                                // trits
     }
-#pragma unroll 2
+    uint32_t m[N][4];
+#pragma unroll 1
     for (int32_t c = 0; c < G; c += 8) {
 #pragma unroll
         for (int k = 0; k < N; ++k) {
+            if (MASKED && (c & 127) == 0) load_code_bytes(mrow[k] + (c >> 3), (G - c) >> 3 < 16 ? (G - c) >> 3 : 16, m[k]);
             float wh[8], dot = 0.0f;
             decode8(5, 0, src[k], c, bpg, sc[k], of[k], trits_of, wh);
-            const uint32_t m = MASKED ? mrow[k][c >> 3] : 0u;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) dot = fmaf(((m >> i) & 1u) != 0u ? 0.0f : wh[i], xs[c + i], dot);
+            for (int i = 0; i < 8; ++i) dot = fmaf(MASKED && ((m[k][0] >> i) & 1u) != 0u ? 0.0f : wh[i], xs[c + i], dot);
             acc[k] += (double)dot;
+            if (MASKED) {
+                m[k][0] = (m[k][0] >> 8) | (m[k][1] << 24); m[k][1] = (m[k][1] >> 8) | (m[k][2] << 24);
+                m[k][2] = (m[k][2] >> 8) | (m[k][3] << 24); m[k][3] >>= 8;
+            }
         }
     }
 }
 
-// RPT rows per thread: a workgroup takes RPT * 256 rows of a unit.
-template <int DT, int RPT>
-__global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatch B) {
+// RPT rows per thread: a workgroup takes RPT * 256 rows of a unit.  Where that leaves the chip short of workgroups, several
+// (1 << parts_shift) are launched for each: they share the rows of a skip unit, all but the first leave any other at once.
+// MASKED: matrices with a protection mask, in launches of their own (compiled into one kernel the two spilled registers:
+// 7B-shaped block under a mask 180 us against 138).
+template <int DT, int RPT, bool MASKED>
+__global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_kernel(const DequantBatch B, const int parts_shift) {
     extern __shared__ __align__(16) char gemv_smem[];
     float* xs = reinterpret_cast<float*>(gemv_smem);
     double* tab = reinterpret_cast<double*>(gemv_smem + WINDQ_MAX_CHUNK * sizeof(float));
     __shared__ double red[GEMV_THREADS / 64];
     constexpr int nt = RPT * GEMV_THREADS;         // rows
-    const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
+    const uint32_t wgs = (uint32_t)B.tile_start[B.n];
+    uint32_t wg = blockIdx.x, part = 0u;
+    if (parts_shift != 0) {
+        part = wg / wgs;
+        wg -= part * wgs;
+    }
+    // masked: neighbouring chunks, whose mask bytes share lines of the cache, on one XCD (workgroups go round the eight): 65 us
+    // against 74 for a 7B-shaped block
+    if (MASKED && wg < (wgs & ~7u)) wg = (wg & 7u) * (wgs >> 3) + (wg >> 3);
+    const int mi = batch_index(B.tile_start, B.n, wg);
     const DequantArgs& A = B.m[mi];
     // workgroups of one matrix: chunks side by side, then row ranges, then row blocks
-    const uint32_t at = (uint32_t)((int64_t)blockIdx.x - B.tile_start[mi]);
+    const uint32_t at = (uint32_t)((int64_t)wg - B.tile_start[mi]);
     const uint32_t nc = (uint32_t)A.g.n_chunks;
     const uint32_t nr = (uint32_t)((A.g.R_u + nt - 1) / nt);
     const uint32_t band = at / nc, j = at - band * nc;
@@ -665,6 +695,19 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
 
     int a = A.action[u];                           // on their way while x is looked over
     const int64_t base = A.code_off[u];
+    const int32_t lpr = G >> 3;
+    const bool lanes_split = (lpr & (lpr - 1)) == 0;
+    // G/8 lanes side by side share a row of a skip unit and, under a mask, of 8-bit codes (a lane's own row of them is a line
+    // of the cache that is gone before the lane has used it up): the routes whose rows the parts share
+    const auto shared_rows = [&](int act) { return act == 0 || (MASKED && act == 1 && lanes_split); };
+    if (part != 0u) {
+        int act = a < WINDQ_N_ACTIONS ? a : 0;
+        const int64_t bytes = dq_bytes_per_group(act, G);
+        if (base < 0 || (base & 15) != 0 || base + bytes * A.g.R_u > A.codes_bytes) act = 0;
+        if (!shared_rows(act)) return;
+    }
+    const int32_t share = nt >> parts_shift, first = (int32_t)part * share;             // this part's rows
+    const int32_t end = first + share < nrows ? first + share : nrows;
     bool odd = false;
     double xsum = 0.0;
     for (int32_t c = tid; c < G; c += GEMV_THREADS) {
@@ -675,7 +718,7 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
     }
     xsum = wave_sum(xsum);
     if ((tid & 63) == 0) red[tid >> 6] = xsum;
-    const bool direct = __syncthreads_or(odd ? 1 : 0) != 0 || A.mask != nullptr;
+    const bool direct = __syncthreads_or(odd ? 1 : 0) != 0 || MASKED;
     if (a >= WINDQ_N_ACTIONS) a = 0;
     const int64_t bpg = dq_bytes_per_group(a, G);
     if (base < 0 || (base & 15) != 0 || base + bpg * A.g.R_u > A.codes_bytes) a = 0;   // a malformed entry reads nothing
@@ -684,20 +727,19 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
     if (a == 0) {
         constexpr int EB = Elem<DT>::bytes;
         const char* __restrict__ w0 = static_cast<const char*>(A.W) + (row0 * A.g.ld + col0) * EB;
-        const int32_t lpr = G >> 3;
-        if ((lpr & (lpr - 1)) == 0) {                      // G/8 lanes side by side share a row
+        if (lanes_split) {                                 // G/8 lanes side by side share a row
             const int sub = tid & (lpr - 1);
             const int step = GEMV_THREADS / lpr;
             float xv[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) xv[i] = A.x[col0 + sub * 8 + i];
             constexpr int NR = DT == WINDQ_BF16 ? 8 : 4;
-            for (int32_t r0 = tid / lpr; r0 < nrows; r0 += NR * step) {        // NR rows in flight; lpr lanes keep together
+            for (int32_t r0 = first + tid / lpr; r0 < end; r0 += NR * step) {  // NR rows in flight; lpr lanes keep together
                 uint4 raw[NR][EB / 2];
 #pragma unroll
                 for (int k = 0; k < NR; ++k) {
                     const int32_t r = r0 + k * step;
-                    __builtin_memcpy(raw[k], w0 + ((int64_t)(r < nrows ? r : nrows - 1) * A.g.ld + sub * 8) * EB, 8 * EB);
+                    __builtin_memcpy(raw[k], w0 + ((int64_t)(r < end ? r : end - 1) * A.g.ld + sub * 8) * EB, 8 * EB);
                 }
 #pragma unroll
                 for (int k = 0; k < NR; ++k) {
@@ -707,11 +749,11 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
                     for (int i = 0; i < 8; ++i) dot = fmaf(w[i], xv[i], dot);
                     double d = (double)dot;
                     for (int mk = 1; mk < lpr; mk <<= 1) d += __shfl_xor(d, mk, 64);
-                    if (sub == 0 && r0 + k * step < nrows) out[r0 + k * step] = d;
+                    if (sub == 0 && r0 + k * step < end) out[r0 + k * step] = d;
                 }
             }
         } else {
-            for (int32_t r = tid; r < nrows; r += GEMV_THREADS) {
+            for (int32_t r = first + tid; r < end; r += GEMV_THREADS) {
                 double acc = 0.0;
                 for (int32_t c = 0; c < G; c += 8) {
                     float w[8], dot = 0.0f;
@@ -728,7 +770,40 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
 
     const int64_t g0 = u * A.g.R_u + lrow0;
     const uint8_t* __restrict__ src0 = A.codes + base + lrow0 * bpg;
-    if (a >= 4 && !direct) {
+    if (shared_rows(a)) {
+        const int32_t sub = tid & (lpr - 1), step = GEMV_THREADS / lpr;
+        const uint8_t* __restrict__ mask0 = A.mask + row0 * A.mask_ld + (col0 >> 3) + sub;
+        float xv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xv[i] = xs[sub * 8 + i];
+        constexpr int NR = 4;
+        for (int32_t r0 = first + tid / lpr; r0 < end; r0 += NR * step) {
+            uint32_t d[NR][2], m[NR];
+            float sc[NR], of[NR];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                const int32_t r = r0 + k * step, row = r < end ? r : end - 1;
+                __builtin_memcpy(d[k], src0 + (int64_t)row * G + sub * 8, 8);
+                m[k] = mask0[row * A.mask_ld];
+                sc[k] = A.scale[g0 + row];
+                of[k] = A.offset[g0 + row];
+            }
+#pragma unroll
+            for (int k = 0; k < NR; ++k) {
+                float dot = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float wh = fmaf((float)((d[k][i >> 2] >> (8 * (i & 3))) & 0xffu), sc[k], of[k]);
+                    dot = fmaf(((m[k] >> i) & 1u) != 0u ? 0.0f : wh, xv[i], dot);
+                }
+                double t = (double)dot;
+                for (int mk = 1; mk < lpr; mk <<= 1) t += __shfl_xor(t, mk, 64);
+                if (sub == 0 && r0 + k * step < end) out[r0 + k * step] = t;
+            }
+        }
+        return;
+    }
+    if (!MASKED && a >= 4 && !direct) {
         // the rows' loads are on their way while the tables are made, the next bytes while these are looked up; a thread
         // past the last row reads the last row's data again and writes nothing
         uint32_t d[RPT][4];
@@ -780,7 +855,6 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
         fill_trits(trits_of);
         __syncthreads();
     }
-    const bool mask4 = A.mask != nullptr && (A.mask_ld & 3) == 0 && ((reinterpret_cast<uintptr_t>(A.mask) + (uintptr_t)(col0 >> 3)) & 3) == 0;
     const uint8_t *src[RPT], *mrow[RPT];
     float sc[RPT], of[RPT];
     double acc[RPT];
@@ -788,16 +862,82 @@ __global__ __launch_bounds__(GEMV_THREADS, 6) void gemv_kernel(const DequantBatc
     for (int k = 0; k < RPT; ++k) {
         const int32_t r = k * GEMV_THREADS + tid, row = r < nrows ? r : nrows - 1;
         src[k] = src0 + (int64_t)row * bpg;
-        mrow[k] = A.mask != nullptr ? A.mask + (row0 + row) * A.mask_ld + (col0 >> 3) : nullptr;
+        mrow[k] = MASKED ? A.mask + (row0 + row) * A.mask_ld + (col0 >> 3) : nullptr;
         sc[k] = A.scale[g0 + row];
         of[k] = A.offset[g0 + row];
         acc[k] = 0.0;
     }
-    if (A.mask != nullptr) gemv_rows_of<true>(a, src, mrow, mask4, G, (int32_t)bpg, sc, of, xs, trits_of, acc);
-    else gemv_rows_of<false>(a, src, mrow, mask4, G, (int32_t)bpg, sc, of, xs, trits_of, acc);
+    gemv_rows_of<MASKED>(a, src, mrow, G, (int32_t)bpg, sc, of, xs, trits_of, acc);
 #pragma unroll
     for (int k = 0; k < RPT; ++k)
         if (k * GEMV_THREADS + tid < nrows) out[k * GEMV_THREADS + tid] = acc[k];
+}
+
+// Short units, and small matrices: G/8 lanes side by side share a row, eight columns each; no tables to make and no lanes
+// without a row.  A workgroup takes a tile of 64 rows, 2048 / G at a time, or, where there are few tiles, one of
+// 1 << parts_shift shares of it (512 x 512 at chunk 128 5.4 us, 8.0 with whole tiles; a share to each workgroup of a large
+// matrix costs it half its speed again: 4096 x 4096 in units of 64 rows 14.0 us, 19.2 in shares).
+template <int DT, bool POW2>
+__global__ __launch_bounds__(GEMV_THREADS) void gemv_split_kernel(const DequantBatch B, const int parts_shift) {
+    __shared__ uint16_t trits_of[256];
+    __shared__ double part[POW2 ? 1 : GEMV_THREADS];
+    const uint32_t wg = blockIdx.x >> parts_shift, share = blockIdx.x & ((1u << parts_shift) - 1u);
+    const int mi = batch_index(B.tile_start, B.n, wg);
+    const DequantArgs& A = B.m[mi];
+    const TileCoord tc = tile_coord(A.g, (int64_t)wg - B.tile_start[mi]);
+    constexpr int EB = Elem<DT>::bytes;
+    const int32_t G = A.g.chunk_w, lpr = G >> 3;
+    const int32_t lpr_shift = 31 - __builtin_clz(lpr);          // POW2
+    const int32_t rpp = POW2 ? GEMV_THREADS >> lpr_shift : GEMV_THREADS / lpr;      // rows of a pass
+    const int32_t rsub = POW2 ? (int32_t)threadIdx.x >> lpr_shift : (int32_t)threadIdx.x / lpr, sub = (int32_t)threadIdx.x - rsub * lpr;
+    const int32_t c = sub * 8;
+
+    int a = A.action[tc.u];
+    if (a >= WINDQ_N_ACTIONS) a = 0;
+    const int64_t bpg = dq_bytes_per_group(a, G);
+    const int64_t base = A.code_off[tc.u];
+    if (base < 0 || (base & 15) != 0 || base + bpg * A.g.R_u > A.codes_bytes) a = 0;   // a malformed entry reads nothing
+    const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : (a == 4 ? 2 : 1)));
+    float xv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) xv[j] = A.x[tc.col0 + c + j];
+    if (a == 5) {
+        fill_trits(trits_of);
+        __syncthreads();
+    }
+    double* __restrict__ out = A.gpart + (tc.col0 / G) * A.g.rows + tc.row0;
+    for (int32_t r0 = (int32_t)share * rpp; r0 < tc.nrows; r0 += rpp << parts_shift) {
+        const int32_t r = r0 + rsub;
+        float dot = 0.0f;
+        if ((POW2 || rsub < rpp) && r < tc.nrows) {
+            float wh[8];
+            uint32_t m = 0u;
+            if (a == 0) {
+                load8_global<DT>(static_cast<const char*>(A.W) + ((tc.row0 + r) * A.g.ld + tc.col0 + c) * EB, wh);
+            } else {
+                if (A.mask != nullptr) m = A.mask[(tc.row0 + r) * A.mask_ld + (tc.col0 >> 3) + sub];
+                const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + r;
+                decode8(a, bits, A.codes + base + (tc.lrow0 + r) * bpg, c, (int32_t)bpg, A.scale[gidx], A.offset[gidx], trits_of, wh);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) dot = fmaf(((m >> j) & 1u) != 0u ? 0.0f : wh[j], xv[j], dot);
+        }
+        // the row's 8-column runs summed in fp64
+        double d = (double)dot;
+        if (POW2) {
+            for (int mk = 1; mk < lpr; mk <<= 1) d += __shfl_xor(d, mk, 64);
+            if (sub == 0 && r < tc.nrows) out[r] = d;
+        } else {
+            __syncthreads();
+            part[threadIdx.x] = d;
+            __syncthreads();
+            if ((int32_t)threadIdx.x < rpp && r0 + (int32_t)threadIdx.x < tc.nrows) {
+                double t = 0.0;
+                for (int32_t i = 0; i < lpr; ++i) t += part[(int32_t)threadIdx.x * lpr + i];
+                out[r0 + (int32_t)threadIdx.x] = t;
+            }
+        }
+    }
 }
 
 // y[row] = the row's chunk partials: 8 phases, phase p adds chunks p, p + 8, ..., the phases in order; fp64,
@@ -940,17 +1080,45 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 
-// The product.  A workgroup takes 512 rows of a unit (two per thread, their loads in flight together) where that still
+// The product: which kernel a matrix takes.  It alone decides, so that a batch gives the bits of single calls.  Lanes that
+// share a row (split) against a row to each lane (rows), us at a mixed 2-bit plan:
+//   rows per unit, 4096 x 4096 bf16, chunk 128           32: 15.3 against 27.7   64: 14.0, 18.0   96: 15.2, 14.6   128: 14.1, 12.7
+//   the same under a mask                               128: 15.3, 25.3         256: 15.3, 12.9
+//   weights, whole columns, chunk 128    1024 x 1024: 5.6, 7.7   2048 x 768: 6.0, 7.7   1024 x 2048: 6.8, 8.1   (4096 x 4096: 14, 8.6)
+//                      chunks 96 and 32  2048 x 768: 6.6, 7.2 and 6.6, 7.9   1024 x 2016: 8.1, 8.2 and 7.0, 7.4
+//   under a mask                         2048 x 2048 at chunk 256: 9, 13, at chunk 32 (512 workgroups of 256 rows): 8.5, 7.9
+constexpr int GEMV_SPLIT = 0, GEMV_ROWS = 1, GEMV_ROWS_MASKED = 2;
+constexpr int64_t GEMV_SHORT_UNIT = 96, GEMV_SHORT_UNIT_MASKED = 256;     // rows
+constexpr int64_t GEMV_SMALL = 3 << 19, GEMV_SMALL_MASKED = 1 << 22;      // weights
+constexpr int64_t GEMV_FEW_WGS_MASKED = 256;
+static int gemv_route(const Geometry& g, bool masked) {
+    const int64_t wgs = g.U * ((g.R_u + GEMV_THREADS - 1) / GEMV_THREADS), n = g.rows * g.cols;
+    if (g.R_u < (masked ? GEMV_SHORT_UNIT_MASKED : GEMV_SHORT_UNIT) || n <= GEMV_SMALL) return GEMV_SPLIT;
+    if (masked && n <= GEMV_SMALL_MASKED && wgs <= GEMV_FEW_WGS_MASKED) return GEMV_SPLIT;
+    return masked ? GEMV_ROWS_MASKED : GEMV_ROWS;
+}
+constexpr int64_t GEMV_SPLIT_WGS = 2048;    // up to which a tile's rows are spread over several workgroups: two rounds of a full chip at most
+
+template <int RPT, bool MASKED>
+static void gemv_rows_launch(const DequantBatch& B, int64_t wgs, int parts_shift, bool bf, size_t lds, hipStream_t hs) {
+    const dim3 grid((unsigned)(wgs << parts_shift)), block(GEMV_THREADS);
+    if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, RPT, MASKED>), grid, block, lds, hs, B, parts_shift);
+    else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, RPT, MASKED>), grid, block, lds, hs, B, parts_shift);
+}
+
+// A workgroup takes 512 rows of a unit (two per thread, their loads in flight together) where that still
 // makes four workgroups per CU, else 256.  1024 rows are as fast when all units have one bit-width, but the few units at
 // 8 bits or skipped then outlast the others: 4096 x 11008 x 4 at a mixed plan 45 us against 35.
 constexpr int64_t GEMV_MIN_WGS = 1024;
 static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int64_t unit_rows, void* stream) {
     if (items == nullptr || n < 1 || n > WINDQ_MAX_BATCH) return WINDQ_EINVAL;
-    DequantBatch B;
-    B.n = n;
+    DequantBatch L[3], All;
+    All.n = n;
+    for (int k = 0; k < 3; ++k) L[k].n = 0;
+    int64_t fin = 0;
     for (int32_t i = 0; i < n; ++i) {
         const DequantItem& it = items[i];
-        DequantArgs& A = B.m[i];
+        DequantArgs& A = All.m[i];
         if (it.W == nullptr) return WINDQ_EINVAL;
         const int st = make_geometry(it.W, chunk_w, unit_rows, &A.g);
         if (st != WINDQ_OK) return st;
@@ -960,40 +1128,60 @@ static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int
         if (it.W->dtype != items[0].W->dtype) return WINDQ_EINVAL;      // one kernel per launch
         if (it.ws == nullptr || it.ws_bytes < dequant_gemv_ws_bytes(A.g) || !aligned(it.ws, 256)) return WINDQ_EWORKSPACE;
         dequant_args(it, &A);
+        DequantBatch& B = L[gemv_route(A.g, A.mask != nullptr)];
+        B.m[B.n++] = A;
     }
-    int rpt = 4;
-    int64_t wgs;
-    do {                        // row_start: the finalize kernel's workgroups
-        rpt >>= 1;
-        wgs = 0;
-        int64_t fin = 0;
-        for (int32_t i = 0; i < n; ++i) {
-            const Geometry& g = B.m[i].g;
-            B.tile_start[i] = wgs;
-            B.row_start[i] = fin;
-            wgs += g.U * ((g.R_u + rpt * GEMV_THREADS - 1) / (rpt * GEMV_THREADS));
-            fin += (g.rows + GEMV_FIN_ROWS - 1) / GEMV_FIN_ROWS;
-        }
-        for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) {
-            B.tile_start[i] = wgs;
-            B.row_start[i] = fin;
-        }
-    } while (rpt > 1 && wgs < GEMV_MIN_WGS);
-    for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) B.unit_start[i] = 0;
-    for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (wgs > (int64_t)0x7fffffff || B.row_start[n] > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    dequant_number(&All);
+    for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) {        // the finalize kernel's workgroups
+        All.row_start[i] = fin;
+        if (i < n) fin += (All.m[i].g.rows + GEMV_FIN_ROWS - 1) / GEMV_FIN_ROWS;
+    }
+    if (All.tile_start[n] > (int64_t)0x7fffffff || fin > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    const dim3 grid((unsigned)wgs), block(GEMV_THREADS);
     const bool bf = items[0].W->dtype == WINDQ_BF16;
-    const size_t lds = gemv_lds(chunk_w);         // at most 41 KB
-    if (rpt == 2) {
-        if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, 2>), grid, block, lds, hs, B);
-        else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, 2>), grid, block, lds, hs, B);
-    } else {
-        if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, 1>), grid, block, lds, hs, B);
-        else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, 1>), grid, block, lds, hs, B);
+    if (L[GEMV_SPLIT].n > 0) {
+        const int64_t tiles = dequant_number(&L[GEMV_SPLIT]);
+        int parts_shift = 0;
+        while ((1 << parts_shift) < dequant_passes(chunk_w) && (tiles << parts_shift) < GEMV_SPLIT_WGS) ++parts_shift;
+        const dim3 grid((unsigned)(tiles << parts_shift)), block(GEMV_THREADS);
+        const bool pow2 = (chunk_w & (chunk_w - 1)) == 0;
+        if (bf && pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, true>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
+        else if (bf) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, false>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
+        else if (pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_F32, true>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
+        else hipLaunchKernelGGL((gemv_split_kernel<WINDQ_F32, false>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
     }
-    hipLaunchKernelGGL(gemv_finalize_kernel, dim3((unsigned)B.row_start[n]), dim3(256), 0, hs, B);
+    for (int k = GEMV_ROWS; k <= GEMV_ROWS_MASKED; ++k) {
+        DequantBatch& B = L[k];
+        if (B.n == 0) continue;
+        dequant_number(&B);
+        int rpt = 4;
+        int64_t wgs;
+        do {
+            rpt >>= 1;
+            wgs = 0;
+            for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) {
+                B.tile_start[i] = wgs;
+                if (i < B.n) wgs += B.m[i].g.U * ((B.m[i].g.R_u + rpt * GEMV_THREADS - 1) / (rpt * GEMV_THREADS));
+            }
+        } while (rpt > 1 && wgs < GEMV_MIN_WGS);
+        // a skip unit's rows in parts, where there are fewer than two workgroups per CU (four under a mask, where 8-bit units share
+        // too), each of at least four loads per thread: skip units of 4096 x 4096 at chunk 512 16.5 us, 38 in one part
+        int parts_shift = 0;
+        while (parts_shift < 2 && (wgs << parts_shift) < (k == GEMV_ROWS ? GEMV_MIN_WGS / 2 : GEMV_MIN_WGS)) {
+            const int64_t rows = rpt * GEMV_THREADS >> (parts_shift + 1);       // of a part
+            if (rows >= B.m[0].g.R_u || rows * chunk_w < 4 * GEMV_THREADS * 8) break;
+            ++parts_shift;
+        }
+        const size_t lds = k == GEMV_ROWS ? gemv_lds(chunk_w) : WINDQ_MAX_CHUNK * sizeof(float) + 256 * sizeof(uint16_t);   // tables: at most 41 KB
+        if (k == GEMV_ROWS) {
+            if (rpt == 2) gemv_rows_launch<2, false>(B, wgs, parts_shift, bf, lds, hs);
+            else gemv_rows_launch<1, false>(B, wgs, parts_shift, bf, lds, hs);
+        } else {
+            if (rpt == 2) gemv_rows_launch<2, true>(B, wgs, parts_shift, bf, lds, hs);
+            else gemv_rows_launch<1, true>(B, wgs, parts_shift, bf, lds, hs);
+        }
+    }
+    hipLaunchKernelGGL(gemv_finalize_kernel, dim3((unsigned)fin), dim3(256), 0, hs, All);
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 

@@ -192,13 +192,75 @@ def test_gemv_at_the_edges_of_its_tables(windq, R, C, G, unit_rows, dtype):
     gemv_case(windq, W, s, G, unit_rows, 4)
 
 
+def random_artefact(windq, R, C, G, unit_rows, dtype, masked, seed):
+    """A packed plan of random bytes with all seven actions, and a random mask of 3 % of the weights."""
+    g = torch.Generator().manual_seed(seed)
+    W = synth.weights_llm(R, C, seed=seed, device=DEV, dtype=dtype)
+    U, R_u = windq.n_units(R, C, G, unit_rows)
+    action = ((torch.arange(U) + seed) % 7).to(torch.uint8)
+    off = windq.windq_plan_layout(action, R_u, G)
+    codes = torch.randint(0, 256, (max(int(off[-1]), 16),), generator=g, dtype=torch.uint8).to(DEV)
+    scale = torch.rand(U * R_u, generator=g).mul(0.1).to(DEV)
+    offset = torch.randn(U * R_u, generator=g).to(DEV)
+    x = (torch.randn(C, generator=g) * torch.exp(torch.randn(C, generator=g))).to(DEV)
+    mask = None
+    if masked:
+        bits = torch.rand(R, C, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV) < 0.03
+        mask = (bits.view(R, C // 8, 8) * (2 ** torch.arange(8, device=DEV))).sum(2).to(torch.uint8)
+    return dict(W=W, action=action.to(DEV), off=off.to(DEV), codes=codes, scale=scale, offset=offset, x=x, mask=mask)
+
+
+def gemv_of(windq, A, G, unit_rows):
+    return windq.windq_dequant_gemv(A["W"], G, unit_rows, A["action"], A["off"], A["codes"], A["scale"], A["offset"], A["x"], mask=A["mask"])
+
+
+def check_against_reconstruction(windq, A, G, unit_rows, y):
+    _, w_hat = windq.windq_dequant_plan(A["W"], torch.ones_like(A["x"]), G, unit_rows, A["action"], A["off"], A["codes"], A["scale"],
+                                        A["offset"], mask=A["mask"])
+    want = w_hat.double() @ A["x"].double()
+    mag = w_hat.double().abs() @ A["x"].double().abs()
+    bad = ((y.double() - want).abs() / (1e-6 * mag + 1e-7 * want.abs() + 1e-300)).max()
+    assert float(bad) <= 1.0, float(bad)
+
+
+# which kernel a matrix takes turns on its rows per unit (96; 256 under a mask), its weights (1.5 * 2^20; 4 * 2^20 under a mask)
+# and, under a mask, the number of 256-row workgroups (256)
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("R,C,G,unit_rows,dtype", [
+    (1760, 7 * 128, 128, 0, torch.bfloat16), (1750, 7 * 128, 128, 0, torch.bfloat16),           # just above 1.5 * 2^20, just below
+    (28100, 7 * 8, 8, 0, torch.bfloat16), (9400, 7 * 24, 24, 0, torch.float32),                 # rows of 1 to 24 bytes
+    (440, 7 * 512, 512, 0, torch.bfloat16), (1200, 7 * 512, 512, 0, torch.float32),             # few workgroups: skip units in parts
+    (2304, 7 * 128, 128, 96, torch.bfloat16), (2280, 7 * 128, 128, 95, torch.float32),          # the shortest unit, and one row less
+    (2352, 7 * 96, 96, 1176, torch.bfloat16), (4700, 7 * 128, 128, 0, torch.bfloat16),
+    (5120, 7 * 128, 128, 256, torch.float32), (5100, 7 * 128, 128, 255, torch.bfloat16),
+    (6300, 7 * 104, 104, 0, torch.bfloat16), (17000, 7 * 40, 40, 0, torch.bfloat16),            # masks of 13 and 5 bytes a row
+    (77, 7 * 504, 504, 11, torch.bfloat16), (9, 7 * 16, 16, 3, torch.float32)])                 # lanes that share a row by LDS, by shuffles
+def test_gemv_at_the_edges_of_its_routes(windq, R, C, G, unit_rows, dtype, masked):
+    A = random_artefact(windq, R, C, G, unit_rows, dtype, masked, seed=R + masked)
+    check_against_reconstruction(windq, A, G, unit_rows, gemv_of(windq, A, G, unit_rows))
+
+
+def test_gemv_batch_of_all_routes(windq):
+    """Small, large, masked and unmasked matrices in one batch: each as it would be alone."""
+    G, shapes = 128, [(300, 512, False), (1800, 1024, False), (300, 512, True), (5000, 1024, True), (5000, 1024, False)]
+    As = [random_artefact(windq, r, c, G, 0, torch.bfloat16, m, seed=50 + i) for i, (r, c, m) in enumerate(shapes)]
+    alone = [gemv_of(windq, A, G, 0) for A in As]
+    both = windq.windq_dequant_gemv_batch([A["W"] for A in As], G, 0, *([A[k] for A in As] for k in ("action", "off", "codes", "scale", "offset", "x")),
+                                          masks=[A["mask"] for A in As])
+    torch.cuda.synchronize()
+    for A, one, b in zip(As, alone, both):
+        assert torch.equal(one.view(torch.int32), b.view(torch.int32))
+        check_against_reconstruction(windq, A, G, 0, b)
+
+
+@pytest.mark.parametrize("R", [96, 4200])               # below and above the size from which tables are used
 @pytest.mark.parametrize("bad", [float("inf"), 2.0 ** 120])
-def test_gemv_with_values_no_table_may_hold(windq, bad):
+def test_gemv_with_values_no_table_may_hold(windq, R, bad):
     """A chunk of x with an infinity or a huge value is summed weight by weight: what the reconstruction times x gives in
     fp32, signs and NaN included, and the other chunks as ever."""
-    W = synth.weights_llm(96, 6 * 64, seed=122, device=DEV)
+    W = synth.weights_llm(R, 6 * 64, seed=122, device=DEV)
     action = torch.tensor([6, 5, 4, 6, 5, 4], dtype=torch.uint8)
-    off = windq.windq_plan_layout(action, 96, 64)
+    off = windq.windq_plan_layout(action, R, 64)
     codes, scale, offset = windq.windq_apply_plan(W, 64, 0, action.to(DEV), None, None, off.to(DEV))
     x = torch.randn(6 * 64, generator=torch.Generator().manual_seed(3)).to(DEV)
     _, w_hat = windq.windq_dequant_plan(W, torch.ones(384, device=DEV), 64, 0, action.to(DEV), off.to(DEV), codes, scale, offset)
@@ -213,12 +275,13 @@ def test_gemv_with_values_no_table_may_hold(windq, bad):
         assert torch.equal(torch.sign(y[torch.isinf(want)]), torch.sign(want[torch.isinf(want)]))
 
 
+@pytest.mark.parametrize("R", [300, 6600])              # below and above the size from which tables are used
 @pytest.mark.parametrize("G", [64, 40])
 @pytest.mark.parametrize("positive", [True, False])
-def test_gemv_with_scales_that_are_not_finite(windq, G, positive):
+def test_gemv_with_scales_that_are_not_finite(windq, R, G, positive):
     """Rows whose stored scale or offset is infinite, NaN or huge: what the reconstruction times x gives, signs and NaN
     included, and the other rows as ever."""
-    R, C = 300, 6 * G
+    C = 6 * G
     W = synth.weights_llm(R, C, seed=123, device=DEV)
     W[:8, :G] = W[:8, :G].abs() + 0.01                 # signs all alike: a product of one sign
     action = torch.tensor([6, 5, 4, 6, 5, 4], dtype=torch.uint8)
