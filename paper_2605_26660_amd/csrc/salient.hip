@@ -385,18 +385,29 @@ __device__ __forceinline__ void wave_select_bin(const uint32_t* __restrict__ h, 
     *below = base + __shfl(in - own, b, 64);
 }
 
-// The bracket, from a sample of whole rows evenly spread over the unit: up to 32768 weights, at least
-// 4096, and half the unit between (so that small units are read one and a half times, not twice).  With p_s
-// protected weights expected in the sample the bracket reaches from rank p_s + d to p_s - d,
-//     d = 5 standard deviations of a random sample's count + 4 % of p_s + 8,
-// to a 128th of an octave: 1 % of a 524288-weight unit at a 3 % rate.  The margin decides nothing but how often a
+// bits = 2 bits + (key >= limit): a compare into the carry and an add with carry, where the compiler makes a
+// compare, a select, a shift and an or of the same in C.
+__device__ __forceinline__ void push_ge(uint32_t& bits, uint32_t key, uint32_t limit) {
+    asm("v_cmp_le_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(key), "s"(limit) : "vcc");
+}
+
+// The bracket, from a sample of the unit: all of it up to 32768 weights (then the bracket is the 128th of an octave that
+// holds T, and no count can refute it); of a larger one 32768 in SAL_SEG_BYTES segments of as many rows as that gives, evenly
+// spread, neighbouring sampled rows in neighbouring columns.  With p_s protected weights expected in the sample
+// the bracket reaches from rank p_s + d to p_s - d,
+//     d = 4 standard deviations of the sample's count + 2, and no more than the list can take,
+// to a 128th of an octave: 1 % of a 524288-weight unit at a 3 % rate.  The deviation is that of the counts of segments in the same
+// columns: where rows differ in norm their weights rise above T together, and the count deviates by more than
+// independent weights would (by half for a log-normal spread of 0.8).  The margin decides nothing but how often a
 // unit has to be selected the long way; whether the bracket holds is counted.
 constexpr int SAL_BIG = 1024;               // threads of the per-unit kernels
-constexpr int SAL_SAMPLE_PIECES = 4096;     // most 8-weight pieces a unit's sample holds
+constexpr int SAL_SAMPLE_LOG = 12, SAL_SAMPLE_PIECES = 1 << SAL_SAMPLE_LOG;     // most 8-weight pieces a unit's sample holds
+constexpr int SAL_SEG_BYTES = 64;
+constexpr float SAL_MARGIN = 4.0f;          // standard deviations
 template <int DT>
 __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
     __shared__ uint32_t lh[FEAT_BINS];
-    __shared__ uint32_t sh_bin[3], sh_below[3];
+    __shared__ uint32_t sh_bin[3], sh_below[3], sh_dev;
     __shared__ float scol[WINDQ_MAX_CHUNK];
     const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
     const SalArgs& A = B.m[mi];
@@ -412,62 +423,110 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
     const int32_t pieces = G >> 3;
     const int64_t rb = u / A.g.n_chunks;
     const int64_t col0 = (u - rb * A.g.n_chunks) * G;
-    // rows of the sample
-    int64_t want = A.g.R_u * pieces / 2;
-    if (want < SAL_SAMPLE_PIECES / 8) want = SAL_SAMPLE_PIECES / 8;
-    if (want > SAL_SAMPLE_PIECES) want = SAL_SAMPLE_PIECES;
-    int64_t rows = want / pieces;
-    if (rows > A.g.R_u) rows = A.g.R_u;                    // at least 8 for the widest chunk (64 pieces)
-    const int64_t stride = A.g.R_u / rows;
-    const int32_t total = (int32_t)rows * pieces;
+    const bool whole = A.g.R_u * pieces <= SAL_SAMPLE_PIECES;
+    const int32_t total = whole ? (int32_t)A.g.R_u * pieces : SAL_SAMPLE_PIECES;
     for (int32_t b = threadIdx.x; b < FEAT_BINS; b += SAL_BIG) lh[b] = 0u;
     for (int32_t c = threadIdx.x; c < G; c += SAL_BIG) scol[c] = A.s[col0 + c];
-    __syncthreads();
+    if (threadIdx.x == 0) sh_dev = 0u;
     constexpr int PER = SAL_SAMPLE_PIECES / SAL_BIG;
     uint32_t key[PER][8];
     Raw8<DT> raw[PER];
+    int32_t pc[PER];
+    // segments of 1 << seg_log pieces, n_pos to a row, 1 << n_seg_log of them in the sample
+    constexpr int SEG_MAX = SAL_SEG_BYTES / (8 * Elem<DT>::bytes);
+    const int seg_log = min(31 - __builtin_clz(SEG_MAX), (int)__builtin_ctz(pieces)), n_seg_log = SAL_SAMPLE_LOG - seg_log;
+    if (whole) {
+        PieceWalk at((int32_t)threadIdx.x, SAL_BIG, pieces);
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int32_t i = k * SAL_BIG + (int32_t)threadIdx.x;
-        if (i < total) {
-            const int32_t r = (int32_t)((uint32_t)i / (uint32_t)pieces), pc = i - r * pieces;
-            raw[k] = load8raw<DT>(A.W, (rb * A.g.R_u + r * stride + stride / 2) * A.g.ld + col0 + pc * 8);
+        for (int k = 0; k < PER; ++k) {
+            pc[k] = at.pc;
+            if (k * SAL_BIG + (int32_t)threadIdx.x < total) raw[k] = load8raw<DT>(A.W, (rb * A.g.R_u + at.r) * A.g.ld + col0 + at.pc * 8);
+            at.next();
+        }
+    } else {
+        const uint32_t n_pos = (uint32_t)pieces >> seg_log, in_seg = threadIdx.x & ((1u << seg_log) - 1u);
+        const bool pow2 = (n_pos & (n_pos - 1u)) == 0u;
+        const uint32_t seg0 = threadIdx.x >> seg_log, seg_step = (uint32_t)SAL_BIG >> seg_log;       // four steps are the sample
+        const bool spread = A.g.R_u >= (int64_t)1 << n_seg_log;
+        int64_t x = (int64_t)seg0 * A.g.R_u + (A.g.R_u >> 1);
+        const int64_t x_step = (int64_t)seg_step * A.g.R_u;
+#pragma unroll
+        for (int k = 0; k < PER; ++k, x += x_step) {
+            uint32_t at = seg0 + k * seg_step;
+            int64_t r = x >> n_seg_log;
+            if (!spread) {                                 // fewer rows than segments: several of a row, in different columns
+                const uint32_t turn = at / (uint32_t)A.g.R_u;
+                r = (int64_t)(at - turn * (uint32_t)A.g.R_u);
+                at = (uint32_t)r + turn;
+            }
+            pc[k] = (int32_t)(((pow2 ? at & (n_pos - 1u) : at % n_pos) << seg_log) + in_seg);
+            raw[k] = load8raw<DT>(A.W, (rb * A.g.R_u + r) * A.g.ld + col0 + pc[k] * 8);
         }
     }
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int32_t i = k * SAL_BIG + (int32_t)threadIdx.x;
-        if (i < total) {
-            const int32_t pc = (int32_t)((uint32_t)i % (uint32_t)pieces);
+        if (k * SAL_BIG + (int32_t)threadIdx.x < total) {
             float w[8];
             unpack8raw<DT>(raw[k], w);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                key[k][j] = sal_key(w[j], scol[pc * 8 + j]);
+                key[k][j] = sal_key(w[j], scol[pc[k] * 8 + j]);
                 atomicAdd(&lh[key[k][j] >> 20], 1u);
             }
         }
     }
     __syncthreads();
-    // ranks from the top, 1-based, of the bracket's ends
-    const double n_s = (double)total * 8.0, n = (double)A.g.R_u * (double)G;
-    const double f = n_s / n, p_s = (double)A.n_p * f;
-    const double d = 5.0 * sqrt(p_s * (1.0 - f)) + 0.04 * p_s + 8.0;
+    // ranks from the top, 1-based, of the bracket's ends (fp32 is exact for a unit sampled whole)
+    const float n_s = (float)total * 8.0f;
+    const float f = whole ? 1.0f : n_s / ((float)A.g.R_u * (float)G), p_s = (float)A.n_p * f;
     const uint32_t ns = (uint32_t)total * 8u;
-    // (the first three wavefronts look for one of them each)
     const int wave = threadIdx.x >> 6;
-    const bool open = wave == 0 ? p_s + d >= n_s : (wave == 1 && p_s - d < 1.0);
-    const double place = wave == 0 ? p_s + d : (wave == 1 ? p_s - d : (p_s < 1.0 ? 1.0 : p_s));
-    const uint32_t rank = open ? (wave == 0 ? 1u : ns) : ns - (uint32_t)place + 1u;      // ascending
-    uint32_t bin = 0, below = 0;
-    if (wave < 3) {
+    float d = 0.0f;
+    bool open = false;
+    uint32_t bin = 0, below = 0, rank = 0;
+    // (the first three wavefronts look for one of them each)
+    const auto find = [&]() {
+        open = wave == 0 ? p_s + d >= n_s : (wave == 1 && p_s - d < 1.0f);
+        const float place = wave == 0 ? p_s + d : (wave == 1 ? p_s - d : (p_s < 1.0f ? 1.0f : p_s));
+        rank = open ? (wave == 0 ? 1u : ns) : ns - (uint32_t)place + 1u;      // ascending
         wave_select_bin(lh, FEAT_BINS, rank, &bin, &below);
         if ((threadIdx.x & 63) == 0) {
             sh_bin[wave] = bin;
             sh_below[wave] = below;
         }
-    }
+    };
+    const float var = p_s * (1.0f - p_s / n_s), most = 0.43f * (float)A.cap * f - 2.0f;
+    if (!whole) d = fminf(SAL_MARGIN * sqrtf(var * (1.0f - f)) + 2.0f, most);
+    if (wave < 3) find();
     __syncthreads();
+    if (!whole) {
+        // how far the number of keys from the middle bin upwards deviates: by the four segments that a thread's pieces belong to,
+        // which are of the same columns, or nearly (n_pos divides the distance between them where it is a power of two)
+        const uint32_t from = __builtin_amdgcn_readfirstlane(sh_bin[2] << 20);
+        uint32_t sum = 0u, sq = 0u;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            uint32_t bits = 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) push_ge(bits, key[k][j], from);
+            uint32_t c = (uint32_t)__builtin_popcount(bits);
+            for (int m = 1; m < 1 << seg_log; m <<= 1) c += __shfl_xor(c, m, 64);
+            sum += c;
+            sq += c * c;
+        }
+        uint32_t dev = (threadIdx.x & ((1u << seg_log) - 1u)) == 0u ? PER * sq - sum * sum : 0u;
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) dev += __shfl_xor(dev, m, 64);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&sh_dev, dev);
+        __syncthreads();
+        const float seen = (float)sh_dev / (PER - 1);
+        if (seen > 1.2f * var) {                           // the same for all threads
+            d = fminf(SAL_MARGIN * sqrtf(seen * (1.0f - f)) + 2.0f, most);
+            if (wave < 2) find();
+            __syncthreads();
+        }
+    }
     // the next four bits of the keys from the lowest of the three bins to the highest
     const uint32_t first = sh_bin[0], below0 = sh_below[0];
     const uint32_t span = (sh_bin[1] - first + 1u) * 16u;
@@ -498,12 +557,6 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
             else A.mid[u] = start;
         }
     }
-}
-
-// bits = 2 bits + (key >= limit): a compare into the carry and an add with carry, where the compiler makes a
-// compare, a select, a shift and an or of the same in C.
-__device__ __forceinline__ void push_ge(uint32_t& bits, uint32_t key, uint32_t limit) {
-    asm("v_cmp_le_u32_e32 vcc, %2, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(key), "s"(limit) : "vcc");
 }
 
 // The pass over W: the mask (inside the bracket as if T were `mid`), the counts, the list.  Bound by HBM: per weight one multiply and two

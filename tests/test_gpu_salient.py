@@ -81,18 +81,65 @@ def test_select_over_the_sizes_of_its_sample(windq, R, C, G, unit_rows, ppm, dty
     check_encode(windq, W, s, G, unit_rows, ppm, mask, keep)
 
 
+def flagged_units(windq, W, s, G, unit_rows, ppm):
+    """The units that a selection took by digit passes over W: the list that it leaves in its workspace (after three histograms
+    of 2048 counters per unit and the units' two ends, middle, counts and flags, each part on 256 bytes)."""
+    code = windq.WINDQ_BF16 if W.dtype == torch.bfloat16 else windq.WINDQ_F32
+    ws = torch.zeros(windq.workspace_bytes(windq.CALL_SALIENT, code, W.shape[0], W.shape[1], G, unit_rows), dtype=torch.uint8, device=DEV)
+    windq.windq_salient_select(W, s, G, unit_rows, ppm, ws=ws)
+    U, _ = windq.n_units(W.shape[0], W.shape[1], G, unit_rows)
+    at = sum((n + 255) // 256 * 256 for n in (3 * U * 2048 * 4, 4 * U, 4 * U, 4 * U, 8 * U, 4 * U))
+    n = int(ws[at:at + 4].view(torch.int32).item())
+    return sorted(ws[at + 256:at + 256 + 4 * n].view(torch.int32).tolist())
+
+
+def sampled_elements(R, G, dtype):
+    """Which weights of a whole-column unit of more than 32768 the selection samples: 64-byte segments, a power of two of them,
+    of evenly spread rows, one after the other along the columns."""
+    seg = min(64 // (2 if dtype == torch.bfloat16 else 4), G & -G)
+    n_seg = 32768 // seg
+    hit = torch.zeros(R, G, dtype=torch.bool)
+    for i in range(n_seg):
+        at = i % (G // seg) * seg
+        hit[(i * R + R // 2) // n_seg, at:at + seg] = True
+    assert int(hit.sum()) == 32768
+    return hit.to(DEV)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_select_and_encode_where_the_sample_misleads(windq, dtype):
-    """The protected weights in rows that no evenly spread sample of that size meets, in every second chunk: the count of the
-    pass over W refutes the bracket and those units are selected the long way (their ties too), the others from
-    their lists; one tile then holds more protected weights than its part of the collection area."""
+    """Large weights only where the sample does not look, only where it does, and equal ones where it does not: the count of the
+    pass over W refutes the bracket of those units, they are selected the long way (their ties too), the others
+    from their lists; one tile then holds more protected weights than its part of the collection area."""
     R, C, G, ppm = 4096, 512, 128, 15000
     W = synth.weights_llm(R, C, seed=79, device=DEV, dtype=dtype)
-    W[129:200, :128] *= 64                        # a solid run of rows: at most 5 of the sample's 256
-    W[1000:1064, 256:384] = 3.0                   # and one of equal weights
+    hit = sampled_elements(R, G, dtype)
+    n_p = windq.windq_n_protected(R * G, ppm)
+    unseen = (~hit[:2000].any(1)).nonzero().squeeze(1)[:70]
+    W[unseen, :128] *= 64                                      # more above the bracket than are to be protected
+    W[:400, 128:256] = torch.where(hit[:400], W[:400, 128:256] * 64, W[:400, 128:256])      # fewer in it
+    assert n_p < 70 * 128 and int(hit[:400].sum()) < n_p
+    W[unseen, 384:512] = 3.0                                   # more equal ones above it
     s = torch.ones(C, device=DEV)
+    assert flagged_units(windq, W, s, G, 0, ppm) == [0, 1, 3]
     mask, keep = check_select(windq, W, s, G, 0, ppm)
     check_encode(windq, W, s, G, 0, ppm, mask, keep)
+
+
+@pytest.mark.parametrize("R,C,G,unit_rows,dtype,spread", [
+    (1024, 512, 64, 128, torch.bfloat16, 0.0), (1024, 512, 64, 128, torch.float32, 0.8),        # 8192 weights a unit: the smallest lists
+    (1024, 512, 128, 256, torch.bfloat16, 0.8), (1028, 512, 128, 257, torch.bfloat16, 0.8),     # 32768, sampled whole, and one row more
+    (4096, 512, 128, 0, torch.bfloat16, 0.0), (4096, 512, 128, 0, torch.float32, 0.5), (4096, 512, 128, 0, torch.bfloat16, 0.8),
+    (1000, 960, 96, 0, torch.bfloat16, 0.8), (600, 512, 512, 0, torch.bfloat16, 0.3), (9000, 40, 40, 0, torch.float32, 0.3)])
+def test_ordinary_weights_are_selected_from_the_list(windq, R, C, G, unit_rows, dtype, spread):
+    """Weights of the usual kind, rows of one norm or of log-normal norms, at rates from 0.5 to 30 %: no unit needs the digit
+    passes; small units hold the same set as the oracle finds."""
+    W = synth.weights_llm(R, C, seed=80, device=DEV, dtype=torch.float32)
+    W = (W * torch.exp(spread * torch.randn(R, 1, generator=torch.Generator().manual_seed(8))).to(DEV)).to(dtype)
+    s = torch.exp(torch.randn(C, generator=torch.Generator().manual_seed(9))).to(DEV)
+    for ppm in (5000, 30000, 50000, 100000) + ((300000,) if spread < 0.5 else ()):
+        assert flagged_units(windq, W, s, G, unit_rows, ppm) == []
+    check_select(windq, W, s, G, unit_rows, 50000)
 
 
 def test_select_routes_agree(windq):
