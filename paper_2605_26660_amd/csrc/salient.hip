@@ -134,17 +134,22 @@ __device__ __forceinline__ void unpack8raw(const Raw8<DT>& r, float (&w)[8]) {
     }
 }
 
-// Weight j (0..7, a run-time index) of the eight.
-template <int DT>
+// Register 0..3 by a run-time index.  By value: picked through a reference, weights lay in scratch (144 bytes a lane).
+__device__ __forceinline__ uint32_t pick4(uint32_t x, uint32_t y, uint32_t z, uint32_t w, int d) {
+    const uint32_t lower = (d & 1) != 0 ? y : x, upper = (d & 1) != 0 ? w : z;
+    return (d & 2) != 0 ? upper : lower;
+}
+// Weight j (0..7, a run-time index) of the eight.  CHAIN (bf16): compares one after the other; the tree has fewer steps, but
+// encode takes 163 us with it and 147 so (7B-shaped block, 3 %).
+template <int DT, bool CHAIN>
 __device__ __forceinline__ float raw_elem(const Raw8<DT>& r, int j) {
     if constexpr (DT == WINDQ_BF16) {
         const int d = j >> 1;
-        const uint32_t dw = d == 0 ? r.a.x : (d == 1 ? r.a.y : (d == 2 ? r.a.z : r.a.w));
+        const uint32_t dw = CHAIN ? (d == 0 ? r.a.x : (d == 1 ? r.a.y : (d == 2 ? r.a.z : r.a.w))) : pick4(r.a.x, r.a.y, r.a.z, r.a.w, d);
         return __uint_as_float((j & 1) != 0 ? dw & 0xffff0000u : dw << 16);
     } else {
-        const int d = j & 3;
-        const uint4& q = j < 4 ? r.a : r.b;
-        return __uint_as_float(d == 0 ? q.x : (d == 1 ? q.y : (d == 2 ? q.z : q.w)));
+        const uint32_t lower = pick4(r.a.x, r.a.y, r.a.z, r.a.w, j), upper = pick4(r.b.x, r.b.y, r.b.z, r.b.w, j);
+        return __uint_as_float(j < 4 ? lower : upper);
     }
 }
 
@@ -635,7 +640,7 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B)
                 uint32_t at = atomicAdd(&n_buf, (uint32_t)__builtin_popcount(in));
                 for (uint32_t m = in; m != 0u; m &= m - 1u, ++at) {        // usually one bit
                     const int j = __ffs(m) - 1;
-                    const uint2 e = make_uint2(sal_key(raw_elem<DT>(raw[k], j), scol[pk[k] * 8 + j]), pos0 + (uint32_t)j);
+                    const uint2 e = make_uint2(sal_key(raw_elem<DT, false>(raw[k], j), scol[pk[k] * 8 + j]), pos0 + (uint32_t)j);
                     above |= (e.x >= mid ? 1u : 0u) << j;
                     if (at < SAL_CAND_BUF) {
                         buf[at] = e;
@@ -864,7 +869,7 @@ __device__ __forceinline__ uint32_t for_protected(const SalArgs& A, const TileCo
                 uint32_t at = before + (uint32_t)((excl >> (16 * k)) & 0xffffu);
                 for (uint32_t b = m[h + k]; b != 0u; b &= b - 1u) {
                     const int j = __ffs(b) - 1;
-                    f(at++, pk[h + k] * 8 + j, raw_elem<DT>(raw[h + k], j));
+                    f(at++, pk[h + k] * 8 + j, raw_elem<DT, true>(raw[h + k], j));
                 }
                 before += (uint32_t)((tot >> (16 * k)) & 0xffffu);
             }
