@@ -74,6 +74,7 @@ struct SalBatch {
     int64_t tile_start[WINDQ_MAX_BATCH + 1];
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     int64_t band_start[WINDQ_MAX_BATCH + 1];     // workgroups of the candidate pass
+    int32_t cand_tiles;         // tiles that one of them takes
     SalArgs m[WINDQ_MAX_BATCH];
 };
 
@@ -569,7 +570,10 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
 // into the workgroup's LDS in any order (the list has none), and are moved to the unit's list with ONE global atomic at
 // the end.  (With a scan, a global atomic and two barriers per 64-row tile the pass took 157 us per 7B-shaped block.)
 constexpr int SAL_CAND_ITERS = 4;       // pieces of 8 weights that a thread has in flight: more take registers from the other wavefronts
-constexpr int SAL_CAND_TILES = 4;       // tiles per workgroup
+// Tiles per workgroup: fewer than four where that leaves less than two workgroups per CU (512 x 512 fp32 at chunk 64, whole
+// columns: the selection takes 26.4 us, 29.1 in the 16 workgroups of four tiles)
+constexpr int SAL_CAND_TILES = 4;
+constexpr int64_t SAL_CAND_WGS = 512;
 constexpr uint32_t SAL_CAND_BUF = 2048; // candidates the LDS holds; beyond that they go straight to the list
 // FIXED: a thread's pieces all lie in the same columns (the pieces of a row divide the workgroup), its scales stay in registers
 template <int DT, bool FIXED>
@@ -582,14 +586,15 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B)
     const SalArgs& A = B.m[mi];
     // chunks side by side, then row ranges, then row blocks
     const uint32_t idx = (uint32_t)((int64_t)blockIdx.x - B.band_start[mi]), nc = (uint32_t)A.g.n_chunks;
-    const uint32_t ranges = (uint32_t)((A.g.tiles_per_unit + SAL_CAND_TILES - 1) / SAL_CAND_TILES);
+    const uint32_t ranges = ((uint32_t)A.g.tiles_per_unit + (uint32_t)B.cand_tiles - 1u) / (uint32_t)B.cand_tiles;
     const uint32_t band = idx / nc, j0 = idx - band * nc;
     const uint32_t rb = band / ranges, rr = band - rb * ranges;
     const int64_t u = (int64_t)rb * nc + j0;
     if (A.flag[u] != 0u) return;
-    const int64_t lrow0 = (int64_t)rr * (SAL_CAND_TILES * TILE_ROWS), row0 = (int64_t)rb * A.g.R_u + lrow0;
+    const int32_t most = B.cand_tiles * TILE_ROWS;
+    const int64_t lrow0 = (int64_t)rr * most, row0 = (int64_t)rb * A.g.R_u + lrow0;
     const int64_t left = A.g.R_u - lrow0;
-    const int32_t nrows = left < SAL_CAND_TILES * TILE_ROWS ? (int32_t)left : SAL_CAND_TILES * TILE_ROWS;
+    const int32_t nrows = left < most ? (int32_t)left : most;
     const int32_t G = A.g.chunk_w;
     const int64_t col0 = (int64_t)j0 * G;
     const int32_t pieces = G >> 3;
@@ -1107,20 +1112,24 @@ static int salient_common(const windq_mat* W, const float* s, int32_t chunk_w, i
 
 // Numbers the tiles and units of the first B->n matrices.
 static int salient_number(SalBatch* B) {
-    int64_t tiles = 0, units = 0, bands = 0;
-    for (int32_t i = 0; i < B->n; ++i) {
+    int64_t tiles = 0, units = 0, bands;
+    for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) {
         B->tile_start[i] = tiles;
         B->unit_start[i] = units;
-        B->band_start[i] = bands;
-        bands += B->m[i].g.U * ((B->m[i].g.tiles_per_unit + SAL_CAND_TILES - 1) / SAL_CAND_TILES);
-        tiles += B->m[i].g.n_tiles;
-        units += B->m[i].g.U;
+        if (i < B->n) {
+            tiles += B->m[i].g.n_tiles;
+            units += B->m[i].g.U;
+        }
     }
-    for (int32_t i = B->n; i <= WINDQ_MAX_BATCH; ++i) {
-        B->tile_start[i] = tiles;
-        B->unit_start[i] = units;
-        B->band_start[i] = bands;
-    }
+    B->cand_tiles = 2 * SAL_CAND_TILES;
+    do {
+        B->cand_tiles /= 2;
+        bands = 0;
+        for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) {
+            B->band_start[i] = bands;
+            if (i < B->n) bands += B->m[i].g.U * ((B->m[i].g.tiles_per_unit + B->cand_tiles - 1) / B->cand_tiles);
+        }
+    } while (B->cand_tiles > 1 && bands < SAL_CAND_WGS);
     for (int32_t i = B->n; i < WINDQ_MAX_BATCH; ++i) B->m[i] = B->m[0];
     B->any_flagged = B->m[0].n_flagged + 1;       // in the 256 bytes of the first matrix's own count
     return tiles > (int64_t)0x7fffffff ? WINDQ_ESHAPE : WINDQ_OK;
