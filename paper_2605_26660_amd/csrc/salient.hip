@@ -173,27 +173,47 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* sh) {
 }
 
 // ------------------------------------------------------- selection by digit passes over W
-// What the histograms of the first `levels` digits say about a flagged unit: the threshold's digits so far, and the
+// What the histograms of the digits so far say about a flagged unit: the threshold's digits, and the
 // 1-based ascending rank still to find among the keys that carry them.  After the last digit the prefix is the
 // threshold T, every key of the bin equals T, and the rank left over, r, says that the wanted key is
 // the r-th of those e ties in ascending order: r - 1 of them count among the kept weights and
-// e - r + 1 among the protected ones.  Every workgroup of a pass works this out for itself.
+// e - r + 1 among the protected ones.
 struct SalFound {
     uint32_t prefix, rank, in_bin;
 };
-__device__ __forceinline__ SalFound sal_find(const SalArgs& A, int64_t u, int levels, uint32_t* sh_part, uint32_t* sh_out) {
+// The step from digit `step` - 1 to `step` (1 to 3; 0: nothing is known yet), by every workgroup that comes to a unit in the pass
+// after that digit's histogram; the one with the unit's first tile keeps it for the next pass (`keep`), in the words of the
+// bracket or, so that nothing is written that another workgroup of the pass still reads, of the unit's counts.
+__device__ __forceinline__ SalFound sal_step(const SalArgs& A, int64_t u, int step, bool keep, uint32_t* sh_part, uint32_t* sh_out) {
     SalFound f = {0u, A.rank0, 0u};
-    for (int level = 0; level < levels; ++level) {
-        const uint32_t* h = A.hist + ((size_t)level * (size_t)A.g.U + (size_t)u) * FEAT_BINS;
-        uint32_t bin;
-        uint64_t below;
-        __syncthreads();
-        select_bin<SAL_THREADS>(h, 1 << sal_bits(level), f.rank, sh_part, sh_out, &bin, &below);
-        f.rank -= (uint32_t)below;
-        f.prefix = (f.prefix << sal_bits(level)) | bin;
-        f.in_bin = h[bin];
+    if (step == 0) return f;
+    if (step == 2) f = {A.lo[u], A.hi[u], 0u};
+    if (step == 3) f = {(uint32_t)A.count[u], (uint32_t)(A.count[u] >> 32), 0u};
+    const uint32_t* h = A.hist + ((size_t)(step - 1) * (size_t)A.g.U + (size_t)u) * FEAT_BINS;
+    uint32_t bin;
+    uint64_t below;
+    __syncthreads();
+    select_bin<SAL_THREADS>(h, 1 << sal_bits(step - 1), f.rank, sh_part, sh_out, &bin, &below);
+    f.rank -= (uint32_t)below;
+    f.prefix = (f.prefix << sal_bits(step - 1)) | bin;
+    f.in_bin = h[bin];
+    if (keep && threadIdx.x == 0) {
+        if (step == 2) {
+            A.count[u] = ((uint64_t)f.rank << 32) | f.prefix;
+        } else {
+            A.lo[u] = f.prefix;
+            A.hi[u] = f.rank;
+            A.mid[u] = f.in_bin;
+        }
     }
     return f;
+}
+
+// The histogram of the next digit is emptied while the one before it is filled (by the workgroup with the unit's first tile).
+template <int NT>
+__device__ __forceinline__ void sal_clear_hist(const SalArgs& A, int64_t u, int level) {
+    uint4* __restrict__ h = reinterpret_cast<uint4*>(A.hist + ((size_t)level * (size_t)A.g.U + (size_t)u) * FEAT_BINS);
+    for (int32_t i = threadIdx.x; i < FEAT_BINS / 4; i += NT) h[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Histogram of digit `level` of the keys of one tile that carry the unit's prefix.
@@ -338,7 +358,7 @@ __device__ __forceinline__ void sal_mask_tile(const SalArgs& A, const TileCoord&
 // The digits, the tie counts and the masks of the units that do not select from a list: a
 // fixed grid walks the tiles of the listed ("flagged") units of every matrix of the launch; with
 // none flagged it returns at once.
-constexpr int SAL_FLAGGED_GRID = 512;
+constexpr int SAL_FLAGGED_GRID = 1024;
 constexpr int SAL_WHAT_HIST = 0, SAL_WHAT_COUNT = 1, SAL_WHAT_MASK = 2;
 template <int DT, int WHAT>
 __global__ __launch_bounds__(SAL_THREADS) void sal_flagged_kernel(const SalBatch B, const int level) {
@@ -348,11 +368,20 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_flagged_kernel(const SalBatch
     __shared__ uint32_t sh[SAL_THREADS / 64], sh_part[SAL_THREADS / 64], sh_out[2];
     for (int mi = 0; mi < B.n; ++mi) {
         const SalArgs& A = B.m[mi];
-        const int64_t items = (int64_t)*A.n_flagged * A.g.tiles_per_unit;
-        for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        // a run of tiles to each workgroup, so that it comes to few units
+        const int64_t items = (int64_t)*A.n_flagged * A.g.tiles_per_unit, run = (items + gridDim.x - 1) / gridDim.x;
+        const int64_t last = (blockIdx.x + 1) * run < items ? (blockIdx.x + 1) * run : items;
+        SalFound found = {0u, 0u, 0u};
+        int64_t unit = -1;
+        for (int64_t it = blockIdx.x * run; it < last; ++it) {
             const int64_t f = it / A.g.tiles_per_unit;
             const TileCoord tc = tile_coord_of_unit(A.g, (int64_t)A.flagged[f], it - f * A.g.tiles_per_unit);
-            const SalFound found = sal_find(A, tc.u, WHAT == SAL_WHAT_HIST ? level : 3, sh_part, sh_out);
+            if (tc.u != unit) {
+                unit = tc.u;
+                if (WHAT == SAL_WHAT_MASK) found = {A.lo[unit], A.hi[unit], A.mid[unit]};
+                else found = sal_step(A, unit, WHAT == SAL_WHAT_HIST ? level : 3, tc.t == 0, sh_part, sh_out);
+            }
+            if (WHAT == SAL_WHAT_HIST && level < 2 && tc.t == 0) sal_clear_hist<SAL_THREADS>(A, unit, level + 1);
             __syncthreads();        // the previous tile's shared state is no longer read
             if (WHAT == SAL_WHAT_HIST) sal_hist_tile<DT>(A, tc, level, found.prefix, lhist, scol);
             else if (WHAT == SAL_WHAT_COUNT) sal_count_tile<DT>(A, tc, found, scol, sh);
@@ -507,12 +536,13 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
     if (wave < 3) find();
     __syncthreads();
     if (!whole) {
-        // how far the number of keys from the middle bin upwards deviates: by the four segments that a thread's pieces belong to,
-        // which are of the same columns, or nearly (n_pos divides the distance between them where it is a power of two)
+        // how far the number of keys from the middle bin upwards deviates: by two of the four segments that a thread's pieces
+        // belong to, which are of the same columns, or nearly (n_pos divides the distance between them where it is a power of two)
+        constexpr int K = 2;
         const uint32_t from = __builtin_amdgcn_readfirstlane(sh_bin[2] << 20);
         uint32_t sum = 0u, sq = 0u;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
+        for (int k = 0; k < K; ++k) {
             uint32_t bits = 0u;
 #pragma unroll
             for (int j = 0; j < 8; ++j) push_ge(bits, key[k][j], from);
@@ -521,12 +551,12 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
             sum += c;
             sq += c * c;
         }
-        uint32_t dev = (threadIdx.x & ((1u << seg_log) - 1u)) == 0u ? PER * sq - sum * sum : 0u;
+        uint32_t dev = (threadIdx.x & ((1u << seg_log) - 1u)) == 0u ? K * sq - sum * sum : 0u;
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) dev += __shfl_xor(dev, m, 64);
         if ((threadIdx.x & 63) == 0) atomicAdd(&sh_dev, dev);
         __syncthreads();
-        const float seen = (float)sh_dev / (PER - 1);
+        const float seen = (float)sh_dev * PER / (K * (K - 1));
         if (seen > 1.2f * var) {                           // the same for all threads
             d = fminf(SAL_MARGIN * sqrtf(seen * (1.0f - f)) + 2.0f, most);
             if (wave < 2) find();
@@ -554,34 +584,40 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
     }
     __syncthreads();
     if (wave < 3) {
-        uint32_t q = (bin - first) << 4, lower;
+        uint32_t q = (bin - first) << 4, lower = 0u;
         if (narrow) wave_select_bin(lh, FEAT_BINS, rank - below0, &q, &lower);
         const uint32_t start = ((first << 4) + q) << 16;                                  // of the 128th of an octave that holds the rank
         if ((threadIdx.x & 63) == 0) {
             if (wave == 0) A.lo[u] = open ? 0u : start;
             else if (wave == 1) A.hi[u] = open ? 0x80000000u : start + (narrow ? 0x10000u : 0x100000u);      // above every key where open
             else A.mid[u] = start;
+            sh_below[wave] = open ? (wave == 0 ? 0u : ns) : below0 + lower + (wave == 1 && narrow ? lh[q] : 0u);       // keys below the end
         }
     }
+    __syncthreads();
+    // a bracket that holds clearly more of the sample than the list does of the unit (many equal keys): not tried
+    if (threadIdx.x == 0 && narrow && (float)(sh_below[1] - sh_below[0]) > 1.25f * (float)A.cap * f) A.flag[u] = 1u;
 }
 
 // The pass over W: the mask (inside the bracket as if T were `mid`), the counts, the list.  Bound by HBM: per weight one multiply and two
 // pushes of a bit.  A workgroup takes 256 rows of a unit and no wavefront waits for another in its loop: candidates go
 // into the workgroup's LDS in any order (the list has none), and are moved to the unit's list with ONE global atomic at
-// the end.  (With a scan, a global atomic and two barriers per 64-row tile the pass took 157 us per 7B-shaped block.)
+// the end.  (With a scan, a global atomic and two barriers per 64-row tile the pass took 157 us per 7B-shaped block.)  A workgroup
+// takes at most 32768 weights, and so has room for twice the share of them that the unit's list holds: one that needs more flags
+// its unit for the digit passes and stops.  (Past the buffer with an atomic per weight, 4096 x 4096 of equal weights took 1.7 ms.)
 constexpr int SAL_CAND_ITERS = 4;       // pieces of 8 weights that a thread has in flight: more take registers from the other wavefronts
 // Tiles per workgroup: fewer than four where that leaves less than two workgroups per CU (512 x 512 fp32 at chunk 64, whole
 // columns: the selection takes 26.4 us, 29.1 in the 16 workgroups of four tiles)
 constexpr int SAL_CAND_TILES = 4;
 constexpr int64_t SAL_CAND_WGS = 512;
-constexpr uint32_t SAL_CAND_BUF = 2048; // candidates the LDS holds; beyond that they go straight to the list
+constexpr uint32_t SAL_CAND_BUF = 2048; // candidates the LDS holds
 // FIXED: a thread's pieces all lie in the same columns (the pieces of a row divide the workgroup), its scales stay in registers
 template <int DT, bool FIXED>
 __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B) {
     __shared__ __align__(16) float scol[WINDQ_MAX_CHUNK];
     __shared__ uint2 buf[SAL_CAND_BUF];
     __shared__ uint32_t sh[SAL_THREADS / 64];
-    __shared__ uint32_t n_buf, base;
+    __shared__ uint32_t n_buf, base, skip, full;
     const int mi = batch_index(B.band_start, B.n, blockIdx.x);
     const SalArgs& A = B.m[mi];
     // chunks side by side, then row ranges, then row blocks
@@ -590,7 +626,6 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B)
     const uint32_t band = idx / nc, j0 = idx - band * nc;
     const uint32_t rb = band / ranges, rr = band - rb * ranges;
     const int64_t u = (int64_t)rb * nc + j0;
-    if (A.flag[u] != 0u) return;
     const int32_t most = B.cand_tiles * TILE_ROWS;
     const int64_t lrow0 = (int64_t)rr * most, row0 = (int64_t)rb * A.g.R_u + lrow0;
     const int64_t left = A.g.R_u - lrow0;
@@ -599,12 +634,18 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B)
     const int64_t col0 = (int64_t)j0 * G;
     const int32_t pieces = G >> 3;
     for (int32_t c = threadIdx.x; c < G; c += SAL_THREADS) scol[c] = A.s[col0 + c];
-    if (threadIdx.x == 0) n_buf = 0u;
+    if (threadIdx.x == 0) {
+        n_buf = 0u;
+        skip = A.flag[u];
+        full = 0u;
+    }
     const uint32_t lo = A.lo[u], hi = A.hi[u], mid = A.mid[u];
     uint2* __restrict__ list = A.cand + (size_t)u * (size_t)A.cap;
     const int32_t total = nrows * pieces;
     PieceWalk walk((int32_t)threadIdx.x, SAL_THREADS, pieces);
     __syncthreads();
+    if (skip != 0u) return;
+    volatile uint32_t* stop = &full;
     float sc[8];
     if (FIXED) {
 #pragma unroll
@@ -612,7 +653,7 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B)
     }
     constexpr int NB = SAL_CAND_ITERS;
     uint32_t n_above = 0u;
-    for (int32_t i0 = threadIdx.x; i0 < total; i0 += NB * SAL_THREADS) {
+    for (int32_t i0 = threadIdx.x; i0 < total && *stop == 0u; i0 += NB * SAL_THREADS) {
         Raw8<DT> raw[NB];                       // kept as loaded: the keys of a candidate piece are formed again
         int32_t rk[NB], pk[NB];                 // row and piece of each
 #pragma unroll
@@ -647,19 +688,19 @@ __global__ __launch_bounds__(SAL_THREADS) void sal_cand_kernel(const SalBatch B)
                     const int j = __ffs(m) - 1;
                     const uint2 e = make_uint2(sal_key(raw_elem<DT, false>(raw[k], j), scol[pk[k] * 8 + j]), pos0 + (uint32_t)j);
                     above |= (e.x >= mid ? 1u : 0u) << j;
-                    if (at < SAL_CAND_BUF) {
-                        buf[at] = e;
-                    } else {
-                        const uint32_t g = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&A.count[u]), 1ull);
-                        if (g < A.cap) list[g] = e;
-                    }
+                    if (at < SAL_CAND_BUF) buf[at] = e;
+                    else *stop = 1u;
                 }
             }
             A.mask[(row0 + rk[k]) * A.mask_ld + (col0 >> 3) + pk[k]] = (uint8_t)above;
         }
     }
     n_above = block_sum_u32(n_above, sh);       // (and a barrier: the buffer is complete)
-    const uint32_t n = min(n_buf, SAL_CAND_BUF);
+    const uint32_t n = n_buf;
+    if (n > SAL_CAND_BUF) {                     // the same for all threads
+        if (threadIdx.x == 0) A.flag[u] = 1u;
+        return;
+    }
     if (threadIdx.x == 0 && (n | n_above) != 0u)
         base = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&A.count[u]), ((unsigned long long)n_above << 32) | n);
     __syncthreads();
@@ -707,8 +748,9 @@ __device__ __forceinline__ void settle(const SalArgs& A, int64_t rb, int64_t col
 // threshold's bin among 2048 over the bracket's width, by one pass over the list; a second settles the mask bits of the
 // weights outside that bin and gathers the bin's own, a handful, which are ranked one against another (key, then flat
 // position).  A bin of more than SAL_BIN weights (ties) is resolved digit by digit instead: the threshold, then, where
-// ties are split, the last position taken, by three digits of the position.
-constexpr uint32_t SAL_BIN = 1024;
+// ties are split, the last position taken, by three digits of the position (ranking a thousand ties one against another
+// took this kernel 60 to 90 us, digits 12 to 29).
+constexpr uint32_t SAL_BIN = 128;
 __global__ __launch_bounds__(SAL_BIG) void sal_list_kernel(const SalBatch B) {
     __shared__ uint32_t lh[FEAT_BINS];
     __shared__ uint2 own[SAL_BIN];
@@ -721,11 +763,11 @@ __global__ __launch_bounds__(SAL_BIG) void sal_list_kernel(const SalBatch B) {
     const uint64_t count = A.count[u];
     const uint32_t n = (uint32_t)count, above = (uint32_t)(count >> 32);
     if (A.flag[u] != 0u || n > A.cap || above > A.n_p || A.n_p - above > n) {
-        for (int32_t i = threadIdx.x; i < 3 * FEAT_BINS; i += SAL_BIG)
-            A.hist[((size_t)(i / FEAT_BINS) * (size_t)A.g.U + (size_t)u) * FEAT_BINS + (size_t)(i % FEAT_BINS)] = 0u;
+        sal_clear_hist<SAL_BIG>(A, u, 0);
         if (threadIdx.x == 0) {
-            A.flagged[atomicAdd(A.n_flagged, 1u)] = (uint32_t)u;
-            atomicAdd(B.any_flagged, 1u);
+            const uint32_t at = atomicAdd(A.n_flagged, 1u);
+            A.flagged[at] = (uint32_t)u;
+            if (at == 0u) atomicAdd(B.any_flagged, 1u);
         }
         return;
     }
@@ -1121,7 +1163,8 @@ static int salient_number(SalBatch* B) {
             units += B->m[i].g.U;
         }
     }
-    B->cand_tiles = 2 * SAL_CAND_TILES;
+    const int32_t wide = 32768 / (TILE_ROWS * B->m[0].g.chunk_w);
+    B->cand_tiles = 2 * (wide < SAL_CAND_TILES ? wide : SAL_CAND_TILES);
     do {
         B->cand_tiles /= 2;
         bands = 0;

@@ -142,6 +142,21 @@ def test_ordinary_weights_are_selected_from_the_list(windq, R, C, G, unit_rows, 
     check_select(windq, W, s, G, unit_rows, 50000)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("R,C,G,unit_rows", [(2048, 512, 128, 0), (1024, 256, 64, 128), (600, 1024, 512, 0), (130, 96, 32, 65), (640, 192, 96, 0)])
+def test_weights_of_few_values(windq, R, C, G, unit_rows, dtype):
+    """Equal weights, and weights rounded to a grid: lists that overflow before or during the pass over W, ties split in a list (more
+    than are ranked one by one, and fewer) and by digit passes."""
+    W = synth.weights_llm(R, C, seed=81, device=DEV, dtype=torch.float32)
+    ones = torch.ones(C, device=DEV)
+    for Wk in (torch.full_like(W, 0.25), torch.round(W / 0.01) * 0.01, torch.round(W / 0.001) * 0.001):
+        Wk = Wk.to(dtype)
+        for ppm in (5000, 30000, 200000):
+            check_select(windq, Wk, ones, G, unit_rows, ppm)
+    few = torch.full_like(W, 0.25).to(dtype)
+    assert len(flagged_units(windq, few, ones, G, unit_rows, 30000)) == windq.n_units(R, C, G, unit_rows)[0]
+
+
 def test_select_routes_agree(windq):
     """Selection from the units' candidate lists (the usual route) and by digit passes over W (taken when the
     mask cannot be addressed in whole dwords, or a unit's threshold bin outgrows its list) give the same mask."""
