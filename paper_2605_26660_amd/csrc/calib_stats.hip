@@ -4,15 +4,17 @@
 //
 // Pure streaming reduction over the token axis, bound by HBM.  A workgroup owns a strip of
 // 8 L channels (L lanes side by side, 8 channels = 16 or 32 bytes each) and a slab of tokens;
-// its 256 / L lane groups take every (256 / L)-th token, eight loads in flight per lane.
+// its 256 / L lane groups take every (256 / L)-th token, eight (or four) loads in flight per lane.
 // fp64 sums, combined in a fixed order: lane groups through LDS, slabs by the finalize kernel.
 //
-// How a matrix is cut (calib_cut):
+// How a matrix is cut (calib_cut; its own size alone decides, so that a batch gives the bits of single calls):
 //   few tokens (the calibration sets of the benchmark configurations: 512): ONE slab and narrow
 //     strips (L = 8, 64 channels), so that the workgroup writes the result itself: two dependent
-//     launches cost more than a few MB do.  Up to 1024 tokens (1024 x 4096: 6.8 us against 9.9 in
-//     slabs), up to 2048 where 4096 channels give at least 64 strips (2048 x 4096: 10.3 against
-//     12.2 us; 2048 x 1024: 9.6 against 8.5, so not there).
+//     launches cost more than a few MB do.  Always below 2048 tokens, and up to 4096 where a token's bytes are more than
+//     1.5 per token, since then the strips (and the other inputs of a batch) fill enough of the chip.  us, one slab against
+//     several, alone and four in a batch, bf16:
+//       1536 x 1024: 5.3, 6.0 and 5.8, 8.0       2048 x 1024: 6.4, 5.6 and 6.9, 7.9     2048 x 4096: 6.6, 7.5 and 12.2, 16.8
+//       3072 x 2048: 8.4, 7.4 and 11.8, 14.2     4096 x 2048: 10.3, 7.4 and 14.6, 16.9  4096 x 4096: 11.5, 10.5 and 21, 28.5
 //   more: L = 64 (512 channels, a wavefront reads 1 KB of a token; less for narrow matrices) and
 //     as many slabs as give the chip about 1024 workgroups, four for each of its 256 CUs (what
 //     the 33 KB of LDS allow; 2048 measured 14 % slower): more slabs only mean more partial sums
@@ -28,8 +30,9 @@ namespace windq {
 
 constexpr int CALIB_THREADS = 256;
 constexpr int CALIB_CPL = 8;                        // channels per lane
-constexpr int CALIB_INFLIGHT = 8;                   // loads in flight per lane
-constexpr int64_t CALIB_DIRECT_ROWS = 1024, CALIB_DIRECT_ROWS_WIDE = 2048, CALIB_DIRECT_WIDE_COLS = 4096;
+constexpr int CALIB_INFLIGHT = 8;                   // loads in flight per lane; 4 for fp32 inputs in one slab each and 128 workgroups or more,
+constexpr int64_t CALIB_FEWER_WGS = 128;            // whose registers cost more (3072 x 8192: 17.7 us with 8, 16.0 with 4; 1024 x 5120: 5.1, 5.3)
+constexpr int64_t CALIB_DIRECT_ROWS = 2047, CALIB_DIRECT_ROWS_WIDE = 4096;
 constexpr int64_t CALIB_TARGET_WGS = 1024;
 constexpr int64_t CALIB_SLAB_LIMIT_ROWS = 4096;     // above this many tokens the number of 32-token slabs is limited
 
@@ -88,7 +91,7 @@ __device__ __forceinline__ void calib_add(const Raw8<DT>& raw, double (&sa)[CALI
     }
 }
 
-template <int DT, bool RMS>
+template <int DT, bool RMS, int INFLIGHT>      // (INFLIGHT changes no sum: a lane adds its tokens in order)
 __global__ __launch_bounds__(CALIB_THREADS) void calib_sum_kernel(const CalibBatch B) {
     constexpr int NV = RMS ? 2 * CALIB_CPL : CALIB_CPL;
     // [value][thread]; the odd row length spreads the eight values of a lane over the banks
@@ -116,12 +119,12 @@ __global__ __launch_bounds__(CALIB_THREADS) void calib_sum_kernel(const CalibBat
         int64_t r = (int64_t)slab * M.slab_rows + tg;
         // whole batches of loads without a bounds check between them; then the rest, four at a time: a token past
         // the end is read from the slab's last one and added as zeros
-        for (; r + (int64_t)groups * (CALIB_INFLIGHT - 1) < r_end; r += (int64_t)groups * CALIB_INFLIGHT) {
-            Raw8<DT> raw[CALIB_INFLIGHT];
+        for (; r + (int64_t)groups * (INFLIGHT - 1) < r_end; r += (int64_t)groups * INFLIGHT) {
+            Raw8<DT> raw[INFLIGHT];
 #pragma unroll
-            for (int k = 0; k < CALIB_INFLIGHT; ++k) raw[k].load(src + (r + (int64_t)k * groups) * step);
+            for (int k = 0; k < INFLIGHT; ++k) raw[k].load(src + (r + (int64_t)k * groups) * step);
 #pragma unroll
-            for (int k = 0; k < CALIB_INFLIGHT; ++k) calib_add<DT, RMS>(raw[k], sa, sq);
+            for (int k = 0; k < INFLIGHT; ++k) calib_add<DT, RMS>(raw[k], sa, sq);
         }
         for (; r < r_end; r += (int64_t)groups * 4) {
             Raw8<DT> raw[4];
@@ -149,10 +152,15 @@ __global__ __launch_bounds__(CALIB_THREADS) void calib_sum_kernel(const CalibBat
         const int col = q & (L * CALIB_CPL - 1);
         const double* __restrict__ row = red[which * CALIB_CPL + (col & (CALIB_CPL - 1))] + (col >> 3);
         double t = 0.0;
-        for (int g = 0; g < groups; g += 4) {                                 // four reads in flight, added in order
-            const double t0 = row[g << M.lane_shift], t1 = row[(g + 1) << M.lane_shift];
-            const double t2 = row[(g + 2) << M.lane_shift], t3 = row[(g + 3) << M.lane_shift];
-            t = (((t + t0) + t1) + t2) + t3;
+        if (groups == 32) {                                                   // all reads in flight, added in order
+#pragma unroll
+            for (int g = 0; g < 32; ++g) t += row[g << 3];
+        } else {
+            for (int g = 0; g < groups; g += 4) {                             // four
+                const double t0 = row[g << M.lane_shift], t1 = row[(g + 1) << M.lane_shift];
+                const double t2 = row[(g + 2) << M.lane_shift], t3 = row[(g + 3) << M.lane_shift];
+                t = (((t + t0) + t1) + t2) + t3;
+            }
         }
         const int64_t c = strip0 + col;
         if (c >= cols) continue;
@@ -215,8 +223,8 @@ static int calib_check(const windq_mat* X, const float* s_absmean, const void* w
 
 // How a matrix is cut into strips and slabs (the rule and its reasons: top of the file).  A slab has
 // at least 32 tokens: the workspace holds one pair of sums per channel and 32 tokens.
-static void calib_cut(CalibMat* M) {
-    const bool direct = M->rows <= CALIB_DIRECT_ROWS || (M->rows <= CALIB_DIRECT_ROWS_WIDE && M->cols >= CALIB_DIRECT_WIDE_COLS);
+static void calib_cut(CalibMat* M, int elem_bytes) {
+    const bool direct = M->rows <= CALIB_DIRECT_ROWS || (M->rows <= CALIB_DIRECT_ROWS_WIDE && 2 * M->cols * elem_bytes > 3 * M->rows);
     M->lane_shift = direct ? 3 : 6;
     while (M->lane_shift > 3 && (int64_t)(CALIB_CPL << (M->lane_shift - 1)) >= M->cols) --M->lane_shift;
     const int64_t strip = (int64_t)CALIB_CPL << M->lane_shift;
@@ -253,11 +261,14 @@ static int calib_launch(const CalibMat* mats, int32_t n, int32_t dtype, hipStrea
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
     const dim3 grid((unsigned)wgs), block(CALIB_THREADS);
     if (dtype == WINDQ_BF16) {
-        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, true>), grid, block, 0, hs, B);
-        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, false>), grid, block, 0, hs, B);
+        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, true, CALIB_INFLIGHT>), grid, block, 0, hs, B);
+        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_BF16, false, CALIB_INFLIGHT>), grid, block, 0, hs, B);
+    } else if (wgs < CALIB_FEWER_WGS || F.n > 0) {
+        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, true, CALIB_INFLIGHT>), grid, block, 0, hs, B);
+        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, false, CALIB_INFLIGHT>), grid, block, 0, hs, B);
     } else {
-        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, true>), grid, block, 0, hs, B);
-        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, false>), grid, block, 0, hs, B);
+        if (rms) hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, true, 4>), grid, block, 0, hs, B);
+        else hipLaunchKernelGGL((calib_sum_kernel<WINDQ_F32, false, 4>), grid, block, 0, hs, B);
     }
     if (F.n > 0) {
         for (int32_t i = F.n; i <= WINDQ_MAX_BATCH; ++i) F.wg_start[i] = fin;
@@ -298,7 +309,7 @@ extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n,
         M.s_rms = items[i].s_rms;
         M.partial = static_cast<double*>(items[i].ws);
         M.reserved = 0;
-        calib_cut(&M);
+        calib_cut(&M, X->dtype == WINDQ_BF16 ? 2 : 4);
         wgs += (int64_t)M.strips * M.slabs;
     }
     if (wgs > (int64_t)0x7fffffff) return WINDQ_ESHAPE;

@@ -89,7 +89,11 @@ def test_calib_stats(windq, T, C, dtype):
 @pytest.mark.parametrize("T,C,ld,dtype", [(1024, 72, 80, torch.bfloat16), (1025, 72, 72, torch.bfloat16), (1025, 8, 8, torch.float32),
                                           (2048, 4096, 4096, torch.bfloat16), (2049, 4104, 4112, torch.bfloat16),
                                           (1055, 520, 520, torch.float32), (1100, 512, 640, torch.bfloat16),
-                                          (255, 136, 136, torch.float32), (257, 64, 64, torch.bfloat16)])
+                                          (255, 136, 136, torch.float32), (257, 64, 64, torch.bfloat16),
+                                          (2047, 72, 80, torch.bfloat16), (2048, 1536, 1536, torch.bfloat16),      # one slab, several
+                                          (2048, 1544, 1544, torch.bfloat16), (2048, 776, 776, torch.float32),     # one
+                                          (4096, 3080, 3080, torch.bfloat16), (4097, 3080, 3080, torch.bfloat16),  # one, several
+                                          (33, 8128, 8128, torch.float32), (33, 8136, 8136, torch.float32)])       # 127 and 128 workgroups
 def test_calib_stats_at_the_edges_of_its_cuts(windq, T, C, ld, dtype):
     """One slab or many, whole and partial load batches, narrow and partial strips; fp64 sums, so what is left is the
     rounding of the fp32 output: 2^-24 and a little."""
