@@ -107,6 +107,11 @@ __device__ __forceinline__ TileCoord tile_coord_of_unit(const Geometry& g, int64
     return tc;
 }
 
+// Does a plan entry's payload lie in the code stream?  An entry that does not counts as skip: `base` may be any number.
+__device__ __forceinline__ bool payload_fits(int64_t base, int64_t bytes, int64_t codes_bytes) {
+    return !(base < 0 || (base & 15) != 0 || (uint64_t)base + (uint64_t)bytes > (uint64_t)codes_bytes);      // (two numbers below 2^63)
+}
+
 template <int DT>
 struct Elem {
     static constexpr int bytes = DT == WINDQ_BF16 ? 2 : 4;

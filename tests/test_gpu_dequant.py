@@ -146,6 +146,30 @@ def test_malformed_entries_read_nothing(windq):
     assert float(err[0]) == 0.0 and torch.equal(w_hat, W.float())
 
 
+def test_offsets_near_the_end_of_int64_are_skipped_everywhere(windq):
+    """An offset whose payload would end past 2^63 - 1 counts as skip in every call that takes a plan."""
+    for R in (64, 3000):                                      # (either kernel of the product)
+        W = synth.weights_llm(R, 1024, seed=108, device=DEV)
+        s = torch.ones(1024, device=DEV)
+        action = torch.tensor([1, 2, 3, 4, 5, 6, 4, 1], dtype=torch.uint8)
+        off = windq.windq_plan_layout(action, R, 128)
+        codes = torch.zeros(int(off[-1]), dtype=torch.uint8, device=DEV)
+        far = torch.cat([torch.full((8,), 2 ** 63 - 16, dtype=torch.int64), off[-1:]]).to(DEV)
+        a = action.to(DEV)
+        _, scale, offset = windq.windq_apply_plan(W, 128, 0, a, None, None, far, codes=codes)
+        assert int(codes.max()) == 0 and float(scale.abs().max()) == 0.0
+        _, scale, offset, err = windq.windq_refine_plan(W, s, 128, 0, a, None, None, far, 2, codes=codes)
+        assert int(codes.max()) == 0 and float(scale.abs().max()) == 0.0 and float(err.max()) == 0.0
+        err, w_hat = windq.windq_dequant_plan(W, s, 128, 0, a, far, codes, scale, offset)
+        assert float(err.max()) == 0.0 and torch.equal(w_hat, W.float())
+        x = torch.ones(1024, device=DEV)
+        mask = torch.zeros(R, 128, dtype=torch.uint8, device=DEV)
+        want = W.double().sum(1)
+        for m in (None, mask):
+            y = windq.windq_dequant_gemv(W, 128, 0, a, far, codes, scale, offset, x, mask=m)
+            assert bool(((y.double() - want).abs() <= 1e-6 * W.double().abs().sum(1)).all())
+
+
 # ------------------------------------------------------- the product from the artefact
 def gemv_case(windq, W, s, G, unit_rows, K, ppm=0):
     cg = synth.clip_grid(K)
