@@ -94,6 +94,7 @@ typedef struct windq_mat {
  *   s_rms[c]     = sqrt(mean_t x_tc^2)    (optional, may be NULL; its square is the
  *                                          diagonal of X^T X / tokens)
  * Sums are accumulated in fp64 in a fixed order (bit-reproducible run to run).
+ * At most 2 097 120 tokens (65535 x 32; WINDQ_ESHAPE beyond): a caller combines longer sets from parts.
  */
 int windq_calib_stats(const windq_mat* X, float* s_absmean /*[cols]*/, float* s_rms /*[cols] or NULL*/,
                       void* ws, size_t ws_bytes, void* stream);

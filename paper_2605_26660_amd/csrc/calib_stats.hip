@@ -34,7 +34,7 @@ constexpr int CALIB_INFLIGHT = 8;                   // loads in flight per lane;
 constexpr int64_t CALIB_FEWER_WGS = 128;            // whose registers cost more (3072 x 8192: 17.7 us with 8, 16.0 with 4; 1024 x 5120: 5.1, 5.3)
 constexpr int64_t CALIB_DIRECT_ROWS = 2047, CALIB_DIRECT_ROWS_WIDE = 4096;
 constexpr int64_t CALIB_TARGET_WGS = 1024;
-constexpr int64_t CALIB_SLAB_LIMIT_ROWS = 4096;     // above this many tokens the number of 32-token slabs is limited
+constexpr int64_t CALIB_MAX_SLABS = 65535;          // of 32 tokens: the interface's limit on one input (no kernel here needs it)
 
 // One activation matrix of a launch; a launch covers up to WINDQ_MAX_BATCH of them, their
 // workgroups (and the finalize kernel's) numbered one matrix after the other.
@@ -217,7 +217,7 @@ static int calib_check(const windq_mat* X, const float* s_absmean, const void* w
     if (s_absmean == nullptr) return WINDQ_EINVAL;
     const size_t need = calib_ws_bytes(X->rows, X->cols);
     if (ws == nullptr || ws_bytes < need || !aligned(ws, 256)) return WINDQ_EWORKSPACE;
-    if (X->rows > CALIB_SLAB_LIMIT_ROWS && calib_slabs(X->rows) > 65535) return WINDQ_ESHAPE;
+    if (calib_slabs(X->rows) > CALIB_MAX_SLABS) return WINDQ_ESHAPE;
     return WINDQ_OK;
 }
 

@@ -146,6 +146,8 @@ def test_argument_validation_happens_before_any_launch(windq):
     assert lib.windq_calib_stats(br(m), None, None, P, 1 << 30, None) == windq.WINDQ_EINVAL
     assert lib.windq_calib_stats(br(m), P, None, None, 0, None) == windq.WINDQ_EWORKSPACE
     assert lib.windq_calib_stats(None, P, None, P, 1 << 30, None) == windq.WINDQ_EINVAL
+    long = _mat(windq, rows=65535 * 32 + 1)                               # one token above the limit
+    assert lib.windq_calib_stats(br(long), P, None, P, 1 << 40, None) == windq.WINDQ_ESHAPE
     assert lib.windq_unit_features(br(m), None, 64, 0, P, P, 1 << 30, None) == windq.WINDQ_EINVAL
     assert lib.windq_unit_features(br(m), P, 64, 0, P, P, 16, None) == windq.WINDQ_EWORKSPACE
     assert lib.windq_unit_features(br(m), P, 60, 0, P, P, 1 << 30, None) == windq.WINDQ_ESHAPE
