@@ -72,7 +72,7 @@ __global__ __launch_bounds__(AP_THREADS) void apply_plan_kernel(const ApplyBatch
     const int64_t base = A.code_off[tc.u];
     const int64_t payload = bpg * A.g.R_u;
     const int64_t padded = (payload + 15) & ~(int64_t)15;
-    if (!payload_fits(base, padded, A.codes_bytes)) a = 0;
+    if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - padded) a = 0;     // (base + padded could pass 2^63)
     if (a == 0) {
         if (valid) {
             A.scale[gidx] = 0.0f;
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(APS_THREADS, MASKED ? 6 : 7) void apply_plan_split_
     const int64_t base = A.code_off[tc.u];
     const int64_t payload = bpg * A.g.R_u;
     const int64_t padded = (payload + 15) & ~(int64_t)15;
-    if (!payload_fits(base, padded, A.codes_bytes)) a = 0;
+    if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - padded) a = 0;     // (base + padded could pass 2^63)
     if (a == 0) {
         if (threadIdx.x < tc.nrows) {
             const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + threadIdx.x;

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(DQ_THREADS) void dequant_split_kernel(const Dequant
     if (a >= WINDQ_N_ACTIONS) a = 0;
     const int64_t bpg = dq_bytes_per_group(a, G);
     const int64_t base = A.code_off[tc.u];
-    if (!payload_fits(base, bpg * A.g.R_u, A.codes_bytes)) a = 0;   // a malformed entry reads nothing
+    if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - bpg * A.g.R_u) a = 0;   // a malformed entry reads nothing; base + bytes could pass 2^63
     const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : (a == 4 ? 2 : 1)));
 
     double ac[8];
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(DQ_THREADS) void dequant_any_kernel(const DequantBa
     if (a >= WINDQ_N_ACTIONS) a = 0;
     const int64_t bpg = dq_bytes_per_group(a, G);
     const int64_t base = A.code_off[tc.u];
-    if (!payload_fits(base, bpg * A.g.R_u, A.codes_bytes)) a = 0;   // a malformed entry reads nothing
+    if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - bpg * A.g.R_u) a = 0;   // a malformed entry reads nothing; base + bytes could pass 2^63
     if (a == 5) {
         fill_trits(trits_of);
         __syncthreads();
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_kernel(cons
     if (part != 0u) {
         int act = a < WINDQ_N_ACTIONS ? a : 0;
         const int64_t bytes = dq_bytes_per_group(act, G);
-        if (!payload_fits(base, bytes * A.g.R_u, A.codes_bytes)) act = 0;
+        if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - bytes * A.g.R_u) act = 0;
         if (!shared_rows(act)) return;
     }
     const int32_t share = nt >> parts_shift, first = (int32_t)part * share;             // this part's rows
@@ -721,7 +721,7 @@ __global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_kernel(cons
     const bool direct = __syncthreads_or(odd ? 1 : 0) != 0 || MASKED;
     if (a >= WINDQ_N_ACTIONS) a = 0;
     const int64_t bpg = dq_bytes_per_group(a, G);
-    if (!payload_fits(base, bpg * A.g.R_u, A.codes_bytes)) a = 0;   // a malformed entry reads nothing
+    if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - bpg * A.g.R_u) a = 0;   // a malformed entry reads nothing; base + bytes could pass 2^63
     double* __restrict__ out = A.gpart + (int64_t)j * A.g.rows + row0;
 
     if (a == 0) {
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(GEMV_THREADS) void gemv_split_kernel(const DequantB
     if (a >= WINDQ_N_ACTIONS) a = 0;
     const int64_t bpg = dq_bytes_per_group(a, G);
     const int64_t base = A.code_off[tc.u];
-    if (!payload_fits(base, bpg * A.g.R_u, A.codes_bytes)) a = 0;   // a malformed entry reads nothing
+    if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - bpg * A.g.R_u) a = 0;   // a malformed entry reads nothing; base + bytes could pass 2^63
     const int bits = a == 1 ? 8 : (a == 2 ? 4 : (a == 3 ? 3 : (a == 4 ? 2 : 1)));
     float xv[8];
 #pragma unroll

@@ -107,11 +107,6 @@ __device__ __forceinline__ TileCoord tile_coord_of_unit(const Geometry& g, int64
     return tc;
 }
 
-// Does a plan entry's payload lie in the code stream?  An entry that does not counts as skip: `base` may be any number.
-__device__ __forceinline__ bool payload_fits(int64_t base, int64_t bytes, int64_t codes_bytes) {
-    return !(base < 0 || (base & 15) != 0 || (uint64_t)base + (uint64_t)bytes > (uint64_t)codes_bytes);      // (two numbers below 2^63)
-}
-
 template <int DT>
 struct Elem {
     static constexpr int bytes = DT == WINDQ_BF16 ? 2 : 4;
@@ -191,8 +186,8 @@ __device__ __forceinline__ void load_tile_raw(const void* __restrict__ data, int
 }
 
 // Cooperative load of a tile's mask bytes (one per 8 columns and row) into LDS, rows past the
-// unit's end as zeros.  Kernels that give a lane a row read them from there: a byte load from
-// global memory inside a lane's column loop would put a memory latency into every step.
+// unit's end as zeros.  Kernels that give a lane a row (fit_score, refine) read them from there: a byte load
+// from global memory inside a lane's column loop would put a memory latency into every step.
 __device__ __forceinline__ void load_mask_tile(const uint8_t* __restrict__ mask, int64_t mask_ld, const TileCoord& tc,
                                                int32_t chunk_w, uint8_t* __restrict__ mtile) {
     const int32_t mb = chunk_w >> 3;                 // mask bytes per row of the tile
