@@ -400,7 +400,7 @@ int windq_salient_encode(const windq_mat* W, const float* s /*[cols]*/, int32_t 
 /*
  * windq_salient_select / windq_salient_encode for up to WINDQ_MAX_BATCH matrices with one
  * launch per kernel instead of one per kernel and matrix (a decoder block has seven
- * matrices: twelve launches to select, four to encode).  Results are bit-identical to the
+ * matrices: eight launches to select, four to encode).  Results are bit-identical to the
  * per-matrix calls.  One chunk width, unit_rows, rate and element type for all items; every
  * item brings its own workspace (WINDQ_CALL_SALIENT for its shape).  select reads W, s and
  * writes mask; encode reads W, s, mask and writes prot_codes, prot_scale, err_prot (select

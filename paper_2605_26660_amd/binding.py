@@ -228,7 +228,7 @@ def workspace_bytes(call: int, dtype: int, rows: int, cols: int, chunk_w: int = 
 
 def _workspace(call, t, chunk_w, unit_rows, K, ws):
     # a given workspace's size is checked by the call itself: asking the library for it here as well cost a batch of
-    # four small matrices a third of its time
+    # four small matrices a fifth of its time (18.7 us to 15.0)
     if ws is not None:
         return ws
     need = workspace_bytes(call, _dtype_code(t), t.shape[0], t.shape[1], chunk_w, unit_rows, K)

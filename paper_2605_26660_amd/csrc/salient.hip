@@ -4,7 +4,7 @@
 //
 // windq_salient_select  finds the protected set EXACTLY: the saliency threshold T of a
 //   unit is the n_p-th largest key (the bit pattern of the fp32 saliency).  A sample of the
-//   unit's rows brackets T between two keys lo <= T < hi; ONE pass over W then writes every
+//   unit (all of a small one) brackets T between two keys lo <= T < hi; ONE pass over W then writes every
 //   mask bit that the bracket decides (key >= hi: protected, key < lo: not), counts the
 //   first kind and lists the keys in between, about 1 % of the unit, with their positions.
 //   The counts prove the bracket: T lies in it if and only if n_p lies between the number
@@ -19,13 +19,15 @@
 // windq_salient_encode  stores the protected weights: per unit one symmetric scale
 //   sigma = fp32(max|w_p| / 127), codes clamp(rne(w * fp32(1/sigma)), -127, 127) in
 //   flat-index order, and the activation-weighted error of that INT8 part.
-// Everything is integer or fixed-order fp64: bit-reproducible.  Select streams W once and a
-// sixteenth (the units that fall back: four times more, and a fifth for the tiles of those whose
-// ties are split); encode reads of W only the pieces that hold protected weights, once.  Every kernel
+// Everything is integer or fixed-order fp64: bit-reproducible.  Select streams W once, and of
+// each unit a sample of at most 32768 weights (the units that fall back: four times more, and a fifth for the
+// tiles of those whose ties are split); encode reads of W only the pieces that hold protected weights, once (again for
+// tiles that hold more of them than their scratch area).  Every kernel
 // takes a batch of matrices, so a decoder block costs eight launches for select and four for encode.
-// 7B-shaped block at 3 %: select and encode 307 us (586 with two passes over W, a histogram atomic per weight in the
-// first, and two gathers): sample 17, the pass over W 113 (3.6 TB/s; a plain copy moves 5.1), lists 26, five passes that
-// find nothing flagged 23, collect 107, codes 30.
+// 7B-shaped block at 3 %: select and encode 301 us (586 with two passes over W, a histogram atomic per weight in the
+// first, and two gathers).  By a kernel trace, whose times are a few per cent longer: sample 21, the pass over W 103
+// (3.9 TB/s; a plain copy moves 5.1), lists 22, five passes that find nothing flagged 22; collect 108, the units' scales
+// 5, codes 29, errors 4.
 // None of this is on the per-step hot path (the mask of a matrix is computed once per
 // protection rate).
 #include <float.h>
