@@ -401,6 +401,7 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
 // that the skip route's loads would take.
 constexpr int GEMV_THREADS = 256;
 constexpr int GEMV_TRIT_WORDS = 48;                 // of a byte of trits: 27 entries at 0, 10 at 32
+constexpr size_t GEMV_BOTH_LDS = GEMV_THREADS * sizeof(double) + 256 * sizeof(uint16_t);        // of lanes that share a row, beside the others
 // LDS of the largest table, trits of whole dwords (2 bits: 8 entries a column, 1 bit: 4), after the chunk's x.
 static size_t gemv_lds(int32_t chunk_w) {
     return (size_t)WINDQ_MAX_CHUNK * sizeof(float) + (size_t)(((chunk_w + 4) / 5 + 3) & ~3) * GEMV_TRIT_WORDS * sizeof(double);
@@ -661,13 +662,11 @@ __device__ __forceinline__ void gemv_rows_of(int a, const uint8_t* const (&src)[
 // MASKED: matrices with a protection mask, in launches of their own (compiled into one kernel the two spilled registers:
 // 7B-shaped block under a mask 180 us against 138).
 template <int DT, int RPT, bool MASKED>
-__global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_kernel(const DequantBatch B, const int parts_shift) {
-    extern __shared__ __align__(16) char gemv_smem[];
-    float* xs = reinterpret_cast<float*>(gemv_smem);
-    double* tab = reinterpret_cast<double*>(gemv_smem + WINDQ_MAX_CHUNK * sizeof(float));
-    __shared__ double red[GEMV_THREADS / 64];
+__device__ __forceinline__ void gemv_rows_wg(const DequantBatch& B, const uint32_t wgs, const int parts_shift, char* __restrict__ smem,
+                                             double* __restrict__ red) {
+    float* xs = reinterpret_cast<float*>(smem);
+    double* tab = reinterpret_cast<double*>(smem + WINDQ_MAX_CHUNK * sizeof(float));
     constexpr int nt = RPT * GEMV_THREADS;         // rows
-    const uint32_t wgs = (uint32_t)B.tile_start[B.n];
     uint32_t wg = blockIdx.x, part = 0u;
     if (parts_shift != 0) {
         part = wg / wgs;
@@ -872,16 +871,20 @@ __global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_kernel(cons
     for (int k = 0; k < RPT; ++k)
         if (k * GEMV_THREADS + tid < nrows) out[k * GEMV_THREADS + tid] = acc[k];
 }
+template <int DT, int RPT, bool MASKED>
+__global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_kernel(const DequantBatch B, const int parts_shift) {
+    extern __shared__ __align__(16) char gemv_smem[];
+    __shared__ double red[GEMV_THREADS / 64];
+    gemv_rows_wg<DT, RPT, MASKED>(B, (uint32_t)B.tile_start[B.n], parts_shift, gemv_smem, red);
+}
 
 // Short units, and small matrices: G/8 lanes side by side share a row, eight columns each; no tables to make and no lanes
 // without a row.  A workgroup takes a tile of 64 rows, 2048 / G at a time, or, where there are few tiles, one of
 // 1 << parts_shift shares of it (512 x 512 at chunk 128 5.4 us, 8.0 with whole tiles; a share to each workgroup of a large
 // matrix costs it half its speed again: 4096 x 4096 in units of 64 rows 14.0 us, 19.2 in shares).
 template <int DT, bool POW2>
-__global__ __launch_bounds__(GEMV_THREADS) void gemv_split_kernel(const DequantBatch B, const int parts_shift) {
-    __shared__ uint16_t trits_of[256];
-    __shared__ double part[POW2 ? 1 : GEMV_THREADS];
-    const uint32_t wg = blockIdx.x >> parts_shift, share = blockIdx.x & ((1u << parts_shift) - 1u);
+__device__ __forceinline__ void gemv_split_wg(const DequantBatch& B, const uint32_t wg, const uint32_t share, const int parts_shift,
+                                              uint16_t* __restrict__ trits_of, double* part) {
     const int mi = batch_index(B.tile_start, B.n, wg);
     const DequantArgs& A = B.m[mi];
     const TileCoord tc = tile_coord(A.g, (int64_t)wg - B.tile_start[mi]);
@@ -938,6 +941,33 @@ __global__ __launch_bounds__(GEMV_THREADS) void gemv_split_kernel(const DequantB
             }
         }
     }
+}
+template <int DT, bool POW2>
+__global__ __launch_bounds__(GEMV_THREADS) void gemv_split_kernel(const DequantBatch B, const int parts_shift) {
+    __shared__ uint16_t trits_of[256];
+    __shared__ double part[POW2 ? 1 : GEMV_THREADS];
+    gemv_split_wg<DT, POW2>(B, blockIdx.x >> parts_shift, blockIdx.x & ((1u << parts_shift) - 1u), parts_shift, trits_of, part);
+}
+
+// A batch of both kinds, in one launch: the first n_rows matrices as gemv_kernel takes them, the others as gemv_split_kernel does.
+// A launch of its own for those took 3.5 us of the host's time (six matrices of 0.1 to 34 M weights 29.4 us a call, so 25.8).  The
+// split tiles come last: before the others, which are the longer, 0 to 2 us slower.
+template <int DT, int RPT, bool MASKED>
+__global__ __launch_bounds__(GEMV_THREADS, MASKED ? 4 : 6) void gemv_both_kernel(const DequantBatch B, const int n_rows, const int parts_shift,
+                                                                                const int split_shift) {
+    extern __shared__ __align__(16) char gemv_smem[];
+    __shared__ double red[GEMV_THREADS / 64];
+    const uint32_t wgs = (uint32_t)B.tile_start[n_rows], rows_blocks = wgs << parts_shift;
+    if (blockIdx.x < rows_blocks) {
+        gemv_rows_wg<DT, RPT, MASKED>(B, wgs, parts_shift, gemv_smem, red);
+        return;
+    }
+    const uint32_t at = blockIdx.x - rows_blocks, wg = wgs + (at >> split_shift), share = at & ((1u << split_shift) - 1u);
+    const int32_t G = B.m[0].g.chunk_w;
+    double* part = reinterpret_cast<double*>(gemv_smem);                     // (GEMV_BOTH_LDS bytes)
+    uint16_t* trits_of = reinterpret_cast<uint16_t*>(part + GEMV_THREADS);
+    if ((G & (G - 1)) == 0) gemv_split_wg<DT, true>(B, wg, share, split_shift, trits_of, part);
+    else gemv_split_wg<DT, false>(B, wg, share, split_shift, trits_of, part);
 }
 
 // y[row] = the row's chunk partials: 8 phases, phase p adds chunks p, p + 8, ..., the phases in order; fp64,
@@ -1099,11 +1129,29 @@ static int gemv_route(const Geometry& g, bool masked) {
 }
 constexpr int64_t GEMV_SPLIT_WGS = 2048;    // up to which a tile's rows are spread over several workgroups: two rounds of a full chip at most
 
+// How many workgroups (as a shift) share a tile's rows where lanes share a row.
+static int gemv_split_shift(int64_t tiles, int32_t chunk_w) {
+    int shift = 0;
+    while ((1 << shift) < dequant_passes(chunk_w) && (tiles << shift) < GEMV_SPLIT_WGS) ++shift;
+    return shift;
+}
+
+// The first n_rows matrices of B in `wgs` workgroups a part; the others, if any, in tiles.
 template <int RPT, bool MASKED>
-static void gemv_rows_launch(const DequantBatch& B, int64_t wgs, int parts_shift, bool bf, size_t lds, hipStream_t hs) {
-    const dim3 grid((unsigned)(wgs << parts_shift)), block(GEMV_THREADS);
-    if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, RPT, MASKED>), grid, block, lds, hs, B, parts_shift);
-    else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, RPT, MASKED>), grid, block, lds, hs, B, parts_shift);
+static void gemv_rows_launch(const DequantBatch& B, int32_t n_rows, int64_t wgs, int parts_shift, bool bf, size_t lds, hipStream_t hs) {
+    const dim3 block(GEMV_THREADS);
+    if (n_rows == B.n) {
+        const dim3 grid((unsigned)(wgs << parts_shift));
+        if (bf) hipLaunchKernelGGL((gemv_kernel<WINDQ_BF16, RPT, MASKED>), grid, block, lds, hs, B, parts_shift);
+        else hipLaunchKernelGGL((gemv_kernel<WINDQ_F32, RPT, MASKED>), grid, block, lds, hs, B, parts_shift);
+        return;
+    }
+    const int64_t tiles = B.tile_start[B.n] - wgs;
+    const int split_shift = gemv_split_shift(tiles, B.m[0].g.chunk_w);
+    const dim3 grid((unsigned)((wgs << parts_shift) + (tiles << split_shift)));
+    if (lds < GEMV_BOTH_LDS) lds = GEMV_BOTH_LDS;
+    if (bf) hipLaunchKernelGGL((gemv_both_kernel<WINDQ_BF16, RPT, MASKED>), grid, block, lds, hs, B, n_rows, parts_shift, split_shift);
+    else hipLaunchKernelGGL((gemv_both_kernel<WINDQ_F32, RPT, MASKED>), grid, block, lds, hs, B, n_rows, parts_shift, split_shift);
 }
 
 // A workgroup takes 512 rows of a unit (two per thread, their loads in flight together) where that still
@@ -1139,16 +1187,16 @@ static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int
     if (All.tile_start[n] > (int64_t)0x7fffffff || fin > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const bool bf = items[0].W->dtype == WINDQ_BF16;
-    if (L[GEMV_SPLIT].n > 0) {
-        const int64_t tiles = dequant_number(&L[GEMV_SPLIT]);
-        int parts_shift = 0;
-        while ((1 << parts_shift) < dequant_passes(chunk_w) && (tiles << parts_shift) < GEMV_SPLIT_WGS) ++parts_shift;
+    DequantBatch& S = L[GEMV_SPLIT];
+    const int64_t tiles = S.n > 0 ? dequant_number(&S) : 0;
+    if (S.n == n) {
+        const int parts_shift = gemv_split_shift(tiles, chunk_w);
         const dim3 grid((unsigned)(tiles << parts_shift)), block(GEMV_THREADS);
         const bool pow2 = (chunk_w & (chunk_w - 1)) == 0;
-        if (bf && pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, true>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
-        else if (bf) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, false>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
-        else if (pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_F32, true>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
-        else hipLaunchKernelGGL((gemv_split_kernel<WINDQ_F32, false>), grid, block, 0, hs, L[GEMV_SPLIT], parts_shift);
+        if (bf && pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, true>), grid, block, 0, hs, S, parts_shift);
+        else if (bf) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, false>), grid, block, 0, hs, S, parts_shift);
+        else if (pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_F32, true>), grid, block, 0, hs, S, parts_shift);
+        else hipLaunchKernelGGL((gemv_split_kernel<WINDQ_F32, false>), grid, block, 0, hs, S, parts_shift);
     }
     for (int k = GEMV_ROWS; k <= GEMV_ROWS_MASKED; ++k) {
         DequantBatch& B = L[k];
@@ -1172,13 +1220,20 @@ static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int
             if (rows >= B.m[0].g.R_u || rows * chunk_w < 4 * GEMV_THREADS * 8) break;
             ++parts_shift;
         }
+        const int32_t n_rows = B.n;
+        for (int32_t i = 0; i < S.n; ++i, ++B.n) {          // into the first launch of the other kind
+            B.m[B.n] = S.m[i];
+            B.tile_start[B.n] = wgs + S.tile_start[i];
+        }
+        for (int32_t i = B.n; i <= WINDQ_MAX_BATCH; ++i) B.tile_start[i] = wgs + (B.n > n_rows ? tiles : 0);
+        S.n = 0;
         const size_t lds = k == GEMV_ROWS ? gemv_lds(chunk_w) : WINDQ_MAX_CHUNK * sizeof(float) + 256 * sizeof(uint16_t);   // tables: at most 41 KB
         if (k == GEMV_ROWS) {
-            if (rpt == 2) gemv_rows_launch<2, false>(B, wgs, parts_shift, bf, lds, hs);
-            else gemv_rows_launch<1, false>(B, wgs, parts_shift, bf, lds, hs);
+            if (rpt == 2) gemv_rows_launch<2, false>(B, n_rows, wgs, parts_shift, bf, lds, hs);
+            else gemv_rows_launch<1, false>(B, n_rows, wgs, parts_shift, bf, lds, hs);
         } else {
-            if (rpt == 2) gemv_rows_launch<2, true>(B, wgs, parts_shift, bf, lds, hs);
-            else gemv_rows_launch<1, true>(B, wgs, parts_shift, bf, lds, hs);
+            if (rpt == 2) gemv_rows_launch<2, true>(B, n_rows, wgs, parts_shift, bf, lds, hs);
+            else gemv_rows_launch<1, true>(B, n_rows, wgs, parts_shift, bf, lds, hs);
         }
     }
     hipLaunchKernelGGL(gemv_finalize_kernel, dim3((unsigned)fin), dim3(256), 0, hs, All);

@@ -277,6 +277,22 @@ def test_gemv_batch_of_all_routes(windq):
         check_against_reconstruction(windq, A, G, 0, b)
 
 
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("G,dtype,large", [(64, torch.bfloat16, (530, 32768)), (96, torch.bfloat16, (4400, 960)), (128, torch.float32, (520, 65536)),
+                                           (72, torch.float32, (3000, 1440))])          # two rows a thread, one; lanes a power of two, or not
+def test_gemv_batch_of_small_and_large(windq, G, dtype, large, masked):
+    """Matrices whose lanes share rows, beside one whose lanes do not, in one launch: each as it would be alone."""
+    shapes = [(200, 3 * G, not masked), (*large, masked), (65, 7 * G, masked), (1000, 2 * G, False)]
+    As = [random_artefact(windq, r, c, G, 0, dtype, m, seed=70 + i) for i, (r, c, m) in enumerate(shapes)]
+    alone = [gemv_of(windq, A, G, 0) for A in As]
+    together = windq.windq_dequant_gemv_batch([A["W"] for A in As], G, 0, *([A[k] for A in As] for k in ("action", "off", "codes", "scale", "offset", "x")),
+                                              masks=[A["mask"] for A in As])
+    torch.cuda.synchronize()
+    for A, one, b in zip(As, alone, together):
+        assert torch.equal(one.view(torch.int32), b.view(torch.int32))
+        check_against_reconstruction(windq, A, G, 0, b)
+
+
 @pytest.mark.parametrize("R", [96, 4200])               # below and above the size from which tables are used
 @pytest.mark.parametrize("bad", [float("inf"), 2.0 ** 120])
 def test_gemv_with_values_no_table_may_hold(windq, R, bad):
