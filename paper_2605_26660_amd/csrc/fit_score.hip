@@ -24,6 +24,9 @@
 //                         acc_b += r' * r'
 //     4 instructions per candidate and no separate clamp of the code (x is already in
 //     [0,1]): 18 per (weight, clip ratio) when all four bit-widths go this short way;
+//   * most 8-bit candidates cannot win, and a bound from the clipped weights alone shows it (see
+//     SKIP8_MARGIN below): 16 or more of 20 are left out, 14 instructions per (weight, clip ratio)
+//     for them (a 7B-shaped block, 202 M weights, K = 20: 1450 us with all of them, 1256 without);
 //   * at 8 bits the residual is ~1/500 of (w - lo), so the fp32 roundings of s_c*w,
 //     s_c*(w - lo) and s_c*code show in it: ~1e-4 of its size per weight, random in sign.
 //     An EXACT 8-bit route, 20 instructions, forms the residual unscaled, relative to an
@@ -104,6 +107,21 @@ constexpr int FS_FEAT_ONLY = 3;     // that first pass alone          // workgro
 // is ~0.4 of this estimate: NOISE_MAX = 3e-6 keeps one standard deviation near 1e-6.)
 constexpr double NOISE_MAX = 3e-6;
 constexpr double NOISE_C1 = 4.0 * 3.552713678800501e-15 / (NOISE_MAX * NOISE_MAX);   // 4 * 2^-48 / NOISE_MAX^2
+// 8-bit candidates that cannot win.  At clip ratio p a weight beyond the clipped range [p min, p max] is off by at
+// least its distance e from that range, at any bit-width: with C(p) = sum s_c^2 e^2, E_b(p) >= C(p).  As p falls C only
+// grows, and at a known rate: e <= (1-p) |max| (or |min|), so e(p') = e(p) + (p-p') |max| >= e(p) (1-p')/(1-p) and
+//     C(p') >= C(p) ((1-p')/(1-p))^2     for p' < p.
+// An 8-bit grid is so fine that C passes the whole error at p = 1 (about step^2/12 a weight, step = (max-min)/255) once
+// p is a few per cent below 1.  So a tile takes C at ONE ratio (skip8_p), and where the bound for a smaller ratio exceeds
+// SKIP8_MARGIN times the expected error at ratio 1 it leaves that 8-bit candidate out and writes the bound, negated,
+// in its place: the sum over the unit's tiles is then a lower bound on the candidate's error, and says so by its sign.
+// The finalize kernel chooses among the candidates that every tile has scored and PROVES the choice: a unit one of
+// whose bounds does not exceed the chosen error by BOUND_SLACK (more than fp32 rounding can have put into either) goes
+// on the list of units whose 8-bit candidates are all scored again.  So a tile's test decides speed, never the result.
+// Margin 1.25: with 1, single units of a batch miss the proof and are scored twice (a batch of 0.9 M to 5 M weights: 125 us, 119 with 1.25).
+constexpr float SKIP8_MARGIN = 1.25f;
+constexpr double BOUND_SLACK = 1e-4;
+constexpr float SKIP8_MAX_P = 0.95f;        // skip8_p: the grid's largest ratio up to here
 // A tile takes the exact sweep when one row holds more than 1 / ROW_SHARE of the sum of the
 // rows' squared ranges (that row would carry most of the tile's 8-bit error by itself).
 constexpr float ROW_SHARE = 1.5f;
@@ -142,7 +160,9 @@ struct FitScoreMat {
 struct FitScoreArgs {
     int32_t n;                                   // matrices in the launch
     int32_t K;
-    int32_t n_kpass;                             // ceil(K / FS_KB)
+    int32_t shares;                              // sweeps the clip grid is dealt to, ceil(K / FS_KB) (see share_ratio)
+    float skip8_p;                               // clip ratio at which the tiles take the clipping error
+    ClipGrid skip8_f;                            // [k]: a lower bound on the clipping error at ratio k over that at skip8_p
     double inv_G;                                // 1 / chunk_w
     int64_t tile_start[WINDQ_MAX_BATCH + 1];     // first tile of matrix i in the grid; [n] = grid size
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
@@ -162,9 +182,14 @@ inline size_t fit_score_lds_bytes(int32_t dtype, int32_t chunk_w, bool masked = 
     return raw_tile_lds_bytes(dtype, chunk_w) + (size_t)chunk_w * sizeof(float) +
            (size_t)FS_WAVES * 16 * fs_nrow(masked) * sizeof(float) + (size_t)FS_WAVES * TILE_ROWS * 2 * sizeof(float) +
            (size_t)chunk_w * sizeof(float) + (size_t)FS_HMAX * sizeof(int32_t) +
-           (size_t)FS_WAVES * TILE_ROWS * sizeof(double) +
+           (size_t)FS_WAVES * TILE_ROWS * sizeof(double) + (size_t)FS_WAVES * 2 * sizeof(float) +
            (masked ? (size_t)FS_WAVES * TILE_ROWS * sizeof(uint16_t) + mask_tile_lds_bytes(chunk_w) : 0);
 }
+
+// The grid's ratios are dealt to the sweeps by turns: ratio i of sweep v is share_ratio(...).  So every sweep has its
+// share of the large ratios, whose 8-bit candidates are scored, at its end.  Numbers below zero (in the first places, where
+// K is no multiple of FS_KB) are scored as ratio 0 and dropped.
+__device__ __forceinline__ int32_t share_ratio(int32_t K, int32_t shares, int32_t i, int32_t v) { return K - shares * (FS_KB - i) + v; }
 
 // The 8-bit residual is ~1/500 of the range, so it is taken relative to an ANCHOR c: a grid
 // point of the 8-bit quantizer, with the code counted from it (qc = code - q0).
@@ -246,17 +271,42 @@ __device__ __forceinline__ void score_weight(const float w, const float sc, cons
     }
 }
 
+// The 4-, 3- and 2-bit candidates of one weight at one clip ratio, side by side, stage by stage (see
+// score_weight_short): 14 instructions.  For the ratios whose 8-bit candidate is left out.
+template <bool ANCHORED>
+__device__ __forceinline__ void score_low_bits(const float w, const float sc, const float w1, const float ms, const KParams& P,
+                                               const float (&Q)[4], const float M, float (&acc)[4]) {
+    const float u1 = fmaf(P.nlo, sc, w1);                         // s_c * (w - lo)
+    const float x = fma_clamp01(ANCHORED ? w : w + P.nc, P.rinv, P.h);
+    float t[4];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 1; b < 4; ++b) t[b] = fmaf(x, Q[b], M);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 1; b < 4; ++b) t[b] = fmaf(t[b], sc, ms);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 1; b < 4; ++b) t[b] = fmaf(t[b], P.nd[b], u1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 1; b < 4; ++b) acc[b] = fmaf(t[b], t[b], acc[b]);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // score_weight with the four bit-widths side by side, stage by stage (see score_weight_short): six live
 // temporaries instead of two, for the sweeps over all columns, which read four columns at a time to
 // make room for them.  The 8-bit candidate's two extra steps run into the next ratio's first ones.
-template <bool ANCHORED, bool NORMATIVE>
+template <bool ANCHORED, bool NORMATIVE, int S8>
 __device__ __forceinline__ void score_weight_staged(const float w, const float sc, const KParams (&P)[FS_KB],
                                                     const float (&Q)[4], const float M, const float nM,
                                                     float (&acc)[FS_KB][4]) {
     const float w1 = w * sc;
     const float ms = sc * nM;
 #pragma unroll
-    for (int i = 0; i < FS_KB; ++i) {
+    for (int i = 0; i < S8; ++i) score_low_bits<ANCHORED>(w, sc, w1, ms, P[i], Q, M, acc[i]);
+#pragma unroll
+    for (int i = S8; i < FS_KB; ++i) {
         if constexpr (NORMATIVE) {
             const float u1 = fmaf(P[i].nlo, sc, w1);                  // s_c * (w - lo)
             const float un = w + P[i].nlo;                            // fl(w - lo): the first of the normative steps
@@ -341,6 +391,7 @@ __device__ __forceinline__ void score_weight_8(const float w, const float sc, co
 // The short route: all four bit-widths like the low ones, 18 instructions per (weight, clip
 // ratio).  Its 8-bit residual carries the fp32 roundings of s_c*w, s_c*(w - lo) and s_c*code:
 // ~1e-4 of its own size per weight, of random sign (see NOISE_MAX for how that is bounded).
+template <int S8>
 __device__ __forceinline__ void score_weight_short(const float w, const float sc, const KParams (&P)[FS_KB],
                                                    const float (&Q)[4], const float M, const float nM,
                                                    float (&acc)[FS_KB][4]) {
@@ -351,7 +402,9 @@ __device__ __forceinline__ void score_weight_short(const float w, const float sc
     const float w1 = w * sc;
     const float ms = sc * nM;
 #pragma unroll
-    for (int i = 0; i < FS_KB; ++i) {
+    for (int i = 0; i < S8; ++i) score_low_bits<true>(w, sc, w1, ms, P[i], Q, M, acc[i]);
+#pragma unroll
+    for (int i = S8; i < FS_KB; ++i) {
         const float u1 = fmaf(P[i].nlo, sc, w1);                  // s_c * (w - lo)
         const float x = fma_clamp01(w, P[i].rinv, P[i].h);        // position in the clipped range, in [0, 1]
         float t[4];
@@ -505,7 +558,7 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
 //   refined to the last bit without reading W again; the count of |w| < 1e-6 is a sum of counters.
 // MASKED: salient weights (Sec. 3.5) marked in A.mask take no part: they are left out of
 // the group statistics, and in every error sum their activation scale counts as zero.
-// rot spreads an uneven number of clip passes over the four SIMDs from tile to tile.
+// rot spreads an uneven number of sweeps over the four SIMDs from tile to tile.
 template <int DT, bool MASKED, int MODE>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
                                                const int rot, char* __restrict__ smem) {
@@ -525,7 +578,8 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     float* __restrict__ sshort = reinterpret_cast<float*>(gstat + FS_WAVES * TILE_ROWS);   // s_c, 0 for the listed columns
     int32_t* __restrict__ hlist = reinterpret_cast<int32_t*>(sshort + G);   // the listed columns
     double* __restrict__ s1tab = reinterpret_cast<double*>(hlist + FS_HMAX);   // [FS_WAVES][TILE_ROWS] sum |w| of a quarter
-    uint16_t* __restrict__ nktab = reinterpret_cast<uint16_t*>(s1tab + FS_WAVES * TILE_ROWS);   // kept weights of a quarter (masked): <= 128
+    float* __restrict__ ctab = reinterpret_cast<float*>(s1tab + FS_WAVES * TILE_ROWS);   // [2][FS_WAVES] clipping error of a quarter; sum of s_c^2 range^2 (masked)
+    uint16_t* __restrict__ nktab = reinterpret_cast<uint16_t*>(ctab + 2 * FS_WAVES);   // kept weights of a quarter (masked): <= 128
     uint8_t* __restrict__ mtile = reinterpret_cast<uint8_t*>(nktab + (MASKED ? FS_WAVES * TILE_ROWS : 0));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: lives in a scalar register
 
@@ -550,6 +604,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     // of the columns on the short route (0 for the listed ones) and the list lie next to each
     // other, in the record as in LDS.
     int32_t nh = -1;           // listed columns; -1: no list, every column takes the exact route
+    float s2 = 0.0f;           // sum s_c^2 over the chunk
     float s4_over_s2 = 0.0f;   // sum s_c^4 / sum s_c^2 over the short route: scales the tile's noise term
     if (SCORE && !ONLY8) {
         const float* __restrict__ rec = A.colsel + (size_t)(tc.col0 / G) * (size_t)colsel_words(G);
@@ -557,6 +612,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         // (wave-uniform: parked in scalar registers across the hot loops)
         nh = __builtin_amdgcn_readfirstlane(__float_as_int(rec[G + FS_HMAX]));
         s4_over_s2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(rec[G + FS_HMAX + 1])));
+        s2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(rec[G + FS_HMAX + 2])));
     }
     __syncthreads();
 
@@ -648,8 +704,9 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     // the record of the feature pass, the tile's largest |w| and the sum of |w| (it only places the
     // record: fp32 will do).
     bool rows_even = true;
+    float tile_rg2 = 0.0f;          // the rows' squared ranges, added up
     float tile_amax = 0.0f, tile_sabs = 0.0f;
-    if (FINE || (SCORE && !ONLY8 && nh >= 0)) {
+    if (FINE || (SCORE && !ONLY8)) {
         const int lane_t = fresh_lane();
         float mn = INFINITY, mx = -INFINITY, sabs = 0.0f;
 #pragma unroll
@@ -669,6 +726,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         }
         wave_sums_maxes(sums, maxes);
         rows_even = maxes[0] * ROW_SHARE <= sums[0];
+        tile_rg2 = sums[0];
         if (FINE) {
             tile_sabs = sums[1];
             tile_amax = maxes[1];
@@ -801,10 +859,27 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     // added in order (exact for bf16 inputs; for fp32 inputs it can differ from the strict
     // column-order sum in the last bit of the fp64, which the conversion to fp32 hides but for
     // ~1e-8 of the groups, and there by one ulp of gamma).
+    // With them goes the error that clipping alone makes at ratio skip8_p: sum s_c^2 (w - clamp(w, lo, hi))^2, a
+    // lower bound on every bit-width's error at that ratio and at any smaller one (see SKIP8_MARGIN).
+    float tile_clip = 0.0f;     // that error over the tile
+    float s2_rg2 = 0.0f;        // the sum of s_c^2 (max - min)^2 over the tile's weights
     if (!ONLY8) {
         const int lane_w = fresh_lane();
         const char* __restrict__ wrow = tile + lane_w * row_bytes;
         const uint8_t* __restrict__ mrow = mtile + lane_w * mstride;
+        const bool bounds = B.skip8_p > 0.0f;
+        float mn = INFINITY, mx = -INFINITY;
+        if (bounds) {
+#pragma unroll
+            for (int q = 0; q < FS_WAVES; ++q) {
+                const float2 st = gstat[q * TILE_ROWS + lane_w];
+                mn = fminf(mn, st.x);
+                mx = fmaxf(mx, st.y);
+            }
+        }
+        if (mn > mx) mn = mx = 0.0f;      // no weight of the group is kept
+        const float clo = pin_vgpr(B.skip8_p * mn), chi = pin_vgpr(B.skip8_p * mx);
+        float accc[MASKED ? 2 : 1] = {};    // clipping error; under a mask, sum of the kept columns' s_c^2 too
         double S1 = 0.0;
         int32_t n_kept = MASKED ? 0 : G;
 #pragma unroll
@@ -848,16 +923,50 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 const float w1 = w[j] * sc;
                 acc3[2] = fmaf(w1, w1, acc3[2]);
             }
+            if (bounds) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float rc = (w[j] - __builtin_amdgcn_fmed3f(w[j], clo, chi)) * s8[j];
+                    accc[0] = fmaf(rc, rc, accc[0]);
+                    if (MASKED) accc[1] = fmaf(s8[j], s8[j], accc[1]);
+                }
+            }
         }
         const int lane_r = fresh_lane();
-        if (lane_r >= tc.nrows) acc3[0] = acc3[1] = acc3[2] = 0.0f;
+        if (lane_r >= tc.nrows) acc3[0] = acc3[1] = acc3[2] = accc[0] = 0.0f;    // (a row past the end has range 0)
         rows_deposit<NROW>(acc3, red, lane_r, ACC3_COL);
+        if (bounds) {
+            if (MASKED) accc[1] *= (mx - mn) * (mx - mn);
+            float none[1] = {0.0f};
+            wave_sums_maxes(accc, none);
+            if (lane_r == 0) {
+                ctab[wave] = accc[0];
+                if (MASKED) ctab[FS_WAVES + wave] = accc[1];
+            }
+            __syncthreads();
+            tile_clip = ((ctab[0] + ctab[1]) + ctab[2]) + ctab[3];
+            if (MASKED) s2_rg2 = ((ctab[4] + ctab[5]) + ctab[6]) + ctab[7];
+            else s2_rg2 = s2 * tile_rg2;
+            tile_clip = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tile_clip)));
+            s2_rg2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s2_rg2)));
+        }
     }
+    // an 8-bit candidate is left out where its bound, tile_clip * skip8_f[k], exceeds this (never where either is NaN)
+    const float skip8_above = s2_rg2 * (SKIP8_MARGIN / (12.0f * 65025.0f));
     int32_t ncollect = ONLY8 ? FS_NRED : NROW;         // columns the next collection takes
 
-    // The clip grid: n_kpass passes over FS_KB clip ratios each.  Pass i goes to wavefront
-    // (i + rot) % 4.
-    for (int item = (wave - rot) & (FS_WAVES - 1); item < B.n_kpass; item += FS_WAVES) {
+    // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4.
+    for (int v = (wave - rot) & (FS_WAVES - 1); v < B.shares; v += FS_WAVES) {
+        const int32_t k0 = share_ratio(K, B.shares, 0, v), dk = B.shares;       // the sweep's ratio i: k0 + dk * i
+        // the sweep's first ratios whose 8-bit candidate may be left out (skip8_f falls as k grows)
+        int32_t skip_here = 0;
+        if (!ONLY8) {
+#pragma unroll
+            for (int i = 0; i < FS_KB; ++i) {
+                const int k = k0 + dk * i;
+                skip_here += tile_clip * B.skip8_f.p[k > 0 ? k : 0] > skip8_above ? 1 : 0;
+            }
+        }
         // The hot loop below needs every register the occupancy target allows.  The lane index
         // is therefore re-read from the hardware where it is needed (before the loop for the
         // row address, after it for the reduction) rather than kept alive across the loop,
@@ -878,8 +987,8 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             float acc[FS_KB][4];
 #pragma unroll
             for (int i = 0; i < FS_KB; ++i) {
-                int k = item * FS_KB + i;
-                k = k < K ? k : K - 1;
+                int k = k0 + dk * i;
+                k = k > 0 ? k : 0;
                 const float p = B.grid.p[k];
                 const float flo = p * mn;
                 const float fhi = p * mx;
@@ -910,22 +1019,23 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             const float Q[4] = {pin_vgpr(255.0f), pin_vgpr(15.0f), pin_vgpr(7.0f), pin_vgpr(3.0f)};
             const float M = pin_vgpr(RNE_POS);
             const float nM = pin_vgpr(-RNE_POS);
-            float nz[FS_KB];     // the noise terms of the short route (zero on the exact ones)
+            float nz[FS_KB];        // the noise terms of the short route (zero on the exact ones)
 #pragma unroll
             for (int i = 0; i < FS_KB; ++i) nz[i] = 0.0f;
             // (the row addresses are formed from a fresh lane index in front of each sweep: kept
             // from here they would be spilled across the parameter set-up)
             __builtin_amdgcn_s_setprio(0);       // the sweeps: issue-bound, ordinary priority
-            auto sweep = [&](auto anchored_t, auto normative_t) {
+            auto sweep = [&](auto anchored_t, auto normative_t, auto s8_t) {
                 constexpr bool AN = decltype(anchored_t)::value, NORM = decltype(normative_t)::value;
+                constexpr int S8 = decltype(s8_t)::value;
                 if (NORM) {         // the 8-bit decision by the normative steps: 1/step in h's place
 #pragma unroll
                     for (int i = 0; i < FS_KB; ++i) {
                         const float d8 = -P[i].nd[0];
                         P[i].h = pin_vgpr(d8 >= FLT_MIN ? 1.0f / d8 : 0.0f);
                         if (ONLY8) {        // (-lo is not kept through the set-up in this mode)
-                            int k = item * FS_KB + i;
-                            k = k < K ? k : K - 1;
+                            int k = k0 + dk * i;
+                            k = k > 0 ? k : 0;
                             P[i].nlo = pin_vgpr(-(B.grid.p[k] * mn));
                         }
                     }
@@ -959,7 +1069,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                             s4[2] = drop_if_set<2>(s4[2], m); s4[3] = drop_if_set<3>(s4[3], m);
                         }
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) score_weight_staged<AN, NORM>(w[j], s4[j], P, Q, M, nM, acc);
+                        for (int j = 0; j < 4; ++j) score_weight_staged<AN, NORM, S8>(w[j], s4[j], P, Q, M, nM, acc);
                     }
                 }
             };
@@ -967,29 +1077,42 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             // unit has few rows: there a single weight near a rounding tie can hold enough of the unit's error
             // for the neighbouring code's residual (the same magnitude to 4e-5) to show; it costs 7 %.
             const bool few_rows = A.g.R_u < FS_FEW_ROWS;
+            using int0 = std::integral_constant<int, 0>;
+            // those left out: all, all but one or two (sweeps are built for these), or none
+            const int32_t s8 = ONLY8 || !anchored || few_rows || skip_here < FS_KB - 2 ? 0 : skip_here;
             if (!anchored) {
-                if (few_rows) sweep(std::false_type{}, std::true_type{});
-                else sweep(std::false_type{}, std::false_type{});
+                if (few_rows) sweep(std::false_type{}, std::true_type{}, int0{});
+                else sweep(std::false_type{}, std::false_type{}, int0{});
             } else if (ONLY8 || nh < 0 || !rows_even) {
-                if (few_rows) sweep(std::true_type{}, std::true_type{});
-                else sweep(std::true_type{}, std::false_type{});
+                if (few_rows) sweep(std::true_type{}, std::true_type{}, int0{});
+                else if (!ONLY8 && s8 == FS_KB) sweep(std::true_type{}, std::false_type{}, std::integral_constant<int, ONLY8 ? 0 : FS_KB>{});
+                else if (!ONLY8 && s8 == FS_KB - 1) sweep(std::true_type{}, std::false_type{}, std::integral_constant<int, ONLY8 ? 0 : FS_KB - 1>{});
+                else if (!ONLY8 && s8 == FS_KB - 2) sweep(std::true_type{}, std::false_type{}, std::integral_constant<int, ONLY8 ? 0 : FS_KB - 2>{});
+                else sweep(std::true_type{}, std::false_type{}, int0{});
             } else {
                 const int lane_v = fresh_lane();
                 const char* __restrict__ wrow = tile + lane_v * row_bytes;
                 const uint8_t* __restrict__ mrow = mtile + lane_v * mstride;
-                for (int32_t c = 0; c < G; c += 8) {
-                    float w[8];
-                    read8<DT>(wrow, c, w);
-                    const float4 sa = *reinterpret_cast<const float4*>(sshort + c);
-                    const float4 sb = *reinterpret_cast<const float4*>(sshort + c + 4);
-                    float s8[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
-                    if (MASKED) {
-                        const uint32_t m = mrow[c >> 3];
-                        drop_masked(s8, m);
-                    }
+                auto sweep_short = [&](auto s8_t) {
+                    constexpr int S8 = decltype(s8_t)::value;
+                    for (int32_t c = 0; c < G; c += 8) {
+                        float w[8];
+                        read8<DT>(wrow, c, w);
+                        const float4 sa = *reinterpret_cast<const float4*>(sshort + c);
+                        const float4 sb = *reinterpret_cast<const float4*>(sshort + c + 4);
+                        float s8[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
+                        if (MASKED) {
+                            const uint32_t m = mrow[c >> 3];
+                            drop_masked(s8, m);
+                        }
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) score_weight_short(w[j], s8[j], P, Q, M, nM, acc);
-                }
+                        for (int j = 0; j < 8; ++j) score_weight_short<S8>(w[j], s8[j], P, Q, M, nM, acc);
+                    }
+                };
+                if (s8 == FS_KB) sweep_short(std::integral_constant<int, FS_KB>{});
+                else if (s8 == FS_KB - 1) sweep_short(std::integral_constant<int, FS_KB - 1>{});
+                else if (s8 == FS_KB - 2) sweep_short(std::integral_constant<int, FS_KB - 2>{});
+                else sweep_short(int0{});
                 // range^2 * (the lane's short-route 8-bit sum); range = 255 * step
 #pragma unroll
                 for (int i = 0; i < FS_KB; ++i) nz[i] = acc[i][0] * (P[i].nd[0] * P[i].nd[0]) * 65025.0f;
@@ -1002,7 +1125,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 }
             }
             __builtin_amdgcn_s_setprio(3);
-            float flat[FS_NRED];
+            float flat[FS_KB * 5];
 #pragma unroll
             for (int i = 0; i < FS_KB; ++i) {
 #pragma unroll
@@ -1012,18 +1135,21 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             const int lane_r = fresh_lane();
             if (lane_r >= tc.nrows) {
 #pragma unroll
-                for (int j = 0; j < FS_NRED; ++j) flat[j] = 0.0f;
+                for (int j = 0; j < FS_KB * 5; ++j) flat[j] = 0.0f;
             }
             rows_deposit<NROW>(flat, red, lane_r, 0);
-            const double tot = rows_collect<NROW>(red, lane_r, ncollect);
+            double tot = rows_collect<NROW>(red, lane_r, ncollect);
             if (!ONLY8 && ncollect > FS_NRED) store_extra(lane_r, tot);
             ncollect = FS_NRED;
             if (lane_r < FS_KB * 4) {
-                const int k = item * FS_KB + (lane_r >> 2);
-                if (k < K && (!ONLY8 || (lane_r & 3) == 0)) out[(lane_r & 3) * K + k] = tot;
-            } else if (lane_r < FS_NRED) {
-                const int k = item * FS_KB + (lane_r - FS_KB * 4);
-                if (k < K) {
+                const int i = lane_r >> 2;
+                const int k = k0 + dk * i;
+                // left out: a lower bound takes the candidate's place, marked as one by its sign
+                if (!ONLY8 && (lane_r & 3) == 0 && i < s8) tot = -(double)(tile_clip * B.skip8_f.p[k > 0 ? k : 0]);
+                if (k >= 0 && (!ONLY8 || (lane_r & 3) == 0)) out[(lane_r & 3) * K + k] = tot;
+            } else if (lane_r < FS_KB * 5) {
+                const int k = k0 + dk * (lane_r - FS_KB * 4);
+                if (k >= 0) {
                     float ratio = s4_over_s2;
                     asm volatile("" : "+s"(ratio));      // converted here, not ahead of the loops
                     out[fit_score_noise_slot(K) + k] = tot * (double)ratio;
@@ -1031,7 +1157,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             }
         }
     }
-    if (!ONLY8 && ncollect > FS_NRED) {     // no clip pass fell to this wavefront
+    if (!ONLY8 && ncollect > FS_NRED) {     // no sweep fell to this wavefront
         const int lane_r = fresh_lane();
         store_extra(lane_r, rows_collect<NROW>(red, lane_r, NROW));
     }
@@ -1070,9 +1196,10 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
         ss = fmaf(sv, sv, ss);
     }
     // below tau = 1 (never a positive tau) nothing is listed short: the threshold 0 lists every column with s_c != 0
-    const float thr = A.tau * wave_sum_f32(ss) / (float)G;
     int32_t nh = 0;
     float t2 = 0.0f, t4 = 0.0f;
+    ss = wave_sum_f32(ss);
+    const float thr = A.tau * ss / (float)G;
     for (int32_t blk = 0; blk < G; blk += 64) {
         const int32_t c = blk + l;
         const float sv = c < G ? scol[c] : 0.0f;
@@ -1093,6 +1220,7 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
     if (l == 0) {
         hlist[FS_HMAX] = nh;
         sshort[G + FS_HMAX + 1] = S2 >= FLT_MIN ? S4 / S2 : 0.0f;
+        sshort[G + FS_HMAX + 2] = ss;
     }
 }
 
@@ -1165,33 +1293,45 @@ __global__ __launch_bounds__(FIN_THREADS) void fit_score_finalize_kernel(const F
     const int phase = threadIdx.x >> 6;
     // phase p adds tiles p, p+16, p+32, ... in order; the 16 phase sums are then added in order
     for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) {
+        // (a sum that holds a lower bound, marked by its sign, is one itself and keeps the mark)
         double acc = 0.0;
+        bool bound = false;
 #pragma unroll 4
-        for (int64_t t = phase; t < tiles_per_unit; t += FIN_PHASES) acc += base[(size_t)t * ncand + cand];
-        part[phase][cand] = acc;
+        for (int64_t t = phase; t < tiles_per_unit; t += FIN_PHASES) {
+            const double v = base[(size_t)t * ncand + cand];
+            bound |= v < 0.0;
+            acc += fabs(v);
+        }
+        part[phase][cand] = bound ? -acc : acc;
     }
     __syncthreads();
     for (int32_t cand = threadIdx.x; cand < ncand; cand += FIN_THREADS) {
         double acc = 0.0;
+        bool bound = false;
 #pragma unroll
-        for (int p = 0; p < FIN_PHASES; ++p) acc += part[p][cand];
-        E[cand] = acc;
+        for (int p = 0; p < FIN_PHASES; ++p) {
+            bound |= part[p][cand] < 0.0;
+            acc += fabs(part[p][cand]);
+        }
+        E[cand] = bound ? -acc : acc;
     }
     __syncthreads();
     const int tid = threadIdx.x;
     if (tid < 4) {
-        double best = E[tid * K];
-        int bk = 0;
-        for (int k = 1; k < K; ++k) {
+        double best = 0.0, bound = INFINITY;
+        int bk = -1;
+        for (int k = 0; k < K; ++k) {       // (the last ratio is never left out)
             const double e = E[tid * K + k];
-            if (e <= best) {
+            if (e < 0.0) bound = fmin(bound, -e);
+            else if (bk < 0 || e <= best) {
                 best = e;
                 bk = k;
             }
         }
         err[u * WINDQ_N_ERR + tid] = (float)best;
         clip_idx[u * 4 + tid] = (uint8_t)bk;
-        if (!REDO && tid == 0 && E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best) {
+        // (tid 0: 8 bits) listed: too much noise, or a candidate that was left out is not proved to be worse
+        if (!REDO && tid == 0 && (E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best || bound * (1.0 - BOUND_SLACK) <= best)) {
             const uint32_t pos = atomicAdd(A.redo_count, 1u);
             A.redo_list[pos] = (uint32_t)u;
         }
@@ -1285,7 +1425,18 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     FitScoreArgs A;
     A.n = n;
     A.K = K;
-    A.n_kpass = (K + FS_KB - 1) / FS_KB;
+    A.shares = (K + FS_KB - 1) / FS_KB;
+    A.skip8_p = 0.0f;
+    for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.skip8_f.p[k] = 0.0f;
+    int32_t t = K - 1;
+    while (t >= 0 && clip_grid[t] > SKIP8_MAX_P) --t;
+    if (t >= 0 && clip_grid[K - 1] == 1.0f) {      // (the error a tile expects is that at ratio 1)
+        A.skip8_p = clip_grid[t];
+        for (int k = 0; k <= t; ++k) {
+            const double f = (1.0 - (double)clip_grid[k]) / (1.0 - (double)clip_grid[t]);
+            A.skip8_f.p[k] = (float)(f * f);
+        }
+    }
     A.inv_G = 1.0 / (double)chunk_w;
     for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.grid.p[k] = clip_grid[k < K ? k : K - 1];
     const bool masked = items[0].mask != nullptr;
@@ -1378,7 +1529,9 @@ int windq::features_launch_tiles(const FeatBatch& F, hipStream_t hs) {
     FitScoreArgs A;
     A.n = F.n;
     A.K = 1;
-    A.n_kpass = 0;
+    A.shares = 0;
+    A.skip8_p = 0.0f;
+    for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.skip8_f.p[k] = 0.0f;
     A.inv_G = 0.0;
     for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.grid.p[k] = 1.0f;
     int64_t tiles = 0, units = 0;

@@ -1,0 +1,119 @@
+"""The 8-bit candidates that fit+score leaves out because clipping alone makes them worse than the chosen one: whatever
+the grid, the shape or the data, the outputs are the oracle's.  Bars as everywhere: errors 1e-5, clip indices the
+oracle's but for ties of 1e-9."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import windq_oracle as O
+from paper_2605_26660_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def check(windq, W, s, G, unit_rows, cg, mask=None):
+    """Returns how many units were scored a second time."""
+    R, C = W.shape
+    dt = windq.WINDQ_F32 if W.dtype == torch.float32 else windq.WINDQ_BF16
+    ws = torch.empty(windq.workspace_bytes(windq.CALL_FIT_SCORE, dt, R, C, G, unit_rows, len(cg)), dtype=torch.uint8, device=DEV)
+    err, clip, ref = windq.windq_fit_score_all_bits(W, s, G, unit_rows, cg, ws=ws, mask=mask)
+    torch.cuda.synchronize()
+    keep = None
+    if mask is not None:
+        keep = np.unpackbits(mask.cpu().numpy(), axis=1, bitorder="little")[:, :C] == 0
+    o_err, o_clip, o_ref, table = O.fit_score_all_bits(W.float().cpu().numpy(), s.cpu().numpy(), G, unit_rows, cg.numpy(), keep=keep)
+    g_err, g_clip = err.cpu().numpy().astype(np.float64), clip.cpu().numpy()
+    for u, b in zip(*np.nonzero(g_clip != o_clip)):
+        assert table[u, b, g_clip[u, b]] <= table[u, b].min() * (1 + 1e-9), (u, b, g_clip[u, b], o_clip[u, b])
+    assert (np.abs(g_err - o_err) <= 1e-5 * o_err).all(), np.max(np.abs(g_err - o_err) / (o_err + 1e-300))
+    assert (np.abs(ref.cpu().numpy() - o_ref) <= 1e-5 * o_ref).all()
+    return windq.windq_fit_score_rescored_units(ws, W, G, unit_rows, len(cg))
+
+
+def scales(C, seed):
+    X = synth.activations_llm(64, C, seed=seed, device="cpu").float()
+    return X.abs().mean(0).to(DEV)
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 8, 9, 10, 13, 16, 17, 20, 21, 25, 32, 33, 40, 41, 61, 64])
+def test_every_share_of_the_clip_grid(windq, K):
+    """One to sixteen ratios per wavefront in one to four sweeps, with and without numbers below zero in the first."""
+    dtype = torch.float32 if K % 2 else torch.bfloat16
+    W = synth.weights_llm(130, 384, seed=K, device=DEV, dtype=dtype)
+    check(windq, W, scales(384, K), 64, 0, synth.clip_grid(K))
+    check(windq, W[:128], scales(384, K), 128, 64, synth.clip_grid(K))         # every column on the exact route
+
+
+@pytest.mark.parametrize("ratios", [
+    [0.1, 1.0], [0.95, 1.0], [0.96, 0.98, 0.99, 1.0],                          # nothing below the bound's ratio
+    [0.3, 0.5, 0.9], list(np.linspace(0.5, 0.95, 20)),                         # no ratio 1: every candidate is scored
+    list(np.linspace(0.9, 1.0, 20)), list(np.linspace(0.94, 1.0, 40)), list(np.linspace(0.01, 1.0, 33)),
+    [0.02 * i for i in range(1, 18)] + [0.9999, 1.0]])
+def test_other_grids(windq, ratios):
+    cg = torch.tensor(ratios, dtype=torch.float32)
+    W = synth.weights_llm(200, 512, seed=len(ratios), device=DEV)
+    check(windq, W, scales(512, 7), 128, 0, cg)
+    check(windq, W[:192], scales(512, 8), 64, 64, cg)
+
+
+@pytest.mark.parametrize("ppm", [5000, 300000])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_under_a_mask(windq, ppm, dtype):
+    W = synth.weights_llm(320, 512, seed=5, device=DEV, dtype=dtype)
+    s = scales(512, 6)
+    for G, unit_rows in ((128, 0), (256, 0), (64, 64)):
+        mask = windq.windq_salient_select(W, s, G, unit_rows, ppm)
+        check(windq, W, s, G, unit_rows, synth.clip_grid(20), mask=mask)
+
+
+def far_from_the_grid(R, G, n_extreme_scale):
+    """Every weight 0.45 steps from the nearest 8-bit grid point at ratio 1, but for the row's extremes: the error at
+    ratio 1 is 12 * 0.45^2 = 2.43 times what the ranges let expect.  The extremes' columns weigh little, so clipping costs
+    little."""
+    gen = torch.Generator().manual_seed(R + G)
+    code = torch.randint(12, 243, (R, G), generator=gen).double()
+    W = (-1.0 + (code + 0.45) * (2.0 / 255.0)).float()
+    W[:, 0], W[:, 1] = -1.0, 1.0
+    s = torch.ones(G)
+    s[:2] = n_extreme_scale
+    return W.to(DEV), s.to(DEV)
+
+
+def test_a_bound_that_proves_nothing(windq):
+    """Tiles leave candidates out, but the unit's bound stays below the error at ratio 1: it is scored again.  Per row at
+    ratio 0.94: clipping 2 * 0.4^2 * 0.06^2 = 0.00115; expected at ratio 1, 126.3 * (2/255)^2 / 12 = 0.00065; there in
+    fact, 2.43 times that = 0.00157."""
+    cg = torch.tensor([0.5, 0.6, 0.7, 0.8, 0.9, 0.94, 1.0])
+    W, s = far_from_the_grid(256, 128, 0.4)
+    assert check(windq, W, s, 128, 0, cg) == 1
+    for e in (0.1, 0.3, 0.35, 0.45, 0.5, 0.6, 0.9):
+        W, s = far_from_the_grid(256, 128, e)
+        check(windq, W, s, 128, 0, cg)
+        check(windq, W, s, 128, 0, synth.clip_grid(20))
+
+
+def test_tiles_that_disagree(windq):
+    """Units in which some tiles leave candidates out and others score them."""
+    W, s = far_from_the_grid(256, 128, 0.1)                           # clipping costs next to nothing: nothing may be left out
+    W2 = synth.weights_llm(256, 128, seed=1, device=DEV, dtype=torch.float32)
+    both = torch.cat([W, 20.0 * W2, W, 0.5 * W2])
+    check(windq, both, s, 128, 0, synth.clip_grid(20))
+    check(windq, torch.cat([W2, 1e-3 * W]), s, 128, 0, synth.clip_grid(40))
+    one_sided = both.clone()
+    one_sided[64:128] = one_sided[64:128].abs() + 0.01       # wavefronts that leave nothing out
+    check(windq, one_sided, s, 128, 0, synth.clip_grid(20))
+
+
+def test_values_that_are_not_finite(windq):
+    """A unit of NaN stays one, its neighbours are untouched."""
+    W = synth.weights_llm(128, 256, seed=9, device=DEV, dtype=torch.float32)
+    s = torch.ones(256, device=DEV)
+    want = windq.windq_fit_score_all_bits(W, s, 128, 0, synth.clip_grid(20))
+    bad = W.clone()
+    bad[70, 5] = float("nan")
+    got = windq.windq_fit_score_all_bits(bad, s, 128, 0, synth.clip_grid(20))
+    assert torch.equal(got[0][1], want[0][1]) and torch.equal(got[1][1], want[1][1])
+    bad[70, 5] = float("inf")
+    got = windq.windq_fit_score_all_bits(bad, s, 128, 0, synth.clip_grid(20))
+    assert torch.equal(got[0][1], want[0][1]) and torch.equal(got[1][1], want[1][1])
