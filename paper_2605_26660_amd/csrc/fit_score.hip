@@ -69,6 +69,7 @@
 
 #include "windq_common.hpp"
 #include "windq_feat.hpp"
+#include "windq_fit.hpp"
 #include "windq_ws.hpp"
 
 namespace windq {
@@ -104,9 +105,7 @@ constexpr int FS_FEAT_ONLY = 3;     // that first pass alone          // workgro
 // and the unit's noise has a standard deviation of at most 2^-23 sqrt(sum_tiles V).  The unit's
 // 8-bit candidates are scored again on the exact route when that exceeds NOISE_MAX times the
 // unit's 8-bit error at the chosen clip index.  (Measured against fp64, the actual deviation
-// is ~0.4 of this estimate: NOISE_MAX = 3e-6 keeps one standard deviation near 1e-6.)
-constexpr double NOISE_MAX = 3e-6;
-constexpr double NOISE_C1 = 4.0 * 3.552713678800501e-15 / (NOISE_MAX * NOISE_MAX);   // 4 * 2^-48 / NOISE_MAX^2
+// is ~0.4 of this estimate: NOISE_MAX = 3e-6 (windq_fit.hpp) keeps one standard deviation near 1e-6.)
 // 8-bit candidates that cannot win.  At clip ratio p a weight beyond the clipped range [p min, p max] is off by at
 // least its distance e from that range, at any bit-width: with C(p) = sum s_c^2 e^2, E_b(p) >= C(p).  As p falls C only
 // grows, and at a known rate: e <= (1-p) |max| (or |min|), so e(p') = e(p) + (p-p') |max| >= e(p) (1-p')/(1-p) and
@@ -120,7 +119,6 @@ constexpr double NOISE_C1 = 4.0 * 3.552713678800501e-15 / (NOISE_MAX * NOISE_MAX
 // on the list of units whose 8-bit candidates are all scored again.  So a tile's test decides speed, never the result.
 // Margin 1.25: with 1, single units of a batch miss the proof and are scored twice (a batch of 0.9 M to 5 M weights: 125 us, 119 with 1.25).
 constexpr float SKIP8_MARGIN = 1.25f;
-constexpr double BOUND_SLACK = 1e-4;
 constexpr float SKIP8_MAX_P = 0.95f;        // skip8_p: the grid's largest ratio up to here
 // A tile takes the exact sweep when one row holds more than 1 / ROW_SHARE of the sum of the
 // rows' squared ranges (that row would carry most of the tile's 8-bit error by itself).
@@ -1146,8 +1144,12 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 const int k = k0 + dk * i;
                 // left out: a lower bound takes the candidate's place, marked as one by its sign
                 if (!ONLY8 && (lane_r & 3) == 0 && i < s8) tot = -(double)(tile_clip * B.skip8_f.p[k > 0 ? k : 0]);
-                if (k >= 0 && (!ONLY8 || (lane_r & 3) == 0)) out[(lane_r & 3) * K + k] = tot;
-            } else if (lane_r < FS_KB * 5) {
+                if (ONLY8) {      // (past this XCD's L2: another workgroup may add it up, see fit_score_redo_kernel)
+                    if (k >= 0 && (lane_r & 3) == 0) __hip_atomic_store(out + k, tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else if (k >= 0) {
+                    out[(lane_r & 3) * K + k] = tot;
+                }
+            } else if (!ONLY8 && lane_r < FS_KB * 5) {
                 const int k = k0 + dk * (lane_r - FS_KB * 4);
                 if (k >= 0) {
                     float ratio = s4_over_s2;
@@ -1235,10 +1237,16 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
 }
 
 // The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
-// walks the list; with nothing listed every workgroup ends after reading the counters.
+// walks the list, each workgroup a run of consecutive tiles; with nothing listed every workgroup ends after reading the
+// counters.  The workgroup that scores a unit's last tile adds the tiles up again (in the order of the finalize kernel) and
+// corrects the unit's 8-bit error and clip index: a launch of its own for that took 4.5 us of every call, with nothing
+// to do in most.  The tiles' sums are stored and loaded past the L2s (device-scope atomic accesses), and a workgroup
+// waits for its stores before it adds its run to the unit's count of finished tiles: with a device-wide release and
+// acquire per tile instead, which write back and drop whole L2s, a matrix with all of its 108 units listed took 912 us.
 template <int DT, bool MASKED>
 __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const FitScoreArgs B) {
     extern __shared__ char smem[];
+    __shared__ uint32_t done;
     // (no table of the matrices' first tiles: indexed by a run-time value it would live in scratch memory)
     auto listed_tiles = [&](int i) -> int64_t {
         int64_t cnt = (int64_t)*B.m[i].redo_count;
@@ -1247,7 +1255,10 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
     };
     int64_t total = 0;
     for (int i = 0; i < B.n; ++i) total += listed_tiles(i);
-    for (int64_t w = blockIdx.x; w < total; w += gridDim.x) {
+    const int64_t per = (total + gridDim.x - 1) / gridDim.x;
+    const int64_t w_end = ((int64_t)blockIdx.x + 1) * per < total ? ((int64_t)blockIdx.x + 1) * per : total;
+    uint32_t run = 0;                // tiles of the current unit that this workgroup has scored
+    for (int64_t w = (int64_t)blockIdx.x * per; w < w_end; ++w) {
         int mi = 0;
         int64_t first = 0;
         for (; mi + 1 < B.n; ++mi) {
@@ -1257,91 +1268,57 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         }
         const FitScoreMat& A = B.m[mi];
         const int64_t local = w - first;
-        const int64_t li = local / A.g.tiles_per_unit;
+        const int64_t tpu = A.g.tiles_per_unit;
+        const int64_t li = local / tpu, t = local - li * tpu;
         const int64_t u = A.redo_list[li];
-        const TileCoord tc = tile_coord_of_unit(A.g, u, local - li * A.g.tiles_per_unit);
+        const TileCoord tc = tile_coord_of_unit(A.g, u, t);
         fit_score_tile<DT, MASKED, FS_ONLY8>(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
-        __syncthreads();      // the next tile overwrites this one's LDS
+        ++run;
+        if (w + 1 < w_end && t + 1 < tpu) {
+            __syncthreads();         // the next tile overwrites this one's LDS
+            continue;
+        }
+        const int32_t K = B.K, ncand = fit_score_ncand(K);
+        double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wavefront's sums have reached memory ...
+        __syncthreads();                                        // ... and the other wavefronts' too
+        if (threadIdx.x == 0) done = __hip_atomic_fetch_add(fit_redo_done(unit, K), run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + run;
+        __syncthreads();
+        run = 0;
+        if (done != (uint32_t)tpu) continue;
+        double* part = reinterpret_cast<double*>(smem);       // [FIN_PHASES][WINDQ_MAX_CLIP], then [WINDQ_MAX_CLIP]
+        static_assert((FIN_PHASES + 1) * WINDQ_MAX_CLIP * sizeof(double) <= FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
+        for (int i = threadIdx.x; i < FIN_PHASES * K; i += FS_THREADS) {
+            const int phase = i / K, k = i - phase * K;
+            double acc = 0.0;
+#pragma unroll 4
+            for (int64_t j = phase; j < tpu; j += FIN_PHASES) acc += __hip_atomic_load(unit + (size_t)j * ncand + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            part[phase * WINDQ_MAX_CLIP + k] = acc;
+        }
+        __syncthreads();
+        double* E = part + FIN_PHASES * WINDQ_MAX_CLIP;
+        if ((int)threadIdx.x < K) {
+            double acc = 0.0;
+#pragma unroll
+            for (int p = 0; p < FIN_PHASES; ++p) acc += part[p * WINDQ_MAX_CLIP + threadIdx.x];
+            E[threadIdx.x] = acc;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double best, bound;
+            const int bk = fit_least(E, K, &best, &bound);
+            A.err[u * WINDQ_N_ERR] = (float)best;
+            A.clip_idx[u * 4] = (uint8_t)bk;
+        }
+        __syncthreads();
     }
 }
 
-// Per unit: add the tiles' partial errors in a fixed order, pick the clip index with the
-// least error for each uniform bit-width (ties to the largest index), emit fp32.
-// REDO = false: every unit; a unit whose 8-bit error may hold too much of the short route's
-// rounding noise (see NOISE_MAX) is put on the list.  REDO = true: the listed units only,
-// after their 8-bit partials have been replaced.
+// The unit's last step by itself (with the unit features riding along, theirs does it: unit_features.hip).
 constexpr int FIN_THREADS = 1024;
-constexpr int FIN_PHASES = FIN_THREADS / 64;
-template <bool REDO>
-__global__ __launch_bounds__(FIN_THREADS) void fit_score_finalize_kernel(const FitScoreArgs B) {
-    __shared__ double part[FIN_PHASES][5 * WINDQ_MAX_CLIP + 12];
-    __shared__ double E[5 * WINDQ_MAX_CLIP + 12];
-    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
-    const FitScoreMat& A = B.m[mi];
-    int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
-    if (REDO) {
-        if (u >= (int64_t)*A.redo_count) return;
-        u = A.redo_list[u];
-    }
-    const int32_t K = B.K;
-    const int64_t tiles_per_unit = A.g.tiles_per_unit;
-    float* __restrict__ err = A.err;
-    uint8_t* __restrict__ clip_idx = A.clip_idx;
-    float* __restrict__ ref_energy = A.ref_energy;
-    const int32_t ncand = fit_score_ncand(K);
-    const double* base = A.partial + (size_t)u * (size_t)tiles_per_unit * (size_t)ncand;
-    const int phase = threadIdx.x >> 6;
-    // phase p adds tiles p, p+16, p+32, ... in order; the 16 phase sums are then added in order
-    for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) {
-        // (a sum that holds a lower bound, marked by its sign, is one itself and keeps the mark)
-        double acc = 0.0;
-        bool bound = false;
-#pragma unroll 4
-        for (int64_t t = phase; t < tiles_per_unit; t += FIN_PHASES) {
-            const double v = base[(size_t)t * ncand + cand];
-            bound |= v < 0.0;
-            acc += fabs(v);
-        }
-        part[phase][cand] = bound ? -acc : acc;
-    }
-    __syncthreads();
-    for (int32_t cand = threadIdx.x; cand < ncand; cand += FIN_THREADS) {
-        double acc = 0.0;
-        bool bound = false;
-#pragma unroll
-        for (int p = 0; p < FIN_PHASES; ++p) {
-            bound |= part[p][cand] < 0.0;
-            acc += fabs(part[p][cand]);
-        }
-        E[cand] = bound ? -acc : acc;
-    }
-    __syncthreads();
-    const int tid = threadIdx.x;
-    if (tid < 4) {
-        double best = 0.0, bound = INFINITY;
-        int bk = -1;
-        for (int k = 0; k < K; ++k) {       // (the last ratio is never left out)
-            const double e = E[tid * K + k];
-            if (e < 0.0) bound = fmin(bound, -e);
-            else if (bk < 0 || e <= best) {
-                best = e;
-                bk = k;
-            }
-        }
-        err[u * WINDQ_N_ERR + tid] = (float)best;
-        clip_idx[u * 4 + tid] = (uint8_t)bk;
-        // (tid 0: 8 bits) listed: too much noise, or a candidate that was left out is not proved to be worse
-        if (!REDO && tid == 0 && (E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best || bound * (1.0 - BOUND_SLACK) <= best)) {
-            const uint32_t pos = atomicAdd(A.redo_count, 1u);
-            A.redo_list[pos] = (uint32_t)u;
-        }
-    } else if (tid < 7) {
-        // ternary, binary, reference energy: the four column quarters, in order
-        const int j = tid - 4;
-        const double e = ((E[4 * K + j] + E[4 * K + 3 + j]) + E[4 * K + 6 + j]) + E[4 * K + 9 + j];
-        if (j < 2) err[u * WINDQ_N_ERR + 4 + j] = (float)e;
-        else if (ref_energy != nullptr) ref_energy[u] = (float)e;
-    }
+__global__ __launch_bounds__(FIN_THREADS) void fit_score_finalize_kernel(const FitFinalBatch B) {
+    extern __shared__ double fin_lds[];
+    fit_finalize_unit<FIN_THREADS>(B, blockIdx.x, fin_lds);
 }
 
 }  // namespace windq
@@ -1505,9 +1482,20 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         st = launch_tiles<FS_SCORE>(A, dtype, masked, lds, grid, hs);
     }
     if (st != WINDQ_OK) return st;
-    hipLaunchKernelGGL(fit_score_finalize_kernel<false>, dim3((unsigned)units), dim3(FIN_THREADS), 0, hs, A);
-    if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
-    // the units the finalize kernel listed: their 8-bit candidates on the exact route, finalized again
+    FitFinalBatch F;
+    F.n = n;
+    F.K = K;
+    for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) F.unit_start[i] = A.unit_start[i];
+    for (int32_t i = 0; i < WINDQ_MAX_BATCH; ++i)
+        F.m[i] = {A.m[i].partial, A.m[i].redo_count, A.m[i].redo_list, A.m[i].err, A.m[i].clip_idx, A.m[i].ref_energy, A.m[i].g.tiles_per_unit};
+    if (feat != nullptr) {
+        st = features_launch_rest(*feat, &F, hs);
+        if (st != WINDQ_OK) return st;
+    } else {
+        hipLaunchKernelGGL(fit_score_finalize_kernel, dim3((unsigned)units), dim3(FIN_THREADS), fit_finalize_lds_bytes(K), hs, F);
+        if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
+    }
+    // the units that step listed: their 8-bit candidates on the exact route
     const dim3 redo_grid((unsigned)(tiles < FS_REDO_GRID ? tiles : FS_REDO_GRID));
     auto launch_redo = [&](auto kernel) -> int {
         const int e = ensure_lds(reinterpret_cast<const void*>(kernel), lds);
@@ -1517,11 +1505,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     };
     if (dtype == WINDQ_BF16) st = masked ? launch_redo(&fit_score_redo_kernel<WINDQ_BF16, true>) : launch_redo(&fit_score_redo_kernel<WINDQ_BF16, false>);
     else st = masked ? launch_redo(&fit_score_redo_kernel<WINDQ_F32, true>) : launch_redo(&fit_score_redo_kernel<WINDQ_F32, false>);
-    if (st != WINDQ_OK) return st;
-    hipLaunchKernelGGL(fit_score_finalize_kernel<true>, dim3((unsigned)units), dim3(FIN_THREADS), 0, hs, A);
-    if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
-    if (feat != nullptr) return features_launch_rest(*feat, hs);
-    return WINDQ_OK;
+    return st;
 }
 
 // The first pass of the unit features by itself (windq_unit_features): the same tile kernel, scoring nothing.

@@ -28,7 +28,7 @@
 //           unit's weights and to count in a third.  W is read only for such units.
 // fp32 (31-bit keys, digits 11 + 11 + 9): one pass per further digit plus a counting pass
 // (2|w| > P99, exact in fp32), each re-deriving the prefix from the finished histograms; units
-// of up to 98304 weights do all of that in one launch, from registers (feat_small_f32_kernel).
+// of up to 98304 weights do all of that in one launch, from registers (feat_small_f32_unit).
 // Passes after the first re-read a matrix that was just streamed; up to the 256 MB
 // last-level cache they are served on chip.  Integer atomics only, fixed-order fp64
 // sums: results are bit-reproducible.
@@ -392,14 +392,14 @@ __device__ __forceinline__ void feat_tail(const FeatArgs& A, int64_t u, const Fe
 // first round of block moments, the activation scales and the refined counters travel
 // together with the first-digit histogram.
 template <int DT>
-__global__ __launch_bounds__(FT_THREADS) void feat_finish_kernel(const FeatBatch B) {
+__device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64_t block) {
     __shared__ double red[6 * FT_WAVES];
     __shared__ uint32_t sh_part[FT_THREADS];
     __shared__ uint32_t sh_out[4];
     __shared__ float smax_sh[FT_WAVES];
-    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
+    const int mi = batch_index(B.unit_start, B.n, block);
     const FeatArgs& A = B.m[mi];
-    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    const int64_t u = block - B.unit_start[mi];
     const int tid = threadIdx.x;
     const FeatTailIn in = feat_tail_load(A, u);      // requested now, used after the selection
     const uint32_t* h0 = A.hist + (size_t)u * FEAT_BINS;
@@ -497,15 +497,15 @@ __global__ __launch_bounds__(FT_THREADS) void feat_finish_kernel(const FeatBatch
 // (one unit of 768 x 128, 98304 weights, alone) the call takes 30.8 us, and 35.6 with a launch per pass.
 constexpr int64_t FEAT_SMALL = 98304;
 template <int NT, int PER>
-__global__ __launch_bounds__(NT) void feat_small_f32_kernel(const FeatBatch B) {
+__device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const int64_t block) {
     __shared__ uint32_t lhist[FEAT_BINS];
     __shared__ double red[6 * FT_WAVES];
     __shared__ uint32_t sh_part[NT / 64];
     __shared__ uint32_t sh_out[2];
     __shared__ float smax_sh[FT_WAVES];
-    const int mi = batch_index(B.unit_start, B.n, blockIdx.x);
+    const int mi = batch_index(B.unit_start, B.n, block);
     const FeatArgs& A = B.m[mi];
-    const int64_t u = (int64_t)blockIdx.x - B.unit_start[mi];
+    const int64_t u = block - B.unit_start[mi];
     const int32_t G = A.g.chunk_w;
     const int32_t pieces = G >> 3;
     const int32_t total = (int32_t)(A.g.R_u * pieces);
@@ -577,23 +577,43 @@ __global__ __launch_bounds__(NT) void feat_small_f32_kernel(const FeatBatch B) {
     feat_tail(A, u, in, (double)cnt, true, red, smax_sh);
 }
 
+// The features' last step, one workgroup per unit, and where fit+score is part of the call (FIT) its last step too, by
+// as many workgroups behind them: each is a chain of memory latencies that leaves the chip idle, and neither needs
+// the other.  PER = 0: the finish step after the passes; else units kept in registers.
+template <int DT, int NT, int PER, bool FIT>
+__global__ __launch_bounds__(NT) void feat_last_kernel(const FeatBatch B, const FitFinalBatch F) {
+    if (!FIT || (int64_t)blockIdx.x < B.units_total) {
+        if constexpr (PER == 0) feat_finish_unit<DT>(B, blockIdx.x);
+        else feat_small_f32_unit<NT, PER>(B, blockIdx.x);
+    } else {
+        extern __shared__ double fin_lds[];
+        fit_finalize_unit<NT>(F, (int64_t)blockIdx.x - B.units_total, fin_lds);
+    }
+}
+
+template <int DT, int NT, int PER>
+static void launch_last(const FeatBatch& B, const FitFinalBatch* fit, hipStream_t hs) {
+    const unsigned units = (unsigned)B.units_total;
+    if (fit != nullptr) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, true>), dim3(2 * units), dim3(NT), fit_finalize_lds_bytes(fit->K), hs, B, *fit);
+    else hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), 0, hs, B, FitFinalBatch{});
+}
+
 template <int DT>
-static int launch_rest(const FeatBatch& B, hipStream_t hs) {
+static int launch_rest(const FeatBatch& B, const FitFinalBatch* fit, hipStream_t hs) {
     if (DT == WINDQ_BF16) {
-        hipLaunchKernelGGL((feat_finish_kernel<DT>), dim3((unsigned)B.units_total), dim3(FT_THREADS), 0, hs, B);
+        launch_last<DT, FT_THREADS, 0>(B, fit, hs);
     } else if (B.largest_unit <= FEAT_SMALL) {
         // threads for about 64 weights each; 96 between 64 K and the limit (1024 threads have 128 registers each)
-        const dim3 units((unsigned)B.units_total);
-        if (B.largest_unit <= 16384) hipLaunchKernelGGL((feat_small_f32_kernel<256, 8>), units, dim3(256), 0, hs, B);
-        else if (B.largest_unit <= 32768) hipLaunchKernelGGL((feat_small_f32_kernel<1024, 4>), units, dim3(1024), 0, hs, B);
-        else if (B.largest_unit <= 65536) hipLaunchKernelGGL((feat_small_f32_kernel<1024, 8>), units, dim3(1024), 0, hs, B);
-        else hipLaunchKernelGGL((feat_small_f32_kernel<1024, 12>), units, dim3(1024), 0, hs, B);
+        if (B.largest_unit <= 16384) launch_last<WINDQ_F32, 256, 8>(B, fit, hs);
+        else if (B.largest_unit <= 32768) launch_last<WINDQ_F32, 1024, 4>(B, fit, hs);
+        else if (B.largest_unit <= 65536) launch_last<WINDQ_F32, 1024, 8>(B, fit, hs);
+        else launch_last<WINDQ_F32, 1024, 12>(B, fit, hs);
     } else {
         const dim3 blocks((unsigned)B.blocks_total);
         hipLaunchKernelGGL((feat_pass_kernel<DT, 1>), blocks, dim3(FT_THREADS), 0, hs, B, 1);
         hipLaunchKernelGGL((feat_pass_kernel<DT, 1>), blocks, dim3(FT_THREADS), 0, hs, B, 2);
         hipLaunchKernelGGL((feat_pass_kernel<DT, 2>), blocks, dim3(FT_THREADS), 0, hs, B, 0);
-        hipLaunchKernelGGL((feat_finish_kernel<DT>), dim3((unsigned)B.units_total), dim3(FT_THREADS), 0, hs, B);
+        launch_last<DT, FT_THREADS, 0>(B, fit, hs);
     }
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
@@ -604,8 +624,8 @@ int features_launch_init(const FeatBatch& B, hipStream_t hs) {
     return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 
-int features_launch_rest(const FeatBatch& B, hipStream_t hs) {
-    return B.dtype == WINDQ_BF16 ? launch_rest<WINDQ_BF16>(B, hs) : launch_rest<WINDQ_F32>(B, hs);
+int features_launch_rest(const FeatBatch& B, const FitFinalBatch* fit, hipStream_t hs) {
+    return B.dtype == WINDQ_BF16 ? launch_rest<WINDQ_BF16>(B, fit, hs) : launch_rest<WINDQ_F32>(B, fit, hs);
 }
 
 int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t unit_rows, FeatBatch* Bp) {
@@ -662,7 +682,7 @@ int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t uni
         B.init_start[i] = inits;
     }
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (blocks > (int64_t)0x7fffffff || inits > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (blocks > (int64_t)0x7fffffff || 2 * units > (int64_t)0x7fffffff || inits > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     B.dtype = items[0].W->dtype;
     B.blocks_total = blocks;
     B.units_total = units;
@@ -685,7 +705,7 @@ static int unit_features_launch(const windq_feat_item* items, int32_t n, int32_t
     hipStream_t hs = static_cast<hipStream_t>(stream);
     st = features_launch_init(B, hs);
     if (st == WINDQ_OK) st = features_launch_tiles(B, hs);
-    if (st == WINDQ_OK) st = features_launch_rest(B, hs);
+    if (st == WINDQ_OK) st = features_launch_rest(B, nullptr, hs);
     return st;
 }
 

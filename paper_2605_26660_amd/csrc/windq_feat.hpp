@@ -3,6 +3,7 @@
 #pragma once
 
 #include "windq_common.hpp"
+#include "windq_fit.hpp"
 #include "windq_ws.hpp"
 
 namespace windq {
@@ -56,7 +57,8 @@ int features_launch_init(const FeatBatch& B, hipStream_t hs);
 // The first pass by itself: per tile, moments, counts and the first-digit histogram.  (fit_score.hip)
 int features_launch_tiles(const FeatBatch& B, hipStream_t hs);
 // Everything after the first pass: bf16, the finish kernel (with the exact pass over the units it lists);
-// fp32, the refining passes and the finish kernel.  (unit_features.hip)
-int features_launch_rest(const FeatBatch& B, hipStream_t hs);
+// fp32, the refining passes and the finish kernel.  fit: nullptr, or the fit+score batch of the same matrices, whose
+// units are then finalized in the same launch.  (unit_features.hip)
+int features_launch_rest(const FeatBatch& B, const FitFinalBatch* fit, hipStream_t hs);
 
 }  // namespace windq

@@ -1,0 +1,131 @@
+// The last step of fit+score for a unit, shared by the kernel that takes it alone (fit_score.hip) and the ones
+// that take it beside the unit features' own last step (unit_features.hip).
+#pragma once
+
+#include "windq_common.hpp"
+#include "windq_ws.hpp"
+
+namespace windq {
+
+struct FitFinalMat {
+    double* partial;       // [n_tiles][5K+12]
+    uint32_t* redo_count;  // number of units listed for the exact 8-bit pass
+    uint32_t* redo_list;   // [U] their indices, in no particular order
+    float* err;
+    uint8_t* clip_idx;
+    float* ref_energy;
+    int64_t tiles_per_unit;
+};
+struct FitFinalBatch {
+    int32_t n;
+    int32_t K;
+    int64_t unit_start[WINDQ_MAX_BATCH + 1];
+    FitFinalMat m[WINDQ_MAX_BATCH];
+};
+
+// The 16 sums a unit's tiles are added in: sum p takes tiles p, p + 16, p + 32, ... in order; the sums are then added
+// in order.  Fixed whatever the workgroup's size, so that every kernel that adds tiles up gives the same bits.
+constexpr int FIN_PHASES = 16;
+
+#ifdef __HIPCC__
+
+// The short 8-bit route's rounding noise that sends a unit to the exact pass, and the margin by which the bound of a
+// left-out candidate has to exceed the chosen error (both derived in fit_score.hip).
+constexpr double NOISE_MAX = 3e-6;
+constexpr double NOISE_C1 = 4.0 * 3.552713678800501e-15 / (NOISE_MAX * NOISE_MAX);   // 4 * 2^-48 / NOISE_MAX^2
+constexpr double BOUND_SLACK = 1e-4;
+
+
+// One phase of one candidate.  (A sum that holds a lower bound, marked by its sign, is one itself and keeps the mark.)
+__device__ __forceinline__ double fit_phase_sum(const double* __restrict__ base, int64_t tiles_per_unit, int32_t ncand, int32_t cand, int phase) {
+    double acc = 0.0;
+    bool bound = false;
+#pragma unroll 4
+    for (int64_t t = phase; t < tiles_per_unit; t += FIN_PHASES) {
+        const double v = base[(size_t)t * ncand + cand];
+        bound |= v < 0.0;
+        acc += fabs(v);
+    }
+    return bound ? -acc : acc;
+}
+
+// Index of the least of E[0..K-1], ties to the largest index; entries below zero are bounds: skipped, the least of
+// their magnitudes to *bound_out.  (The last entry is never a bound.)
+__device__ __forceinline__ int fit_least(const double* E, int32_t K, double* best_out, double* bound_out) {
+    double best = 0.0, bound = INFINITY;
+    int bk = -1;
+    for (int k = 0; k < K; ++k) {
+        const double e = E[k];
+        if (e < 0.0) bound = fmin(bound, -e);
+        else if (bk < 0 || e <= best) {
+            best = e;
+            bk = k;
+        }
+    }
+    *best_out = best;
+    *bound_out = bound;
+    return bk;
+}
+
+// How many tiles of a listed unit have been scored again: a word in the unit's own partials (the first noise slot of its
+// first tile, which nothing reads once the unit is listed).
+__device__ __forceinline__ uint32_t* fit_redo_done(double* unit_partial, int32_t K) {
+    return reinterpret_cast<uint32_t*>(unit_partial + fit_score_noise_slot(K));
+}
+
+// Dynamic LDS of a workgroup that finalizes: [FIN_PHASES][ncand] phase sums, [ncand] totals.
+inline size_t fit_finalize_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES + 1) * (size_t)fit_score_ncand(K) * sizeof(double); }
+
+// Per unit: add the tiles' partial errors in a fixed order, pick the clip index with the
+// least error for each uniform bit-width (ties to the largest index), emit fp32.  A unit whose 8-bit
+// error may hold too much of the short route's rounding noise, or one of whose left-out candidates is not
+// proved to be worse, is put on the list.  Called by all NT threads of a workgroup.
+template <int NT>
+__device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_t block, double* __restrict__ lds) {
+    const int mi = batch_index(B.unit_start, B.n, block);
+    const FitFinalMat& A = B.m[mi];
+    const int64_t u = block - B.unit_start[mi];
+    const int32_t K = B.K;
+    const int64_t tiles_per_unit = A.tiles_per_unit;
+    const int32_t ncand = fit_score_ncand(K);
+    double* __restrict__ E = lds + FIN_PHASES * ncand;
+    double* base = A.partial + (size_t)u * (size_t)tiles_per_unit * (size_t)ncand;
+    for (int phase = threadIdx.x >> 6; phase < FIN_PHASES; phase += NT / 64)
+        for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) lds[phase * ncand + cand] = fit_phase_sum(base, tiles_per_unit, ncand, cand, phase);
+    __syncthreads();
+    for (int32_t cand = threadIdx.x; cand < ncand; cand += NT) {
+        double acc = 0.0;
+        bool bound = false;
+#pragma unroll
+        for (int p = 0; p < FIN_PHASES; ++p) {
+            const double v = lds[p * ncand + cand];
+            bound |= v < 0.0;
+            acc += fabs(v);
+        }
+        E[cand] = bound ? -acc : acc;
+    }
+    __syncthreads();
+    const int tid = threadIdx.x;
+    if (tid < 4) {
+        double best, bound;
+        const int bk = fit_least(E + tid * K, K, &best, &bound);
+        A.err[u * WINDQ_N_ERR + tid] = (float)best;
+        A.clip_idx[u * 4 + tid] = (uint8_t)bk;
+        // (tid 0: 8 bits) listed: too much noise, or a candidate that was left out is not proved to be worse
+        if (tid == 0 && (E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best || bound * (1.0 - BOUND_SLACK) <= best)) {
+            *fit_redo_done(base, K) = 0u;
+            const uint32_t pos = atomicAdd(A.redo_count, 1u);
+            A.redo_list[pos] = (uint32_t)u;
+        }
+    } else if (tid < 7) {
+        // ternary, binary, reference energy: the four column quarters, in order
+        const int j = tid - 4;
+        const double e = ((E[4 * K + j] + E[4 * K + 3 + j]) + E[4 * K + 6 + j]) + E[4 * K + 9 + j];
+        if (j < 2) A.err[u * WINDQ_N_ERR + 4 + j] = (float)e;
+        else if (A.ref_energy != nullptr) A.ref_energy[u] = (float)e;
+    }
+}
+
+#endif  // __HIPCC__
+
+}  // namespace windq
