@@ -139,6 +139,7 @@ struct FitScoreMat {
     float* ref_energy;
     Geometry g;
     float tau;         // columns with s_c^2 > tau * mean(s^2) of the chunk take the exact 8-bit route; 0: all do
+    int32_t parts;     // workgroups per tile: 0, one that takes every sweep; else see split_parts
     float* colsel;     // [n_chunks][colsel_words]: the chunks' column selection, written by the preparing kernel
     // first pass of the unit features (FS_SCORE_FEAT, FS_FEAT_ONLY), else unused
     double* fmoments;      // [n_tiles][4 column quarters][4]: sum w, sum w^2, sum |w|, count(|w| < 1e-6)
@@ -162,7 +163,7 @@ struct FitScoreArgs {
     float skip8_p;                               // clip ratio at which the tiles take the clipping error
     ClipGrid skip8_f;                            // [k]: a lower bound on the clipping error at ratio k over that at skip8_p
     double inv_G;                                // 1 / chunk_w
-    int64_t tile_start[WINDQ_MAX_BATCH + 1];     // first tile of matrix i in the grid; [n] = grid size
+    int64_t tile_start[WINDQ_MAX_BATCH + 1];     // first workgroup of matrix i in the grid; [n] = grid size
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     int64_t prep_start[WINDQ_MAX_BATCH + 1];     // first workgroup of matrix i in the preparing kernel's grid
     FitScoreMat m[WINDQ_MAX_BATCH];
@@ -188,6 +189,23 @@ inline size_t fit_score_lds_bytes(int32_t dtype, int32_t chunk_w, bool masked = 
 // share of the large ratios, whose 8-bit candidates are scored, at its end.  Numbers below zero (in the first places, where
 // K is no multiple of FS_KB) are scored as ratio 0 and dropped.
 __device__ __forceinline__ int32_t share_ratio(int32_t K, int32_t shares, int32_t i, int32_t v) { return K - shares * (FS_KB - i) + v; }
+
+// How a matrix's tiles are cut into workgroups: 0, one per tile, its wavefronts a sweep each over all columns; else
+// this many per tile, each sweep by all four wavefronts of one of them, a quarter of the columns each.  The matrix alone
+// decides, so that a batch gives the bits of the single calls (a quarter's sums are added in fp64, not in the lane's
+// fp32: other last bits).
+//   Up to 256 tiles there is at most one tile per CU, and what a call waits for is one wavefront's sweep over the whole
+//   chunk on an otherwise idle SIMD: every sweep gets a workgroup.  bf16 at chunk 128, 64 tiles, features and 40 ratios:
+//   70 -> 33 us; 256 tiles, 20 ratios: 46.7 -> 39.7 (512 tiles: 53.7, and 57.6 cut up: each part makes its own load and
+//   statistics).
+//   With one, two or three sweeps per tile (K <= 15) wavefronts go idle; all four share each sweep where a quarter of the
+//   chunk is worth a wavefront its own set of parameters and sums: K = 5, chunk 64, 2048 tiles: 37.7 -> 34.5, chunk 32,
+//   4096 tiles: 40.9 -> 43.2; K = 10, chunk 128, 5504 tiles: 213 -> 195, chunk 64, 11008 tiles: 219 -> 228; K = 15, chunk
+//   256, 2752 tiles: 283 -> 261, chunk 128, 5504 tiles: 255 -> 260.
+inline int32_t split_parts(const Geometry& g, int32_t shares) {
+    if (g.n_tiles <= 256) return shares;
+    return shares <= 3 && g.chunk_w >= 64 * shares ? 1 : 0;
+}
 
 // The 8-bit residual is ~1/500 of the range, so it is taken relative to an ANCHOR c: a grid
 // point of the 8-bit quantizer, with the code counted from it (qc = code - q0).
@@ -557,9 +575,13 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
 // MASKED: salient weights (Sec. 3.5) marked in A.mask take no part: they are left out of
 // the group statistics, and in every error sum their activation scale counts as zero.
 // rot spreads an uneven number of sweeps over the four SIMDs from tile to tile.
-template <int DT, bool MASKED, int MODE>
+// part < 0: the workgroup's wavefronts take a sweep each, over all columns.  part >= 0 (SPLIT): the workgroup takes sweeps
+// part, part + A.parts, ..., a quarter of the columns per wavefront; part 0 also makes what a tile produces once.
+template <int DT, bool MASKED, int MODE, bool SPLIT>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
-                                               const int rot, char* __restrict__ smem) {
+                                               const int rot, const int part, char* __restrict__ smem) {
+    const bool split = SPLIT && part >= 0;
+    const bool once = !split || part == 0;
     constexpr bool ONLY8 = MODE == FS_ONLY8;
     constexpr bool FEAT = MODE == FS_SCORE_FEAT || MODE == FS_FEAT_ONLY;
     constexpr bool SCORE = MODE != FS_FEAT_ONLY;
@@ -595,7 +617,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     load_tile_raw<DT, 2>(A.W, A.g.ld, tc, G, tile);      // 256 threads: four pieces each, two loads in flight at a time
     for (int32_t c = threadIdx.x; c < G; c += FS_THREADS) scol[c] = A.s[tc.col0 + c];
     if (MASKED) load_mask_tile(A.mask, A.mask_ld, tc, G, mtile);
-    if (FEAT) {
+    if (FEAT && once) {
         for (int32_t b = threadIdx.x; b < LH_DWORDS; b += FS_THREADS) lhist[b] = 0u;
     }
     // Column selection for the 8-bit candidate, prepared per chunk (fit_score_prepare_kernel): s_c
@@ -648,7 +670,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                     f_sw2 = fmaf(w[j], w[j], f_sw2);
                 }
             }
-            if (FINE) {
+            if (FINE && once) {
                 // key = bits 16..30 of the pattern; its pair (key >> 1) is dword pair - 8 * FEAT_FINE_COARSE0
                 // of the histogram, clamped: everything below the resolved range lands in the first
                 // dword, everything above in the last.  Bit 16 picks the half.
@@ -662,7 +684,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                         atomicAdd(reinterpret_cast<uint32_t*>(lh + off), max(bits & 0x10000u, 1u));
                     }
                 }
-            } else if (FEAT) {
+            } else if (FEAT && once) {
                 // bin of |w| = bits 20..30 of the pattern: dword (bin & 1023) of the LDS histogram, half
                 // (bin >> 10).  The upper half is |w| >= 2: rare, so the wavefront asks once per eight
                 // columns whether any of its rows needs it.
@@ -731,7 +753,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         }
     }
 
-    if (FINE) {
+    if (FINE && once) {
         // (every counter at most 8192: the halves never carry)
         // The record covers the FEAT_WIN first-digit bins that end 5 octaves above the mean: P99
         // and half of it lie 0.7-2.7 octaves above the mean |w| of Gaussian to heavy-tailed
@@ -770,7 +792,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             f_cnt = (float)cnt;
         }
         __syncthreads();        // the scratch is free for the sums from here on
-    } else if (FEAT) {
+    } else if (FEAT && once) {
         // the tile's histogram into the unit's (every bin at most 8192: the halves never carry)
         uint32_t* __restrict__ gh = A.fhist + (size_t)tc.u * FEAT_BINS;
         const uint32_t thr_bin = (__float_as_uint(A.sparse_thr) >> 20) & 1023u;      // 1e-6 lies far below 2: lower half
@@ -801,7 +823,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     // The tile's sums over rows wait in the scratch (columns FS_NRED ..) for the first clip pass,
     // whose sums they are collected with; a wavefront without a pass collects them by themselves.
     const size_t tile_index = (size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t;
-    if (FEAT) {
+    if (FEAT && once) {
         const int lane_f = fresh_lane();
         // sum |w| stays fp64: lanes through the wavefront's scratch, four at a time, then sixteen, in order
         double* __restrict__ dred = reinterpret_cast<double*>(red);
@@ -933,7 +955,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         const int lane_r = fresh_lane();
         if (lane_r >= tc.nrows) acc3[0] = acc3[1] = acc3[2] = accc[0] = 0.0f;    // (a row past the end has range 0)
         rows_deposit<NROW>(acc3, red, lane_r, ACC3_COL);
-        if (bounds) {
+        if (bounds || split) {
             if (MASKED) accc[1] *= (mx - mn) * (mx - mn);
             float none[1] = {0.0f};
             wave_sums_maxes(accc, none);
@@ -953,8 +975,12 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     const float skip8_above = s2_rg2 * (SKIP8_MARGIN / (12.0f * 65025.0f));
     int32_t ncollect = ONLY8 ? FS_NRED : NROW;         // columns the next collection takes
 
-    // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4.
-    for (int v = (wave - rot) & (FS_WAVES - 1); v < B.shares; v += FS_WAVES) {
+    // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4, or by
+    // quarters to all of them.
+    const int32_t sc0 = split ? qc0 : 0, sc1 = split ? qc1 : G;
+    const int vstep = split ? A.parts : FS_WAVES;
+    int half = 0;
+    for (int v = split ? part : ((wave - rot) & (FS_WAVES - 1)); v < B.shares; v += vstep) {
         const int32_t k0 = share_ratio(K, B.shares, 0, v), dk = B.shares;       // the sweep's ratio i: k0 + dk * i
         // the sweep's first ratios whose 8-bit candidate may be left out (skip8_f falls as k grows)
         int32_t skip_here = 0;
@@ -1042,7 +1068,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 const char* __restrict__ wrow = tile + lane_v * row_bytes;
                 const uint8_t* __restrict__ mrow = mtile + lane_v * mstride;
                 if (ONLY8) {
-                    for (int32_t c = 0; c < G; c += 8) {
+                    for (int32_t c = sc0; c < sc1; c += 8) {
                         float w[8];
                         read8<DT>(wrow, c, w);
                         const float4 sa = *reinterpret_cast<const float4*>(scol + c);
@@ -1056,7 +1082,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                         for (int j = 0; j < 8; ++j) score_weight_8<AN, NORM>(w[j], s8[j], P, Q[0], M, acc);
                     }
                 } else {
-                    for (int32_t c = 0; c < G; c += 4) {
+                    for (int32_t c = sc0; c < sc1; c += 4) {
                         float w[4];
                         read4<DT>(wrow, c, w);
                         const float4 sa = *reinterpret_cast<const float4*>(scol + c);
@@ -1093,7 +1119,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 const uint8_t* __restrict__ mrow = mtile + lane_v * mstride;
                 auto sweep_short = [&](auto s8_t) {
                     constexpr int S8 = decltype(s8_t)::value;
-                    for (int32_t c = 0; c < G; c += 8) {
+                    for (int32_t c = sc0; c < sc1; c += 8) {
                         float w[8];
                         read8<DT>(wrow, c, w);
                         const float4 sa = *reinterpret_cast<const float4*>(sshort + c);
@@ -1116,6 +1142,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 for (int i = 0; i < FS_KB; ++i) nz[i] = acc[i][0] * (P[i].nd[0] * P[i].nd[0]) * 65025.0f;
                 for (int32_t hi = 0; hi < nh; ++hi) {
                     const int32_t c = __builtin_amdgcn_readfirstlane(hlist[hi]);
+                    if (split && (c < sc0 || c >= sc1)) continue;
                     const float w = read1<DT>(wrow, c);
                     float sc = scol[c];
                     if (MASKED) sc = ((mrow[c >> 3] >> (c & 7)) & 1u) != 0u ? 0.0f : sc;
@@ -1137,8 +1164,18 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             }
             rows_deposit<NROW>(flat, red, lane_r, 0);
             double tot = rows_collect<NROW>(red, lane_r, ncollect);
-            if (!ONLY8 && ncollect > FS_NRED) store_extra(lane_r, tot);
+            if (!ONLY8 && once && ncollect > FS_NRED) store_extra(lane_r, tot);
             ncollect = FS_NRED;
+            if (split) {         // the quarters' sums, in order, by the first wavefront (s1tab's quarters are read by now)
+                static_assert(FS_NRED <= TILE_ROWS / 2, "two sweeps' sums: the next sweep's are laid down while these are read");
+                double* __restrict__ qsum = s1tab + half;
+                half ^= TILE_ROWS / 2;
+                if (lane_r < FS_NRED) qsum[wave * TILE_ROWS + lane_r] = tot;
+                __syncthreads();
+                if (wave != 0) continue;
+                if (lane_r < FS_NRED)
+                    tot = ((qsum[lane_r] + qsum[TILE_ROWS + lane_r]) + qsum[2 * TILE_ROWS + lane_r]) + qsum[3 * TILE_ROWS + lane_r];
+            }
             if (lane_r < FS_KB * 4) {
                 const int i = lane_r >> 2;
                 const int k = k0 + dk * i;
@@ -1159,7 +1196,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             }
         }
     }
-    if (!ONLY8 && ncollect > FS_NRED) {     // no sweep fell to this wavefront
+    if (!ONLY8 && !split && ncollect > FS_NRED) {     // no sweep fell to this wavefront
         const int lane_r = fresh_lane();
         store_extra(lane_r, rows_collect<NROW>(red, lane_r, NROW));
     }
@@ -1226,14 +1263,19 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
     }
 }
 
-template <int DT, bool MASKED, int MODE>
+template <int DT, bool MASKED, int MODE, bool SPLIT>
 __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScoreArgs B) {
     extern __shared__ char smem[];
     const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
-    const int64_t local = (int64_t)blockIdx.x - B.tile_start[mi];
+    int64_t local = (int64_t)blockIdx.x - B.tile_start[mi];
+    int part = -1;
+    if (SPLIT && A.parts > 0) {         // all tiles' first parts, then all tiles' second parts, ...
+        part = (int)((uint32_t)local / (uint32_t)A.g.n_tiles);
+        local -= (int64_t)part * A.g.n_tiles;
+    }
     const TileCoord tc = tile_coord(A.g, local);
-    fit_score_tile<DT, MASKED, MODE>(B, A, tc, blockIdx.x & (FS_WAVES - 1), smem);
+    fit_score_tile<DT, MASKED, MODE, SPLIT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, smem);
 }
 
 // The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
@@ -1272,7 +1314,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const int64_t li = local / tpu, t = local - li * tpu;
         const int64_t u = A.redo_list[li];
         const TileCoord tc = tile_coord_of_unit(A.g, u, t);
-        fit_score_tile<DT, MASKED, FS_ONLY8>(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
+        fit_score_tile<DT, MASKED, FS_ONLY8, false>(B, A, tc, (int)(w & (FS_WAVES - 1)), -1, smem);
         ++run;
         if (w + 1 < w_end && t + 1 < tpu) {
             __syncthreads();         // the next tile overwrites this one's LDS
@@ -1383,13 +1425,19 @@ static int launch_tiles_untimed(const FitScoreArgs& A, int32_t dtype, bool maske
         hipLaunchKernelGGL(kernel, grid, dim3(FS_THREADS), lds, hs, A);
         return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
     };
-    constexpr bool CAN_MASK = MODE == FS_SCORE;
-    if (dtype == WINDQ_BF16) {
-        if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_BF16, CAN_MASK, MODE>);
-        return launch(&fit_score_kernel<WINDQ_BF16, false, MODE>);
-    }
-    if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_F32, CAN_MASK, MODE>);
-    return launch(&fit_score_kernel<WINDQ_F32, false, MODE>);
+    constexpr bool CAN_MASK = MODE == FS_SCORE, CAN_SPLIT = MODE != FS_FEAT_ONLY;
+    bool split = false;
+    for (int32_t i = 0; i < A.n; ++i) split |= A.m[i].parts > 0;
+    auto by_input = [&](auto split_t) -> int {
+        constexpr bool SPLIT = decltype(split_t)::value;
+        if (dtype == WINDQ_BF16) {
+            if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_BF16, CAN_MASK, MODE, SPLIT>);
+            return launch(&fit_score_kernel<WINDQ_BF16, false, MODE, SPLIT>);
+        }
+        if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_F32, CAN_MASK, MODE, SPLIT>);
+        return launch(&fit_score_kernel<WINDQ_F32, false, MODE, SPLIT>);
+    };
+    return split ? by_input(std::integral_constant<bool, CAN_SPLIT>{}) : by_input(std::false_type{});
 }
 
 // feat: nullptr, or the filled feature batch of the same matrices: the main kernel then also makes the
@@ -1456,10 +1504,11 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         // tau = 1 every column takes the exact route.
         const float t = 7e-5f * (float)chunk_w * (float)M.g.R_u;
         M.tau = t < 1.0f ? 0.0f : t;
+        M.parts = split_parts(M.g, A.shares);
         A.tile_start[i] = tiles;
         A.unit_start[i] = units;
         A.prep_start[i] = preps;
-        tiles += M.g.n_tiles;
+        tiles += M.g.n_tiles * (M.parts > 0 ? M.parts : 1);
         units += M.g.U;
         preps += (M.g.n_chunks + FS_PREP_CHUNKS - 1) / FS_PREP_CHUNKS + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
     }

@@ -1,0 +1,63 @@
+"""fit+score where a tile's sweeps go to several workgroups, or all wavefronts share a sweep by columns: at the sizes where
+the cut changes, against the oracle (errors 1e-5, clip indices but for ties of 1e-9), and a batch of both kinds against
+the single calls, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import windq_oracle as O
+from paper_2605_26660_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def inputs(R, C, seed, dtype):
+    W = synth.weights_llm(R, C, seed=seed, device=DEV, dtype=dtype)
+    s = synth.activations_llm(64, C, seed=seed, device=DEV).float().abs().mean(0)
+    return W, s
+
+
+def compare(W, s, G, unit_rows, cg, out, mask=None):
+    keep = None if mask is None else np.unpackbits(mask.cpu().numpy(), axis=1, bitorder="little")[:, :W.shape[1]] == 0
+    o_err, o_clip, o_ref, table = O.fit_score_all_bits(W.float().cpu().numpy(), s.cpu().numpy(), G, unit_rows, cg.numpy(), keep=keep)
+    g_err, g_clip = out[0].cpu().numpy().astype(np.float64), out[1].cpu().numpy()
+    for u, b in zip(*np.nonzero(g_clip != o_clip)):
+        assert table[u, b, g_clip[u, b]] <= table[u, b].min() * (1 + 1e-9), (u, b, g_clip[u, b], o_clip[u, b])
+    assert (np.abs(g_err - o_err) <= 1e-5 * o_err).all(), np.max(np.abs(g_err - o_err) / (o_err + 1e-300))
+    assert (np.abs(out[2].cpu().numpy() - o_ref) <= 1e-5 * o_ref).all()
+
+
+@pytest.mark.parametrize("tiles", [1, 256, 257])
+@pytest.mark.parametrize("G,K", [(8, 5), (40, 10), (64, 5), (64, 6), (120, 10), (128, 10), (184, 15), (192, 15), (64, 21)])
+def test_at_the_edges_of_the_cut(windq, tiles, G, K):
+    """Chunks on both sides of 64 columns per sweep, widths whose quarters are uneven or empty, 256 and 257 tiles; the last
+    tile is not full."""
+    rows = 64 * tiles - 5
+    W, s = inputs(rows, G, tiles + G + K, torch.float32 if K % 2 else torch.bfloat16)
+    cg = synth.clip_grid(K)
+    compare(W, s, G, 0, cg, windq.windq_fit_score_all_bits(W, s, G, 0, cg))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("G,unit_rows,K", [(128, 0, 20), (64, 0, 40), (64, 64, 20), (256, 0, 64), (96, 0, 1)])
+def test_small_matrices_of_every_route(windq, G, unit_rows, K, dtype):
+    """With and without a mask, whole columns (the short route) and units of one tile (every column exact)."""
+    W, s = inputs(448, 4 * G, G + K, dtype)
+    cg = synth.clip_grid(K)
+    compare(W, s, G, unit_rows, cg, windq.windq_fit_score_all_bits(W, s, G, unit_rows, cg))
+    mask = windq.windq_salient_select(W, s, G, unit_rows, 30000)
+    compare(W, s, G, unit_rows, cg, windq.windq_fit_score_all_bits(W, s, G, unit_rows, cg, mask=mask), mask=mask)
+
+
+@pytest.mark.parametrize("K", [5, 10, 20, 40])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_a_batch_of_small_and_large_equals_the_single_calls(windq, dtype, K):
+    shapes = [(130, 256), (64 * 140, 256), (64, 128), (3000, 768)]
+    mats = [inputs(r, c, 10 + i, dtype) for i, (r, c) in enumerate(shapes)]
+    cg = synth.clip_grid(K)
+    batch = windq.windq_features_fit_score_batch([m[0] for m in mats], [m[1] for m in mats], 128, 0, cg)
+    for (W, s), got in zip(mats, batch):
+        feat = windq.windq_unit_features(W, s, 128, 0)
+        want = (feat, *windq.windq_fit_score_all_bits(W, s, 128, 0, cg))
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
