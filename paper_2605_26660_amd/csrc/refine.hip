@@ -17,8 +17,10 @@
 // 128), read eight weights at a time by register indexing: a tile staged in LDS (17 KB) leaves room for two wavefronts
 // per SIMD, too few to fill the ALU.  LDS only turns the tile round on its way in, 128 bytes of every row at a
 // time, and the packed codes on their way out.  Wider rows stay in LDS.  Refining a 7B-shaped block at 2 bits, three rounds:
-// 303 us (610 with the tile in LDS, a select per weight for a mask that is not there, and passes of their own for error
-// and codes); five wavefronts per SIMD would spill (1.4 ms), an unrolled pair of blocks is 7 % slower.
+// 285 us (610 with the tile in LDS, a select per weight for a mask that is not there, and passes of their own for error
+// and codes; 303 with a code and a product by it per ternary weight, base-3 bytes by integer multiplies, and the sign in
+// a binary weight's residual); five wavefronts per SIMD would spill (1.4 ms), an unrolled pair of blocks is 7 % slower, and
+// s_c^2 read from LDS weight by weight between a ternary round's adds costs 13 us.
 #include <float.h>
 
 #include "windq_common.hpp"
@@ -138,6 +140,25 @@ __device__ __forceinline__ void load_rows(const RefineArgs& A, const TileCoord& 
     __syncthreads();
 }
 
+// Adds p to n and a to d in the lanes whose |t| is above 0.5 (or NaN), by a compare that writes the execution mask: three
+// vector instructions where a select of two fp64 values takes seven.
+__device__ __forceinline__ void add_where_above_half(float t, double p, double a, double& n, double& d) {
+    uint64_t all;
+    asm volatile("s_mov_b64 %2, exec\n\t"
+                 "v_cmpx_nle_f32_e64 vcc, |%3|, 0.5\n\t"
+                 "v_add_f64 %0, %0, %4\n\t"
+                 "v_add_f64 %1, %1, %5\n\t"
+                 "s_mov_b64 exec, %2"
+                 : "+v"(n), "+v"(d), "=&s"(all)
+                 : "v"(t), "v"(p), "v"(a)
+                 : "vcc");
+}
+
+// bits = 2 bits + (w >= 0): a compare into the carry and an add with carry.
+__device__ __forceinline__ void push_not_negative(uint32_t& bits, float w) {
+    asm("v_cmp_le_f32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(w) : "vcc");
+}
+
 // One group: its row, its protection bits (masked calls), s_c^2 of the columns.
 template <int DT, bool MASKED, typename Row>
 struct RefineGroup {
@@ -146,6 +167,7 @@ struct RefineGroup {
     const double* acol;
     int32_t G;
     bool protects;              // MASKED: the item has a mask (else its mask bytes are zeros)
+    bool finite;                // every s_c^2 of the chunk is
 
     __device__ __forceinline__ uint32_t bits(int32_t c) const { return MASKED ? mrow[c >> 3] : 0u; }
     __device__ __forceinline__ bool kept(uint32_t m, int j) const { return !MASKED || ((m >> j) & 1u) == 0u; }
@@ -186,7 +208,9 @@ struct RefineGroup {
     // The sums of one round of the uniform refinement.  S0 = sum a and T0 = sum a w do not depend on the
     // codes: the first round computes them (FIRST), later rounds reuse them; the
     // order of every sum is the column order either way.
-    template <bool FIRST>
+    // TWO: 2 bits.  s_c^2 has at most 48 significant bits, so s_c^2 q^2 is exact for q up to 3, and a fused multiply-add
+    // rounds as the product and the sum do.
+    template <bool FIRST, bool TWO>
     __device__ __forceinline__ void uniform_sums(float lo, float inv, float qmax, double& S0, double& T0, double& S1, double& S2,
                                                  double& T1) const {
         if (FIRST) S0 = T0 = 0.0;
@@ -206,12 +230,13 @@ struct RefineGroup {
                     T0 = T0 + a * wd;
                 }
                 S1 = S1 + aq;
-                S2 = S2 + aq * q;
+                S2 = TWO ? __builtin_fma(aq, q, S2) : S2 + aq * q;
                 T1 = T1 + aq * wd;
             }
         });
     }
 
+    template <bool TWO>
     __device__ __forceinline__ void uniform(float qmax, int n_iter, float* lo_io, float* d_io) const {
         float lo = *lo_io, d = *d_io;
         double S0 = 0.0, T0 = 0.0;
@@ -219,8 +244,8 @@ struct RefineGroup {
             if (!(d >= FLT_MIN)) break;
             const float inv = 1.0f / d;
             double S1, S2, T1;
-            if (it == 0) uniform_sums<true>(lo, inv, qmax, S0, T0, S1, S2, T1);
-            else uniform_sums<false>(lo, inv, qmax, S0, T0, S1, S2, T1);
+            if (it == 0) uniform_sums<true, TWO>(lo, inv, qmax, S0, T0, S1, S2, T1);
+            else uniform_sums<false, TWO>(lo, inv, qmax, S0, T0, S1, S2, T1);
             const double det = S0 * S2 - S1 * S1;
             if (!(det > 0.0)) break;
             const double d_new = (S0 * T1 - S1 * T0) / det;
@@ -234,13 +259,29 @@ struct RefineGroup {
         *d_io = d;
     }
 
+    // q = clamp(rne(w / gamma)) is the sign of w where |w / gamma| > 0.5, else 0.  Without a mask the sums are
+    // therefore those of s_c^2 |w| and of s_c^2 over these weights: the terms left out are zeros, the others have the same
+    // bits as (s_c^2 q) w.  (A column whose s_c^2 is not finite makes both sums infinite or NaN, their quotient NaN: no round
+    // changes gamma.)
     __device__ __forceinline__ float ternary(int n_iter, float gamma) const {
+        if (!MASKED && !finite) return gamma;
         for (int it = 0; it < n_iter; ++it) {
             if (!(gamma >= FLT_MIN)) break;
             const float inv = 1.0f / gamma;
             double N1 = 0.0, D1 = 0.0;
             row.blocks(G, [&](int32_t c, const float (&w)[8]) {
                 const uint32_t m = bits(c);
+                if constexpr (!MASKED) {        // (all eight products first: the adds do not wait for LDS one by one)
+                    double a[8], p[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) a[j] = acol[c + j];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) p[j] = a[j] * (double)fabsf(w[j]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) add_where_above_half(w[j] * inv, p[j], a[j], N1, D1);
+                    return;
+                }
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const float t = w[j] * inv;
@@ -289,7 +330,7 @@ struct RefineGroup {
             for (int j = 0; j < 8; ++j) {
                 const float t = (w[j] - of) * inv;
                 const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(t), 0.0f, qmax);
-                const double what = (double)of + (double)q * (double)sc;
+                const double what = __builtin_fma((double)q, (double)sc, (double)of);      // (the product is exact)
                 const double d = (double)w[j] - what;
                 e = e + weight(m, c, j) * d * d;
                 code[j] = kept(m, j) ? (uint32_t)q : 0u;
@@ -299,31 +340,42 @@ struct RefineGroup {
         return e;
     }
 
+    // Eight weights of which the first has place AT in its byte of five trits; sum: sum of q 3^place of the byte under way.
+    template <int AT>
+    __device__ __forceinline__ void ternary_block(int32_t c, const float (&w)[8], float sc, float inv, double& e, float& sum, uint8_t*& dst) const {
+        constexpr float POW[5] = {1.0f, 3.0f, 9.0f, 27.0f, 81.0f};
+        const uint32_t m = bits(c);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int at = (AT + j) % 5;
+            const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(w[j] * inv), -1.0f, 1.0f);
+            const double d = (double)w[j] - (double)(sc * q);                // sc q is exact
+            e = e + weight(m, c, j) * d * d;
+            const float trit = kept(m, j) ? q : -1.0f;                       // less one: a protected weight's trit is 0
+            sum = at == 0 ? trit : __builtin_fmaf(trit, POW[at], sum);
+            if (at == 4) *dst++ = (uint8_t)(uint32_t)(sum + 121.0f);
+        }
+    }
     __device__ __forceinline__ double ternary_finish(float sc, uint8_t* dst) const {
         const float inv = sc >= FLT_MIN ? 1.0f / sc : 0.0f;
         double e = 0.0;
-        uint32_t byte = 0, mul = 1;
-        int32_t nb = 0;
+        float sum = 0.0f;
+        int at = 0;                                                          // the same in every lane
         row.blocks(G, [&](int32_t c, const float (&w)[8]) {
-            const uint32_t m = bits(c);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float q = __builtin_amdgcn_fmed3f(__builtin_rintf(w[j] * inv), -1.0f, 1.0f);
-                const double d = (double)w[j] - (double)sc * (double)q;
-                e = e + weight(m, c, j) * d * d;
-                byte += (kept(m, j) ? (uint32_t)((int32_t)q + 1) : 0u) * mul;
-                mul *= 3;
-                if (mul == 243) {
-                    dst[nb++] = (uint8_t)byte;
-                    byte = 0;
-                    mul = 1;
-                }
+            switch (at) {
+                case 0: ternary_block<0>(c, w, sc, inv, e, sum, dst); break;
+                case 1: ternary_block<1>(c, w, sc, inv, e, sum, dst); break;
+                case 2: ternary_block<2>(c, w, sc, inv, e, sum, dst); break;
+                case 3: ternary_block<3>(c, w, sc, inv, e, sum, dst); break;
+                default: ternary_block<4>(c, w, sc, inv, e, sum, dst); break;
             }
+            at = at >= 2 ? at - 2 : at + 3;                                  // eight further, by fives
         });
-        if (mul != 1) dst[nb] = (uint8_t)byte;
+        if (at != 0) *dst = (uint8_t)(uint32_t)(sum + (at == 1 ? 1.0f : (at == 2 ? 4.0f : (at == 3 ? 13.0f : 40.0f))));
         return e;
     }
 
+    // (|w| - alpha is the residual of w but for its sign, which its square does not show)
     __device__ __forceinline__ double binary_finish(float sc, uint8_t* dst) const {
         double e = 0.0;
         row.blocks(G, [&](int32_t c, const float (&w)[8]) {
@@ -331,12 +383,12 @@ struct RefineGroup {
             uint32_t byte = 0;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const bool plus = w[j] >= 0.0f;
-                const double d = (double)w[j] - (plus ? (double)sc : -(double)sc);
+                const double d = (double)fabsf(w[j]) - (double)sc;
                 e = e + weight(m, c, j) * d * d;
-                byte |= (plus && kept(m, j) ? 1u : 0u) << j;
             }
-            dst[c >> 3] = (uint8_t)byte;
+#pragma unroll
+            for (int j = 7; j >= 0; --j) push_not_negative(byte, w[j]);
+            dst[c >> 3] = (uint8_t)(byte & ~m);
         });
         return e;
     }
@@ -394,10 +446,13 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
     const int32_t turn = TILE_ROWS * (NV == 0 || stride > RF_SLAB_STRIDE ? stride : RF_SLAB_STRIDE);
     uint8_t* mtile = reinterpret_cast<uint8_t*>(tile + turn);                    // the tile's mask bytes (masked calls)
     RefineGroup<DT, MASKED, typename RefineRowOf<DT, NV>::type> g;
+    bool finite = true;
     for (int32_t c = lane; c < G; c += RF_THREADS) {
         const double sv = (double)A.s[tc.col0 + c];
         acol[c] = sv * sv;
+        finite = finite && sv * sv < (double)INFINITY;
     }
+    g.finite = __all(finite);
     if (MASKED) {
         if (A.mask != nullptr) {
             load_mask_tile(A.mask, A.mask_ld, tc, G, mtile);
@@ -433,7 +488,8 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
             float mn, mx;
             g.min_max(&mn, &mx);
             uniform_params(mn, mx, p, qmax, &of, &sc);
-            g.uniform(qmax, B.n_iter, &of, &sc);
+            if (a == 4) g.template uniform<true>(qmax, B.n_iter, &of, &sc);
+            else g.template uniform<false>(qmax, B.n_iter, &of, &sc);
             switch (a) {
                 case 1: err = g.template uniform_finish<8>(sc, of, dst); break;
                 case 2: err = g.template uniform_finish<4>(sc, of, dst); break;

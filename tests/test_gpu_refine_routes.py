@@ -1,0 +1,76 @@
+"""windq_refine_plan where its kernels can go wrong: trits whose bytes straddle blocks of eight weights, weights at the ends
+of the ternary rule, scales that are not finite, and launches that come to their units in the order of their cost.
+Against the oracle bit for bit, or against calls small enough to keep the matrix's own order."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import windq_oracle as O
+from paper_2605_26660_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def against_oracle(windq, W, s, G, action, n_iter, ppm=0, err=True):
+    cg = synth.clip_grid(5)
+    U, R_u = windq.n_units(W.shape[0], W.shape[1], G, 0)
+    gen = torch.Generator().manual_seed(U)
+    clip = torch.randint(0, 5, (U, 4), generator=gen, dtype=torch.uint8)
+    off = windq.windq_plan_layout(action, R_u, G)
+    mask = keep = None
+    Wn, sn = W.float().cpu().numpy(), s.cpu().numpy()
+    if ppm:
+        mask = windq.windq_salient_select(W, s, G, 0, ppm)
+        keep = O.salient_select(Wn, sn, G, 0, ppm)
+    poison = torch.full((max(int(off[-1]), 16),), 0xAB, dtype=torch.uint8, device=DEV)
+    codes, scale, offset, e = windq.windq_refine_plan(W, s, G, 0, action.to(DEV), clip.to(DEV), cg, off.to(DEV), n_iter, codes=poison, mask=mask)
+    with np.errstate(all="ignore"):
+        oc, osc, oof, oe = O.refine_plan(Wn, sn, G, 0, action.numpy(), clip.numpy(), cg.numpy(), off.numpy(), n_iter, keep=keep)
+    assert np.array_equal(codes.cpu().numpy()[:int(off[-1])], oc)
+    assert np.array_equal(scale.cpu().numpy().view(np.uint32), osc.view(np.uint32))
+    assert np.array_equal(offset.cpu().numpy().view(np.uint32), oof.view(np.uint32))
+    if err:
+        assert np.all(np.abs(e.cpu().numpy() - oe) <= 1e-5 * oe)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("G", [8, 16, 24, 32, 40, 48, 64, 104])
+def test_trits_at_every_place(windq, G, dtype):
+    """Chunk widths that end at each of the five places of a byte, with and without a mask."""
+    W = synth.weights_llm(9, 4 * G, seed=G, device=DEV, dtype=dtype)
+    s = torch.rand(4 * G, generator=torch.Generator().manual_seed(G)).to(DEV) + 0.1
+    action = torch.tensor([5, 6, 4, 5], dtype=torch.uint8)
+    for n_iter in (0, 1, 3):
+        against_oracle(windq, W, s, G, action, n_iter)
+    against_oracle(windq, W, s, G, action, 2, ppm=200000)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_weights_at_the_ends_of_the_ternary_rule(windq, dtype):
+    """|w| = gamma / 2 and 3 gamma / 2 (ties go to the even code), zeros of both signs, rows of one magnitude, one outlier."""
+    G = 64
+    W = torch.zeros(8, 3 * G)
+    W[0, :] = torch.tensor([0.5, 1.5, -0.5, -1.5, 1.0, 1.0, -1.0, 1.0] * 24)       # mean 1
+    W[1, :] = 0.25
+    W[2, ::2] = -0.0
+    W[2, 1::2] = 3.0
+    W[3, 7::G] = -100.0
+    W[4, :] = torch.tensor([1.0, -1.0, 0.0, -0.0] * 48)
+    W[5, :] = torch.linspace(-2, 2, 3 * G)
+    W[6, :] = torch.tensor([0.499, 0.501, 1.0, 2.0] * 48)
+    s = torch.rand(3 * G, generator=torch.Generator().manual_seed(1)) + 0.5
+    s[3::16] = 0.0
+    for n_iter in (1, 2, 4):
+        against_oracle(windq, W.to(dtype).to(DEV), s.to(DEV), G, torch.tensor([5, 6, 5], dtype=torch.uint8), n_iter)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_scales_that_are_not_finite(windq, bad):
+    """Such a column makes a round's sums infinite or NaN, and the round changes nothing."""
+    G = 64
+    W = synth.weights_llm(70, 3 * G, seed=3, device=DEV)
+    s = torch.ones(3 * G)
+    s[G + 5] = bad
+    for n_iter in (1, 3):
+        against_oracle(windq, W, s.to(DEV), G, torch.tensor([5, 5, 4], dtype=torch.uint8), n_iter, err=False)
