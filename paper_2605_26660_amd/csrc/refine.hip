@@ -17,14 +17,16 @@
 // 128), read eight weights at a time by register indexing: a tile staged in LDS (17 KB) leaves room for two wavefronts
 // per SIMD, too few to fill the ALU.  LDS only turns the tile round on its way in, 128 bytes of every row at a
 // time, and the packed codes on their way out.  Wider rows stay in LDS.  Refining a 7B-shaped block at 2 bits, three rounds:
-// 285 us (610 with the tile in LDS, a select per weight for a mask that is not there, and passes of their own for error
-// and codes; 303 with a code and a product by it per ternary weight, base-3 bytes by integer multiplies, and the sign in
-// a binary weight's residual); five wavefronts per SIMD would spill (1.4 ms), an unrolled pair of blocks is 7 % slower, and
-// s_c^2 read from LDS weight by weight between a ternary round's adds costs 13 us.
+// 231 us, dear units first (285 in the matrix's own order, see RF_ORDERED_TILES); 610 with the tile in LDS, a select per
+// weight for a mask that is not there, and passes of their own for error and codes; then 303 with a code and a product
+// by it per ternary weight, base-3 bytes by integer multiplies, and the sign in a binary weight's residual.  Five wavefronts
+// per SIMD would spill (1.4 ms), an unrolled pair of blocks is 7 % slower, and s_c^2 read from LDS weight by weight
+// between a ternary round's adds costs 13 us.
 #include <float.h>
 
 #include "windq_common.hpp"
 #include "windq_group.hpp"
+#include "windq_order.hpp"
 #include "windq_ws.hpp"
 
 namespace windq {
@@ -52,6 +54,7 @@ struct RefineBatch {
     int32_t n;
     int32_t K;
     int32_t n_iter;
+    int32_t by_cost;           // tiles in the order of what their units cost (see RF_ORDERED_TILES)
     int64_t tile_start[WINDQ_MAX_BATCH + 1];
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     RefineArgs m[WINDQ_MAX_BATCH];
@@ -411,13 +414,28 @@ struct RefineRowOf<DT, 0> {
     using type = LdsRow<DT>;
 };
 
+// A tile of a uniform unit takes four times as long as one of a binary unit (at three rounds), and a launch of more
+// tiles than the chip holds at once (4096 at chunk 128, bf16) ends with what came last: in the matrix's own order, where every band
+// of rows has units of each kind, a 7B-shaped block took 285 us, dear units first 232.  Launches that fit keep that order:
+// with 500 tiles the look at the actions costs 1 us of 20.
+constexpr int64_t RF_ORDERED_TILES = 2048;
+// action:        skip      8, 4, 3, 2 bits   ternary        binary         outside the plan's
+constexpr uint32_t RF_CLASSES = 3u | 0u | (1u << 10) | (2u << 12) | (3u << (2 * WINDQ_N_ACTIONS));
+
 // NV: registers of a row / 32; 0: the row in LDS.  128 VGPRs (four wavefronts per SIMD) for NV = 2.
 template <int DT, int NV, bool MASKED>
 __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kernel(const RefineBatch B) {
     extern __shared__ __align__(16) char smem[];
     const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
     const RefineArgs& A = B.m[mi];
-    const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.tile_start[mi]);
+    const uint32_t local = (uint32_t)((int64_t)blockIdx.x - B.tile_start[mi]);
+    TileCoord tc;
+    if (B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
+        const uint32_t tpu = (uint32_t)A.g.tiles_per_unit, place = local / tpu;
+        tc = tile_coord_of_unit(A.g, unit_by_cost(A.action, (int32_t)A.g.U, (int32_t)place, RF_CLASSES), (int64_t)(local - place * tpu));
+    } else {
+        tc = tile_coord(A.g, (int64_t)local);
+    }
     const int32_t G = A.g.chunk_w;
     const int lane = threadIdx.x;
     const bool valid = lane < tc.nrows;
@@ -613,6 +631,7 @@ static int refine_launch(const windq_refine_item* items, int32_t n, int32_t chun
     if (tiles > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
+    B.by_cost = tiles > RF_ORDERED_TILES ? 1 : 0;
     const dim3 grid((unsigned)tiles);
     st = dtype == WINDQ_BF16 ? refine_launch_rows<WINDQ_BF16>(B, chunk_w, any_mask, grid, hs) : refine_launch_rows<WINDQ_F32>(B, chunk_w, any_mask, grid, hs);
     if (st != WINDQ_OK) return st;

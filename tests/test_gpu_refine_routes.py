@@ -74,3 +74,29 @@ def test_scales_that_are_not_finite(windq, bad):
     s[G + 5] = bad
     for n_iter in (1, 3):
         against_oracle(windq, W, s.to(DEV), G, torch.tensor([5, 5, 4], dtype=torch.uint8), n_iter, err=False)
+
+
+@pytest.mark.parametrize("units", [512, 513, 5])
+def test_order_by_cost_changes_nothing(windq, units):
+    """More than 2048 tiles in a launch: units by cost where a matrix has at most 512, each tile as in a call of its own;
+    entries that are no action, or lie outside the code stream, are skipped as ever."""
+    G, n_iter = 8, 2
+    rows = 64 * 3 if units > 5 else 64 * 300 - 7
+    W = synth.weights_llm(rows, units * G, seed=units, device=DEV)
+    s = torch.rand(units * G, generator=torch.Generator().manual_seed(2)).to(DEV) + 0.1
+    U, R_u = windq.n_units(rows, units * G, G, 0)
+    gen = torch.Generator().manual_seed(4)
+    action = torch.randint(0, 7, (U,), generator=gen, dtype=torch.uint8)
+    off = windq.windq_plan_layout(action, R_u, G)
+    action[3], off[1] = 9, -16                                  # (off is read per unit)
+    total = int(off[-1])
+    clip = torch.randint(0, 5, (U, 4), generator=gen, dtype=torch.uint8).to(DEV)
+    cg = synth.clip_grid(5)
+    n = 2200 // (U * ((R_u + 63) // 64)) + 1
+    assert n * U * ((R_u + 63) // 64) > 2048 >= U * ((R_u + 63) // 64)
+    codes = [torch.full((max(total, 16),), 0xCD, dtype=torch.uint8, device=DEV) for _ in range(n + 1)]
+    act_d, off_d = action.to(DEV), off.to(DEV)
+    alone = windq.windq_refine_plan(W, s, G, 0, act_d, clip, cg, off_d, n_iter, codes=codes[n])
+    batch = windq.windq_refine_plan_batch([W] * n, [s] * n, G, 0, [act_d] * n, [clip] * n, cg, [off_d] * n, n_iter, codes[:n])
+    for got in batch:
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, alone))
