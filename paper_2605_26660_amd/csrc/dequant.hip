@@ -14,6 +14,7 @@
 // weights s_c^2 of its columns.  Other widths, and buffers off those alignments: the same
 // pieces, numbered through the tile, a thread's columns found per piece.
 #include "windq_common.hpp"
+#include "windq_order.hpp"
 #include "windq_ws.hpp"
 
 namespace windq {
@@ -45,6 +46,7 @@ struct DequantArgs {
 // tiles and units are numbered one matrix after the other.
 struct DequantBatch {
     int32_t n;
+    int32_t by_cost;            // the product: workgroups in the order of what their units cost
     int64_t tile_start[WINDQ_MAX_BATCH + 1];
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     int64_t row_start[WINDQ_MAX_BATCH + 1];
@@ -396,10 +398,14 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
 // share), units under a protection mask, and what infinite or NaN weights would show in: chunks of x that hold a value no
 // fp32 sum of a few columns may meet (infinite, NaN or above 2^96), rows whose scale or offset is such a value.  Skip
 // units read W, G/8 lanes a row.
-//   7B-shaped block at a 2-bit plan: 38 us (109 with G/8 lanes a row), of which the sums over chunks take 5; with 3 % of the
+//   7B-shaped block at a 2-bit plan: 36 to 41 us by the card (109 with G/8 lanes a row), of which the sums over chunks take 5; with 3 % of the
 // weights protected 65 (115).  The six wavefronts per SIMD that 84 registers allow are worth 5 to 10 % over the four
 // that the skip route's loads would take.
 constexpr int GEMV_THREADS = 256;
+// Dear units first (windq_order.hpp) where a launch has four workgroups per CU or more: skipped units and those taken weight by
+// weight (8, 4 and 3 bits), then tables of trits and of 2 bits, then of 1 bit.  7B-shaped block at 2 bits 42.5 -> 40.7 us,
+// 11008 x 4096 18.7 -> 15.5, 28672 x 8192 56 -> 35; with 392 workgroups the look at the actions costs 0.4 us of 13.9.
+constexpr uint32_t GEMV_CLASSES = (1u << 8) | (1u << 10) | (2u << 12);
 constexpr int GEMV_TRIT_WORDS = 48;                 // of a byte of trits: 27 entries at 0, 10 at 32
 constexpr size_t GEMV_BOTH_LDS = GEMV_THREADS * sizeof(double) + 256 * sizeof(uint16_t);        // of lanes that share a row, beside the others
 // LDS of the largest table, trits of whole dwords (2 bits: 8 entries a column, 1 bit: 4), after the chunk's x.
@@ -681,8 +687,19 @@ __device__ __forceinline__ void gemv_rows_wg(const DequantBatch& B, const uint32
     const uint32_t at = (uint32_t)((int64_t)wg - B.tile_start[mi]);
     const uint32_t nc = (uint32_t)A.g.n_chunks;
     const uint32_t nr = (uint32_t)((A.g.R_u + nt - 1) / nt);
-    const uint32_t band = at / nc, j = at - band * nc;
-    const uint32_t rb = band / nr, rr = band - rb * nr;
+    uint32_t rb, rr, j;
+    if (!MASKED && B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
+        const uint32_t place = at / nr;
+        const uint32_t unit = (uint32_t)unit_by_cost(A.action, (int32_t)A.g.U, (int32_t)place, GEMV_CLASSES);
+        rr = at - place * nr;
+        rb = unit / nc;
+        j = unit - rb * nc;
+    } else {
+        const uint32_t band = at / nc;
+        j = at - band * nc;
+        rb = band / nr;
+        rr = band - rb * nr;
+    }
     const int64_t u = (int64_t)rb * nc + j;
     const int64_t lrow0 = (int64_t)rr * nt;                            // first row, local to the unit
     const int64_t row0 = (int64_t)rb * A.g.R_u + lrow0;
@@ -1214,6 +1231,7 @@ static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int
         } while (rpt > 1 && wgs < GEMV_MIN_WGS);
         // a skip unit's rows in parts, where there are fewer than two workgroups per CU (four under a mask, where 8-bit units share
         // too), each of at least four loads per thread: skip units of 4096 x 4096 at chunk 512 16.5 us, 38 in one part
+        B.by_cost = k == GEMV_ROWS && wgs >= GEMV_MIN_WGS ? 1 : 0;
         int parts_shift = 0;
         while (parts_shift < 2 && (wgs << parts_shift) < (k == GEMV_ROWS ? GEMV_MIN_WGS / 2 : GEMV_MIN_WGS)) {
             const int64_t rows = rpt * GEMV_THREADS >> (parts_shift + 1);       // of a part
