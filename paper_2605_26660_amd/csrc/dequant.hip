@@ -398,13 +398,14 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
 // share), units under a protection mask, and what infinite or NaN weights would show in: chunks of x that hold a value no
 // fp32 sum of a few columns may meet (infinite, NaN or above 2^96), rows whose scale or offset is such a value.  Skip
 // units read W, G/8 lanes a row.
-//   7B-shaped block at a 2-bit plan: 36 to 41 us by the card (109 with G/8 lanes a row), of which the sums over chunks take 5; with 3 % of the
+//   7B-shaped block at a 2-bit plan: 34 to 38 us by the card (109 with G/8 lanes a row), of which the sums over chunks take 5; with 3 % of the
 // weights protected 65 (115).  The six wavefronts per SIMD that 84 registers allow are worth 5 to 10 % over the four
 // that the skip route's loads would take.
 constexpr int GEMV_THREADS = 256;
 // Dear units first (windq_order.hpp) where a launch has four workgroups per CU or more: skipped units and those taken weight by
-// weight (8, 4 and 3 bits), then tables of trits and of 2 bits, then of 1 bit.  7B-shaped block at 2 bits 42.5 -> 40.7 us,
-// 11008 x 4096 18.7 -> 15.5, 28672 x 8192 56 -> 35; with 392 workgroups the look at the actions costs 0.4 us of 13.9.
+// weight (8, 4 and 3 bits), then tables of trits and of 2 bits, then of 1 bit.  7B-shaped block at 2 bits 41.9 -> 37.8 us,
+// 28672 x 8192 and the others of its block 60 -> 42; plans of one width keep their times; with 392 workgroups the look at the
+// actions costs 0.4 us of 13.9.
 constexpr uint32_t GEMV_CLASSES = (1u << 8) | (1u << 10) | (2u << 12);
 constexpr int GEMV_TRIT_WORDS = 48;                 // of a byte of trits: 27 entries at 0, 10 at 32
 constexpr size_t GEMV_BOTH_LDS = GEMV_THREADS * sizeof(double) + 256 * sizeof(uint16_t);        // of lanes that share a row, beside the others
@@ -689,11 +690,10 @@ __device__ __forceinline__ void gemv_rows_wg(const DequantBatch& B, const uint32
     const uint32_t nr = (uint32_t)((A.g.R_u + nt - 1) / nt);
     uint32_t rb, rr, j;
     if (!MASKED && B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
-        const uint32_t place = at / nr;
-        const uint32_t unit = (uint32_t)unit_by_cost(A.action, (int32_t)A.g.U, (int32_t)place, GEMV_CLASSES);
-        rr = at - place * nr;
-        rb = unit / nc;
-        j = unit - rb * nc;
+        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, (int32_t)nr, (int32_t)at, GEMV_CLASSES);
+        rr = (uint32_t)o.item;
+        rb = (uint32_t)o.unit / nc;
+        j = (uint32_t)o.unit - rb * nc;
     } else {
         const uint32_t band = at / nc;
         j = at - band * nc;

@@ -17,7 +17,7 @@
 // 128), read eight weights at a time by register indexing: a tile staged in LDS (17 KB) leaves room for two wavefronts
 // per SIMD, too few to fill the ALU.  LDS only turns the tile round on its way in, 128 bytes of every row at a
 // time, and the packed codes on their way out.  Wider rows stay in LDS.  Refining a 7B-shaped block at 2 bits, three rounds:
-// 231 us, dear units first (285 in the matrix's own order, see RF_ORDERED_TILES); 610 with the tile in LDS, a select per
+// 225 us, dear units first (285 in the matrix's own order, see RF_ORDERED_TILES); 610 with the tile in LDS, a select per
 // weight for a mask that is not there, and passes of their own for error and codes; then 303 with a code and a product
 // by it per ternary weight, base-3 bytes by integer multiplies, and the sign in a binary weight's residual.  Five wavefronts
 // per SIMD would spill (1.4 ms), an unrolled pair of blocks is 7 % slower, and s_c^2 read from LDS weight by weight
@@ -416,7 +416,7 @@ struct RefineRowOf<DT, 0> {
 
 // A tile of a uniform unit takes four times as long as one of a binary unit (at three rounds), and a launch of more
 // tiles than the chip holds at once (4096 at chunk 128, bf16) ends with what came last: in the matrix's own order, where every band
-// of rows has units of each kind, a 7B-shaped block took 285 us, dear units first 232.  Launches that fit keep that order:
+// of rows has units of each kind, a 7B-shaped block took 285 us, dear units first 225.  Launches that fit keep that order:
 // with 500 tiles the look at the actions costs 1 us of 20.
 constexpr int64_t RF_ORDERED_TILES = 2048;
 // action:        skip      8, 4, 3, 2 bits   ternary        binary         outside the plan's
@@ -431,8 +431,8 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
     const uint32_t local = (uint32_t)((int64_t)blockIdx.x - B.tile_start[mi]);
     TileCoord tc;
     if (B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
-        const uint32_t tpu = (uint32_t)A.g.tiles_per_unit, place = local / tpu;
-        tc = tile_coord_of_unit(A.g, unit_by_cost(A.action, (int32_t)A.g.U, (int32_t)place, RF_CLASSES), (int64_t)(local - place * tpu));
+        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, (int32_t)A.g.tiles_per_unit, (int32_t)local, RF_CLASSES);
+        tc = tile_coord_of_unit(A.g, o.unit, o.item);
     } else {
         tc = tile_coord(A.g, (int64_t)local);
     }

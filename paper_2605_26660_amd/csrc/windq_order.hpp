@@ -10,48 +10,53 @@ constexpr int64_t ORDER_MAX_UNITS = 512;     // of a matrix; one with more keeps
 
 #ifdef __HIPCC__
 
-// The unit that comes at place `place` when a matrix's U (<= ORDER_MAX_UNITS) units are sorted by class, each class in its own
-// order; classes holds the class (0: dearest, to 3) of action a in bits 2a and 2a + 1, of an action outside the plan's in those
-// of WINDQ_N_ACTIONS.  From the actions themselves, by every wavefront that calls it (all lanes): a byte load and three
-// ballots per 64 units.
-__device__ __forceinline__ int64_t unit_by_cost(const uint8_t* __restrict__ action, int32_t U, int32_t place, uint32_t classes) {
+// Work item `item` of a matrix's U (<= ORDER_MAX_UNITS) units of `per` items each, sorted by class; inside a class the items
+// with the same number in their units come one after the other, so that neighbours in a launch read neighbouring columns.
+// Returns the unit and its item.  classes holds the class (0: dearest, to 3) of action a in bits 2a and 2a + 1, of an action
+// outside the plan's in those of WINDQ_N_ACTIONS.  From the actions themselves, by every wavefront that calls it (all lanes): a
+// byte load and four ballots per 64 units.  A workgroup waits for it before its first load, so it is kept short: with the rounds
+// unrolled and every ballot held, a product at a plan of 2-bit units only took 27.4 us where the matrix's own order took 24.4; 24.5
+// so.  (A unit's items one after the other: 8-bit units only 55 us, 47.5 so.)
+struct OrderedItem {
+    int32_t unit;
+    int32_t item;
+};
+__device__ __forceinline__ OrderedItem item_by_cost(const uint8_t* __restrict__ action, int32_t U, int32_t per, int32_t item, uint32_t classes) {
     const int lane = threadIdx.x & 63;
-    constexpr int ROUNDS = (int)(ORDER_MAX_UNITS / 64);
-    uint32_t cls[ROUNDS];                   // 4: no unit
-#pragma unroll
-    for (int k = 0; k < ROUNDS; ++k) {
-        cls[k] = WINDQ_N_ACTIONS;
-        if (64 * k + lane < U) cls[k] = action[64 * k + lane];
-    }
-    uint64_t is[ROUNDS][4];
     int32_t n[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < ROUNDS; ++k) {
-        const uint32_t a = cls[k] < WINDQ_N_ACTIONS ? cls[k] : WINDQ_N_ACTIONS;
-        const uint32_t c = 64 * k + lane < U ? (classes >> (2u * a)) & 3u : 4u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            is[k][q] = __ballot(c == (uint32_t)q);
-            n[q] += __builtin_popcountll(is[k][q]);
+    uint32_t mine = 0;                      // 4 bits a round: class of this lane's unit, 4: no unit
+    for (int32_t u0 = 0, k = 0; u0 < U; u0 += 64, ++k) {
+        uint32_t c = 4u;
+        if (u0 + lane < U) {
+            const uint32_t a = action[u0 + lane];
+            c = (classes >> (2u * (a < WINDQ_N_ACTIONS ? a : WINDQ_N_ACTIONS))) & 3u;
         }
+        mine |= c << (4 * k);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n[q] += __builtin_popcountll(__ballot(c == (uint32_t)q));
     }
-    int32_t left = place;
+    int32_t left = item;
     int want = 0;
-    while (want < 3 && left >= n[want]) left -= n[want++];
-    int32_t u = 0;
-    bool found = false;
-#pragma unroll
-    for (int k = 0; k < ROUNDS; ++k) {
-        const uint64_t m = want == 0 ? is[k][0] : (want == 1 ? is[k][1] : (want == 2 ? is[k][2] : is[k][3]));
-        const int32_t here = __builtin_popcountll(m);
-        if (!found && left < here) {
-            const uint64_t at = __ballot((m >> lane & 1ull) != 0ull && (int32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull)) == left);
-            u = 64 * k + __builtin_ctzll(at);
-            found = true;
-        }
-        if (!found) left -= here;
+    while (want < 3 && left >= n[want] * per) left -= n[want++] * per;
+    const int32_t of = want == 0 ? n[0] : (want == 1 ? n[1] : (want == 2 ? n[2] : n[3]));
+    OrderedItem r;
+    r.item = (int32_t)((uint32_t)left / (uint32_t)of);
+    left -= r.item * of;
+    if (of == U) {
+        r.unit = left;
+        return r;
     }
-    return u;
+    int32_t u0 = 0;
+    uint64_t m = __ballot((mine & 15u) == (uint32_t)want);
+    while (left >= (int32_t)__builtin_popcountll(m)) {
+        left -= (int32_t)__builtin_popcountll(m);
+        u0 += 64;
+        mine >>= 4;
+        m = __ballot((mine & 15u) == (uint32_t)want);
+    }
+    const uint64_t at = __ballot((m >> lane & 1ull) != 0ull && (int32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull)) == left);
+    r.unit = u0 + (int32_t)__builtin_ctzll(at);
+    return r;
 }
 
 #endif  // __HIPCC__

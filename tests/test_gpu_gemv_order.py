@@ -9,21 +9,25 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-@pytest.mark.parametrize("R,units,G,dtype", [
-    (4096, 128, 32, torch.bfloat16),        # 1024 workgroups: the first size that is ordered
-    (3585, 128, 32, torch.bfloat16),        # 1024, the last row range of a single row
-    (3584, 128, 32, torch.float32),         # 896: in the matrix's own order
-    (1024, 512, 8, torch.bfloat16), (1025, 513, 8, torch.bfloat16),       # as many units as are ordered, and one more
-    (300, 511, 24, torch.float32)])
-def test_every_unit_is_multiplied_once(windq, R, units, G, dtype):
+@pytest.mark.parametrize("R,units,G,dtype,only", [
+    (4096, 128, 32, torch.bfloat16, None),        # 1024 workgroups: the first size that is ordered
+    (3585, 128, 32, torch.bfloat16, None),        # 1024, the last row range of a single row
+    (3584, 128, 32, torch.float32, None),         # 896: in the matrix's own order
+    (1024, 512, 8, torch.bfloat16, None), (1025, 513, 8, torch.bfloat16, None),       # as many units as are ordered, and one more
+    (300, 511, 24, torch.float32, None),
+    (4095, 130, 32, torch.bfloat16, (4,)), (4096, 128, 32, torch.bfloat16, (0, 6))])         # one class alone; the first and the last
+def test_every_unit_is_multiplied_once(windq, R, units, G, dtype, only):
     C = units * G
     W = synth.weights_llm(R, C, seed=R + units, device=DEV, dtype=dtype)
     gen = torch.Generator().manual_seed(R)
     action = torch.randint(0, 7, (units,), generator=gen, dtype=torch.uint8)
+    if only is not None:
+        action = torch.tensor(only, dtype=torch.uint8)[action.long() % len(only)]
     off = windq.windq_plan_layout(action, R, G)
     clip = torch.zeros(units, 4, dtype=torch.uint8, device=DEV)
     codes = torch.zeros(int(off[-1]), dtype=torch.uint8, device=DEV)
-    action[7 % units], off[2] = 200, 1 << 62
+    if only is None:
+        action[7 % units], off[2] = 200, 1 << 62
     act_d, off_d = action.to(DEV), off.to(DEV)
     _, scale, offset = windq.windq_apply_plan(W, G, 0, act_d, clip, synth.clip_grid(3), off_d, codes=codes)
     s = torch.ones(C, device=DEV)
