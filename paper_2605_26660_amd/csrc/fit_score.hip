@@ -112,13 +112,17 @@ constexpr int FS_FEAT_ONLY = 3;     // that first pass alone          // workgro
 //     C(p') >= C(p) ((1-p')/(1-p))^2     for p' < p.
 // An 8-bit grid is so fine that C passes the whole error at p = 1 (about step^2/12 a weight, step = (max-min)/255) once
 // p is a few per cent below 1.  So a tile takes C at ONE ratio (skip8_p), and where the bound for a smaller ratio exceeds
-// SKIP8_MARGIN times the expected error at ratio 1 it leaves that 8-bit candidate out and writes the bound, negated,
+// SKIP8_MARGIN (units of few tiles: SKIP8_MARGIN_FEW) times the expected error at ratio 1 it leaves that 8-bit candidate out and writes the bound, negated,
 // in its place: the sum over the unit's tiles is then a lower bound on the candidate's error, and says so by its sign.
 // The finalize kernel chooses among the candidates that every tile has scored and PROVES the choice: a unit one of
 // whose bounds does not exceed the chosen error by BOUND_SLACK (more than fp32 rounding can have put into either) goes
 // on the list of units whose 8-bit candidates are all scored again.  So a tile's test decides speed, never the result.
 // Margin 1.25: with 1, single units of a batch miss the proof and are scored twice (a batch of 0.9 M to 5 M weights: 125 us, 119 with 1.25).
 constexpr float SKIP8_MARGIN = 1.25f;
+// Units of few tiles average over less and miss it more often, and a single unit scored twice costs a launch 15 to 25 us: they take
+// margin 2 (units of 128 x 128, fp32, K = 40: a batch of 604 tiles 168 us with 1.25, 145 with 2, 149 with 4; 4096 x 4096 296, 274, 276).
+constexpr float SKIP8_MARGIN_FEW = 2.0f;
+constexpr int64_t SKIP8_FEW_TILES = 4;
 constexpr float SKIP8_MAX_P = 0.95f;        // skip8_p: the grid's largest ratio up to here
 // A tile takes the exact sweep when one row holds more than 1 / ROW_SHARE of the sum of the
 // rows' squared ranges (that row would carry most of the tile's 8-bit error by itself).
@@ -972,7 +976,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         }
     }
     // an 8-bit candidate is left out where its bound, tile_clip * skip8_f[k], exceeds this (never where either is NaN)
-    const float skip8_above = s2_rg2 * (SKIP8_MARGIN / (12.0f * 65025.0f));
+    const float skip8_above = s2_rg2 * ((A.g.tiles_per_unit <= SKIP8_FEW_TILES ? SKIP8_MARGIN_FEW : SKIP8_MARGIN) / (12.0f * 65025.0f));
     int32_t ncollect = ONLY8 ? FS_NRED : NROW;         // columns the next collection takes
 
     // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4, or by
