@@ -154,8 +154,9 @@ int windq_unit_features(const windq_mat* W, const float* s /*[cols]*/, int32_t c
  * summed from its own per-row errors (each rounding taken at its largest possible size).  A
  * unit whose noise could exceed 3e-6 of its 8-bit error (one standard deviation; measured
  * deviations are ~0.4 of that estimate) has its 8-bit candidates scored again on the exact
- * route before the call's work ends, whatever the input.  |s_c * w| must square inside fp32's
- * normal range.
+ * route before the call's work ends, whatever the input.  8-bit candidates that clipping alone rules out
+ * (a lower bound on the unit's error, proven per unit) are left out; a unit without that proof is scored again too.
+ * |s_c * w| must square inside fp32's normal range.
  *   That accuracy is a unit's, not a single weight's.  A weight's residual s_c (w - lo - code step)
  * comes from fp32-rounded products: an absolute error near 1e-7 s_c (hi - lo) at 4 bits and below
  * (1e-7 s_c step at 8 bits, exact route), and at 8 bits a weight within ~2e-5 steps of a rounding
@@ -209,7 +210,8 @@ int windq_kernel_timer_read(double* total_ms /*HOST*/, int64_t* launches /*HOST*
 
 /*
  * Diagnostic: how many units of the last windq_fit_score_all_bits (or _prot, or batch item) call
- * that used workspace `ws` had their 8-bit candidates scored a second time on the exact route.
+ * that used workspace `ws` had their 8-bit candidates scored a second time on the exact route (for their noise, or because a
+ * candidate that was left out could not be ruled out).
  * Pass the shape arguments of that call.  Unlike every other entry point this one copies a
  * counter to the host and therefore waits for the device: call it after the stream has finished.
  */
