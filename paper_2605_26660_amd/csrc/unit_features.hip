@@ -391,12 +391,27 @@ __device__ __forceinline__ void feat_tail(const FeatArgs& A, int64_t u, const Fe
 // with), so everything the selection does not decide is requested before it starts: the
 // first round of block moments, the activation scales and the refined counters travel
 // together with the first-digit histogram.
+struct FeatFinishLds {
+    double red[6 * FT_WAVES];
+    uint32_t sh_part[FT_THREADS];
+    uint32_t sh_out[4];
+    float smax[FT_WAVES];
+};
+struct FeatRecordLds {                    // bf16 besides
+    uint32_t sub[32];                     // full-resolution counters of bins e0 and e0 - 8
+    uint32_t tcnt[FT_THREADS * 33];
+    uint32_t xh[256];
+    uint32_t xsum[FT_WAVES];
+    int miss;
+};
 template <int DT>
-__device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64_t block) {
-    __shared__ double red[6 * FT_WAVES];
-    __shared__ uint32_t sh_part[FT_THREADS];
-    __shared__ uint32_t sh_out[4];
-    __shared__ float smax_sh[FT_WAVES];
+constexpr size_t feat_finish_lds_bytes() { return sizeof(FeatFinishLds) + (DT == WINDQ_BF16 ? sizeof(FeatRecordLds) : 0); }
+template <int DT>
+__device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64_t block, char* __restrict__ smem) {
+    FeatFinishLds& L = *reinterpret_cast<FeatFinishLds*>(smem);
+    double* __restrict__ red = L.red;
+    uint32_t* __restrict__ sh_part = L.sh_part;
+    uint32_t* __restrict__ sh_out = L.sh_out;
     const int mi = batch_index(B.unit_start, B.n, block);
     const FeatArgs& A = B.m[mi];
     const int64_t u = block - B.unit_start[mi];
@@ -407,9 +422,10 @@ __device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64
     double above = 0.0;
     bool listed = false;        // bf16: left to the exact pass
     if (DT == WINDQ_BF16) {
-        __shared__ uint32_t sub[32];          // full-resolution counters of bins e0 and e0 - 8
-        __shared__ uint32_t tcnt[FT_THREADS * 33];
-        __shared__ int miss;
+        FeatRecordLds& R = *reinterpret_cast<FeatRecordLds*>(smem + sizeof(FeatFinishLds));
+        uint32_t* __restrict__ sub = R.sub;
+        uint32_t* __restrict__ tcnt = R.tcnt;
+        int& miss = R.miss;
         uint32_t e0, l1;
         uint64_t rank1, below;
         if (tid == 0) miss = 0;
@@ -479,11 +495,10 @@ __device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64
         for (int64_t b = tid; b < A.bpu; b += FT_THREADS) above += (double)A.above[(size_t)u * A.bpu + b];
     }
 
-    feat_tail(A, u, in, above, !listed, red, smax_sh);
+    feat_tail(A, u, in, above, !listed, red, L.smax);
     if (DT == WINDQ_BF16 && listed) {          // (the same decision in every thread)
-        __shared__ uint32_t xh[256];
-        __shared__ uint32_t xsum[FT_WAVES];
-        feat_exact_bf16_unit(A, u, xh, sh_part, sh_out, xsum);
+        FeatRecordLds& R = *reinterpret_cast<FeatRecordLds*>(smem + sizeof(FeatFinishLds));
+        feat_exact_bf16_unit(A, u, R.xh, sh_part, sh_out, R.xsum);
     }
 }
 
@@ -496,13 +511,19 @@ __device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64
 // last one, gains nothing (its counter is one more wait).  The limit is what 1024 threads hold at 128 registers each; there
 // (one unit of 768 x 128, 98304 weights, alone) the call takes 30.8 us, and 35.6 with a launch per pass.
 constexpr int64_t FEAT_SMALL = 98304;
+struct FeatSmallLds {
+    double red[6 * FT_WAVES];
+    uint32_t lhist[FEAT_BINS];
+    uint32_t sh_part[1024 / 64];
+    uint32_t sh_out[2];
+    float smax[FT_WAVES];
+};
 template <int NT, int PER>
-__device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const int64_t block) {
-    __shared__ uint32_t lhist[FEAT_BINS];
-    __shared__ double red[6 * FT_WAVES];
-    __shared__ uint32_t sh_part[NT / 64];
-    __shared__ uint32_t sh_out[2];
-    __shared__ float smax_sh[FT_WAVES];
+__device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const int64_t block, char* __restrict__ smem) {
+    FeatSmallLds& L = *reinterpret_cast<FeatSmallLds*>(smem);
+    uint32_t* __restrict__ lhist = L.lhist;
+    uint32_t* __restrict__ sh_part = L.sh_part;
+    uint32_t* __restrict__ sh_out = L.sh_out;
     const int mi = batch_index(B.unit_start, B.n, block);
     const FeatArgs& A = B.m[mi];
     const int64_t u = block - B.unit_start[mi];
@@ -574,28 +595,36 @@ __device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const in
         cnt = threadIdx.x < NT / 64 ? sh_part[threadIdx.x] : 0u;
     }
     if (PER > 8) in = feat_tail_load(A, u);
-    feat_tail(A, u, in, (double)cnt, true, red, smax_sh);
+    feat_tail(A, u, in, (double)cnt, true, L.red, L.smax);
 }
 
 // The features' last step, one workgroup per unit, and where fit+score is part of the call (FIT) its last step too, by
 // as many workgroups behind them: each is a chain of memory latencies that leaves the chip idle, and neither needs
-// the other.  PER = 0: the finish step after the passes; else units kept in registers.
+// the other.  PER = 0: the finish step after the passes; else units kept in registers.  A workgroup does one or the other,
+// so both use the same LDS, all of it asked for with the launch (at most 46 KB; no kernel here may pass the 64 KB that a
+// workgroup gets without ensure_lds).
 template <int DT, int NT, int PER, bool FIT>
 __global__ __launch_bounds__(NT) void feat_last_kernel(const FeatBatch B, const FitFinalBatch F) {
+    extern __shared__ __align__(16) char last_lds[];
     if (!FIT || (int64_t)blockIdx.x < B.units_total) {
-        if constexpr (PER == 0) feat_finish_unit<DT>(B, blockIdx.x);
-        else feat_small_f32_unit<NT, PER>(B, blockIdx.x);
+        if constexpr (PER == 0) feat_finish_unit<DT>(B, blockIdx.x, last_lds);
+        else feat_small_f32_unit<NT, PER>(B, blockIdx.x, last_lds);
     } else {
-        extern __shared__ double fin_lds[];
-        fit_finalize_unit<NT>(F, (int64_t)blockIdx.x - B.units_total, fin_lds);
+        fit_finalize_unit<NT>(F, (int64_t)blockIdx.x - B.units_total, reinterpret_cast<double*>(last_lds));
     }
 }
 
 template <int DT, int NT, int PER>
 static void launch_last(const FeatBatch& B, const FitFinalBatch* fit, hipStream_t hs) {
     const unsigned units = (unsigned)B.units_total;
-    if (fit != nullptr) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, true>), dim3(2 * units), dim3(NT), fit_finalize_lds_bytes(fit->K), hs, B, *fit);
-    else hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), 0, hs, B, FitFinalBatch{});
+    constexpr size_t feat_lds = PER == 0 ? feat_finish_lds_bytes<DT>() : sizeof(FeatSmallLds);
+    static_assert(feat_lds <= 64 * 1024 && fit_finalize_lds_bytes(WINDQ_MAX_CLIP) <= 64 * 1024, "what a workgroup gets by default");
+    if (fit != nullptr) {
+        const size_t fit_lds = fit_finalize_lds_bytes(fit->K);
+        hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, true>), dim3(2 * units), dim3(NT), feat_lds > fit_lds ? feat_lds : fit_lds, hs, B, *fit);
+    } else {
+        hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
+    }
 }
 
 template <int DT>

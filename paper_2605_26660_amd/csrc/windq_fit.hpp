@@ -74,7 +74,7 @@ __device__ __forceinline__ uint32_t* fit_redo_done(double* unit_partial, int32_t
 }
 
 // Dynamic LDS of a workgroup that finalizes: [FIN_PHASES][ncand] phase sums, [ncand] totals.
-inline size_t fit_finalize_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES + 1) * (size_t)fit_score_ncand(K) * sizeof(double); }
+constexpr size_t fit_finalize_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES + 1) * (size_t)fit_score_ncand(K) * sizeof(double); }
 
 // Per unit: add the tiles' partial errors in a fixed order, pick the clip index with the
 // least error for each uniform bit-width (ties to the largest index), emit fp32.  A unit whose 8-bit

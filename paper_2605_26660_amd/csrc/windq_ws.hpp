@@ -17,7 +17,7 @@ inline size_t calib_ws_bytes(int64_t rows, int64_t cols) {
 // candidates: [b][k] for b in 8,4,3,2 (index b*K + k); then for each quarter of the chunk's
 // columns: ternary, binary, reference energy (12 slots); then [k] the variance term of the
 // 8-bit short route's rounding noise at clip index k
-__host__ __device__ inline int32_t fit_score_ncand(int32_t K) { return 5 * K + 12; }
+__host__ __device__ constexpr int32_t fit_score_ncand(int32_t K) { return 5 * K + 12; }
 __host__ __device__ inline int32_t fit_score_noise_slot(int32_t K) { return 4 * K + 12; }
 // What fit+score prepares once per chunk of columns (it depends on s alone): the activation scales
 // of the columns that take the short 8-bit route (0 for the others), the list of the others, their

@@ -5,6 +5,8 @@ agree with hand-computed values and with the oracle."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -103,6 +105,34 @@ def test_workspace_sizes(windq):
     assert windq.workspace_bytes(windq.CALL_FIT_SCORE, B, 4096, 4096, 128, 100, 20) == 0
     assert windq.workspace_bytes(windq.CALL_FIT_SCORE, B, 4096, 4096, 128, 0, 65) == 0
     assert windq.workspace_bytes(windq.CALL_FIT_SCORE, 2, 4096, 4096, 128, 0, 20) == 0
+
+
+def kernel_static_lds(path, tmp):
+    """name -> LDS bytes that the kernel declares itself, from the code objects' metadata."""
+    llvm = next((d for d in ("/opt/rocm/llvm/bin", "/opt/rocm/lib/llvm/bin") if os.path.exists(os.path.join(d, "llvm-readelf"))), None)
+    if llvm is None:
+        pytest.skip("no llvm-readelf")
+    shutil.copy(path, os.path.join(tmp, "lib.so"))
+    subprocess.run([os.path.join(llvm, "llvm-objdump"), "--offloading", "lib.so"], cwd=tmp, check=True, capture_output=True)
+    found = {}
+    for f in os.listdir(tmp):
+        if "gfx950" not in f:
+            continue
+        notes = subprocess.run([os.path.join(llvm, "llvm-readelf"), "--notes", f], cwd=tmp, check=True, capture_output=True, text=True).stdout
+        for kernel in notes.split("  - .agpr_count")[1:]:
+            name = re.search(r"\.name: +(\S+)", kernel).group(1)
+            found[name] = int(re.search(r"\.group_segment_fixed_size: +(\d+)", kernel).group(1))
+    return found
+
+
+def test_last_step_stays_inside_the_default_lds(windq, tmp_path):
+    """The launches that finalize fit+score ask for up to 17 x (5 K + 12) doubles without raising the kernel's limit: with what
+    the kernel declares itself that stays inside the 64 KB a workgroup gets by default, at the longest clip grid too."""
+    lds = kernel_static_lds(windq.LIB_PATH, str(tmp_path))
+    most = 17 * (5 * windq.MAX_CLIP + 12) * 8
+    kernels = [n for n in lds if "feat_last_kernel" in n or "fit_score_finalize_kernel" in n]
+    assert len(kernels) >= 8
+    assert all(lds[n] + most <= 64 * 1024 for n in kernels), {n: lds[n] for n in kernels}
 
 
 def _mat(windq, rows=128, cols=128, dtype=None, data=4096, ld=None):
