@@ -619,11 +619,14 @@ static void launch_last(const FeatBatch& B, const FitFinalBatch* fit, hipStream_
     const unsigned units = (unsigned)B.units_total;
     constexpr size_t feat_lds = PER == 0 ? feat_finish_lds_bytes<DT>() : sizeof(FeatSmallLds);
     static_assert(feat_lds <= 64 * 1024 && fit_finalize_lds_bytes(WINDQ_MAX_CLIP) <= 64 * 1024, "what a workgroup gets by default");
+    // (a launch holds fewer than 2^32 threads: 2^21 units of fp32 in registers take a launch for each half)
+    const bool both = fit != nullptr && 2 * B.units_total * NT <= (int64_t)0xffffffff;
+    if (!both) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
     if (fit != nullptr) {
         const size_t fit_lds = fit_finalize_lds_bytes(fit->K);
-        hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, true>), dim3(2 * units), dim3(NT), feat_lds > fit_lds ? feat_lds : fit_lds, hs, B, *fit);
-    } else {
-        hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
+        FeatBatch F = B;
+        F.units_total = both ? B.units_total : 0;
+        hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, true>), dim3(both ? 2 * units : units), dim3(NT), feat_lds > fit_lds ? feat_lds : fit_lds, hs, F, *fit);
     }
 }
 
@@ -711,7 +714,7 @@ int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t uni
         B.init_start[i] = inits;
     }
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (blocks > (int64_t)0x7fffffff || 2 * units > (int64_t)0x7fffffff || inits > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (blocks > (int64_t)0x7fffffff || units > (int64_t)0x7fffffff || inits > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     B.dtype = items[0].W->dtype;
     B.blocks_total = blocks;
     B.units_total = units;

@@ -97,3 +97,23 @@ def test_70b_shapes_40_point_grid(windq, name, rows, cols, G):
 
 def test_70b_tile_units(windq):
     run_case(windq, 8192, 8192, 64, 40, 128, seed=5555, chunks=[0, 127], row_blocks=[0, 63])
+
+
+def test_more_units_than_one_launch_of_the_last_step_holds(windq):
+    """2.1 M fp32 units of 33 x 512 in one fused call: the features' and the fit's last steps, 1024 threads a unit each, would be
+    more than 2^32 threads in one launch.  Eight items read the same matrix (17.8 GB); each must give what it gives alone."""
+    G, unit_rows, rows, cols = 512, 33, 33 * 512, 512 * 513
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    W = torch.empty(rows, cols, device=DEV)
+    for r in range(0, rows, 2112):
+        W[r:r + 2112].normal_(generator=gen)
+    s = torch.rand(cols, generator=gen, device=DEV) + 0.5
+    cg = torch.tensor([1.0])
+    alone = windq.windq_features_fit_score(W, s, G, unit_rows, cg)
+    assert 2 * 8 * alone[0].shape[0] * 1024 > 1 << 32
+    poison = lambda: tuple(torch.full_like(t, 77) for t in alone)
+    for got in windq.windq_features_fit_score_batch([W] * 8, [s] * 8, G, unit_rows, cg, outs=[poison() for _ in range(8)]):
+        assert all(torch.equal(a, b) for a, b in zip(got, alone))
+    torch.cuda.empty_cache()
