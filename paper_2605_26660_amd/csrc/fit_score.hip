@@ -91,6 +91,7 @@ constexpr int FS_REDO_GRID = 512;
 constexpr int FS_SCORE = 0;         // every candidate quantizer
 constexpr int FS_ONLY8 = 1;         // the 8-bit candidates alone, exact route (listed units)
 constexpr int FS_SCORE_FEAT = 2;    // every candidate, and the first pass of the unit features (Table 1)
+constexpr int FS_WHOLE = 0, FS_SPLIT = 1, FS_SERIAL = 2;       // cuts, see choose_cut
 constexpr int FS_FEAT_ONLY = 3;     // that first pass alone          // workgroups of the launch that scores listed units again
 
 // The short route's rounding noise in a unit's 8-bit error.  On the short route the residual
@@ -143,7 +144,8 @@ struct FitScoreMat {
     float* ref_energy;
     Geometry g;
     float tau;         // columns with s_c^2 > tau * mean(s^2) of the chunk take the exact 8-bit route; 0: all do
-    int32_t parts;     // workgroups per tile: 0, one that takes every sweep; else see split_parts
+    int32_t cut;       // FS_WHOLE, FS_SPLIT or FS_SERIAL (see choose_cut)
+    int32_t parts;     // workgroups per tile
     float* colsel;     // [n_chunks][colsel_words]: the chunks' column selection, written by the preparing kernel
     // first pass of the unit features (FS_SCORE_FEAT, FS_FEAT_ONLY), else unused
     double* fmoments;      // [n_tiles][4 column quarters][4]: sum w, sum w^2, sum |w|, count(|w| < 1e-6)
@@ -194,21 +196,41 @@ inline size_t fit_score_lds_bytes(int32_t dtype, int32_t chunk_w, bool masked = 
 // K is no multiple of FS_KB) are scored as ratio 0 and dropped.
 __device__ __forceinline__ int32_t share_ratio(int32_t K, int32_t shares, int32_t i, int32_t v) { return K - shares * (FS_KB - i) + v; }
 
-// How a matrix's tiles are cut into workgroups: 0, one per tile, its wavefronts a sweep each over all columns; else
-// this many per tile, each sweep by all four wavefronts of one of them, a quarter of the columns each.  The matrix alone
-// decides, so that a batch gives the bits of the single calls (a quarter's sums are added in fp64, not in the lane's
-// fp32: other last bits).
-//   Up to 256 tiles there is at most one tile per CU, and what a call waits for is one wavefront's sweep over the whole
-//   chunk on an otherwise idle SIMD: every sweep gets a workgroup.  bf16 at chunk 128, 64 tiles, features and 40 ratios:
-//   70 -> 33 us; 256 tiles, 20 ratios: 46.7 -> 39.7 (512 tiles: 53.7, and 57.6 cut up: each part makes its own load and
-//   statistics).
-//   With one, two or three sweeps per tile (K <= 15) wavefronts go idle; all four share each sweep where a quarter of the
-//   chunk is worth a wavefront its own set of parameters and sums: K = 5, chunk 64, 2048 tiles: 37.7 -> 34.5, chunk 32,
-//   4096 tiles: 40.9 -> 43.2; K = 10, chunk 128, 5504 tiles: 213 -> 195, chunk 64, 11008 tiles: 219 -> 228; K = 15, chunk
-//   256, 2752 tiles: 283 -> 261, chunk 128, 5504 tiles: 255 -> 260.
-inline int32_t split_parts(const Geometry& g, int32_t shares) {
-    if (g.n_tiles <= 256) return shares;
-    return shares <= 3 && g.chunk_w >= 64 * shares ? 1 : 0;
+// How a matrix's tiles are cut.  The columns: in one piece (FS_WHOLE), every wavefront a sweep of its own over all of them; or in
+// quarters whose sums are added in fp64 (other last bits than a lane's fp32 sum over all columns), either at the same time by the
+// four wavefronts of a workgroup (FS_SPLIT) or one after the other by one wavefront (FS_SERIAL).  The matrix alone decides
+// between one piece and quarters, so that a batch gives the bits of the single calls; how the quarters are taken and how many
+// workgroups a tile's sweeps go to (parts) gives no other bits and follows from the tiles of the whole launch.
+//   Quarters up to 256 tiles (chunks below 64 columns: 64): alone such a matrix has at most a tile per CU, and what a
+// call waits for is one wavefront's sweep over the whole chunk on an otherwise idle SIMD.  bf16, chunk 128, 64 tiles, 40
+// ratios, features too: 70 -> 33 us; 256 tiles, 20 ratios: 52 -> 37.  Below 64 columns a quarter is worth too little: in full launches
+// of chunk 32 quarters cost 7 to 30 %.  Also with one, two or three sweeps per tile (K <= 15), where wavefronts would go idle, if the
+// chunk has 64 columns per sweep: K = 5, chunk 64, 2048 tiles: 37.7 -> 34.5, chunk 32, 4096 tiles: 40.9 -> 43.2; K = 10, chunk 128,
+// 5504 tiles: 213 -> 195, chunk 64, 11008 tiles: 219 -> 228; K = 15, chunk 256, 2752 tiles: 283 -> 261, chunk 128, 5504 tiles:
+// 255 -> 260.
+//   The launch: a workgroup per sweep up to 384 tiles (1.5 per CU; three matrices of 128 tiles at chunk 64, 40 ratios: 57 us, a wavefront
+// per sweep 61); beyond, the sweeps fill the chip and each workgroup's own load and statistics of the tile only cost: eight matrices of
+// 256 tiles, chunk 128, 20 ratios: a workgroup per sweep 172 us, a wavefront per sweep 146; 40 ratios 315 and 252; chunk 64: 111 and
+// 94, 203 and 158.  Up to 640 tiles no wavefront takes two sweeps (512 tiles, 40 ratios: 84 us, with one workgroup per tile 86, chunk 64: 57 and
+// 63), beyond, two workgroups per tile at most (2048 tiles, 64 ratios: chunk 128 411 with one, 416 with two, 451 with four).
+// Up to three sweeps go to a workgroup each up to 1024 tiles (chunk 64, 10 ratios: 45 us, a wavefront per sweep 46).
+static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
+    const int32_t waves = (A.shares + FS_WAVES - 1) / FS_WAVES;          // workgroups for a wavefront per sweep
+    for (int32_t i = 0; i < A.n; ++i) {
+        FitScoreMat& M = A.m[i];
+        const bool small = M.g.n_tiles <= (chunk_w < 64 ? 64 : 256);
+        const bool few = A.shares <= 3;
+        if (!small && !(few && chunk_w >= 64 * A.shares)) {
+            M.cut = FS_WHOLE;
+            M.parts = tiles <= 640 ? waves : 1;
+        } else if (few || tiles <= 384) {
+            M.cut = FS_SPLIT;
+            M.parts = small && tiles <= 1024 ? A.shares : 1;
+        } else {
+            M.cut = FS_SERIAL;
+            M.parts = tiles <= 640 || waves < 2 ? waves : 2;
+        }
+    }
 }
 
 // The 8-bit residual is ~1/500 of the range, so it is taken relative to an ANCHOR c: a grid
@@ -579,13 +601,14 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
 // MASKED: salient weights (Sec. 3.5) marked in A.mask take no part: they are left out of
 // the group statistics, and in every error sum their activation scale counts as zero.
 // rot spreads an uneven number of sweeps over the four SIMDs from tile to tile.
-// part < 0: the workgroup's wavefronts take a sweep each, over all columns.  part >= 0 (SPLIT): the workgroup takes sweeps
-// part, part + A.parts, ..., a quarter of the columns per wavefront; part 0 also makes what a tile produces once.
-template <int DT, bool MASKED, int MODE, bool SPLIT>
+// CUT: what the launch's matrices may be cut like (FS_WHOLE in every case; with it alone, one workgroup per tile).  The workgroup is part `part` of A.parts
+// of the tile; part 0 also makes what a tile produces once.
+template <int DT, bool MASKED, int MODE, int CUT>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
                                                const int rot, const int part, char* __restrict__ smem) {
-    const bool split = SPLIT && part >= 0;
-    const bool once = !split || part == 0;
+    const bool split = CUT == FS_SPLIT && A.cut == FS_SPLIT;
+    const bool serial = CUT == FS_SERIAL && A.cut == FS_SERIAL;
+    const bool once = CUT == FS_WHOLE || part == 0;
     constexpr bool ONLY8 = MODE == FS_ONLY8;
     constexpr bool FEAT = MODE == FS_SCORE_FEAT || MODE == FS_FEAT_ONLY;
     constexpr bool SCORE = MODE != FS_FEAT_ONLY;
@@ -959,7 +982,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         const int lane_r = fresh_lane();
         if (lane_r >= tc.nrows) acc3[0] = acc3[1] = acc3[2] = accc[0] = 0.0f;    // (a row past the end has range 0)
         rows_deposit<NROW>(acc3, red, lane_r, ACC3_COL);
-        if (bounds || split) {
+        if (bounds || split || serial) {
             if (MASKED) accc[1] *= (mx - mn) * (mx - mn);
             float none[1] = {0.0f};
             wave_sums_maxes(accc, none);
@@ -981,10 +1004,10 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
 
     // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4, or by
     // quarters to all of them.
-    const int32_t sc0 = split ? qc0 : 0, sc1 = split ? qc1 : G;
-    const int vstep = split ? A.parts : FS_WAVES;
+    int32_t sc0 = split ? qc0 : 0, sc1 = split ? qc1 : G;          // columns
+    const int vstep = CUT == FS_WHOLE ? FS_WAVES : (split ? A.parts : FS_WAVES * A.parts);
     int half = 0;
-    for (int v = split ? part : ((wave - rot) & (FS_WAVES - 1)); v < B.shares; v += vstep) {
+    for (int v = split ? part : (CUT == FS_WHOLE ? 0 : FS_WAVES * part) + ((wave - rot) & (FS_WAVES - 1)); v < B.shares; v += vstep) {
         const int32_t k0 = share_ratio(K, B.shares, 0, v), dk = B.shares;       // the sweep's ratio i: k0 + dk * i
         // the sweep's first ratios whose 8-bit candidate may be left out (skip8_f falls as k grows)
         int32_t skip_here = 0;
@@ -1032,7 +1055,6 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                     d = d >= FLT_MIN ? d : 0.0f;
                     if (b == 0) d8 = d;
                     if (!ONLY8 || b == 0) P[i].nd[b] = pin_vgpr(-d);
-                    acc[i][b] = 0.0f;
                 }
                 // anchor: the 8-bit grid point nearest zero when zero lies inside the range, else lo
                 float q0 = 0.0f;
@@ -1047,9 +1069,18 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             const float Q[4] = {pin_vgpr(255.0f), pin_vgpr(15.0f), pin_vgpr(7.0f), pin_vgpr(3.0f)};
             const float M = pin_vgpr(RNE_POS);
             const float nM = pin_vgpr(-RNE_POS);
+            for (int quarter = 0; quarter < (serial ? FS_WAVES : 1); ++quarter) {
+            if (serial) {
+                sc0 = ((quarter * runs) >> 2) << 3;
+                sc1 = (((quarter + 1) * runs) >> 2) << 3;
+            }
             float nz[FS_KB];        // the noise terms of the short route (zero on the exact ones)
 #pragma unroll
-            for (int i = 0; i < FS_KB; ++i) nz[i] = 0.0f;
+            for (int i = 0; i < FS_KB; ++i) {
+                nz[i] = 0.0f;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) acc[i][b] = 0.0f;
+            }
             // (the row addresses are formed from a fresh lane index in front of each sweep: kept
             // from here they would be spilled across the parameter set-up)
             __builtin_amdgcn_s_setprio(0);       // the sweeps: issue-bound, ordinary priority
@@ -1146,7 +1177,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 for (int i = 0; i < FS_KB; ++i) nz[i] = acc[i][0] * (P[i].nd[0] * P[i].nd[0]) * 65025.0f;
                 for (int32_t hi = 0; hi < nh; ++hi) {
                     const int32_t c = __builtin_amdgcn_readfirstlane(hlist[hi]);
-                    if (split && (c < sc0 || c >= sc1)) continue;
+                    if (CUT != FS_WHOLE && (c < sc0 || c >= sc1)) continue;
                     const float w = read1<DT>(wrow, c);
                     float sc = scol[c];
                     if (MASKED) sc = ((mrow[c >> 3] >> (c & 7)) & 1u) != 0u ? 0.0f : sc;
@@ -1180,6 +1211,14 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 if (lane_r < FS_NRED)
                     tot = ((qsum[lane_r] + qsum[TILE_ROWS + lane_r]) + qsum[2 * TILE_ROWS + lane_r]) + qsum[3 * TILE_ROWS + lane_r];
             }
+            if (serial) {        // the same sums, in the same order
+                double* __restrict__ qsum = s1tab + wave * TILE_ROWS;
+                if (lane_r < FS_NRED) {
+                    if (quarter > 0) tot = qsum[lane_r] + tot;
+                    qsum[lane_r] = tot;
+                }
+                if (quarter < FS_WAVES - 1) continue;
+            }
             if (lane_r < FS_KB * 4) {
                 const int i = lane_r >> 2;
                 const int k = k0 + dk * i;
@@ -1198,9 +1237,10 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                     out[fit_score_noise_slot(K) + k] = tot * (double)ratio;
                 }
             }
+            }
         }
     }
-    if (!ONLY8 && !split && ncollect > FS_NRED) {     // no sweep fell to this wavefront
+    if (!ONLY8 && !split && once && ncollect > FS_NRED) {     // no sweep fell to this wavefront
         const int lane_r = fresh_lane();
         store_extra(lane_r, rows_collect<NROW>(red, lane_r, NROW));
     }
@@ -1267,19 +1307,19 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
     }
 }
 
-template <int DT, bool MASKED, int MODE, bool SPLIT>
+template <int DT, bool MASKED, int MODE, int CUT>
 __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScoreArgs B) {
     extern __shared__ char smem[];
     const int mi = batch_index(B.tile_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
     int64_t local = (int64_t)blockIdx.x - B.tile_start[mi];
-    int part = -1;
-    if (SPLIT && A.parts > 0) {         // all tiles' first parts, then all tiles' second parts, ...
+    int part = 0;
+    if (CUT != FS_WHOLE) {              // all tiles' first parts, then all tiles' second parts, ...
         part = (int)((uint32_t)local / (uint32_t)A.g.n_tiles);
         local -= (int64_t)part * A.g.n_tiles;
     }
     const TileCoord tc = tile_coord(A.g, local);
-    fit_score_tile<DT, MASKED, MODE, SPLIT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, smem);
+    fit_score_tile<DT, MASKED, MODE, CUT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, smem);
 }
 
 // The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
@@ -1318,7 +1358,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const int64_t li = local / tpu, t = local - li * tpu;
         const int64_t u = A.redo_list[li];
         const TileCoord tc = tile_coord_of_unit(A.g, u, t);
-        fit_score_tile<DT, MASKED, FS_ONLY8, false>(B, A, tc, (int)(w & (FS_WAVES - 1)), -1, smem);
+        fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, smem);
         ++run;
         if (w + 1 < w_end && t + 1 < tpu) {
             __syncthreads();         // the next tile overwrites this one's LDS
@@ -1429,19 +1469,24 @@ static int launch_tiles_untimed(const FitScoreArgs& A, int32_t dtype, bool maske
         hipLaunchKernelGGL(kernel, grid, dim3(FS_THREADS), lds, hs, A);
         return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
     };
-    constexpr bool CAN_MASK = MODE == FS_SCORE, CAN_SPLIT = MODE != FS_FEAT_ONLY;
-    bool split = false;
-    for (int32_t i = 0; i < A.n; ++i) split |= A.m[i].parts > 0;
-    auto by_input = [&](auto split_t) -> int {
-        constexpr bool SPLIT = decltype(split_t)::value;
+    constexpr bool CAN_MASK = MODE == FS_SCORE, CAN_CUT = MODE != FS_FEAT_ONLY;
+    int cut = FS_WHOLE;             // FS_SPLIT and FS_SERIAL do not meet in a launch; with either, whole ones may have parts
+    for (int32_t i = 0; i < A.n; ++i) {
+        if (A.m[i].cut != FS_WHOLE) cut = A.m[i].cut;
+        else if (A.m[i].parts > 1 && cut == FS_WHOLE) cut = FS_SERIAL;
+    }
+    auto by_input = [&](auto cut_t) -> int {
+        constexpr int CUT = decltype(cut_t)::value;
         if (dtype == WINDQ_BF16) {
-            if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_BF16, CAN_MASK, MODE, SPLIT>);
-            return launch(&fit_score_kernel<WINDQ_BF16, false, MODE, SPLIT>);
+            if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_BF16, CAN_MASK, MODE, CUT>);
+            return launch(&fit_score_kernel<WINDQ_BF16, false, MODE, CUT>);
         }
-        if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_F32, CAN_MASK, MODE, SPLIT>);
-        return launch(&fit_score_kernel<WINDQ_F32, false, MODE, SPLIT>);
+        if (CAN_MASK && masked) return launch(&fit_score_kernel<WINDQ_F32, CAN_MASK, MODE, CUT>);
+        return launch(&fit_score_kernel<WINDQ_F32, false, MODE, CUT>);
     };
-    return split ? by_input(std::integral_constant<bool, CAN_SPLIT>{}) : by_input(std::false_type{});
+    if (cut == FS_SPLIT) return by_input(std::integral_constant<int, CAN_CUT ? FS_SPLIT : FS_WHOLE>{});
+    if (cut == FS_SERIAL) return by_input(std::integral_constant<int, CAN_CUT ? FS_SERIAL : FS_WHOLE>{});
+    return by_input(std::integral_constant<int, FS_WHOLE>{});
 }
 
 // feat: nullptr, or the filled feature batch of the same matrices: the main kernel then also makes the
@@ -1508,19 +1553,23 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         // tau = 1 every column takes the exact route.
         const float t = 7e-5f * (float)chunk_w * (float)M.g.R_u;
         M.tau = t < 1.0f ? 0.0f : t;
-        M.parts = split_parts(M.g, A.shares);
-        A.tile_start[i] = tiles;
         A.unit_start[i] = units;
         A.prep_start[i] = preps;
-        tiles += M.g.n_tiles * (M.parts > 0 ? M.parts : 1);
+        tiles += M.g.n_tiles;
         units += M.g.U;
         preps += (M.g.n_chunks + FS_PREP_CHUNKS - 1) / FS_PREP_CHUNKS + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) {
-        A.tile_start[i] = tiles;
         A.unit_start[i] = units;
         A.prep_start[i] = preps;
     }
+    choose_cut(A, chunk_w, tiles);
+    tiles = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        A.tile_start[i] = tiles;
+        tiles += A.m[i].g.n_tiles * A.m[i].parts;
+    }
+    for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) A.tile_start[i] = tiles;
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) A.m[i] = A.m[0];
     if (tiles > (int64_t)0x7fffffff || preps > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);

@@ -61,3 +61,36 @@ def test_a_batch_of_small_and_large_equals_the_single_calls(windq, dtype, K):
         feat = windq.windq_unit_features(W, s, 128, 0)
         want = (feat, *windq.windq_fit_score_all_bits(W, s, 128, 0, cg))
         assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
+
+
+@pytest.mark.parametrize("G,K", [(64, 20), (64, 40), (64, 64), (96, 33), (128, 10), (64, 15), (32, 40), (40, 64), (256, 20)])
+@pytest.mark.parametrize("tiles", [384, 385, 640, 641, 1024, 1025])
+def test_the_size_of_the_launch_changes_no_bits(windq, tiles, G, K):
+    """Launches on both sides of where a tile's sweeps go to fewer workgroups: matrices cut in quarters (of 256 tiles, or 64 where the
+    chunk is narrow) and in one piece side by side, each as in its own call."""
+    dtype = torch.float32 if K % 2 else torch.bfloat16
+    per = 64 if G < 64 else 128
+    rows = [64 * per - 5, 64 * per] + ([64 * (tiles - 2 * per)] if tiles <= 640 else [64 * 257, 64 * (tiles - 2 * per - 257)])
+    mats = [inputs(r, G, 20 + i, dtype) for i, r in enumerate(rows)]
+    cg = synth.clip_grid(K)
+    batch = windq.windq_fit_score_all_bits_batch([m[0] for m in mats], [m[1] for m in mats], G, 0, cg)
+    fused = windq.windq_features_fit_score_batch([m[0] for m in mats], [m[1] for m in mats], G, 0, cg)
+    for i, ((W, s), got, both) in enumerate(zip(mats, batch, fused)):
+        want = windq.windq_fit_score_all_bits(W, s, G, 0, cg)
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(both[1:], want))
+        assert torch.equal(both[0], windq.windq_unit_features(W, s, G, 0))
+        if i == 0 and tiles == 385:
+            compare(W, s, G, 0, cg, got)
+
+
+@pytest.mark.parametrize("G,K", [(64, 40), (128, 20), (32, 64)])
+def test_the_size_of_a_masked_launch_changes_no_bits(windq, G, K):
+    mats = [inputs(64 * 128 - 5, G, 30 + i, torch.bfloat16) for i in range(4)]
+    masks = [windq.windq_salient_select(W, s, G, 0, 30000) for W, s in mats]
+    cg = synth.clip_grid(K)
+    batch = windq.windq_fit_score_all_bits_batch([m[0] for m in mats], [m[1] for m in mats], G, 0, cg, masks=masks)
+    for (W, s), mask, got in zip(mats, masks, batch):
+        want = windq.windq_fit_score_all_bits(W, s, G, 0, cg, mask=mask)
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
+    compare(*mats[0], G, 0, cg, batch[0], mask=masks[0])
