@@ -155,7 +155,8 @@ int windq_unit_features(const windq_mat* W, const float* s /*[cols]*/, int32_t c
  * unit whose noise could exceed 3e-6 of its 8-bit error (one standard deviation; measured
  * deviations are ~0.4 of that estimate) has its 8-bit candidates scored again on the exact
  * route before the call's work ends, whatever the input.  8-bit candidates that clipping alone rules out
- * (a lower bound on the unit's error, proven per unit) are left out; a unit without that proof is scored again too.
+ * (a lower bound on the unit's error, proven per unit) are left out; in a unit without that proof the
+ * ones it leaves open are scored, on the exact route too.
  * |s_c * w| must square inside fp32's normal range.
  *   That accuracy is a unit's, not a single weight's.  A weight's residual s_c (w - lo - code step)
  * comes from fp32-rounded products: an absolute error near 1e-7 s_c (hi - lo) at 4 bits and below
@@ -210,8 +211,8 @@ int windq_kernel_timer_read(double* total_ms /*HOST*/, int64_t* launches /*HOST*
 
 /*
  * Diagnostic: how many units of the last windq_fit_score_all_bits (or _prot, or batch item) call
- * that used workspace `ws` had their 8-bit candidates scored a second time on the exact route (for their noise, or because a
- * candidate that was left out could not be ruled out).
+ * that used workspace `ws` had 8-bit candidates scored in a second pass, on the exact route (all of them for their noise, or
+ * those that were left out and could not be ruled out).
  * Pass the shape arguments of that call.  Unlike every other entry point this one copies a
  * counter to the host and therefore waits for the device: call it after the stream has finished.
  */

@@ -76,7 +76,6 @@ namespace windq {
 
 constexpr int FS_THREADS = 256;
 constexpr int FS_WAVES = FS_THREADS / 64;
-constexpr int FS_KB = 5;                    // clip ratios evaluated together by one wavefront pass
 constexpr int FS_NRED = FS_KB * 5;          // per-lane sums a pass produces: 4 errors + 1 noise term per clip ratio
 constexpr int FS_NEXTRA = 6;                // sums a tile produces once: 3 of the unit features, then ternary / binary / reference
 constexpr int FS_NROW = FS_NRED + FS_NEXTRA;    // row of a wavefront's scratch for combining rows
@@ -602,11 +601,12 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
 // the group statistics, and in every error sum their activation scale counts as zero.
 // rot spreads an uneven number of sweeps over the four SIMDs from tile to tile.
 // CUT: what the launch's matrices may be cut like (FS_WHOLE in every case; with it alone, one workgroup per tile).  The workgroup is part `part` of A.parts
-// of the tile; part 0 also makes what a tile produces once.
+// of the tile; part 0 also makes what a tile produces once.  sweeps: FS_ONLY8, a bit for each sweep to take; fewer than there are
+// wavefronts are taken by quarters of the columns.
 template <int DT, bool MASKED, int MODE, int CUT>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
-                                               const int rot, const int part, char* __restrict__ smem) {
-    const bool split = CUT == FS_SPLIT && A.cut == FS_SPLIT;
+                                               const int rot, const int part, const uint32_t sweeps, char* __restrict__ smem) {
+    const bool split = MODE == FS_ONLY8 ? __builtin_popcount(sweeps) < FS_WAVES : CUT == FS_SPLIT && A.cut == FS_SPLIT;
     const bool serial = CUT == FS_SERIAL && A.cut == FS_SERIAL;
     const bool once = CUT == FS_WHOLE || part == 0;
     constexpr bool ONLY8 = MODE == FS_ONLY8;
@@ -1005,9 +1005,10 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4, or by
     // quarters to all of them.
     int32_t sc0 = split ? qc0 : 0, sc1 = split ? qc1 : G;          // columns
-    const int vstep = CUT == FS_WHOLE ? FS_WAVES : (split ? A.parts : FS_WAVES * A.parts);
+    const int vstep = ONLY8 ? (split ? 1 : FS_WAVES) : (CUT == FS_WHOLE ? FS_WAVES : (split ? A.parts : FS_WAVES * A.parts));
     int half = 0;
     for (int v = split ? part : (CUT == FS_WHOLE ? 0 : FS_WAVES * part) + ((wave - rot) & (FS_WAVES - 1)); v < B.shares; v += vstep) {
+        if (ONLY8 && ((sweeps >> v) & 1u) == 0u) continue;
         const int32_t k0 = share_ratio(K, B.shares, 0, v), dk = B.shares;       // the sweep's ratio i: k0 + dk * i
         // the sweep's first ratios whose 8-bit candidate may be left out (skip8_f falls as k grows)
         int32_t skip_here = 0;
@@ -1319,12 +1320,15 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
         local -= (int64_t)part * A.g.n_tiles;
     }
     const TileCoord tc = tile_coord(A.g, local);
-    fit_score_tile<DT, MASKED, MODE, CUT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, smem);
+    fit_score_tile<DT, MASKED, MODE, CUT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, 0u, smem);
 }
 
 // The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
 // walks the list, each workgroup a run of consecutive tiles; with nothing listed every workgroup ends after reading the
-// counters.  The workgroup that scores a unit's last tile adds the tiles up again (in the order of the finalize kernel) and
+// counters.  A unit listed only because a candidate
+// that was left out is not ruled out takes the sweeps that hold such candidates, one to three by all four wavefronts: one
+// unit of 16 tiles listed beside 23 others at chunk 256, 64 ratios: 294 us with every sweep, 216 so (266 without the bound).
+// The workgroup that scores a unit's last tile adds the tiles up again (in the order of the finalize kernel) and
 // corrects the unit's 8-bit error and clip index: a launch of its own for that took 4.5 us of every call, with nothing
 // to do in most.  The tiles' sums are stored and loaded past the L2s (device-scope atomic accesses), and a workgroup
 // waits for its stores before it adds its run to the unit's count of finished tiles: with a device-wide release and
@@ -1358,14 +1362,15 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const int64_t li = local / tpu, t = local - li * tpu;
         const int64_t u = A.redo_list[li];
         const TileCoord tc = tile_coord_of_unit(A.g, u, t);
-        fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, smem);
+        const int32_t K = B.K, ncand = fit_score_ncand(K);
+        double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
+        const uint32_t sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
+        fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);
         ++run;
         if (w + 1 < w_end && t + 1 < tpu) {
             __syncthreads();         // the next tile overwrites this one's LDS
             continue;
         }
-        const int32_t K = B.K, ncand = fit_score_ncand(K);
-        double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // this wavefront's sums have reached memory ...
         __syncthreads();                                        // ... and the other wavefronts' too
         if (threadIdx.x == 0) done = __hip_atomic_fetch_add(fit_redo_done(unit, K), run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + run;
@@ -1376,19 +1381,11 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         static_assert((FIN_PHASES + 1) * WINDQ_MAX_CLIP * sizeof(double) <= FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
         for (int i = threadIdx.x; i < FIN_PHASES * K; i += FS_THREADS) {
             const int phase = i / K, k = i - phase * K;
-            double acc = 0.0;
-#pragma unroll 4
-            for (int64_t j = phase; j < tpu; j += FIN_PHASES) acc += __hip_atomic_load(unit + (size_t)j * ncand + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            part[phase * WINDQ_MAX_CLIP + k] = acc;
+            part[phase * WINDQ_MAX_CLIP + k] = fit_phase_sum<true>(unit, tpu, ncand, k, phase);
         }
         __syncthreads();
         double* E = part + FIN_PHASES * WINDQ_MAX_CLIP;
-        if ((int)threadIdx.x < K) {
-            double acc = 0.0;
-#pragma unroll
-            for (int p = 0; p < FIN_PHASES; ++p) acc += part[p * WINDQ_MAX_CLIP + threadIdx.x];
-            E[threadIdx.x] = acc;
-        }
+        if ((int)threadIdx.x < K) E[threadIdx.x] = fit_phases_total(part, WINDQ_MAX_CLIP, threadIdx.x);
         __syncthreads();
         if (threadIdx.x == 0) {
             double best, bound;
@@ -1587,6 +1584,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     FitFinalBatch F;
     F.n = n;
     F.K = K;
+    F.shares = A.shares;
     for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) F.unit_start[i] = A.unit_start[i];
     for (int32_t i = 0; i < WINDQ_MAX_BATCH; ++i)
         F.m[i] = {A.m[i].partial, A.m[i].redo_count, A.m[i].redo_list, A.m[i].err, A.m[i].clip_idx, A.m[i].ref_energy, A.m[i].g.tiles_per_unit};

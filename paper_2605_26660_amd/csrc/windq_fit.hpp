@@ -19,6 +19,7 @@ struct FitFinalMat {
 struct FitFinalBatch {
     int32_t n;
     int32_t K;
+    int32_t shares;        // sweeps the clip grid is dealt to: ratio k belongs to sweep (k - K) mod shares
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     FitFinalMat m[WINDQ_MAX_BATCH];
 };
@@ -26,6 +27,8 @@ struct FitFinalBatch {
 // The 16 sums a unit's tiles are added in: sum p takes tiles p, p + 16, p + 32, ... in order; the sums are then added
 // in order.  Fixed whatever the workgroup's size, so that every kernel that adds tiles up gives the same bits.
 constexpr int FIN_PHASES = 16;
+
+constexpr int FS_KB = 5;         // clip ratios of a sweep
 
 #ifdef __HIPCC__
 
@@ -37,12 +40,28 @@ constexpr double BOUND_SLACK = 1e-4;
 
 
 // One phase of one candidate.  (A sum that holds a lower bound, marked by its sign, is one itself and keeps the mark.)
+// SHARED: the tiles' sums may have been stored by other workgroups of this launch (past the L2s).
+template <bool SHARED>
 __device__ __forceinline__ double fit_phase_sum(const double* __restrict__ base, int64_t tiles_per_unit, int32_t ncand, int32_t cand, int phase) {
     double acc = 0.0;
     bool bound = false;
 #pragma unroll 4
     for (int64_t t = phase; t < tiles_per_unit; t += FIN_PHASES) {
-        const double v = base[(size_t)t * ncand + cand];
+        const double* at = base + (size_t)t * ncand + cand;
+        const double v = SHARED ? __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *at;
+        bound |= v < 0.0;
+        acc += fabs(v);
+    }
+    return bound ? -acc : acc;
+}
+
+// The phases of one candidate, in order, from [FIN_PHASES][stride].
+__device__ __forceinline__ double fit_phases_total(const double* lds, int32_t stride, int32_t cand) {
+    double acc = 0.0;
+    bool bound = false;
+#pragma unroll
+    for (int p = 0; p < FIN_PHASES; ++p) {
+        const double v = lds[p * stride + cand];
         bound |= v < 0.0;
         acc += fabs(v);
     }
@@ -67,11 +86,12 @@ __device__ __forceinline__ int fit_least(const double* E, int32_t K, double* bes
     return bk;
 }
 
-// How many tiles of a listed unit have been scored again: a word in the unit's own partials (the first noise slot of its
-// first tile, which nothing reads once the unit is listed).
+// How many tiles of a listed unit have been scored again, and which sweeps they take (a bit each): two words in the unit's own
+// partials (the first noise slot of its first tile, which nothing reads once the unit is listed).
 __device__ __forceinline__ uint32_t* fit_redo_done(double* unit_partial, int32_t K) {
     return reinterpret_cast<uint32_t*>(unit_partial + fit_score_noise_slot(K));
 }
+__device__ __forceinline__ uint32_t* fit_redo_sweeps(double* unit_partial, int32_t K) { return fit_redo_done(unit_partial, K) + 1; }
 
 // Dynamic LDS of a workgroup that finalizes: [FIN_PHASES][ncand] phase sums, [ncand] totals.
 constexpr size_t fit_finalize_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES + 1) * (size_t)fit_score_ncand(K) * sizeof(double); }
@@ -91,19 +111,9 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     double* __restrict__ E = lds + FIN_PHASES * ncand;
     double* base = A.partial + (size_t)u * (size_t)tiles_per_unit * (size_t)ncand;
     for (int phase = threadIdx.x >> 6; phase < FIN_PHASES; phase += NT / 64)
-        for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) lds[phase * ncand + cand] = fit_phase_sum(base, tiles_per_unit, ncand, cand, phase);
+        for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) lds[phase * ncand + cand] = fit_phase_sum<false>(base, tiles_per_unit, ncand, cand, phase);
     __syncthreads();
-    for (int32_t cand = threadIdx.x; cand < ncand; cand += NT) {
-        double acc = 0.0;
-        bool bound = false;
-#pragma unroll
-        for (int p = 0; p < FIN_PHASES; ++p) {
-            const double v = lds[p * ncand + cand];
-            bound |= v < 0.0;
-            acc += fabs(v);
-        }
-        E[cand] = bound ? -acc : acc;
-    }
+    for (int32_t cand = threadIdx.x; cand < ncand; cand += NT) E[cand] = fit_phases_total(lds, ncand, cand);
     __syncthreads();
     const int tid = threadIdx.x;
     if (tid < 4) {
@@ -111,9 +121,17 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
         const int bk = fit_least(E + tid * K, K, &best, &bound);
         A.err[u * WINDQ_N_ERR + tid] = (float)best;
         A.clip_idx[u * 4 + tid] = (uint8_t)bk;
-        // (tid 0: 8 bits) listed: too much noise, or a candidate that was left out is not proved to be worse
-        if (tid == 0 && (E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best || bound * (1.0 - BOUND_SLACK) <= best)) {
+        // (tid 0: 8 bits) listed: too much noise, then every sweep is taken again; or a candidate that was left out is not
+        // proved to be worse, then the sweeps of such candidates
+        const bool noisy = tid == 0 && E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best;
+        if (tid == 0 && (noisy || bound * (1.0 - BOUND_SLACK) <= best)) {
+            uint32_t sweeps = 0u;
+            for (int k = 0; k < K; ++k) {
+                const uint32_t v = (uint32_t)(k + FS_KB * B.shares - K) % (uint32_t)B.shares;
+                if (noisy || (E[k] < 0.0 && -E[k] * (1.0 - BOUND_SLACK) <= best)) sweeps |= 1u << v;
+            }
             *fit_redo_done(base, K) = 0u;
+            *fit_redo_sweeps(base, K) = sweeps;
             const uint32_t pos = atomicAdd(A.redo_count, 1u);
             A.redo_list[pos] = (uint32_t)u;
         }

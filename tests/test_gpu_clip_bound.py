@@ -118,3 +118,18 @@ def test_values_that_are_not_finite(windq):
     bad[70, 5] = float("inf")
     got = windq.windq_fit_score_all_bits(bad, s, 128, 0, synth.clip_grid(20))
     assert torch.equal(got[0][1], want[0][1]) and torch.equal(got[1][1], want[1][1])
+
+
+@pytest.mark.parametrize("R", [320, 64 * 260 - 7])
+@pytest.mark.parametrize("K,extreme,low", [(20, 0.4, 0.5), (20, 0.3, 0.5), (20, 0.3, 0.85), (64, 0.4, 0.5), (64, 0.3, 0.85), (15, 0.3, 0.85)])
+def test_the_sweeps_that_are_scored_again(windq, R, K, extreme, low):
+    """Left out and not ruled out: ratios 1 - d with 2 e^2 d^2 between 1.25 times the error expected at ratio 1 and the 2.43 times that
+    it has, d from 0.0202 / e to 0.0281 / e; the grid has nothing between them and ratio 1.  One to all of its sweeps, and the unit's
+    best ratio lies in them.  Five tiles, swept by quarters, and 260, swept in one piece."""
+    cg = torch.tensor(list(np.linspace(low, 1.0 - 0.0206 / extreme, K - 1)) + [1.0], dtype=torch.float32)
+    W, s = far_from_the_grid(R, 128, extreme)
+    assert check(windq, W, s, 128, 0, cg) == 1
+    batch = windq.windq_features_fit_score_batch([W, W], [s, s], 128, 0, cg)
+    alone = windq.windq_fit_score_all_bits(W, s, 128, 0, cg)
+    assert all(torch.equal(a, b) for got in batch for a, b in zip(got[1:], alone))
+    assert int(alone[1][0, 0]) < K - 1
