@@ -106,14 +106,15 @@ constexpr int FS_FEAT_ONLY = 3;     // that first pass alone          // workgro
 // 8-bit candidates are scored again on the exact route when that exceeds NOISE_MAX times the
 // unit's 8-bit error at the chosen clip index.  (Measured against fp64, the actual deviation
 // is ~0.4 of this estimate: NOISE_MAX = 3e-6 (windq_fit.hpp) keeps one standard deviation near 1e-6.)
+//
 // 8-bit candidates that cannot win.  At clip ratio p a weight beyond the clipped range [p min, p max] is off by at
 // least its distance e from that range, at any bit-width: with C(p) = sum s_c^2 e^2, E_b(p) >= C(p).  As p falls C only
 // grows, and at a known rate: e <= (1-p) |max| (or |min|), so e(p') = e(p) + (p-p') |max| >= e(p) (1-p')/(1-p) and
 //     C(p') >= C(p) ((1-p')/(1-p))^2     for p' < p.
-// An 8-bit grid is so fine that C passes the whole error at p = 1 (about step^2/12 a weight, step = (max-min)/255) once
-// p is a few per cent below 1.  So a tile takes C at ONE ratio (skip8_p), and where the bound for a smaller ratio exceeds
-// SKIP8_MARGIN (units of few tiles: SKIP8_MARGIN_FEW) times the expected error at ratio 1 it leaves that 8-bit candidate out and writes the bound, negated,
-// in its place: the sum over the unit's tiles is then a lower bound on the candidate's error, and says so by its sign.
+// An 8-bit grid is so fine that C passes the whole error at the grid's last ratio P (about P^2 step^2/12 a weight, step = (max-min)/255,
+// and C(P) <= C(p) ((1-P)/(1-p))^2) once p is a few per cent below P.  So a tile takes C at ONE ratio (skip8_p), and where the bound
+// for a smaller ratio exceeds the error expected at P, its first part times SKIP8_MARGIN (units of few tiles:
+// SKIP8_MARGIN_FEW) and its second a thousandth more, it leaves that 8-bit candidate out and writes the bound, negated, in its place: the sum over the unit's tiles is then a lower bound on the candidate's error, and says so by its sign.
 // The finalize kernel chooses among the candidates that every tile has scored and PROVES the choice: a unit one of
 // whose bounds does not exceed the chosen error by BOUND_SLACK (more than fp32 rounding can have put into either) goes
 // on the list of units whose 8-bit candidates are all scored again.  So a tile's test decides speed, never the result.
@@ -166,6 +167,8 @@ struct FitScoreArgs {
     int32_t K;
     int32_t shares;                              // sweeps the clip grid is dealt to, ceil(K / FS_KB) (see share_ratio)
     float skip8_p;                               // clip ratio at which the tiles take the clipping error
+    float skip8_q;                               // the grid's last ratio, squared
+    float skip8_last;                            // most that the clipping error there can be of that at skip8_p, and a thousandth
     ClipGrid skip8_f;                            // [k]: a lower bound on the clipping error at ratio k over that at skip8_p
     double inv_G;                                // 1 / chunk_w
     int64_t tile_start[WINDQ_MAX_BATCH + 1];     // first workgroup of matrix i in the grid; [n] = grid size
@@ -999,7 +1002,8 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         }
     }
     // an 8-bit candidate is left out where its bound, tile_clip * skip8_f[k], exceeds this (never where either is NaN)
-    const float skip8_above = s2_rg2 * ((A.g.tiles_per_unit <= SKIP8_FEW_TILES ? SKIP8_MARGIN_FEW : SKIP8_MARGIN) / (12.0f * 65025.0f));
+    const float skip8_above = s2_rg2 * ((A.g.tiles_per_unit <= SKIP8_FEW_TILES ? SKIP8_MARGIN_FEW : SKIP8_MARGIN) / (12.0f * 65025.0f)) * B.skip8_q +
+                              tile_clip * B.skip8_last;
     int32_t ncollect = ONLY8 ? FS_NRED : NROW;         // columns the next collection takes
 
     // The clip grid, a sweep over the tile for every FS_KB ratios.  Sweep v goes to wavefront (v + rot) % 4, or by
@@ -1501,10 +1505,14 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.skip8_f.p[k] = 0.0f;
     int32_t t = K - 1;
     while (t >= 0 && clip_grid[t] > SKIP8_MAX_P) --t;
-    if (t >= 0 && clip_grid[K - 1] == 1.0f) {      // (the error a tile expects is that at ratio 1)
+    A.skip8_q = clip_grid[K - 1] * clip_grid[K - 1];
+    A.skip8_last = 0.0f;
+    if (t >= 0) {
+        const double at = 1.0 - (double)clip_grid[t], last = (1.0 - (double)clip_grid[K - 1]) / at;
         A.skip8_p = clip_grid[t];
+        A.skip8_last = (float)(1.001 * last * last);
         for (int k = 0; k <= t; ++k) {
-            const double f = (1.0 - (double)clip_grid[k]) / (1.0 - (double)clip_grid[t]);
+            const double f = (1.0 - (double)clip_grid[k]) / at;
             A.skip8_f.p[k] = (float)(f * f);
         }
     }
@@ -1614,7 +1622,7 @@ int windq::features_launch_tiles(const FeatBatch& F, hipStream_t hs) {
     A.n = F.n;
     A.K = 1;
     A.shares = 0;
-    A.skip8_p = 0.0f;
+    A.skip8_p = A.skip8_q = A.skip8_last = 0.0f;
     for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.skip8_f.p[k] = 0.0f;
     A.inv_G = 0.0;
     for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.grid.p[k] = 1.0f;

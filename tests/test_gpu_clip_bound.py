@@ -133,3 +133,19 @@ def test_the_sweeps_that_are_scored_again(windq, R, K, extreme, low):
     alone = windq.windq_fit_score_all_bits(W, s, 128, 0, cg)
     assert all(torch.equal(a, b) for got in batch for a, b in zip(got[1:], alone))
     assert int(alone[1][0, 0]) < K - 1
+
+
+@pytest.mark.parametrize("ratios", [list(np.linspace(0.5, 0.9, 20)), list(np.linspace(0.1, 0.99, 40)), list(np.linspace(0.89, 0.9, 16)),
+                                    list(np.linspace(0.8999, 0.9, 16)), list(np.linspace(0.05, 0.3, 10)), [0.2, 0.94, 0.96]])
+@pytest.mark.parametrize("G,unit_rows", [(128, 0), (64, 64), (256, 128)])
+def test_grids_that_end_below_one(windq, ratios, G, unit_rows):
+    """Here the last ratio clips too: it must be part of the error that a bound has to pass.  Down to steps at which a bound
+    and the last ratio's error differ by less than fp32 sums can tell; units of five tiles and of one or two; more than 256 tiles."""
+    cg = torch.tensor(ratios, dtype=torch.float32)
+    W = synth.weights_llm(320 if unit_rows == 0 else 4 * unit_rows, 512, seed=len(ratios), device=DEV)
+    listed = check(windq, W, scales(512, 7), G, unit_rows, cg)
+    assert listed == 0 or ratios[-1] - ratios[0] < 0.001
+    if G == 128:
+        check(windq, synth.weights_llm(64 * 65 - 3, 512, seed=3, device=DEV, dtype=torch.float32), scales(512, 9), G, 0, cg)
+        mask = windq.windq_salient_select(W, scales(512, 7), G, unit_rows, 30000)
+        check(windq, W, scales(512, 7), G, unit_rows, cg, mask=mask)
