@@ -404,8 +404,9 @@ __global__ __launch_bounds__(256) void dequant_finalize_kernel(const DequantBatc
 constexpr int GEMV_THREADS = 256;
 // Dear units first (windq_order.hpp) where a launch has four workgroups per CU or more: skipped units and those taken weight by
 // weight (8, 4 and 3 bits), then tables of trits and of 2 bits, then of 1 bit.  7B-shaped block at 2 bits 41.9 -> 37.8 us,
-// 28672 x 8192 and the others of its block 60 -> 42; plans of one width keep their times; with 392 workgroups the look at the
-// actions costs 0.4 us of 13.9.
+// 28672 x 8192 and the others of its block 60 -> 42; the look at the actions costs plans of one width 0.5 to 1.4 us
+// (7B-shaped block, 4 bits 41.5 -> 42.2, 2 bits 30.5 -> 31.6, binary 24.2 -> 25.5; asking for x or the action ahead of it, or one wavefront
+// looking for all, takes 0.2 of that back and costs mixed plans more), and with 392 workgroups 0.4 of 13.9.
 constexpr uint32_t GEMV_CLASSES = (1u << 8) | (1u << 10) | (2u << 12);
 constexpr int GEMV_TRIT_WORDS = 48;                 // of a byte of trits: 27 entries at 0, 10 at 32
 constexpr size_t GEMV_BOTH_LDS = GEMV_THREADS * sizeof(double) + 256 * sizeof(uint16_t);        // of lanes that share a row, beside the others
@@ -690,7 +691,7 @@ __device__ __forceinline__ void gemv_rows_wg(const DequantBatch& B, const uint32
     const uint32_t nr = (uint32_t)((A.g.R_u + nt - 1) / nt);
     uint32_t rb, rr, j;
     if (!MASKED && B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
-        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, (int32_t)nr, (int32_t)at, GEMV_CLASSES);
+        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, (int32_t)nr, (int32_t)nr, (int32_t)at, GEMV_CLASSES);
         rr = (uint32_t)o.item;
         rb = (uint32_t)o.unit / nc;
         j = (uint32_t)o.unit - rb * nc;

@@ -417,10 +417,25 @@ struct RefineRowOf<DT, 0> {
 // A tile of a uniform unit takes four times as long as one of a binary unit (at three rounds), and a launch of more
 // tiles than the chip holds at once (4096 at chunk 128, bf16) ends with what came last: in the matrix's own order, where every band
 // of rows has units of each kind, a 7B-shaped block took 285 us, dear units first 225.  Launches that fit keep that order:
-// with 500 tiles the look at the actions costs 1 us of 20.
+// with 500 tiles the look at the actions costs 1 us of 20.  Skipped units come last, and one workgroup takes 16 of such a unit's
+// tiles: where each looked for its own, a plan of nothing else took 18.4 us (7B-shaped block) and 17.0 (28672 x 8192), 14.4 and
+// 12.7 so, 14.7 and 13.2 in the matrix's own order; 8192 x 28672, with four loads of actions per look, 20.8, 15.7 and 13.0.
 constexpr int64_t RF_ORDERED_TILES = 2048;
 // action:        skip      8, 4, 3, 2 bits   ternary        binary         outside the plan's
 constexpr uint32_t RF_CLASSES = 3u | 0u | (1u << 10) | (2u << 12) | (3u << (2 * WINDQ_N_ACTIONS));
+
+// Tiles of a skipped unit that one workgroup of an ordered launch takes.
+constexpr int32_t RF_SKIP_TILES = 16;
+// A tile of a skipped unit: scales, offsets and error are zeros.
+__device__ __forceinline__ void skip_tile(const RefineArgs& A, const TileCoord& tc) {
+    const int lane = threadIdx.x;
+    if (lane < tc.nrows) {
+        const int64_t gidx = tc.u * A.g.R_u + tc.lrow0 + lane;
+        A.scale[gidx] = 0.0f;
+        A.offset[gidx] = 0.0f;
+    }
+    if (lane == 0) A.part[(size_t)tc.u * (size_t)A.g.tiles_per_unit + (size_t)tc.t] = 0.0;
+}
 
 // NV: registers of a row / 32; 0: the row in LDS.  128 VGPRs (four wavefronts per SIMD) for NV = 2.
 template <int DT, int NV, bool MASKED>
@@ -431,7 +446,13 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
     const uint32_t local = (uint32_t)((int64_t)blockIdx.x - B.tile_start[mi]);
     TileCoord tc;
     if (B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
-        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, (int32_t)A.g.tiles_per_unit, (int32_t)local, RF_CLASSES);
+        const int32_t tiles = (int32_t)A.g.tiles_per_unit, per_skipped = (tiles + RF_SKIP_TILES - 1) / RF_SKIP_TILES;
+        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, tiles, per_skipped, (int32_t)local, RF_CLASSES);
+        if (o.cls == 3) {               // zeros for every per_skipped'th tile of a skipped unit; the others have nothing to do
+            if (o.unit < 0) return;
+            for (int32_t t = o.item; t < tiles; t += per_skipped) skip_tile(A, tile_coord_of_unit(A.g, o.unit, t));
+            return;
+        }
         tc = tile_coord_of_unit(A.g, o.unit, o.item);
     } else {
         tc = tile_coord(A.g, (int64_t)local);
@@ -450,11 +471,7 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
     const int64_t padded = (payload + 15) & ~(int64_t)15;
     if (base < 0 || (base & 15) != 0 || base > A.codes_bytes - padded) a = 0;     // (base + padded could pass 2^63)
     if (a == 0) {
-        if (valid) {
-            A.scale[gidx] = 0.0f;
-            A.offset[gidx] = 0.0f;
-        }
-        if (lane == 0) A.part[tile_idx] = 0.0;
+        skip_tile(A, tc);
         return;
     }
 

@@ -100,3 +100,35 @@ def test_order_by_cost_changes_nothing(windq, units):
     batch = windq.windq_refine_plan_batch([W] * n, [s] * n, G, 0, [act_d] * n, [clip] * n, cg, [off_d] * n, n_iter, codes[:n])
     for got in batch:
         assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, alone))
+
+
+@pytest.mark.parametrize("rows", [64 * 31, 64 * 16 + 1, 64 * 40 - 7])
+def test_skipped_units_of_an_ordered_launch(windq, rows):
+    """A workgroup takes several tiles of a skipped unit: every scale, offset and error of one is zero, whatever lay there, and the
+    units between them are what they are in a call of their own."""
+    G, units = 8, 150
+    W = synth.weights_llm(rows, units * G, seed=rows, device=DEV)
+    s = torch.ones(units * G, device=DEV)
+    cg = synth.clip_grid(5)
+    tiles = units * ((rows + 63) // 64)
+    for every in (units + 1, 40, 2):                         # none, four and half of the units are not skipped
+        action = torch.zeros(units, dtype=torch.uint8)
+        action[every - 1::every] = 4
+        off = windq.windq_plan_layout(action, rows, G)
+        clip = torch.zeros(units, 4, dtype=torch.uint8, device=DEV)
+        poison = lambda: tuple(torch.full((k,), 77.0, device=DEV) for k in (units * rows, units * rows, units))
+        codes = [torch.full((max(int(off[-1]), 16),), 0xEE, dtype=torch.uint8, device=DEV) for _ in range(3)]
+        n = 2048 // tiles + 1
+        act_d, off_d = action.to(DEV), off.to(DEV)
+        got = windq.windq_refine_plan_batch([W] * n, [s] * n, G, 0, [act_d] * n, [clip] * n, cg, [off_d] * n, 2, codes[:n], outs=[poison() for _ in range(n)])
+        zero = action == 0
+        for c, scale, offset, err in got:
+            assert float(scale.view(units, rows)[zero.to(DEV)].abs().max()) == 0.0
+            assert float(offset.view(units, rows)[zero.to(DEV)].abs().max()) == 0.0 and float(err[zero.to(DEV)].abs().max()) == 0.0
+        if every <= units:
+            u = every - 1                                     # its own call: a window of one chunk
+            one = windq.windq_plan_layout(action[u:u + 1], rows, G)
+            c1, sc1, of1, e1 = windq.windq_refine_plan(W[:, u * G:(u + 1) * G], s[:G], G, 0, act_d[u:u + 1], clip[:1], cg, one.to(DEV), 2)
+            c, scale, offset, err = got[0]
+            assert torch.equal(c[int(off[u]):int(off[u]) + int(one[-1])], c1[:int(one[-1])])
+            assert torch.equal(scale.view(units, rows)[u], sc1) and torch.equal(offset.view(units, rows)[u], of1) and torch.equal(err[u], e1[0])
