@@ -917,7 +917,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         const int lane_w = fresh_lane();
         const char* __restrict__ wrow = tile + lane_w * row_bytes;
         const uint8_t* __restrict__ mrow = mtile + lane_w * mstride;
-        const bool bounds = B.skip8_p > 0.0f;
+        const bool bounds = B.skip8_p > 0.0f && A.g.R_u >= FS_FEW_ROWS;     // (units of fewer rows leave nothing out)
         float mn = INFINITY, mx = -INFINITY;
         if (bounds) {
 #pragma unroll
