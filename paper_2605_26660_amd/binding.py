@@ -106,22 +106,29 @@ class windq_calib_item(ctypes.Structure):
                 ("ws", ctypes.c_void_p), ("ws_bytes", ctypes.c_size_t)]
 
 
-_lib = None
+_lib = None          # what lib() gives: descriptors and items are the structures above, checked by ctypes
+_packed_lib = None   # the same entry points for this module's own calls, which pass the same words packed (_mats)
 
 
 def load(path: str | None = None):
     """dlopen the in-tree library and declare the signatures.  Raises if it is not built."""
-    global _lib
+    global _lib, _packed_lib
     if _lib is not None:
         return _lib
     path = path or LIB_PATH
     if not os.path.exists(path):
         raise RuntimeError(f"{path} is missing: build it with `python -m paper_2605_26660_amd.build` "
                            "(there is no fallback path)")
-    lib = ctypes.CDLL(path)
+    _packed_lib = _declare(ctypes.CDLL(path), lambda structure: ctypes.c_void_p)
+    _lib = _declare(ctypes.CDLL(path), ctypes.POINTER)
+    return _lib
+
+
+def _declare(lib, by_address):
+    """Signatures; by_address(structure) is the type of a pointer to such structures."""
     c = ctypes
     vp, i32, i64, sz = c.c_void_p, c.c_int32, c.c_int64, c.c_size_t
-    pm = vp         # descriptors and item arrays go by address: structures by reference, or the packed words of _mats and of the batch calls
+    pm = by_address(windq_mat)
     lib.windq_calib_stats.argtypes = [pm, vp, vp, vp, sz, vp]
     lib.windq_unit_features.argtypes = [pm, vp, i32, i64, vp, vp, sz, vp]
     lib.windq_fit_score_all_bits.argtypes = [pm, vp, i32, i64, vp, i32, vp, vp, vp, vp, sz, vp]
@@ -144,13 +151,13 @@ def load(path: str | None = None):
     lib.windq_fallback_promote.argtypes = [vp, vp, vp, i64, c.c_float, c.POINTER(i64)]
     lib.windq_dequant_plan.argtypes = [pm, vp, i32, i64, vp, vp, vp, vp, sz, vp, vp, vp, vp, vp, sz, vp]
     lib.windq_refine_plan.argtypes = [pm, vp, i32, i64, vp, vp, vp, vp, i32, i32, vp, vp, sz, vp, vp, vp, vp, sz, vp]
-    lib.windq_fit_score_all_bits_batch.argtypes = [vp, i32, i32, i64, vp, i32, vp]
-    lib.windq_unit_features_batch.argtypes = [vp, i32, i32, i64, vp]
-    lib.windq_apply_plan_batch.argtypes = [vp, i32, i32, i64, vp, i32, vp]
-    lib.windq_calib_stats_batch.argtypes = [vp, i32, vp]
+    lib.windq_fit_score_all_bits_batch.argtypes = [by_address(windq_fit_item), i32, i32, i64, vp, i32, vp]
+    lib.windq_unit_features_batch.argtypes = [by_address(windq_feat_item), i32, i32, i64, vp]
+    lib.windq_apply_plan_batch.argtypes = [by_address(windq_apply_item), i32, i32, i64, vp, i32, vp]
+    lib.windq_calib_stats_batch.argtypes = [by_address(windq_calib_item), i32, vp]
     lib.windq_features_fit_score.argtypes = [pm, vp, i32, i64, vp, i32, vp, vp, vp, vp, vp, sz, vp]
     lib.windq_features_fit_score.restype = c.c_int
-    lib.windq_features_fit_score_batch.argtypes = [vp, i32, i32, i64, vp, i32, vp]
+    lib.windq_features_fit_score_batch.argtypes = [by_address(windq_fused_item), i32, i32, i64, vp, i32, vp]
     lib.windq_features_fit_score_batch.restype = c.c_int
     lib.windq_kernel_timer.argtypes = [i32]
     lib.windq_kernel_timer.restype = c.c_int
@@ -160,17 +167,17 @@ def load(path: str | None = None):
     lib.windq_fit_score_all_bits_static.restype = c.c_int
     lib.windq_fit_score_rescored_units.argtypes = [vp, i32, i64, i64, i32, i64, i32, c.POINTER(i64)]
     lib.windq_fit_score_rescored_units.restype = c.c_int
-    lib.windq_salient_select_batch.argtypes = [vp, i32, i32, i64, u32, vp]
+    lib.windq_salient_select_batch.argtypes = [by_address(windq_salient_item), i32, i32, i64, u32, vp]
     lib.windq_salient_select_batch.restype = c.c_int
-    lib.windq_salient_encode_batch.argtypes = [vp, i32, i32, i64, u32, vp]
+    lib.windq_salient_encode_batch.argtypes = [by_address(windq_salient_item), i32, i32, i64, u32, vp]
     lib.windq_salient_encode_batch.restype = c.c_int
-    lib.windq_refine_plan_batch.argtypes = [vp, i32, i32, i64, vp, i32, i32, vp]
+    lib.windq_refine_plan_batch.argtypes = [by_address(windq_refine_item), i32, i32, i64, vp, i32, i32, vp]
     lib.windq_refine_plan_batch.restype = c.c_int
-    lib.windq_dequant_plan_batch.argtypes = [vp, i32, i32, i64, vp]
+    lib.windq_dequant_plan_batch.argtypes = [by_address(windq_dequant_item), i32, i32, i64, vp]
     lib.windq_dequant_plan_batch.restype = c.c_int
     lib.windq_dequant_gemv.argtypes = [pm, i32, i64, vp, vp, vp, vp, sz, vp, vp, vp, vp, vp, sz, vp]
     lib.windq_dequant_gemv.restype = c.c_int
-    lib.windq_dequant_gemv_batch.argtypes = [vp, i32, i32, i64, vp]
+    lib.windq_dequant_gemv_batch.argtypes = [by_address(windq_gemv_item), i32, i32, i64, vp]
     lib.windq_dequant_gemv_batch.restype = c.c_int
     lib.windq_unit_features_exact_units.argtypes = [vp, i32, i64, i64, i32, i64, c.POINTER(i64)]
     lib.windq_unit_features_exact_units.restype = c.c_int
@@ -182,12 +189,17 @@ def load(path: str | None = None):
                  "windq_heuristic_plan", "windq_fallback_promote", "windq_dequant_plan",
                  "windq_refine_plan", "windq_fit_score_all_bits_batch", "windq_unit_features_batch", "windq_apply_plan_batch", "windq_calib_stats_batch"):
         getattr(lib, name).restype = c.c_int
-    _lib = lib
     return lib
 
 
 def lib():
     return load()
+
+
+def _packed():
+    if _packed_lib is None:
+        load()
+    return _packed_lib
 
 
 def _check(status: int, where: str):
@@ -218,8 +230,8 @@ def as_mat(t: torch.Tensor) -> windq_mat:
 
 
 # Marshalling is what small calls wait for, so descriptors and batch items are laid out as packed 64-bit words (every field
-# of windq_mat is one but for dtype and reserved, which share one) instead of ctypes structures, and the stream comes from
-# torch's own accessor for it: torch.cuda.current_stream() builds a Stream object in 2.5 us.  Calibration statistics of four
+# of windq_mat is one but for dtype and reserved, which share one) instead of ctypes structures (whose bytes they are, word for
+# word), and the stream comes from torch's own accessor for it, where it has one: torch.cuda.current_stream() builds a Stream object in 2.5 us.  Calibration statistics of four
 # matrices, bound by this code: 14.0 us a call before, 9.0 now.
 _MAT_WORDS = ctypes.sizeof(windq_mat) // 8
 
@@ -238,10 +250,14 @@ def _addr(words: array) -> int:
     return words.buffer_info()[0]
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    if not torch.cuda.is_initialized():
+    if _raw_stream is None or _current_device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _raw_stream(_current_device())
 
 
 def _ptr(t):
@@ -281,7 +297,7 @@ def windq_calib_stats(X: torch.Tensor, want_rms: bool = True, ws: torch.Tensor |
     s_rms = torch.empty(C, dtype=torch.float32, device=X.device) if want_rms else None
     ws = _workspace(CALL_CALIB_STATS, X, 8, 0, 1, ws)
     m = _mats((X,))
-    _check(load().windq_calib_stats(_addr(m), s_abs.data_ptr(), _ptr(s_rms), ws.data_ptr(), ws.numel(),
+    _check(_packed().windq_calib_stats(_addr(m), s_abs.data_ptr(), _ptr(s_rms), ws.data_ptr(), ws.numel(),
                                     _stream()), "windq_calib_stats")
     return s_abs, s_rms
 
@@ -303,7 +319,7 @@ def windq_calib_stats_batch(Xs, want_rms: bool = True, wss=None, outs=None):
         keep.append(ws)
         items += (at + 8 * _MAT_WORDS * i, s_abs.data_ptr(), _ptr0(s_rms), ws.data_ptr(), ws.numel())
         res.append((s_abs, s_rms))
-    _check(load().windq_calib_stats_batch(_addr(items := array("Q", items)), n, _stream()), "windq_calib_stats_batch")
+    _check(_packed().windq_calib_stats_batch(_addr(items := array("Q", items)), n, _stream()), "windq_calib_stats_batch")
     return res
 
 
@@ -315,7 +331,7 @@ def windq_unit_features(W: torch.Tensor, s: torch.Tensor, chunk_w: int, unit_row
     feat = out if out is not None else torch.empty(U, N_FEAT, dtype=torch.float32, device=W.device)
     ws = _workspace(CALL_UNIT_FEATURES, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_unit_features(_addr(m), s.data_ptr(), chunk_w, unit_rows, feat.data_ptr(),
+    _check(_packed().windq_unit_features(_addr(m), s.data_ptr(), chunk_w, unit_rows, feat.data_ptr(),
                                       ws.data_ptr(), ws.numel(), _stream()), "windq_unit_features")
     return feat
 
@@ -336,7 +352,7 @@ def windq_unit_features_batch(Ws, ss, chunk_w: int, unit_rows: int, wss=None, ou
         keep.append(ws)
         items += (at + 8 * _MAT_WORDS * i, s.data_ptr(), feat.data_ptr(), ws.data_ptr(), ws.numel())
         res.append(feat)
-    _check(load().windq_unit_features_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, _stream()), "windq_unit_features_batch")
+    _check(_packed().windq_unit_features_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, _stream()), "windq_unit_features_batch")
     return res
 
 
@@ -357,11 +373,11 @@ def windq_fit_score_all_bits(W: torch.Tensor, s: torch.Tensor, chunk_w: int, uni
     ws = _workspace(CALL_FIT_SCORE, W, chunk_w, unit_rows, K, ws)
     m = _mats((W,))
     if mask is None:
-        _check(load().windq_fit_score_all_bits(_addr(m), s.data_ptr(), chunk_w, unit_rows, clip_grid.data_ptr(),
+        _check(_packed().windq_fit_score_all_bits(_addr(m), s.data_ptr(), chunk_w, unit_rows, clip_grid.data_ptr(),
                                                K, err.data_ptr(), clip_idx.data_ptr(), ref.data_ptr(), ws.data_ptr(),
                                                ws.numel(), _stream()), "windq_fit_score_all_bits")
     else:
-        _check(load().windq_fit_score_all_bits_prot(_addr(m), s.data_ptr(), chunk_w, unit_rows, mask.data_ptr(),
+        _check(_packed().windq_fit_score_all_bits_prot(_addr(m), s.data_ptr(), chunk_w, unit_rows, mask.data_ptr(),
                                                     clip_grid.data_ptr(), K, err.data_ptr(), clip_idx.data_ptr(),
                                                     ref.data_ptr(), ws.data_ptr(), ws.numel(), _stream()),
                "windq_fit_score_all_bits_prot")
@@ -394,7 +410,7 @@ def windq_fit_score_all_bits_batch(Ws, ss, chunk_w: int, unit_rows: int, clip_gr
         items += (at + 8 * _MAT_WORDS * i, s.data_ptr(), 0 if masks is None else _ptr0(masks[i]), o[0].data_ptr(), o[1].data_ptr(),
                   o[2].data_ptr(), ws.data_ptr(), ws.numel())
         res.append(o)
-    _check(load().windq_fit_score_all_bits_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, clip_grid.data_ptr(), K, _stream()),
+    _check(_packed().windq_fit_score_all_bits_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, clip_grid.data_ptr(), K, _stream()),
            "windq_fit_score_all_bits_batch")
     return res
 
@@ -412,7 +428,7 @@ def windq_features_fit_score(W: torch.Tensor, s: torch.Tensor, chunk_w: int, uni
     feat, err, clip_idx, ref = out
     ws = _workspace(CALL_FEATURES_FIT_SCORE, W, chunk_w, unit_rows, K, ws)
     m = _mats((W,))
-    _check(load().windq_features_fit_score(_addr(m), s.data_ptr(), chunk_w, unit_rows, clip_grid.data_ptr(), K,
+    _check(_packed().windq_features_fit_score(_addr(m), s.data_ptr(), chunk_w, unit_rows, clip_grid.data_ptr(), K,
                                            feat.data_ptr(), err.data_ptr(), clip_idx.data_ptr(), ref.data_ptr(),
                                            ws.data_ptr(), ws.numel(), _stream()), "windq_features_fit_score")
     return feat, err, clip_idx, ref
@@ -441,7 +457,7 @@ def windq_features_fit_score_batch(Ws, ss, chunk_w: int, unit_rows: int, clip_gr
         items += (at + 8 * _MAT_WORDS * i, s.data_ptr(), o[0].data_ptr(), o[1].data_ptr(), o[2].data_ptr(), o[3].data_ptr(), ws.data_ptr(),
                   ws.numel())
         res.append(o)
-    _check(load().windq_features_fit_score_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, clip_grid.data_ptr(), K, _stream()),
+    _check(_packed().windq_features_fit_score_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, clip_grid.data_ptr(), K, _stream()),
            "windq_features_fit_score_batch")
     return res
 
@@ -454,7 +470,7 @@ def windq_fit_score_all_bits_static(W: torch.Tensor, s: torch.Tensor, chunk_w: i
     assert not clip_grid.is_cuda and clip_grid.dtype == torch.float32 and clip_grid.is_contiguous()
     err, clip_idx, ref = out
     m = _mats((W,))
-    _check(load().windq_fit_score_all_bits_static(_addr(m), s.data_ptr(), chunk_w, unit_rows, clip_grid.data_ptr(),
+    _check(_packed().windq_fit_score_all_bits_static(_addr(m), s.data_ptr(), chunk_w, unit_rows, clip_grid.data_ptr(),
                                                   clip_grid.numel(), err.data_ptr(), clip_idx.data_ptr(), ref.data_ptr(),
                                                   _stream()), "windq_fit_score_all_bits_static")
     return err, clip_idx, ref
@@ -527,9 +543,9 @@ def windq_apply_plan(W: torch.Tensor, chunk_w: int, unit_rows: int, action: torc
             code_off.data_ptr(), codes.data_ptr(), codes.numel(), scale.data_ptr(), offset.data_ptr(),
             ws.data_ptr(), ws.numel(), _stream())
     if mask is None:
-        _check(load().windq_apply_plan(_addr(m), chunk_w, unit_rows, *tail), "windq_apply_plan")
+        _check(_packed().windq_apply_plan(_addr(m), chunk_w, unit_rows, *tail), "windq_apply_plan")
     else:
-        _check(load().windq_apply_plan_prot(_addr(m), chunk_w, unit_rows, mask.data_ptr(), *tail),
+        _check(_packed().windq_apply_plan_prot(_addr(m), chunk_w, unit_rows, mask.data_ptr(), *tail),
                "windq_apply_plan_prot")
     return codes, scale, offset
 
@@ -553,7 +569,7 @@ def windq_apply_plan_batch(Ws, chunk_w: int, unit_rows: int, actions, clip_idxs,
         items += (at + 8 * _MAT_WORDS * i, 0 if masks is None else _ptr0(masks[i]), actions[i].data_ptr(), _ptr0(ci),
                   code_offs[i].data_ptr(), codes[i].data_ptr(), codes[i].numel(), outs[i][0].data_ptr(), outs[i][1].data_ptr(),
                   ws.data_ptr(), ws.numel())
-    _check(load().windq_apply_plan_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, None if clip_grid is None else clip_grid.data_ptr(),
+    _check(_packed().windq_apply_plan_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, None if clip_grid is None else clip_grid.data_ptr(),
                                          K, _stream()), "windq_apply_plan_batch")
     return [(codes[i], outs[i][0], outs[i][1]) for i in range(n)]
 
@@ -579,7 +595,7 @@ def windq_salient_select(W: torch.Tensor, s: torch.Tensor, chunk_w: int, unit_ro
     mask = out if out is not None else torch.empty(W.shape[0], W.shape[1] // 8, dtype=torch.uint8, device=W.device)
     ws = _workspace(CALL_SALIENT, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_salient_select(_addr(m), s.data_ptr(), chunk_w, unit_rows, rate_ppm, mask.data_ptr(),
+    _check(_packed().windq_salient_select(_addr(m), s.data_ptr(), chunk_w, unit_rows, rate_ppm, mask.data_ptr(),
                                        ws.data_ptr(), ws.numel(), _stream()), "windq_salient_select")
     return mask
 
@@ -599,7 +615,7 @@ def windq_salient_encode(W: torch.Tensor, s: torch.Tensor, chunk_w: int, unit_ro
         codes, scale, err = out
     ws = _workspace(CALL_SALIENT, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_salient_encode(_addr(m), s.data_ptr(), chunk_w, unit_rows, mask.data_ptr(), rate_ppm,
+    _check(_packed().windq_salient_encode(_addr(m), s.data_ptr(), chunk_w, unit_rows, mask.data_ptr(), rate_ppm,
                                        codes.data_ptr() if n_p > 0 else None, scale.data_ptr(), err.data_ptr(),
                                        ws.data_ptr(), ws.numel(), _stream()), "windq_salient_encode")
     return codes, scale, err
@@ -627,7 +643,7 @@ def windq_salient_select_batch(Ws, ss, chunk_w: int, unit_rows: int, rate_ppm: i
         masks.append(mask)
         keep.append(ws)
         items += (at + 8 * _MAT_WORDS * i, ss[i].data_ptr(), mask.data_ptr(), 0, 0, 0, ws.data_ptr(), ws.numel())
-    _check(load().windq_salient_select_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, rate_ppm, _stream()), "windq_salient_select_batch")
+    _check(_packed().windq_salient_select_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, rate_ppm, _stream()), "windq_salient_select_batch")
     return masks
 
 
@@ -647,7 +663,7 @@ def windq_salient_encode_batch(Ws, ss, chunk_w: int, unit_rows: int, masks, rate
         keep.append(ws)
         items += (at + 8 * _MAT_WORDS * i, ss[i].data_ptr(), masks[i].data_ptr(), codes.data_ptr() if codes.numel() > 0 else 0,
                   scale.data_ptr(), err.data_ptr(), ws.data_ptr(), ws.numel())
-    _check(load().windq_salient_encode_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, rate_ppm, _stream()), "windq_salient_encode_batch")
+    _check(_packed().windq_salient_encode_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, rate_ppm, _stream()), "windq_salient_encode_batch")
     return res
 
 
@@ -660,7 +676,7 @@ def windq_unit_saliency(W: torch.Tensor, s: torch.Tensor, chunk_w: int, unit_row
     sal = out if out is not None else torch.empty(U, dtype=torch.float32, device=W.device)
     ws = _workspace(CALL_UNIT_SALIENCY, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_unit_saliency(_addr(m), s.data_ptr(), chunk_w, unit_rows, sal.data_ptr(), ws.data_ptr(),
+    _check(_packed().windq_unit_saliency(_addr(m), s.data_ptr(), chunk_w, unit_rows, sal.data_ptr(), ws.data_ptr(),
                                       ws.numel(), _stream()), "windq_unit_saliency")
     return sal
 
@@ -699,7 +715,7 @@ def windq_dequant_plan(W: torch.Tensor, s: torch.Tensor, chunk_w: int, unit_rows
     w_hat = torch.empty(W.shape[0], W.shape[1], dtype=torch.float32, device=W.device) if want_w_hat else None
     ws = _workspace(CALL_DEQUANT, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_dequant_plan(_addr(m), s.data_ptr(), chunk_w, unit_rows, _ptr(mask), action.data_ptr(),
+    _check(_packed().windq_dequant_plan(_addr(m), s.data_ptr(), chunk_w, unit_rows, _ptr(mask), action.data_ptr(),
                                      code_off.data_ptr(), codes.data_ptr(), codes.numel(), scale.data_ptr(),
                                      offset.data_ptr(), err.data_ptr(), _ptr(w_hat), ws.data_ptr(), ws.numel(),
                                      _stream()), "windq_dequant_plan")
@@ -722,7 +738,7 @@ def windq_refine_plan(W: torch.Tensor, s: torch.Tensor, chunk_w: int, unit_rows:
     K = 0 if clip_grid is None else clip_grid.numel()
     ws = _workspace(CALL_REFINE, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_refine_plan(_addr(m), s.data_ptr(), chunk_w, unit_rows, _ptr(mask), action.data_ptr(),
+    _check(_packed().windq_refine_plan(_addr(m), s.data_ptr(), chunk_w, unit_rows, _ptr(mask), action.data_ptr(),
                                     _ptr(clip_idx), None if clip_grid is None else clip_grid.data_ptr(), K, n_iter,
                                     code_off.data_ptr(), codes.data_ptr(), codes.numel(), scale.data_ptr(),
                                     offset.data_ptr(), err.data_ptr(), ws.data_ptr(), ws.numel(), _stream()),
@@ -756,7 +772,7 @@ def windq_refine_plan_batch(Ws, ss, chunk_w: int, unit_rows: int, actions, clip_
         items += (at + 8 * _MAT_WORDS * i, ss[i].data_ptr(), 0 if masks is None else _ptr0(masks[i]), actions[i].data_ptr(),
                   _ptr0(clip_idxs[i]), code_offs[i].data_ptr(), codes[i].data_ptr(), codes[i].numel(), scale.data_ptr(), offset.data_ptr(),
                   err.data_ptr(), ws.data_ptr(), ws.numel())
-    _check(load().windq_refine_plan_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, None if clip_grid is None else clip_grid.data_ptr(),
+    _check(_packed().windq_refine_plan_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, None if clip_grid is None else clip_grid.data_ptr(),
                                           K, n_iter, _stream()), "windq_refine_plan_batch")
     return res
 
@@ -784,7 +800,7 @@ def windq_dequant_plan_batch(Ws, ss, chunk_w: int, unit_rows: int, actions, code
         items += (at + 8 * _MAT_WORDS * i, ss[i].data_ptr(), 0 if masks is None else _ptr0(masks[i]), actions[i].data_ptr(),
                   code_offs[i].data_ptr(), codes[i].data_ptr(), codes[i].numel(), scales[i].data_ptr(), offsets[i].data_ptr(), _ptr0(err),
                   _ptr0(w_hat), ws.data_ptr(), ws.numel())
-    _check(load().windq_dequant_plan_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, _stream()), "windq_dequant_plan_batch")
+    _check(_packed().windq_dequant_plan_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, _stream()), "windq_dequant_plan_batch")
     return res
 
 
@@ -797,7 +813,7 @@ def windq_dequant_gemv(W: torch.Tensor, chunk_w: int, unit_rows: int, action: to
     y = out if out is not None else torch.empty(W.shape[0], dtype=torch.float32, device=W.device)
     ws = _workspace(CALL_DEQUANT_GEMV, W, chunk_w, unit_rows, 1, ws)
     m = _mats((W,))
-    _check(load().windq_dequant_gemv(_addr(m), chunk_w, unit_rows, _ptr(mask), action.data_ptr(), code_off.data_ptr(),
+    _check(_packed().windq_dequant_gemv(_addr(m), chunk_w, unit_rows, _ptr(mask), action.data_ptr(), code_off.data_ptr(),
                                      codes.data_ptr(), codes.numel(), scale.data_ptr(), offset.data_ptr(), x.data_ptr(),
                                      y.data_ptr(), ws.data_ptr(), ws.numel(), _stream()), "windq_dequant_gemv")
     return y
@@ -821,5 +837,5 @@ def windq_dequant_gemv_batch(Ws, chunk_w: int, unit_rows: int, actions, code_off
         items += (at + 8 * _MAT_WORDS * i, 0 if masks is None else _ptr0(masks[i]), actions[i].data_ptr(), code_offs[i].data_ptr(),
                   codes[i].data_ptr(), codes[i].numel(), scales[i].data_ptr(), offsets[i].data_ptr(), xs[i].data_ptr(), y.data_ptr(),
                   ws.data_ptr(), ws.numel())
-    _check(load().windq_dequant_gemv_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, _stream()), "windq_dequant_gemv_batch")
+    _check(_packed().windq_dequant_gemv_batch(_addr(items := array("Q", items)), n, chunk_w, unit_rows, _stream()), "windq_dequant_gemv_batch")
     return ys

@@ -365,3 +365,138 @@ def test_argument_validation_of_the_batch_calls(windq):
     assert lib.windq_calib_stats_batch(cal, 2, None) == windq.WINDQ_EINVAL
     cal[1] = B.windq_calib_item(None, P, None, P, 1 << 30)
     assert lib.windq_calib_stats_batch(cal, 2, None) == windq.WINDQ_EINVAL
+
+
+# --------------------------------------------------------- what the binding passes for descriptors and items
+class Recorder:
+    """Stands in for the library that the binding's own calls go to: keeps each call's name, first argument and the bytes there."""
+
+    def __init__(self, sizes):
+        self.sizes, self.calls = sizes, []
+
+    def __getattr__(self, name):
+        def call(address, *rest):
+            n = rest[0] if name.endswith("_batch") else 1
+            self.calls.append((name, ctypes.string_at(address, n * self.sizes(name)), rest))
+            return 0
+        return call
+
+
+def packed_calls(windq, monkeypatch, n):
+    """Every wrapper that passes packed words, on CPU tensors (nothing is launched).  -> (recorder, the tensors)."""
+    from paper_2605_26660_amd import binding as B
+    items = {"fit_score_all_bits": B.windq_fit_item, "unit_features": B.windq_feat_item, "apply_plan": B.windq_apply_item,
+             "calib_stats": B.windq_calib_item, "features_fit_score": B.windq_fused_item, "salient_select": B.windq_salient_item,
+             "salient_encode": B.windq_salient_item, "refine_plan": B.windq_refine_item, "dequant_plan": B.windq_dequant_item,
+             "dequant_gemv": B.windq_gemv_item}
+    kind = lambda name: items[name[len("windq_"):-len("_batch")]] if name.endswith("_batch") else B.windq_mat
+    rec = Recorder(lambda name: ctypes.sizeof(kind(name)))
+    monkeypatch.setattr(B, "_packed", lambda: rec)
+    monkeypatch.setattr(B, "_stream", lambda: 0)
+    monkeypatch.setattr(B, "_require_cuda", lambda *t: None)
+    return B, rec, kind
+
+
+@pytest.mark.parametrize("n", [1, 2])
+def test_batch_items_are_the_structures_words(windq, monkeypatch, n):
+    """Word for word what the item structure holds, in its order: every tensor's address is its own, so a swapped, missing or extra
+    word shows.  With and without masks and clip indices; the descriptors are the matrices', strides included."""
+    B, rec, kind = packed_calls(windq, monkeypatch, n)
+    G, R, C, U = 64, 128, 256, 4
+    f32 = lambda *s: [torch.zeros(*s) for _ in range(n)]
+    u8 = lambda *s: [torch.zeros(*s, dtype=torch.uint8) for _ in range(n)]
+    Ws = [torch.zeros(R, C + 64 + 8 * i, dtype=torch.bfloat16)[:, :C] for i in range(n)]
+    ss, xs, w_hats, ys = f32(C), f32(C), f32(R, C), f32(R)
+    feats, errs, clips, refs = f32(U, 8), f32(U, 6), u8(U, 4), f32(U)
+    scales, offsets, uerrs = f32(U * R), f32(U * R), f32(U)
+    acts, masks, codes = u8(U), u8(R, C // 8), u8(1 << 16)
+    offs = [torch.zeros(U + 1, dtype=torch.int64) for _ in range(n)]
+    pcodes, pscales, perrs = [torch.zeros(U, 9, dtype=torch.int8) for _ in range(n)], f32(U), f32(U)
+    wss = [torch.zeros(1 << 22, dtype=torch.uint8) for _ in range(n)]
+    cg = torch.linspace(0.5, 1.0, 5)
+    at = lambda ts, i: 0 if ts is None else ts[i].data_ptr()
+
+    def expect(**fields):
+        name, raw, rest = rec.calls.pop()
+        assert not rec.calls and rest[0] == n
+        st = kind(name)
+        assert set(fields) | {"W", "X", "ws", "ws_bytes"} >= {f for f, _ in st._fields_}, name
+        for i, it in enumerate((st * n).from_buffer_copy(raw)):
+            mat = (it.X if st is B.windq_calib_item else it.W).contents
+            W = Ws[i]
+            assert (mat.data, mat.dtype, mat.reserved, mat.rows, mat.cols, mat.ld) == (W.data_ptr(), B.WINDQ_BF16, 0, R, C, W.stride(0))
+            assert (it.ws, it.ws_bytes) == (wss[i].data_ptr(), 1 << 22)
+            for f, want in fields.items():
+                value = want if isinstance(want, int) else at(want, i)
+                assert (getattr(it, f) or 0) == value, (name, f)
+
+    # (the descriptors live as long as the wrapper runs: they are read back while it is on the stack)
+    def run(fn, *a, fields, **kw):
+        seen = []
+        orig = Recorder.__getattr__
+
+        def spy(self, name):
+            call = orig(self, name)
+            def both(*args):
+                st = call(*args)
+                expect(**fields)
+                seen.append(name)
+                return st
+            return both
+        monkeypatch.setattr(Recorder, "__getattr__", spy)
+        fn(*a, **kw)
+        monkeypatch.setattr(Recorder, "__getattr__", orig)
+        assert seen == [fn.__name__]
+
+    run(B.windq_calib_stats_batch, Ws, want_rms=False, wss=wss, outs=ss, fields=dict(s_absmean=ss, s_rms=None))
+    run(B.windq_unit_features_batch, Ws, ss, G, 0, wss=wss, outs=feats, fields=dict(s=ss, feat=feats))
+    run(B.windq_features_fit_score_batch, Ws, ss, G, 0, cg, wss=wss, outs=list(zip(feats, errs, clips, refs)),
+        fields=dict(s=ss, feat=feats, err=errs, clip_idx=clips, ref_energy=refs))
+    run(B.windq_salient_select_batch, Ws, ss, G, 0, 30000, wss=wss, outs=masks,
+        fields=dict(s=ss, mask=masks, prot_codes=None, prot_scale=None, err_prot=None))
+    run(B.windq_salient_encode_batch, Ws, ss, G, 0, masks, 30000, wss=wss, outs=list(zip(pcodes, pscales, perrs)),
+        fields=dict(s=ss, mask=masks, prot_codes=pcodes, prot_scale=pscales, err_prot=perrs))
+    for ms in (None, masks):
+        run(B.windq_fit_score_all_bits_batch, Ws, ss, G, 0, cg, wss=wss, outs=list(zip(errs, clips, refs)), masks=ms,
+            fields=dict(s=ss, mask=ms, err=errs, clip_idx=clips, ref_energy=refs))
+        for ci in (clips, [None] * n):
+            cf = None if ci[0] is None else ci
+            run(B.windq_apply_plan_batch, Ws, G, 0, acts, ci, cg, offs, codes, list(zip(scales, offsets)), wss=wss, masks=ms,
+                fields=dict(mask=ms, action=acts, clip_idx=cf, code_off=offs, codes=codes, codes_bytes=1 << 16, scale=scales, offset=offsets))
+            run(B.windq_refine_plan_batch, Ws, ss, G, 0, acts, ci, cg, offs, 2, codes, outs=list(zip(scales, offsets, uerrs)), masks=ms, wss=wss,
+                fields=dict(s=ss, mask=ms, action=acts, clip_idx=cf, code_off=offs, codes=codes, codes_bytes=1 << 16, scale=scales,
+                            offset=offsets, err=uerrs))
+        for wh in (w_hats, [None] * n):
+            run(B.windq_dequant_plan_batch, Ws, ss, G, 0, acts, offs, codes, scales, offsets, masks=ms, wss=wss, outs=list(zip(uerrs, wh)),
+                fields=dict(s=ss, mask=ms, action=acts, code_off=offs, codes=codes, codes_bytes=1 << 16, scale=scales, offset=offsets,
+                            err=uerrs, w_hat=None if wh[0] is None else wh))
+        run(B.windq_dequant_gemv_batch, Ws, G, 0, acts, offs, codes, scales, offsets, xs, masks=ms, wss=wss, outs=ys,
+            fields=dict(mask=ms, action=acts, code_off=offs, codes=codes, codes_bytes=1 << 16, scale=scales, offset=offsets, x=xs, y=ys))
+
+
+def test_the_library_itself_checks_what_it_is_given(windq):
+    """lib()'s entry points take the structures by reference, or a structure itself, and refuse one of another kind."""
+    from paper_2605_26660_amd import binding as B
+    lib, P, m = windq.lib(), 4096, _mat(windq, data=None)
+    args = (P, 64, 0, P, P, 1 << 30, None)
+    assert lib.windq_unit_features(ctypes.byref(m), *args) == lib.windq_unit_features(m, *args) == windq.WINDQ_EINVAL
+    items = (B.windq_feat_item * 1)()
+    items[0] = B.windq_feat_item(ctypes.pointer(m), P, P, P, 1 << 30)
+    assert lib.windq_unit_features_batch(items, 1, 64, 0, None) == windq.WINDQ_EINVAL
+    with pytest.raises(ctypes.ArgumentError):
+        lib.windq_unit_features(ctypes.byref(items[0]), *args)
+    for name in ("fit_score_all_bits", "calib_stats", "features_fit_score", "salient_select", "refine_plan", "dequant_plan", "dequant_gemv", "apply_plan"):
+        fn = getattr(lib, "windq_%s_batch" % name)
+        with pytest.raises(ctypes.ArgumentError):
+            fn(items, *[0] * (len(fn.argtypes) - 1))
+
+
+def test_stream_without_torchs_raw_accessor(windq, monkeypatch):
+    """A torch without it: the stream of the Stream object."""
+    from types import SimpleNamespace
+
+    from paper_2605_26660_amd import binding as B
+    monkeypatch.setattr(B, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=4711))
+    assert B._stream() == 4711
