@@ -149,3 +149,59 @@ def test_grids_that_end_below_one(windq, ratios, G, unit_rows):
         check(windq, synth.weights_llm(64 * 65 - 3, 512, seed=3, device=DEV, dtype=torch.float32), scales(512, 9), G, 0, cg)
         mask = windq.windq_salient_select(W, scales(512, 7), G, unit_rows, 30000)
         check(windq, W, scales(512, 7), G, unit_rows, cg, mask=mask)
+
+
+def many_far_from_the_grid(R, chunks, extreme):
+    cols = [far_from_the_grid(R, 128, extreme) for _ in range(chunks)]
+    W = torch.cat([(-1.0) ** i * w.roll(i, 0) for i, (w, _) in enumerate(cols)], 1)             # units of different bits
+    return W.contiguous(), torch.cat([s for _, s in cols])
+
+
+@pytest.mark.parametrize("K,extreme,low", [(20, 0.4, 0.5), (20, 0.3, 0.85)])
+def test_more_listed_tiles_than_workgroups_of_the_second_pass(windq, K, extreme, low):
+    """Runs of two and three tiles over units of 131 and 67, which end inside runs, and from one matrix of a batch into the next.
+    By quarters (one sweep) and by whole sweeps (all four)."""
+    cg = torch.tensor(list(np.linspace(low, 1.0 - 0.0206 / extreme, K - 1)) + [1.0], dtype=torch.float32)
+    mats = [many_far_from_the_grid(64 * 131 - 9, 5, extreme), many_far_from_the_grid(64 * 67, 9, extreme)]
+    alone = []
+    for W, s in mats:
+        tiles = (W.shape[0] + 63) // 64
+        listed = check(windq, W, s, 128, 0, cg)
+        assert listed == W.shape[1] // 128 and listed * tiles > 512
+        alone.append(windq.windq_fit_score_all_bits(W, s, 128, 0, cg))
+    for got, want in zip(windq.windq_fit_score_all_bits_batch([m[0] for m in mats], [m[1] for m in mats], 128, 0, cg), alone):
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+    for got, want in zip(windq.windq_features_fit_score_batch([m[0] for m in mats], [m[1] for m in mats], 128, 0, cg), alone):
+        assert all(torch.equal(a, b) for a, b in zip(got[1:], want))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_on_the_route_of_large_matrices(windq, dtype):
+    """More than 256 tiles, each swept in one piece: tiles that disagree, one-sided rows, odd grids, tile units and masks."""
+    R, G = 64 * 130 - 11, 64
+    s = scales(2 * G, 11)
+    W = synth.weights_llm(R, 2 * G, seed=12, device=DEV, dtype=dtype)
+    W[64:128] *= 20
+    W[1000:1100] = W[1000:1100].abs() + 0.01
+    if dtype == torch.float32:
+        far, _ = far_from_the_grid(2048, G, 1.0)
+        W[2048:4096, :G] = far
+    for cg in (synth.clip_grid(20), synth.clip_grid(33), torch.tensor([0.3, 0.5, 0.9]), torch.tensor([0.02 * i for i in range(1, 18)] + [0.9999, 1.0])):
+        check(windq, W, s, G, 0, cg)
+    check(windq, W, s, G, 0, synth.clip_grid(20), mask=windq.windq_salient_select(W, s, G, 0, 30000))
+    T = W[:64 * 128]
+    check(windq, T, s, G, 128, synth.clip_grid(20))
+    check(windq, T, s, G, 64, synth.clip_grid(20), mask=windq.windq_salient_select(T, s, G, 64, 300000))
+
+
+@pytest.mark.parametrize("R", [128, 64 * 140])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_a_unit_that_is_not_finite_says_so(windq, R, bad):
+    """Every error of the unit that holds such a weight is NaN or infinite; its neighbour is untouched (both routes)."""
+    W = synth.weights_llm(R, 256, seed=9, device=DEV, dtype=torch.float32)
+    s = torch.ones(256, device=DEV)
+    want = windq.windq_fit_score_all_bits(W, s, 128, 0, synth.clip_grid(20))
+    W[70, 5] = bad
+    got = windq.windq_fit_score_all_bits(W, s, 128, 0, synth.clip_grid(20))
+    assert not bool(torch.isfinite(got[0][0]).any()) and not bool(torch.isfinite(got[2][0]))
+    assert torch.equal(got[0][1], want[0][1]) and torch.equal(got[1][1], want[1][1]) and torch.equal(got[2][1], want[2][1])
