@@ -659,21 +659,22 @@ static int apply_plan_launch(const ApplyItem* items, int32_t n, int32_t chunk_w,
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) B.tile_start[i] = tiles;
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (tiles > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
     const size_t lds = raw_tile_lds_bytes(dtype, chunk_w);
-    const dim3 grid((unsigned)tiles);
     const bool fast = dtype == WINDQ_BF16;
+    const bool split = fast && (chunk_w == 128 || chunk_w == 64 || (chunk_w == 32 && !masked));     // (32 masked: the general kernel below)
+    if (!fits_launch(tiles, split ? APS_THREADS : AP_THREADS)) return WINDQ_ESHAPE;
+    const dim3 grid((unsigned)tiles);
     auto launch_split = [&](auto plain, auto prot) {
         if (masked) hipLaunchKernelGGL(prot, grid, dim3(APS_THREADS), 0, hs, B);
         else hipLaunchKernelGGL(plain, grid, dim3(APS_THREADS), 0, hs, B);
     };
-    if (fast && chunk_w == 128) {
+    if (split && chunk_w == 128) {
         launch_split(&apply_plan_split_kernel<16, false>, &apply_plan_split_kernel<16, true>);
-    } else if (fast && chunk_w == 64) {
+    } else if (split && chunk_w == 64) {
         launch_split(&apply_plan_split_kernel<8, false>, &apply_plan_split_kernel<8, true>);
-    } else if (fast && chunk_w == 32 && !masked) {      // (masked at this width: the general kernel below)
+    } else if (split) {
         hipLaunchKernelGGL((apply_plan_split_kernel<4, false>), grid, dim3(APS_THREADS), 0, hs, B);
     } else if (dtype == WINDQ_BF16) {
         st = ensure_lds(reinterpret_cast<const void*>(&apply_plan_kernel<WINDQ_BF16>), lds);

@@ -312,7 +312,7 @@ extern "C" int windq_calib_stats_batch(const windq_calib_item* items, int32_t n,
         calib_cut(&M, X->dtype == WINDQ_BF16 ? 2 : 4);
         wgs += (int64_t)M.strips * M.slabs;
     }
-    if (wgs > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (!fits_launch(wgs, CALIB_THREADS)) return WINDQ_ESHAPE;
     int32_t left = n;
     while (left > 0) {
         CalibMat now[WINDQ_MAX_BATCH];

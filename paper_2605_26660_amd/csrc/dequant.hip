@@ -1111,7 +1111,7 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
         DequantBatch& B = L[un];
         if (B.n == 0) continue;
         const int64_t tiles = dequant_number(&B);
-        if (tiles * passes > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+        if (!fits_launch(tiles * passes, DQ_THREADS)) return WINDQ_ESHAPE;
         const dim3 grid((unsigned)(tiles * passes));
         if (un == 1) {
             if (dtype == WINDQ_BF16) hipLaunchKernelGGL((dequant_any_kernel<WINDQ_BF16, false>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);
@@ -1202,13 +1202,14 @@ static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int
         All.row_start[i] = fin;
         if (i < n) fin += (All.m[i].g.rows + GEMV_FIN_ROWS - 1) / GEMV_FIN_ROWS;
     }
-    if (All.tile_start[n] > (int64_t)0x7fffffff || fin > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (All.tile_start[n] > (int64_t)0x7fffffff || !fits_launch(fin, 256)) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const bool bf = items[0].W->dtype == WINDQ_BF16;
     DequantBatch& S = L[GEMV_SPLIT];
     const int64_t tiles = S.n > 0 ? dequant_number(&S) : 0;
     if (S.n == n) {
         const int parts_shift = gemv_split_shift(tiles, chunk_w);
+        if (!fits_launch(tiles << parts_shift, GEMV_THREADS)) return WINDQ_ESHAPE;
         const dim3 grid((unsigned)(tiles << parts_shift)), block(GEMV_THREADS);
         const bool pow2 = (chunk_w & (chunk_w - 1)) == 0;
         if (bf && pow2) hipLaunchKernelGGL((gemv_split_kernel<WINDQ_BF16, true>), grid, block, 0, hs, S, parts_shift);
@@ -1239,6 +1240,7 @@ static int gemv_launch(const DequantItem* items, int32_t n, int32_t chunk_w, int
             if (rows >= B.m[0].g.R_u || rows * chunk_w < 4 * GEMV_THREADS * 8) break;
             ++parts_shift;
         }
+        if (!fits_launch((wgs << parts_shift) + (S.n > 0 ? tiles << gemv_split_shift(tiles, chunk_w) : 0), GEMV_THREADS)) return WINDQ_ESHAPE;
         const int32_t n_rows = B.n;
         for (int32_t i = 0; i < S.n; ++i, ++B.n) {          // into the first launch of the other kind
             B.m[B.n] = S.m[i];

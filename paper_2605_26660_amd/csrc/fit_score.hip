@@ -1576,7 +1576,8 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) A.tile_start[i] = tiles;
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) A.m[i] = A.m[0];
-    if (tiles > (int64_t)0x7fffffff || preps > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (!fits_launch(tiles, FS_THREADS) || !fits_launch(preps, FS_THREADS)) return WINDQ_ESHAPE;
+    if (feat == nullptr && !fits_launch(units, FIN_THREADS)) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
     const size_t lds = fit_score_lds_bytes(dtype, chunk_w, masked);
@@ -1651,7 +1652,7 @@ int windq::features_launch_tiles(const FeatBatch& F, hipStream_t hs) {
         A.tile_start[i] = tiles;
         A.unit_start[i] = units;
     }
-    if (tiles > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (!fits_launch(tiles, FS_THREADS)) return WINDQ_ESHAPE;
     const size_t lds = fit_score_lds_bytes(F.dtype, F.m[0].g.chunk_w, false);
     return launch_tiles<FS_FEAT_ONLY>(A, F.dtype, false, lds, dim3((unsigned)tiles), hs);
 }

@@ -645,7 +645,7 @@ static int refine_launch(const windq_refine_item* items, int32_t n, int32_t chun
         B.unit_start[i] = units;
     }
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (tiles > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    if (!fits_launch(tiles, RF_THREADS) || !fits_launch(units, 256)) return WINDQ_ESHAPE;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
     B.by_cost = tiles > RF_ORDERED_TILES ? 1 : 0;

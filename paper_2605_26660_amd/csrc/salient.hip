@@ -1154,8 +1154,8 @@ static int salient_common(const windq_mat* W, const float* s, int32_t chunk_w, i
     return WINDQ_OK;
 }
 
-// Numbers the tiles and units of the first B->n matrices.
-static int salient_number(SalBatch* B) {
+// Numbers the tiles and units of the first B->n matrices.  unit_threads: the most a kernel of the call gives a unit.
+static int salient_number(SalBatch* B, int unit_threads) {
     int64_t tiles = 0, units = 0, bands;
     for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) {
         B->tile_start[i] = tiles;
@@ -1177,7 +1177,7 @@ static int salient_number(SalBatch* B) {
     } while (B->cand_tiles > 1 && bands < SAL_CAND_WGS);
     for (int32_t i = B->n; i < WINDQ_MAX_BATCH; ++i) B->m[i] = B->m[0];
     B->any_flagged = B->m[0].n_flagged + 1;       // in the 256 bytes of the first matrix's own count
-    return tiles > (int64_t)0x7fffffff ? WINDQ_ESHAPE : WINDQ_OK;
+    return fits_launch(units, unit_threads) && fits_launch(bands, SAL_THREADS) && fits_launch(tiles, 64) ? WINDQ_OK : WINDQ_ESHAPE;
 }
 
 static int salient_select_launch(const windq_salient_item* items, int32_t n, int32_t chunk_w, int64_t unit_rows,
@@ -1195,6 +1195,7 @@ static int salient_select_launch(const windq_salient_item* items, int32_t n, int
         if (st != WINDQ_OK) return st;
         if (items[i].W->dtype != items[0].W->dtype) return WINDQ_EINVAL;      // one kernel per launch
         if (A.n_p == 0) {
+            if (!fits_launch((items[i].W->rows * A.mask_ld + 255) / 256, 256)) return WINDQ_ESHAPE;
             empty[n_empty] = items[i].mask;
             empty_bytes[n_empty++] = items[i].W->rows * A.mask_ld;
         } else {
@@ -1206,7 +1207,7 @@ static int salient_select_launch(const windq_salient_item* items, int32_t n, int
         hipLaunchKernelGGL(sal_clear_mask_kernel, dim3((unsigned)((empty_bytes[i] + 255) / 256)), dim3(256), 0, hs,
                            const_cast<uint8_t*>(empty[i]), empty_bytes[i]);
     if (B.n == 0) return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
-    const int st = salient_number(&B);
+    const int st = salient_number(&B, SAL_BIG);
     if (st != WINDQ_OK) return st;
     const int32_t dtype = items[0].W->dtype;
     return dtype == WINDQ_BF16 ? launch_select<WINDQ_BF16>(B, hs) : launch_select<WINDQ_F32>(B, hs);
@@ -1229,7 +1230,7 @@ static int salient_encode_launch(const windq_salient_item* items, int32_t n, int
         A.prot_scale = items[i].prot_scale;
         A.err_prot = items[i].err_prot;
     }
-    const int st = salient_number(&B);
+    const int st = salient_number(&B, SAL_THREADS);
     if (st != WINDQ_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int32_t dtype = items[0].W->dtype;
@@ -1268,6 +1269,7 @@ extern "C" int windq_unit_saliency(const windq_mat* W, const float* s, int32_t c
     if (ws == nullptr || ws_bytes < unit_saliency_ws_bytes(g) || !aligned(ws, 256)) return WINDQ_EWORKSPACE;
     double* part = static_cast<double*>(ws);
     hipStream_t hs = static_cast<hipStream_t>(stream);
+    if (!fits_launch(g.n_tiles, SAL_THREADS)) return WINDQ_ESHAPE;
     const dim3 tiles((unsigned)g.n_tiles);
     if (W->dtype == WINDQ_BF16)
         hipLaunchKernelGGL(unit_saliency_tile_kernel<WINDQ_BF16>, tiles, dim3(SAL_THREADS), 0, hs, W->data, s, g, part);

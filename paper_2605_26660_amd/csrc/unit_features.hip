@@ -619,8 +619,7 @@ static void launch_last(const FeatBatch& B, const FitFinalBatch* fit, hipStream_
     const unsigned units = (unsigned)B.units_total;
     constexpr size_t feat_lds = PER == 0 ? feat_finish_lds_bytes<DT>() : sizeof(FeatSmallLds);
     static_assert(feat_lds <= 64 * 1024 && fit_finalize_lds_bytes(WINDQ_MAX_CLIP) <= 64 * 1024, "what a workgroup gets by default");
-    // (a launch holds fewer than 2^32 threads: 2^21 units of fp32 in registers take a launch for each half)
-    const bool both = fit != nullptr && 2 * B.units_total * NT <= (int64_t)0xffffffff;
+    const bool both = fit != nullptr && fits_launch(2 * B.units_total, NT);         // (2^21 units of fp32 in registers: a launch for each half)
     if (!both) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
     if (fit != nullptr) {
         const size_t fit_lds = fit_finalize_lds_bytes(fit->K);
@@ -714,7 +713,8 @@ int features_fill(const FeatItem* items, int32_t n, int32_t chunk_w, int64_t uni
         B.init_start[i] = inits;
     }
     for (int32_t i = n; i < WINDQ_MAX_BATCH; ++i) B.m[i] = B.m[0];
-    if (blocks > (int64_t)0x7fffffff || units > (int64_t)0x7fffffff || inits > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
+    const bool in_registers = items[0].W->dtype == WINDQ_F32 && largest <= FEAT_SMALL && largest > 16384;      // 1024 threads a unit
+    if (!fits_launch(blocks, FT_THREADS) || !fits_launch(units, in_registers ? 1024 : FT_THREADS) || inits > (int64_t)0x7fffffff) return WINDQ_ESHAPE;
     B.dtype = items[0].W->dtype;
     B.blocks_total = blocks;
     B.units_total = units;
@@ -735,6 +735,7 @@ static int unit_features_launch(const windq_feat_item* items, int32_t n, int32_t
     int st = features_fill(its, n, chunk_w, unit_rows, &B);
     if (st != WINDQ_OK) return st;
     hipStream_t hs = static_cast<hipStream_t>(stream);
+    if (!fits_launch(B.init_total, 256)) return WINDQ_ESHAPE;          // (with fit+score its own first kernel clears the counters)
     st = features_launch_init(B, hs);
     if (st == WINDQ_OK) st = features_launch_tiles(B, hs);
     if (st == WINDQ_OK) st = features_launch_rest(B, nullptr, hs);

@@ -36,6 +36,9 @@ int check_clip_grid(const float* clip_grid, int32_t K);
 bool aligned(const void* p, size_t a);
 size_t round_up(size_t x, size_t a);
 
+// A launch holds fewer than 2^32 threads: the runtime cuts a larger one short and reports no error, so the launchers refuse it.
+inline bool fits_launch(int64_t workgroups, int64_t threads) { return workgroups <= (int64_t)0x7fffffff && workgroups * threads <= (int64_t)0xffffffff; }
+
 // Clip grid handed to kernels by value (lands in the kernarg segment, read with
 // scalar loads).
 struct ClipGrid {

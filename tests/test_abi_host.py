@@ -500,3 +500,21 @@ def test_stream_without_torchs_raw_accessor(windq, monkeypatch):
     monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=4711))
     assert B._stream() == 4711
+
+
+def test_launches_of_too_many_threads_are_refused(windq):
+    """A launch of 2^32 threads or more is cut short by the runtime, without an error: units of one row and eight columns reach it
+    with 34 to 134 M weights.  Refused before anything is launched (the addresses are never dereferenced)."""
+    lib, P, big = windq.lib(), 4096, 1 << 60
+    grid = torch.ones(1)
+    br = ctypes.byref
+    u22 = _mat(windq, rows=4096, cols=8192, dtype=windq.WINDQ_F32)               # 2^22 units, 1024 threads each
+    u24 = _mat(windq, rows=4096, cols=32768, dtype=windq.WINDQ_F32)              # 2^24 units and tiles, 256 threads each
+    fit = lambda m: lib.windq_fit_score_all_bits(br(m), P, 8, 1, grid.data_ptr(), 1, P, P, None, P, big, None)
+    assert fit(u22) == fit(u24) == windq.WINDQ_ESHAPE
+    assert lib.windq_features_fit_score(br(u24), P, 8, 1, grid.data_ptr(), 1, P, P, P, P, P, big, None) == windq.WINDQ_ESHAPE
+    assert lib.windq_unit_features(br(u22), P, 8, 1, P, P, big, None) == windq.WINDQ_ESHAPE          # 3 x 2048 counters a unit
+    assert lib.windq_salient_select(br(u22), P, 8, 1, 500000, P, P, big, None) == windq.WINDQ_ESHAPE
+    assert lib.windq_unit_saliency(br(u24), P, 8, 1, P, P, big, None) == windq.WINDQ_ESHAPE
+    assert lib.windq_dequant_plan(br(u24), P, 8, 1, None, P, P, P, big, P, P, P, None, P, big, None) == windq.WINDQ_ESHAPE
+    assert lib.windq_refine_plan(br(u24), P, 8, 1, None, P, None, None, 0, 1, P, P, big, P, P, P, P, big, None) == windq.WINDQ_ESHAPE
