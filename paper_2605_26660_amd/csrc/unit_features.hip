@@ -511,19 +511,13 @@ __device__ __forceinline__ void feat_finish_unit(const FeatBatch& B, const int64
 // last one, gains nothing (its counter is one more wait).  The limit is what 1024 threads hold at 128 registers each; there
 // (one unit of 768 x 128, 98304 weights, alone) the call takes 30.8 us, and 35.6 with a launch per pass.
 constexpr int64_t FEAT_SMALL = 98304;
-struct FeatSmallLds {
-    double red[6 * FT_WAVES];
-    uint32_t lhist[FEAT_BINS];
-    uint32_t sh_part[1024 / 64];
-    uint32_t sh_out[2];
-    float smax[FT_WAVES];
-};
 template <int NT, int PER>
-__device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const int64_t block, char* __restrict__ smem) {
-    FeatSmallLds& L = *reinterpret_cast<FeatSmallLds*>(smem);
-    uint32_t* __restrict__ lhist = L.lhist;
-    uint32_t* __restrict__ sh_part = L.sh_part;
-    uint32_t* __restrict__ sh_out = L.sh_out;
+__device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const int64_t block) {
+    __shared__ uint32_t lhist[FEAT_BINS];
+    __shared__ double red[6 * FT_WAVES];
+    __shared__ uint32_t sh_part[NT / 64];
+    __shared__ uint32_t sh_out[2];
+    __shared__ float smax_sh[FT_WAVES];
     const int mi = batch_index(B.unit_start, B.n, block);
     const FeatArgs& A = B.m[mi];
     const int64_t u = block - B.unit_start[mi];
@@ -595,20 +589,21 @@ __device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const in
         cnt = threadIdx.x < NT / 64 ? sh_part[threadIdx.x] : 0u;
     }
     if (PER > 8) in = feat_tail_load(A, u);
-    feat_tail(A, u, in, (double)cnt, true, L.red, L.smax);
+    feat_tail(A, u, in, (double)cnt, true, red, smax_sh);
 }
 
 // The features' last step, one workgroup per unit, and where fit+score is part of the call (FIT) its last step too, by
 // as many workgroups behind them: each is a chain of memory latencies that leaves the chip idle, and neither needs
-// the other.  PER = 0: the finish step after the passes; else units kept in registers.  A workgroup does one or the other,
-// so both use the same LDS, all of it asked for with the launch (at most 46 KB; no kernel here may pass the 64 KB that a
-// workgroup gets without ensure_lds).
+// the other.  PER = 0: the finish step after the passes; else units kept in registers.  The finish step uses the LDS that the launch
+// asks for, as the fit's step does: a workgroup does one or the other, and the two side by side (36 KB for bf16, 45 KB at 64
+// ratios) would pass the 64 KB that a workgroup gets without ensure_lds.  The units in registers have 8 KB of their own (a
+// pointer to it spills registers at PER = 12: 27.4 us for 26.0).
 template <int DT, int NT, int PER, bool FIT>
 __global__ __launch_bounds__(NT) void feat_last_kernel(const FeatBatch B, const FitFinalBatch F) {
     extern __shared__ __align__(16) char last_lds[];
     if (!FIT || (int64_t)blockIdx.x < B.units_total) {
         if constexpr (PER == 0) feat_finish_unit<DT>(B, blockIdx.x, last_lds);
-        else feat_small_f32_unit<NT, PER>(B, blockIdx.x, last_lds);
+        else feat_small_f32_unit<NT, PER>(B, blockIdx.x);
     } else {
         fit_finalize_unit<NT>(F, (int64_t)blockIdx.x - B.units_total, reinterpret_cast<double*>(last_lds));
     }
@@ -617,7 +612,7 @@ __global__ __launch_bounds__(NT) void feat_last_kernel(const FeatBatch B, const 
 template <int DT, int NT, int PER>
 static void launch_last(const FeatBatch& B, const FitFinalBatch* fit, hipStream_t hs) {
     const unsigned units = (unsigned)B.units_total;
-    constexpr size_t feat_lds = PER == 0 ? feat_finish_lds_bytes<DT>() : sizeof(FeatSmallLds);
+    constexpr size_t feat_lds = PER == 0 ? feat_finish_lds_bytes<DT>() : 0;
     static_assert(feat_lds <= 64 * 1024 && fit_finalize_lds_bytes(WINDQ_MAX_CLIP) <= 64 * 1024, "what a workgroup gets by default");
     const bool both = fit != nullptr && fits_launch(2 * B.units_total, NT);         // (2^21 units of fp32 in registers: a launch for each half)
     if (!both) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
