@@ -1385,7 +1385,9 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         static_assert((FIN_PHASES + 1) * WINDQ_MAX_CLIP * sizeof(double) <= FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
         for (int i = threadIdx.x; i < FIN_PHASES * K; i += FS_THREADS) {
             const int phase = i / K, k = i - phase * K;
-            part[phase * WINDQ_MAX_CLIP + k] = fit_phase_sum<true>(unit, tpu, ncand, k, phase);
+            double sum[1];
+            fit_phase_sums<1, true>(unit, tpu, ncand, k, phase, 0, sum);
+            part[phase * WINDQ_MAX_CLIP + k] = sum[0];
         }
         __syncthreads();
         double* E = part + FIN_PHASES * WINDQ_MAX_CLIP;

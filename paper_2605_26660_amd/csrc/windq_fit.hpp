@@ -39,20 +39,35 @@ constexpr double NOISE_C1 = 4.0 * 3.552713678800501e-15 / (NOISE_MAX * NOISE_MAX
 constexpr double BOUND_SLACK = 1e-4;
 
 
-// One phase of one candidate.  (A sum that holds a lower bound, marked by its sign, is one itself and keeps the mark.)
+// NP phases (first, first + step, ...) of one candidate side by side: a unit is added up by one workgroup, a chain of loads that
+// is as long as few of them are in flight.  (A sum that holds a lower bound, marked by its sign, is one itself and keeps the mark.)
 // SHARED: the tiles' sums may have been stored by other workgroups of this launch (past the L2s).
-template <bool SHARED>
-__device__ __forceinline__ double fit_phase_sum(const double* __restrict__ base, int64_t tiles_per_unit, int32_t ncand, int32_t cand, int phase) {
-    double acc = 0.0;
-    bool bound = false;
-#pragma unroll 4
-    for (int64_t t = phase; t < tiles_per_unit; t += FIN_PHASES) {
+template <int NP, bool SHARED>
+__device__ __forceinline__ void fit_phase_sums(const double* __restrict__ base, int64_t tiles_per_unit, int32_t ncand, int32_t cand, int first, int step,
+                                               double (&sum)[NP]) {
+    bool bound[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        sum[p] = 0.0;
+        bound[p] = false;
+    }
+    const auto add = [&](int64_t t, int p) {
         const double* at = base + (size_t)t * ncand + cand;
         const double v = SHARED ? __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *at;
-        bound |= v < 0.0;
-        acc += fabs(v);
+        bound[p] |= v < 0.0;
+        sum[p] += fabs(v);
+    };
+    int64_t t = 0;
+#pragma unroll 4
+    for (; t + FIN_PHASES <= tiles_per_unit; t += FIN_PHASES) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) add(t + first + p * step, p);
     }
-    return bound ? -acc : acc;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        if (t + first + p * step < tiles_per_unit) add(t + first + p * step, p);
+        sum[p] = bound[p] ? -sum[p] : sum[p];
+    }
 }
 
 // The phases of one candidate, in order, from [FIN_PHASES][stride].
@@ -110,8 +125,15 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     const int32_t ncand = fit_score_ncand(K);
     double* __restrict__ E = lds + FIN_PHASES * ncand;
     double* base = A.partial + (size_t)u * (size_t)tiles_per_unit * (size_t)ncand;
-    for (int phase = threadIdx.x >> 6; phase < FIN_PHASES; phase += NT / 64)
-        for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) lds[phase * ncand + cand] = fit_phase_sum<false>(base, tiles_per_unit, ncand, cand, phase);
+    constexpr int WAVES = NT / 64, NP = FIN_PHASES / WAVES;
+    static_assert(NP * WAVES == FIN_PHASES, "a wavefront's phases");
+    for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) {
+        const int first = threadIdx.x >> 6;
+        double sum[NP];
+        fit_phase_sums<NP, false>(base, tiles_per_unit, ncand, cand, first, WAVES, sum);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) lds[(first + p * WAVES) * ncand + cand] = sum[p];
+    }
     __syncthreads();
     for (int32_t cand = threadIdx.x; cand < ncand; cand += NT) E[cand] = fit_phases_total(lds, ncand, cand);
     __syncthreads();

@@ -94,3 +94,17 @@ def test_the_size_of_a_masked_launch_changes_no_bits(windq, G, K):
         want = windq.windq_fit_score_all_bits(W, s, G, 0, cg, mask=mask)
         assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, want))
     compare(*mats[0], G, 0, cg, batch[0], mask=masks[0])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("tiles", [1, 15, 16, 17, 31, 33, 64, 80, 1001])
+def test_a_units_tiles_are_added_in_one_order(windq, tiles, dtype):
+    """Sixteen phases, side by side in four wavefronts (with the features) or one in each of sixteen (alone): the same bits, rounds
+    that are full or not; the sums against the oracle."""
+    W, s = inputs(64 * tiles - 1, 64, tiles, dtype)
+    for K in (1, 13):
+        cg = synth.clip_grid(K)
+        alone = windq.windq_fit_score_all_bits(W, s, 64, 0, cg)
+        fused = windq.windq_features_fit_score(W, s, 64, 0, cg)
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(fused[1:], alone))
+        compare(W, s, 64, 0, cg, alone)
