@@ -215,19 +215,28 @@ __device__ __forceinline__ int32_t share_ratio(int32_t K, int32_t shares, int32_
 // 256 tiles, chunk 128, 20 ratios: a workgroup per sweep 172 us, a wavefront per sweep 146; 40 ratios 315 and 252; chunk 64: 111 and
 // 94, 203 and 158.  Up to 640 tiles no wavefront takes two sweeps (512 tiles, 40 ratios: 84 us, with one workgroup per tile 86, chunk 64: 57 and
 // 63), beyond, two workgroups per tile at most (2048 tiles, 64 ratios: chunk 128 411 with one, 416 with two, 451 with four).
+// Beside matrices in one piece of half their tiles or more, and with four sweeps up to 640 tiles, two workgroups share a tile's
+// sweeps by quarters: shorter ones, which the launch ends better with (1200 tiles in one piece and 512 in quarters, chunk 64, 20
+// ratios: a wavefront per sweep 119 us, so 115, with 128 in quarters 110 and 100; 512 in quarters alone 42.0 and 41.2).
 // Up to three sweeps go to a workgroup each up to 1024 tiles (chunk 64, 10 ratios: 45 us, a wavefront per sweep 46).
 static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
     const int32_t waves = (A.shares + FS_WAVES - 1) / FS_WAVES;          // workgroups for a wavefront per sweep
+    const bool few = A.shares <= 3;
+    const auto small = [&](const FitScoreMat& M) { return M.g.n_tiles <= (chunk_w < 64 ? 64 : 256); };
+    int64_t in_quarters = 0;                 // tiles
+    for (int32_t i = 0; i < A.n; ++i) in_quarters += small(A.m[i]) ? A.m[i].g.n_tiles : 0;
+    const bool mixed = 2 * (tiles - in_quarters) >= in_quarters;
     for (int32_t i = 0; i < A.n; ++i) {
         FitScoreMat& M = A.m[i];
-        const bool small = M.g.n_tiles <= (chunk_w < 64 ? 64 : 256);
-        const bool few = A.shares <= 3;
-        if (!small && !(few && chunk_w >= 64 * A.shares)) {
+        if (!small(M) && !(few && chunk_w >= 64 * A.shares)) {
             M.cut = FS_WHOLE;
             M.parts = tiles <= 640 ? waves : 1;
         } else if (few || tiles <= 384) {
             M.cut = FS_SPLIT;
-            M.parts = small && tiles <= 1024 ? A.shares : 1;
+            M.parts = small(M) && tiles <= 1024 ? A.shares : 1;
+        } else if (mixed || (waves == 1 && tiles <= 640)) {
+            M.cut = FS_SPLIT;
+            M.parts = 2;
         } else {
             M.cut = FS_SERIAL;
             M.parts = tiles <= 640 || waves < 2 ? waves : 2;
@@ -1182,7 +1191,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
                 for (int i = 0; i < FS_KB; ++i) nz[i] = acc[i][0] * (P[i].nd[0] * P[i].nd[0]) * 65025.0f;
                 for (int32_t hi = 0; hi < nh; ++hi) {
                     const int32_t c = __builtin_amdgcn_readfirstlane(hlist[hi]);
-                    if (CUT != FS_WHOLE && (c < sc0 || c >= sc1)) continue;
+                    if ((split || serial) && (c < sc0 || c >= sc1)) continue;
                     const float w = read1<DT>(wrow, c);
                     float sc = scol[c];
                     if (MASKED) sc = ((mrow[c >> 3] >> (c & 7)) & 1u) != 0u ? 0.0f : sc;
@@ -1319,7 +1328,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
     const FitScoreMat& A = B.m[mi];
     int64_t local = (int64_t)blockIdx.x - B.tile_start[mi];
     int part = 0;
-    if (CUT != FS_WHOLE) {              // all tiles' first parts, then all tiles' second parts, ...
+    if (CUT != FS_WHOLE && A.parts > 1) {          // all tiles' first parts, then all tiles' second parts, ...
         part = (int)((uint32_t)local / (uint32_t)A.g.n_tiles);
         local -= (int64_t)part * A.g.n_tiles;
     }
