@@ -595,6 +595,10 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
     return tot;
 }
 
+// FS_ONLY8: whether n sweeps are taken by all wavefronts, a quarter of the columns each, or by a wavefront each.  A sweep's parameters
+// take a wavefront as long as 24 columns do.
+__device__ __forceinline__ bool by_quarters(int n, int32_t chunk_w) { return n * (24 * FS_WAVES + chunk_w) < FS_WAVES * (24 + chunk_w); }
+
 // One tile in one of the FS_* modes.  FS_ONLY8 leaves every other partial of the tile as it is.
 // The feature modes add, in the scan that finds the groups' min / max / sum |w| anyway: per
 // wavefront (column quarter) the sums of w and w^2 (fp32 per lane over <= 128 weights, products
@@ -613,12 +617,11 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
 // the group statistics, and in every error sum their activation scale counts as zero.
 // rot spreads an uneven number of sweeps over the four SIMDs from tile to tile.
 // CUT: what the launch's matrices may be cut like (FS_WHOLE in every case; with it alone, one workgroup per tile).  The workgroup is part `part` of A.parts
-// of the tile; part 0 also makes what a tile produces once.  sweeps: FS_ONLY8, a bit for each sweep to take; fewer than there are
-// wavefronts are taken by quarters of the columns.
+// of the tile; part 0 also makes what a tile produces once.  sweeps: FS_ONLY8, a bit for each sweep to take (by_quarters).
 template <int DT, bool MASKED, int MODE, int CUT>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
                                                const int rot, const int part, const uint32_t sweeps, char* __restrict__ smem) {
-    const bool split = MODE == FS_ONLY8 ? __builtin_popcount(sweeps) < FS_WAVES : CUT == FS_SPLIT && A.cut == FS_SPLIT;
+    const bool split = MODE == FS_ONLY8 ? by_quarters(__builtin_popcount(sweeps), A.g.chunk_w) : CUT == FS_SPLIT && A.cut == FS_SPLIT;
     const bool serial = CUT == FS_SERIAL && A.cut == FS_SERIAL;
     const bool once = CUT == FS_WHOLE || part == 0;
     constexpr bool ONLY8 = MODE == FS_ONLY8;
@@ -1339,7 +1342,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
 // The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
 // walks the list, each workgroup a run of consecutive tiles; with nothing listed every workgroup ends after reading the
 // counters.  A unit listed only because a candidate
-// that was left out is not ruled out takes the sweeps that hold such candidates, one to three by all four wavefronts: one
+// that was left out is not ruled out takes the sweeps that hold such candidates, a few of them by all four wavefronts: one
 // unit of 16 tiles listed beside 23 others at chunk 256, 64 ratios: 294 us with every sweep, 216 so (266 without the bound).
 // The workgroup that scores a unit's last tile adds the tiles up again (in the order of the finalize kernel) and
 // corrects the unit's 8-bit error and clip index: a launch of its own for that took 4.5 us of every call, with nothing
@@ -1361,6 +1364,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
     const int64_t per = (total + gridDim.x - 1) / gridDim.x;
     const int64_t w_end = ((int64_t)blockIdx.x + 1) * per < total ? ((int64_t)blockIdx.x + 1) * per : total;
     uint32_t run = 0;                // tiles of the current unit that this workgroup has scored
+    uint32_t sweeps = 0;             // the unit's
     for (int64_t w = (int64_t)blockIdx.x * per; w < w_end; ++w) {
         int mi = 0;
         int64_t first = 0;
@@ -1377,7 +1381,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const TileCoord tc = tile_coord_of_unit(A.g, u, t);
         const int32_t K = B.K, ncand = fit_score_ncand(K);
         double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
-        const uint32_t sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
+        if (run == 0) sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));       // (a wait for memory: once a run)
         fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);
         ++run;
         if (w + 1 < w_end && t + 1 < tpu) {
