@@ -202,27 +202,30 @@ __device__ __forceinline__ int32_t share_ratio(int32_t K, int32_t shares, int32_
 // quarters whose sums are added in fp64 (other last bits than a lane's fp32 sum over all columns), either at the same time by the
 // four wavefronts of a workgroup (FS_SPLIT) or one after the other by one wavefront (FS_SERIAL).  The matrix alone decides
 // between one piece and quarters, so that a batch gives the bits of the single calls; how the quarters are taken and how many
-// workgroups a tile's sweeps go to (parts) gives no other bits and follows from the tiles of the whole launch.
-//   Quarters up to 256 tiles (chunks below 64 columns: 64): alone such a matrix has at most a tile per CU, and what a
-// call waits for is one wavefront's sweep over the whole chunk on an otherwise idle SIMD.  bf16, chunk 128, 64 tiles, 40
-// ratios, features too: 70 -> 33 us; 256 tiles, 20 ratios: 52 -> 37.  Below 64 columns a quarter is worth too little: in full launches
-// of chunk 32 quarters cost 7 to 30 %.  Also with one, two or three sweeps per tile (K <= 15), where wavefronts would go idle, if the
-// chunk has 64 columns per sweep: K = 5, chunk 64, 2048 tiles: 37.7 -> 34.5, chunk 32, 4096 tiles: 40.9 -> 43.2; K = 10, chunk 128,
-// 5504 tiles: 213 -> 195, chunk 64, 11008 tiles: 219 -> 228; K = 15, chunk 256, 2752 tiles: 283 -> 261, chunk 128, 5504 tiles:
-// 255 -> 260.
+// workgroups a tile's sweeps go to (parts) gives no other bits and follows from the tiles of the whole launch.  (Times are of features
+// and fit, bf16 unless said; a matrix "in one piece, one workgroup per tile" is what the others are compared with.)
+//   Quarters up to 256 tiles (chunks below 64 columns and more than two sweeps: 64): alone such a matrix has at most a tile per
+// CU, and what a call waits for is one wavefront's sweep over the whole chunk on an otherwise idle SIMD.  Chunk 128, 64 tiles, 40
+// ratios: 70 -> 33 us; 256 tiles, 20 ratios: 52 -> 37; chunk 32, 256 tiles, 10 ratios: 30 -> 22.6.  Below 64 columns a quarter of a sweep
+// is worth too little in full launches (eight matrices of 256 tiles, chunk 32, 40 ratios: 98 us, 117 at best).  Also with one, two or three
+// sweeps per tile (K <= 15), where wavefronts would go idle, if the chunk has 64 columns per sweep: K = 5, chunk 64, 2048 tiles:
+// 37.7 -> 34.5, chunk 32, 4096 tiles: 40.9 -> 43.2; K = 10, chunk 128, 5504 tiles: 213 -> 195, chunk 64, 11008 tiles: 219 -> 228; K = 15,
+// chunk 256, 2752 tiles: 283 -> 261, chunk 128, 5504 tiles: 255 -> 260.
 //   The launch: a workgroup per sweep up to 384 tiles (1.5 per CU; three matrices of 128 tiles at chunk 64, 40 ratios: 57 us, a wavefront
-// per sweep 61); beyond, the sweeps fill the chip and each workgroup's own load and statistics of the tile only cost: eight matrices of
-// 256 tiles, chunk 128, 20 ratios: a workgroup per sweep 172 us, a wavefront per sweep 146; 40 ratios 315 and 252; chunk 64: 111 and
-// 94, 203 and 158.  Up to 640 tiles no wavefront takes two sweeps (512 tiles, 40 ratios: 84 us, with one workgroup per tile 86, chunk 64: 57 and
-// 63), beyond, two workgroups per tile at most (2048 tiles, 64 ratios: chunk 128 411 with one, 416 with two, 451 with four).
-// Beside matrices in one piece of half their tiles or more, and with four sweeps up to 640 tiles, two workgroups share a tile's
+// per sweep 61), and up to 640 with at most three sweeps (five of 128 tiles, 10 ratios: 34 us, 42 in one piece; eight: 45 with a
+// workgroup per sweep, 42 with one per tile).  Beyond, the sweeps fill the chip and each workgroup's own load and statistics
+// of the tile only cost: eight matrices of 256 tiles, chunk 128, 20 ratios: a workgroup per sweep 172 us, a wavefront per sweep 146; 40
+// ratios 315 and 252; chunk 64: 111 and 94, 203 and 158.  Up to 640 tiles no wavefront takes two sweeps (512 tiles, 40 ratios: 84 us,
+// with one workgroup per tile 86, chunk 64: 57 and 63); beyond, two workgroups per tile at most (2048 tiles, 64 ratios, chunk 128: 411 us
+// with one, 416 with two, 451 with four).
+//   Beside matrices in one piece of half their tiles or more, and with four sweeps up to 640 tiles, two workgroups share a tile's
 // sweeps by quarters: shorter ones, which the launch ends better with (1200 tiles in one piece and 512 in quarters, chunk 64, 20
-// ratios: a wavefront per sweep 119 us, so 115, with 128 in quarters 110 and 100; 512 in quarters alone 42.0 and 41.2).
-// Up to three sweeps go to a workgroup each up to 1024 tiles (chunk 64, 10 ratios: 45 us, a wavefront per sweep 46).
+// ratios: a wavefront per sweep 119 us, so 115, with 128 in quarters 110 and 100; 512 in quarters alone 42.0 and 41.2).  Up to 256
+// tiles in quarters beside others: again a workgroup per sweep (3 beside 1278, chunk 32, 40 ratios, fp32: 70 us, two per tile 75).
 static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
     const int32_t waves = (A.shares + FS_WAVES - 1) / FS_WAVES;          // workgroups for a wavefront per sweep
     const bool few = A.shares <= 3;
-    const auto small = [&](const FitScoreMat& M) { return M.g.n_tiles <= (chunk_w < 64 ? 64 : 256); };
+    const auto small = [&](const FitScoreMat& M) { return M.g.n_tiles <= (chunk_w < 64 && A.shares > 2 ? 64 : 256); };
     int64_t in_quarters = 0;                 // tiles
     for (int32_t i = 0; i < A.n; ++i) in_quarters += small(A.m[i]) ? A.m[i].g.n_tiles : 0;
     const bool mixed = 2 * (tiles - in_quarters) >= in_quarters;
@@ -233,10 +236,10 @@ static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
             M.parts = tiles <= 640 ? waves : 1;
         } else if (few || tiles <= 384) {
             M.cut = FS_SPLIT;
-            M.parts = small(M) && tiles <= 1024 ? A.shares : 1;
+            M.parts = small(M) && tiles <= 640 ? A.shares : 1;
         } else if (mixed || (waves == 1 && tiles <= 640)) {
             M.cut = FS_SPLIT;
-            M.parts = 2;
+            M.parts = mixed && in_quarters <= 256 ? A.shares : 2;
         } else {
             M.cut = FS_SERIAL;
             M.parts = tiles <= 640 || waves < 2 ? waves : 2;

@@ -108,3 +108,16 @@ def test_a_units_tiles_are_added_in_one_order(windq, tiles, dtype):
         fused = windq.windq_features_fit_score(W, s, 64, 0, cg)
         assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(fused[1:], alone))
         compare(W, s, 64, 0, cg, alone)
+
+
+@pytest.mark.parametrize("G,K", [(64, 20), (64, 40), (128, 64), (32, 10), (48, 15), (32, 40), (64, 10)])
+@pytest.mark.parametrize("small,large", [((3,), 700), ((60, 64, 64, 61), 300), ((256, 130), 700), ((250, 256), 200)])
+def test_small_matrices_beside_large_ones(windq, small, large, G, K):
+    """In quarters by two workgroups per tile or one per sweep, beside a matrix in one piece; the launch decides, no bit changes."""
+    mats = [inputs(64 * t - 3, G, 40 + i, torch.bfloat16) for i, t in enumerate(small)] + [inputs(64 * 130, G * (large // 100), 50, torch.bfloat16)]
+    cg = synth.clip_grid(K)
+    batch = windq.windq_features_fit_score_batch([m[0] for m in mats], [m[1] for m in mats], G, 0, cg)
+    for (W, s), got in zip(mats, batch):
+        want = windq.windq_fit_score_all_bits(W, s, G, 0, cg)
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got[1:], want))
+    compare(*mats[0], G, 0, cg, batch[0][1:])
