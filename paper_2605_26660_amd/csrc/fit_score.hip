@@ -25,7 +25,7 @@
 //     4 instructions per candidate and no separate clamp of the code (x is already in
 //     [0,1]): 18 per (weight, clip ratio) when all four bit-widths go this short way;
 //   * most 8-bit candidates cannot win, and a bound from the clipped weights alone shows it (see
-//     SKIP8_MARGIN below): 16 or more of 20 are left out, 14 instructions per (weight, clip ratio)
+//     SKIP8_MARGIN below): 87 % are left out, 14 instructions per (weight, clip ratio)
 //     for them (a 7B-shaped block, 202 M weights, K = 20: 1450 us with all of them, 1256 without);
 //   * at 8 bits the residual is ~1/500 of (w - lo), so the fp32 roundings of s_c*w,
 //     s_c*(w - lo) and s_c*code show in it: ~1e-4 of its size per weight, random in sign.
@@ -44,9 +44,9 @@
 //                variance its roundings can have put into the 8-bit error (see
 //                NOISE_MAX below); the finalize kernel adds these up per unit and, where
 //                the standard deviation exceeds NOISE_MAX of the unit's 8-bit error at the
-//                chosen clip index, puts the unit on a list; a second pair of launches
-//                scores the 8-bit candidates of the listed units again, exact route only,
-//                and finalizes them again.  With nothing listed those launches end at once.
+//                chosen clip index, puts the unit on a list; one more launch scores the
+//                8-bit candidates of the listed units again, exact route only, and finalizes
+//                them.  With nothing listed it ends at once.
 //   * lanes accumulate in fp32 over the chunk's columns only (<= 512 terms); rows are
 //     combined in fp64 in a fixed order (LDS transpose), tiles by the finalize kernel;
 //   * what depends on s alone (the column list, s_c of the other columns) is prepared once per

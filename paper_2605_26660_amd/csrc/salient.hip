@@ -601,8 +601,8 @@ __global__ __launch_bounds__(SAL_BIG) void sal_sample_kernel(const SalBatch B) {
     if (threadIdx.x == 0 && narrow && (float)(sh_below[1] - sh_below[0]) > 1.25f * (float)A.cap * f) A.flag[u] = 1u;
 }
 
-// The pass over W: the mask (inside the bracket as if T were `mid`), the counts, the list.  Bound by HBM: per weight one multiply and two
-// pushes of a bit.  A workgroup takes 256 rows of a unit and no wavefront waits for another in its loop: candidates go
+// The pass over W: the mask (inside the bracket as if T were `mid`), the counts, the list.  Bound by vector issue (18.5 lane-slots per
+// weight, 3.9 TB/s where a large copy reaches 5.1): per weight one multiply and two pushes of a bit.  A workgroup takes 256 rows of a unit and no wavefront waits for another in its loop: candidates go
 // into the workgroup's LDS in any order (the list has none), and are moved to the unit's list with ONE global atomic at
 // the end.  (With a scan, a global atomic and two barriers per 64-row tile the pass took 157 us per 7B-shaped block.)  A workgroup
 // takes at most 32768 weights, and so has room for twice the share of them that the unit's list holds: one that needs more flags
