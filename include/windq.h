@@ -33,7 +33,9 @@
  *     launch: on any status other than WINDQ_OK / WINDQ_EHIP no output was touched.
  *   - Shape limits of the kernels: cols % chunk_w == 0, chunk_w % 8 == 0,
  *     8 <= chunk_w <= WINDQ_MAX_CHUNK, unit_rows == 0 or rows % unit_rows == 0,
- *     data pointers 16-byte aligned, ld % 8 == 0.
+ *     data pointers 16-byte aligned, ld % 8 == 0.  A call whose largest launch would hold 2^32 threads or more is
+ *     refused too (WINDQ_ESHAPE; units of one row and eight columns reach it with 34 to 134 M weights, tiles of 64 rows
+ *     and eight columns with some 4 G in a batch).
  */
 #ifndef WINDQ_H
 #define WINDQ_H

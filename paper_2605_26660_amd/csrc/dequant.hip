@@ -1107,12 +1107,15 @@ static int dequant_launch(const DequantItem* items, int32_t n, int32_t chunk_w, 
     int lpr_shift = -1;         // chunk_w = 8 << lpr_shift
     for (int k = 0; k <= 6; ++k)
         if (chunk_w == (8 << k)) lpr_shift = k;
+    int64_t wgs[2];
+    for (int un = 0; un < 2; ++un) {
+        wgs[un] = dequant_number(&L[un]) * passes;
+        if (!fits_launch(wgs[un], DQ_THREADS)) return WINDQ_ESHAPE;
+    }
     for (int un = 0; un < 2; ++un) {
         DequantBatch& B = L[un];
         if (B.n == 0) continue;
-        const int64_t tiles = dequant_number(&B);
-        if (!fits_launch(tiles * passes, DQ_THREADS)) return WINDQ_ESHAPE;
-        const dim3 grid((unsigned)(tiles * passes));
+        const dim3 grid((unsigned)wgs[un]);
         if (un == 1) {
             if (dtype == WINDQ_BF16) hipLaunchKernelGGL((dequant_any_kernel<WINDQ_BF16, false>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);
             else hipLaunchKernelGGL((dequant_any_kernel<WINDQ_F32, false>), grid, dim3(DQ_THREADS), 0, hs, B, chunk_w);

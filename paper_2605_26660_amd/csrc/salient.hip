@@ -1202,13 +1202,15 @@ static int salient_select_launch(const windq_salient_item* items, int32_t n, int
             ++B.n;
         }
     }
+    if (B.n > 0) {
+        const int st = salient_number(&B, SAL_BIG);
+        if (st != WINDQ_OK) return st;
+    }
     hipStream_t hs = static_cast<hipStream_t>(stream);
     for (int32_t i = 0; i < n_empty; ++i)
         hipLaunchKernelGGL(sal_clear_mask_kernel, dim3((unsigned)((empty_bytes[i] + 255) / 256)), dim3(256), 0, hs,
                            const_cast<uint8_t*>(empty[i]), empty_bytes[i]);
     if (B.n == 0) return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
-    const int st = salient_number(&B, SAL_BIG);
-    if (st != WINDQ_OK) return st;
     const int32_t dtype = items[0].W->dtype;
     return dtype == WINDQ_BF16 ? launch_select<WINDQ_BF16>(B, hs) : launch_select<WINDQ_F32>(B, hs);
 }

@@ -117,3 +117,38 @@ def test_more_units_than_one_launch_of_the_last_step_holds(windq):
     for got in windq.windq_features_fit_score_batch([W] * 8, [s] * 8, G, unit_rows, cg, outs=[poison() for _ in range(8)]):
         assert all(torch.equal(a, b) for a, b in zip(got, alone))
     torch.cuda.empty_cache()
+
+
+def test_too_large_launches_are_refused_before_the_others_of_the_call(windq):
+    """A batch whose matrices take more than one kind of launch, one of them too large (2^32 threads; its addresses are never
+    dereferenced): refused with no output touched, also not those of the launches that would come first."""
+    import ctypes
+    from paper_2605_26660_amd import binding as B
+    lib, P, big = windq.lib(), 4096, 1 << 60
+
+    def too_large(rows, cols):
+        return ctypes.pointer(windq.windq_mat(P, windq.WINDQ_F32, 0, rows, cols, cols))
+
+    # codes on an odd address take a kernel of their own, launched after the other's
+    W = torch.randn(8, 8, device=DEV)
+    action = torch.zeros(8, dtype=torch.uint8, device=DEV)
+    off = windq.windq_plan_layout(action.cpu(), 1, 8).to(DEV)
+    meta = torch.zeros(8, device=DEV)
+    w_hat = torch.full((8, 8), 7.0, device=DEV)
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device=DEV)
+    first = B.windq_dequant_item(ctypes.pointer(windq.as_mat(W)), meta.data_ptr(), None, action.data_ptr(), off.data_ptr(), ws.data_ptr(), 0,
+                                 meta.data_ptr(), meta.data_ptr(), None, w_hat.data_ptr(), ws.data_ptr(), ws.numel())
+    items = (B.windq_dequant_item * 2)(first, B.windq_dequant_item(too_large(4096, 32768), P, None, P, P, P + 1, big, P, P, None, P, P, big))
+    assert lib.windq_dequant_plan_batch(items, 2, 8, 1, B._stream()) == windq.WINDQ_ESHAPE
+    assert (w_hat == 7.0).all()
+    assert lib.windq_dequant_plan_batch(items, 1, 8, 1, B._stream()) == windq.WINDQ_OK      # (alone it runs)
+    assert (w_hat == W).all()
+
+    # units too small to protect anything (8 weights at 10 %) have their masks cleared first
+    mask = torch.full((8,), 0x55, dtype=torch.uint8, device=DEV)
+    first = B.windq_salient_item(ctypes.pointer(windq.as_mat(W[:1])), meta.data_ptr(), mask.data_ptr(), None, None, None, ws.data_ptr(), ws.numel())
+    items = (B.windq_salient_item * 2)(first, B.windq_salient_item(too_large(16, 8 << 22), P, P, None, None, None, P, big))
+    assert lib.windq_salient_select_batch(items, 2, 8, 0, 100000, B._stream()) == windq.WINDQ_ESHAPE
+    assert (mask == 0x55).all()
+    assert lib.windq_salient_select_batch(items, 1, 8, 0, 100000, B._stream()) == windq.WINDQ_OK
+    assert mask[0] == 0 and (mask[1:] == 0x55).all()
