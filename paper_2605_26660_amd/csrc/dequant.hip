@@ -691,7 +691,7 @@ __device__ __forceinline__ void gemv_rows_wg(const DequantBatch& B, const uint32
     const uint32_t nr = (uint32_t)((A.g.R_u + nt - 1) / nt);
     uint32_t rb, rr, j;
     if (!MASKED && B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
-        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, (int32_t)nr, (int32_t)nr, (int32_t)at, GEMV_CLASSES);
+        const OrderedItem o = item_by_cost<false>(A.action, (int32_t)A.g.U, (int32_t)nr, (int32_t)nr, (int32_t)at, GEMV_CLASSES);
         rr = (uint32_t)o.item;
         rb = (uint32_t)o.unit / nc;
         j = (uint32_t)o.unit - rb * nc;

@@ -447,7 +447,7 @@ __global__ __launch_bounds__(RF_THREADS, NV == 2 ? 4 : 2) void refine_plan_kerne
     TileCoord tc;
     if (B.by_cost != 0 && A.g.U <= ORDER_MAX_UNITS) {
         const int32_t tiles = (int32_t)A.g.tiles_per_unit, per_skipped = (tiles + RF_SKIP_TILES - 1) / RF_SKIP_TILES;
-        const OrderedItem o = item_by_cost(A.action, (int32_t)A.g.U, tiles, per_skipped, (int32_t)local, RF_CLASSES);
+        const OrderedItem o = item_by_cost<true>(A.action, (int32_t)A.g.U, tiles, per_skipped, (int32_t)local, RF_CLASSES);
         if (o.cls == 3) {               // zeros for every per_skipped'th tile of a skipped unit; the others have nothing to do
             if (o.unit < 0) return;
             for (int32_t t = o.item; t < tiles; t += per_skipped) skip_tile(A, tile_coord_of_unit(A.g, o.unit, t));
