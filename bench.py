@@ -27,29 +27,46 @@ HBM_PEAK_GBS = 8000.0
 FP32_VECTOR_PEAK_TFLOPS = 157.3    # published fp32 vector peak: 256 CU x 128 lanes x 2 flop (FMA) x 2.4 GHz
 
 
-def fit_score_flops_per_weight(k: int, left_out: float = 0.0) -> float:
+def fit_score_flops_per_weight(k: int) -> float:
     """Arithmetic of the definition, FMA = 2: per (weight, clip ratio) 1 subtract + 2 for the
     clamp + 4 bit-widths x (scale 1, rounding 1, residual 2, weighted square-accumulate 3) = 31;
-    plus ternary 9, binary 4, reference energy 3, group statistics 3.  left_out: the share of the 8-bit
-    candidates that were not scored (7 each; see left_out_8bit), so that only executed work is counted."""
-    return 31 * k + 19 - 7 * k * left_out
+    plus ternary 9, binary 4, reference energy 3, group statistics 3."""
+    return 31 * k + 19
 
 
-def left_out_8bit(wq, torch, mats, wss, G, unit_rows, K, fused):
-    """Share of the 8-bit candidates that the last fit+score call with these workspaces left out (those that clipping alone shows to
-    lose): the tiles' partial sums there hold a bound, marked by its sign, in such a candidate's place.  Layout: per 64-row tile 5 K + 12
-    doubles, the 8-bit candidates first; with the fused call, behind the unit features' part of the workspace."""
-    out = total = 0.0
+def executed_work(wq, torch, mats, wss, G, unit_rows, K, fused):
+    """(flops per weight, share of the (weight, candidate) pairs) that the last fit+score call with these workspaces scored: candidates that
+    are shown to lose are left out, on some columns or on all.  Read from what the call leaves in the workspaces (with the fused
+    call, behind the unit features' part): per 64-row tile 5 K + 12 doubles, the 8-bit candidates first, below zero where left out; and
+    for units that are scored heavy columns first the unit's plan, in the last K of its first tile's doubles, and the chunks' records behind the list of units."""
+    steps = [((G * t + (G if t == 15 else 0)) >> 4) for t in (1, 2, 3, 4, 5, 7, 11, 15)]
+    steps = torch.tensor([max(n & ~7, 8) for n in steps], dtype=torch.float64)
+    flops = pairs = total = 0.0
     for m, ws in zip(mats, wss):
         sp = m.spec
         dt = wq.WINDQ_BF16 if m.W.dtype == torch.bfloat16 else wq.WINDQ_F32
         at = wq.workspace_bytes(wq.CALL_UNIT_FEATURES, dt, sp.rows, sp.cols, G, unit_rows, 1) if fused else 0
-        tiles = m.U * ((m.R_u + 63) // 64)
-        sums = ws[at:at + tiles * (5 * K + 12) * 8].view(torch.float64).view(tiles, 5 * K + 12)[:, :K]
+        tpu, nc = (m.R_u + 63) // 64, 5 * K + 12
+        size = m.U * tpu * nc * 8
+        sums = ws[at:at + size].view(torch.float64).view(m.U, tpu, nc)
+        out8 = (sums[:, :, :K] < 0).double().mean((1, 2)).cpu()
+        pos = at + (size + 255) // 256 * 256 + 256
+        pos += (4 * m.U + 255) // 256 * 256
+        words = G + 64 + 4
+        rec = ws[pos:pos + sp.cols // G * words * 4].view(torch.int32).view(sp.cols // G, words)[:, G + 64].cpu()
+        heavy = torch.where(rec < -1, -1 - rec, torch.zeros_like(rec)).double().repeat(m.U // rec.numel())
+        f = 31.0 * K - 7.0 * K * out8
+        q = 4.0 * K - K * out8
+        if K >= 16 and bool((heavy > 0).any()):
+            plan = ws[at:at + size].view(m.U, tpu, nc * 8)[:, 0, (4 * K + 12) * 8 + 8:(4 * K + 12) * 8 + 24].cpu().double()
+            on = (plan[:, :8] + plan[:, 8:]) * (steps[None, :] - heavy[:, None]).clamp(min=0)
+            f = torch.where(heavy > 0, (f * heavy + 10.0 * on.sum(1)) / G, f)
+            q = torch.where(heavy > 0, (q * heavy + on.sum(1)) / G, q)
         w = float(sp.rows) * sp.cols
-        out += w * float((sums < 0).double().mean())
+        flops += w * (float(f.mean()) + 19.0)
+        pairs += w * float(q.mean()) / (4.0 * K)
         total += w
-    return out / total
+    return flops / total, pairs / total
 
 
 def profile_value(fname: str, key: str):
@@ -144,17 +161,17 @@ def per_call_pass(torch, stack, steps, per_matrix, fused=True):
     return calls
 
 
-def roofline(stack, fit_ms, steps, per_matrix, left_out, fused=True):
-    """The main fit+score kernel against the fp32 vector peak: executed flops of one launch (the definition's without the
-    8-bit candidates left out, counted over the last block) / its duration
-    between a pair of HIP events that the library records around that kernel alone (windq_kernel_timer), over
+def roofline(stack, fit_ms, steps, per_matrix, work, fused=True):
+    """The fit+score kernels that score the tiles against the fp32 vector peak: executed flops of one call (those of the candidates that are
+    scored, counted over the last block) / the duration
+    between a pair of HIP events that the library records around those launches alone (windq_kernel_timer), over
     the timed region.  With the fused call the kernel also makes the unit features' pass over W; its flops
     (2 per weight for the sums of w and w^2) are not counted."""
     kernel_ms, total_launches = fit_ms
     n_launch = total_launches // steps
     avg_ms = kernel_ms / total_launches
     w_per_launch = stack.n_weights / n_launch
-    flops = fit_score_flops_per_weight(stack.K, left_out)
+    flops = work[0]
     achieved = flops * w_per_launch / (avg_ms * 1e-3) / 1e12
     es = stack.blocks[0].mats[0].W.element_size()
     # HBM bytes per launch over one 7B-shaped block, from the tracked rocprofv3 --pmc summary (not measured live)
@@ -165,11 +182,11 @@ def roofline(stack, fit_ms, steps, per_matrix, left_out, fused=True):
             "traffic": traffic if same_shape else None,
             "traffic_source": "profiles/hot_path_7b_block_pmc_traffic.txt (rocprofv3 --pmc FETCH_SIZE, WRITE_SIZE; bytes per launch)",
             "algorithmic_bytes_per_launch": w_per_launch * es,
-            "kernel": "fit_score_kernel%s, %d launch%s per step: %s" % (
+            "kernel": "fit_score_kernel%s, with fit_heavy_kernel and fit_plan_kernel where heavy columns go first, %d launch%s per step: %s" % (
                 " (with the unit features' pass over W: windq_features_fit_score)" if fused else "",
                 n_launch, "es" if n_launch > 1 else "", "one per matrix" if per_matrix else "one per decoder block"),
             "avg_launch_ms": avg_ms, "flops_per_weight": flops, "flops_per_weight_of_the_definition": fit_score_flops_per_weight(stack.K),
-            "left_out_8bit_candidates": left_out,
+            "scored_share_of_candidates": work[1],
             "weight_GBps": w_per_launch * es / (avg_ms * 1e-3) / 1e9,
             "pct_hbm_peak": 100.0 * w_per_launch * es / (avg_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
             "valu_issue_frac": profile_value("fit_score_issue_counters.txt", "VALU_ISSUE_FRAC"),
@@ -183,10 +200,10 @@ def one_block(wq, torch, stack, steps, warmup, fused=True):
     ms, fit_ms, _, _ = timed_steps(torch, sub, steps, warmup, False, fused)
     es = stack.blocks[0].mats[0].W.element_size()
     fit = fit_ms[0] / fit_ms[1]
-    left_out = left_out_8bit(wq, torch, sub.blocks[0].mats, sub.ws, sub.G, sub.unit_rows, sub.K, fused)
+    work = executed_work(wq, torch, sub.blocks[0].mats, sub.ws, sub.G, sub.unit_rows, sub.K, fused)
     return {"weights": sub.n_weights, "units": sub.n_units, "ms_per_step": ms, "GBps": sub.n_weights * es / (ms * 1e-3) / 1e9,
             "fit_score_kernel_ms": fit, "fit_score_GBps": sub.n_weights * es / (fit * 1e-3) / 1e9,
-            "fit_score_frac_of_fp32_peak": fit_score_flops_per_weight(stack.K, left_out) * sub.n_weights / (fit * 1e-3) / 1e12 / FP32_VECTOR_PEAK_TFLOPS}
+            "fit_score_frac_of_fp32_peak": work[0] * sub.n_weights / (fit * 1e-3) / 1e12 / FP32_VECTOR_PEAK_TFLOPS}
 
 
 def protected_pass(wq, torch, stack, ppm, reps):
@@ -258,9 +275,9 @@ def protected_pass(wq, torch, stack, ppm, reps):
         res[name] = {"ms_per_block_median": med, "weight_GBps": n_weights * es / (med * 1e-3) / 1e9,
                      "pct_hbm_peak": 100.0 * n_weights * es / (med * 1e-3) / 1e9 / HBM_PEAK_GBS}
     fit = res["fit_score_all_bits_prot"]["ms_per_block_median"]
-    left_out = left_out_8bit(wq, torch, mats, stack.ws, G, unit_rows, stack.K, False)
-    res["fit_score_all_bits_prot"]["left_out_8bit_candidates"] = left_out
-    res["fit_score_all_bits_prot"]["TFLOPs"] = fit_score_flops_per_weight(stack.K, left_out) * n_weights / (fit * 1e-3) / 1e12
+    work = executed_work(wq, torch, mats, stack.ws, G, unit_rows, stack.K, False)
+    res["fit_score_all_bits_prot"]["scored_share_of_candidates"] = work[1]
+    res["fit_score_all_bits_prot"]["TFLOPs"] = work[0] * n_weights / (fit * 1e-3) / 1e12
     # the plain plan has to be back in place for the parity leg
     stack.subset([0]).run_step()
     torch.cuda.synchronize()
@@ -293,9 +310,9 @@ def clip_sweep(wq, synth, torch, stack, reps=3):
             t = e0.elapsed_time(e1)
             best = t if best is None else min(best, t)
         gbs = n_weights * es / (best * 1e-3) / 1e9
-        left_out = left_out_8bit(wq, torch, mats, ws, G, unit_rows, k, False)
-        rows.append({"K": k, "ms": best, "weight_GBps": gbs, "pct_hbm_peak": 100.0 * gbs / HBM_PEAK_GBS, "left_out_8bit_candidates": left_out,
-                     "TFLOPs": fit_score_flops_per_weight(k, left_out) * n_weights / (best * 1e-3) / 1e12})
+        work = executed_work(wq, torch, mats, ws, G, unit_rows, k, False)
+        rows.append({"K": k, "ms": best, "weight_GBps": gbs, "pct_hbm_peak": 100.0 * gbs / HBM_PEAK_GBS, "scored_share_of_candidates": work[1],
+                     "TFLOPs": work[0] * n_weights / (best * 1e-3) / 1e12})
     return rows
 
 
@@ -411,14 +428,14 @@ def main():
         ms_per_step, fit_ms, total_cb, total_n = timed_steps(torch, stack, args.steps, args.warmup, args.per_matrix, fused)
         stack.run_step_totals = (total_cb, total_n)
         es = stack.blocks[0].mats[0].W.element_size()
-        left_out = left_out_8bit(wq, torch, stack.blocks[-1].mats, stack.ws, G, stack.unit_rows, stack.K, fused)
+        work = executed_work(wq, torch, stack.blocks[-1].mats, stack.ws, G, stack.unit_rows, stack.K, fused)
         r = {
             "chunk_w": G, "ms_per_step": ms_per_step, "GBps": stack.n_weights * es / (ms_per_step * 1e-3) / 1e9,
             "units": stack.n_units, "units_per_s": stack.n_units / (ms_per_step * 1e-3),
             "avg_bits": total_cb / (100.0 * total_n), "target_bits": stack.target_centibits / 100.0,
             "budget_met": total_cb <= stack.target_centibits * total_n,
             "packed_code_bytes": stack.code_bytes, "scale_offset_bytes": stack.meta_bytes(),
-            "roofline": roofline(stack, fit_ms, args.steps, args.per_matrix, left_out, fused),
+            "roofline": roofline(stack, fit_ms, args.steps, args.per_matrix, work, fused),
             "calls": per_call_pass(torch, stack, max(1, min(args.steps, 5)), args.per_matrix, fused),
         }
         # units of the last block whose P99 needed the exact pass over their weights (the workspaces are

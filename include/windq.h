@@ -199,10 +199,10 @@ int windq_fit_score_all_bits_static(const windq_mat* W, const float* s /*[cols]*
                                     void* stream);
 
 /*
- * Profiling aid for the dominant kernel.  windq_kernel_timer(1) switches it on: from then on every
- * launch of the main fit+score kernel (by any of the fit+score entry points, the fused ones included)
- * is bracketed by a pair of HIP events on the launch stream, so that the kernel's own duration can be
- * told apart from the small kernels that follow it in the same call.  windq_kernel_timer_read waits
+ * Profiling aid for the dominant kernels.  windq_kernel_timer(1) switches it on: from then on every
+ * call's launches that score tiles (by any of the fit+score entry points, the fused ones included)
+ * are bracketed by a pair of HIP events on the launch stream, so that their duration can be
+ * told apart from the small kernels around them in the same call.  windq_kernel_timer_read waits
  * for the recorded launches, returns the sum of their durations in milliseconds and their number, and
  * forgets them.  windq_kernel_timer(0) switches it off.  Off by default.  While it is on the library
  * creates events (host-side state, nothing on the device) and must not be used under graph capture;
@@ -213,8 +213,8 @@ int windq_kernel_timer_read(double* total_ms /*HOST*/, int64_t* launches /*HOST*
 
 /*
  * Diagnostic: how many units of the last windq_fit_score_all_bits (or _prot, or batch item) call
- * that used workspace `ws` had 8-bit candidates scored in a second pass, on the exact route (all of them for their noise, or
- * those that were left out and could not be ruled out).
+ * that used workspace `ws` had candidates scored in a second pass (8-bit ones on the exact route, all of them for their noise, or
+ * those that were left out and could not be ruled out; others that had not taken every column and could not be ruled out).
  * Pass the shape arguments of that call.  Unlike every other entry point this one copies a
  * counter to the host and therefore waits for the device: call it after the stream has finished.
  */

@@ -47,6 +47,8 @@
 //                chosen clip index, puts the unit on a list; one more launch scores the
 //                8-bit candidates of the listed units again, exact route only, and finalizes
 //                them.  With nothing listed it ends at once.
+//   * large bf16 matrices are scored heavy columns first: a few columns carry most of every error, and what they add up to
+//     shows most candidates to lose (windq_plan.hpp; a 7B-shaped block 1250 -> 930 us);
 //   * lanes accumulate in fp32 over the chunk's columns only (<= 512 terms); rows are
 //     combined in fp64 in a fixed order (LDS transpose), tiles by the finalize kernel;
 //   * what depends on s alone (the column list, s_c of the other columns) is prepared once per
@@ -85,7 +87,7 @@ __host__ __device__ constexpr int fs_nrow(bool masked) { return masked ? FS_NRED
 constexpr float RNE_POS = 8388608.0f;       // 2^23: x + 2^23 rounds x >= 0 to the nearest-even integer
 constexpr int FS_PREP_CHUNKS = FS_THREADS / 64;     // chunks a workgroup of the preparing kernel takes, one per wavefront
 constexpr int FS_PREP_CLEAR = FS_THREADS * 4;       // counters one of its workgroups clears
-constexpr int FS_REDO_GRID = 512; 
+constexpr int FS_REDO_GRID = 512, FS_REDO_GRID_PLANNED = 1280;       // (units that are scored by a plan: a tile's few candidates are over soon)
 // What a pass over a tile does.
 constexpr int FS_SCORE = 0;         // every candidate quantizer
 constexpr int FS_ONLY8 = 1;         // the 8-bit candidates alone, exact route (listed units)
@@ -146,6 +148,7 @@ struct FitScoreMat {
     float tau;         // columns with s_c^2 > tau * mean(s^2) of the chunk take the exact 8-bit route; 0: all do
     int32_t cut;       // FS_WHOLE, FS_SPLIT or FS_SERIAL (see choose_cut)
     int32_t parts;     // workgroups per tile
+    int32_t planned;   // nonzero: chunks whose columns differ much are scored heavy columns first (windq_plan.hpp)
     float* colsel;     // [n_chunks][colsel_words]: the chunks' column selection, written by the preparing kernel
     // first pass of the unit features (FS_SCORE_FEAT, FS_FEAT_ONLY), else unused
     double* fmoments;      // [n_tiles][4 column quarters][4]: sum w, sum w^2, sum |w|, count(|w| < 1e-6)
@@ -174,6 +177,8 @@ struct FitScoreArgs {
     int64_t tile_start[WINDQ_MAX_BATCH + 1];     // first workgroup of matrix i in the grid; [n] = grid size
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     int64_t prep_start[WINDQ_MAX_BATCH + 1];     // first workgroup of matrix i in the preparing kernel's grid
+    int64_t heavy_start[WINDQ_MAX_BATCH + 1];    // first workgroup of matrix i in the launch that scores the heavy columns (one per tile)
+    int64_t plan_start[WINDQ_MAX_BATCH + 1];     // ... and in the one that makes the plans (one per unit)
     FitScoreMat m[WINDQ_MAX_BATCH];
     ClipGrid grid;
 };
@@ -598,6 +603,41 @@ __device__ __forceinline__ double rows_collect(const float* __restrict__ red, in
     return tot;
 }
 
+// The columns of a tile's rows (bf16) in another order: column c to place[c].  A wavefront takes sixteen rows, as many at a time as it has
+// lanes for their 16-byte pieces; a row's pieces are all read before any of them is written (a wavefront's LDS
+// instructions are carried out in order), so the wavefronts need not wait for each other.
+__device__ __forceinline__ void scatter_piece(char* __restrict__ row, const uint4 v, const uint8_t* __restrict__ place) {
+    const uint2 at = *reinterpret_cast<const uint2*>(place);
+    const uint32_t x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t to = ((j < 4 ? at.x : at.y) >> (8 * (j & 3))) & 0xffu;
+        *reinterpret_cast<uint16_t*>(row + to * 2) = (uint16_t)(j & 1 ? x[j >> 1] >> 16 : x[j >> 1]);
+    }
+}
+__device__ __forceinline__ void permute_tile(char* __restrict__ tile, const uint8_t* __restrict__ place, int32_t G, int wave, int lane) {
+    const uint32_t pieces = (uint32_t)G >> 3;                // at most 32 (FS_PLAN_MAX_CHUNK)
+    const uint32_t r = (uint32_t)lane / pieces, pc = (uint32_t)lane - r * pieces, rows = 64u / pieces;
+    const int32_t row_bytes = G * 2 + 16;
+    for (uint32_t r0 = 0; r0 < TILE_ROWS / FS_WAVES; r0 += rows) {
+        const bool on = r < rows && r0 + r < TILE_ROWS / FS_WAVES;
+        char* __restrict__ row = tile + (int32_t)(wave * (TILE_ROWS / FS_WAVES) + r0 + r) * row_bytes;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (on) v = *reinterpret_cast<const uint4*>(row + pc * 16);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (on) scatter_piece(row, v, place + pc * 8);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+}  // namespace windq
+
+#include "windq_plan.hpp"
+
+namespace windq {
+
 // FS_ONLY8: whether n sweeps are taken by all wavefronts, a quarter of the columns each, or by a wavefront each.  A sweep's parameters
 // take a wavefront as long as 24 columns do.
 __device__ __forceinline__ bool by_quarters(int n, int32_t chunk_w) { return n * (24 * FS_WAVES + chunk_w) < FS_WAVES * (24 + chunk_w); }
@@ -668,7 +708,8 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     // Column selection for the 8-bit candidate, prepared per chunk (fit_score_prepare_kernel): s_c
     // of the columns on the short route (0 for the listed ones) and the list lie next to each
     // other, in the record as in LDS.
-    int32_t nh = -1;           // listed columns; -1: no list, every column takes the exact route
+    int32_t nh = -1;           // listed columns; -1: no list, every column takes the exact route; below -1: heavy columns, scored before (windq_plan.hpp)
+    int32_t heavy = 0;         // (nh below -1)
     float s2 = 0.0f;           // sum s_c^2 over the chunk
     float s4_over_s2 = 0.0f;   // sum s_c^4 / sum s_c^2 over the short route: scales the tile's noise term
     if (SCORE && !ONLY8) {
@@ -676,6 +717,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         for (int32_t c = threadIdx.x; c < G + FS_HMAX; c += FS_THREADS) sshort[c] = rec[c];
         // (wave-uniform: parked in scalar registers across the hot loops)
         nh = __builtin_amdgcn_readfirstlane(__float_as_int(rec[G + FS_HMAX]));
+        if constexpr (!MASKED && DT == WINDQ_BF16) heavy = heavy_columns(nh);
         s4_over_s2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(rec[G + FS_HMAX + 1])));
         s2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(rec[G + FS_HMAX + 2])));
     }
@@ -932,7 +974,8 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         const int lane_w = fresh_lane();
         const char* __restrict__ wrow = tile + lane_w * row_bytes;
         const uint8_t* __restrict__ mrow = mtile + lane_w * mstride;
-        const bool bounds = B.skip8_p > 0.0f && A.g.R_u >= FS_FEW_ROWS;     // (units of fewer rows leave nothing out)
+        // (units of fewer rows leave nothing out; where the heavy columns have been scored, that has been done)
+        const bool bounds = B.skip8_p > 0.0f && A.g.R_u >= FS_FEW_ROWS && heavy == 0;
         float mn = INFINITY, mx = -INFINITY;
         if (bounds) {
 #pragma unroll
@@ -1014,6 +1057,30 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             else s2_rg2 = s2 * tile_rg2;
             tile_clip = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(tile_clip)));
             s2_rg2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s2_rg2)));
+        }
+    }
+    if constexpr (SCORE && !ONLY8 && !MASKED && DT == WINDQ_BF16) {
+        if (heavy != 0) {          // the light columns, by the unit's plan
+            const FitPlan* __restrict__ plan = fit_plan(A.partial + (size_t)tc.u * (size_t)A.g.tiles_per_unit * (size_t)fit_score_ncand(K), K);
+            __syncthreads();           // the rows have been read in the matrix's order, the quarters' sums of |w| too
+            const uint8_t* __restrict__ place = reinterpret_cast<const uint8_t*>(hlist);
+            permute_tile(tile, place, G, wave, fresh_lane());
+            float2* __restrict__ table = reinterpret_cast<float2*>(s1tab);
+            static_assert(FS_WAVES * TILE_ROWS * sizeof(double) >= 4 * WINDQ_MAX_CLIP * sizeof(float2), "the table in the place of the quarters' sums");
+            plan_table(B.grid.p, plan, G, table);
+            __syncthreads();
+            const float2 range = row_range(gstat, fresh_lane());
+            bool extras = once;
+            score_list<false, NROW, LIST_MOST>(B, plan, table, tile, row_bytes, sshort, heavy, tc.nrows, range.x, range.y, wave, rot, red, out,
+                                                [&](int lane, double tot) {
+                                                    if (extras) store_extra(lane, tot);
+                                                    extras = false;
+                                                });
+            if (extras) {
+                const int lane_r = fresh_lane();
+                store_extra(lane_r, rows_collect<NROW>(red, lane_r, NROW));
+            }
+            return;
         }
     }
     // an 8-bit candidate is left out where its bound, tile_clip * skip8_f[k], exceeds this (never where either is NaN)
@@ -1278,7 +1345,7 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
     const int mi = batch_index(B.prep_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
     const int64_t local = (int64_t)blockIdx.x - B.prep_start[mi];
-    const int64_t sel_groups = (A.g.n_chunks + FS_PREP_CHUNKS - 1) / FS_PREP_CHUNKS;
+    const int64_t sel_groups = prepare_groups(A);
     if (local >= sel_groups) {
         const int64_t i = ((local - sel_groups) * FS_THREADS + (int64_t)threadIdx.x) * 4;
         if (i < A.fclear_words) *reinterpret_cast<uint4*>(A.fclear + i) = make_uint4(0u, 0u, 0u, 0u);
@@ -1286,7 +1353,10 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
         return;
     }
     if (local == 0 && threadIdx.x == 0) *A.redo_count = 0u;      // the list the finalize kernel fills
-    const int64_t j = local * FS_PREP_CHUNKS + (int64_t)(threadIdx.x >> 6);
+    if (A.planned != 0) {           // a workgroup per chunk; where it makes no such record its first wavefront makes the other
+        if (prepare_planned(B, A, local) || threadIdx.x >= 64) return;
+    }
+    const int64_t j = A.planned != 0 ? local : local * FS_PREP_CHUNKS + (int64_t)(threadIdx.x >> 6);
     if (j >= A.g.n_chunks) return;
     const int l = threadIdx.x & 63;
     const int32_t G = A.g.chunk_w;
@@ -1342,7 +1412,8 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
     fit_score_tile<DT, MASKED, MODE, CUT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, 0u, smem);
 }
 
-// The tiles of the listed units once more, 8-bit candidates only, exact route.  A fixed grid
+// The tiles of the listed units once more, 8-bit candidates only, exact route; of units that were scored heavy columns first, the candidates
+// that are still open (windq_plan.hpp).  A fixed grid
 // walks the list, each workgroup a run of consecutive tiles; with nothing listed every workgroup ends after reading the
 // counters.  A unit listed only because a candidate
 // that was left out is not ruled out takes the sweeps that hold such candidates, a few of them by all four wavefronts: one
@@ -1356,25 +1427,33 @@ template <int DT, bool MASKED>
 __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const FitScoreArgs B) {
     extern __shared__ char smem[];
     __shared__ uint32_t done;
-    // (no table of the matrices' first tiles: indexed by a run-time value it would live in scratch memory)
-    auto listed_tiles = [&](int i) -> int64_t {
-        int64_t cnt = (int64_t)*B.m[i].redo_count;
-        cnt = cnt < B.m[i].g.U ? cnt : B.m[i].g.U;
-        return cnt * B.m[i].g.tiles_per_unit;
-    };
+    constexpr bool CAN_PLAN = DT == WINDQ_BF16 && !MASKED;
+    // (the tables are only indexed in unrolled loops: otherwise they would live in scratch memory)
+    int64_t listed[WINDQ_MAX_BATCH];
+#pragma unroll
+    for (int i = 0; i < WINDQ_MAX_BATCH; ++i) {
+        const int at = i < B.n ? i : 0;
+        const int64_t cnt = (int64_t)*B.m[at].redo_count;
+        listed[i] = i < B.n ? (cnt < B.m[at].g.U ? cnt : B.m[at].g.U) * B.m[at].g.tiles_per_unit : 0;
+    }
     int64_t total = 0;
-    for (int i = 0; i < B.n; ++i) total += listed_tiles(i);
+#pragma unroll
+    for (int i = 0; i < WINDQ_MAX_BATCH; ++i) total += listed[i];
     const int64_t per = (total + gridDim.x - 1) / gridDim.x;
     const int64_t w_end = ((int64_t)blockIdx.x + 1) * per < total ? ((int64_t)blockIdx.x + 1) * per : total;
     uint32_t run = 0;                // tiles of the current unit that this workgroup has scored
     uint32_t sweeps = 0;             // the unit's
+    bool planned = false;
     for (int64_t w = (int64_t)blockIdx.x * per; w < w_end; ++w) {
         int mi = 0;
-        int64_t first = 0;
-        for (; mi + 1 < B.n; ++mi) {
-            const int64_t nt = listed_tiles(mi);
-            if (w < first + nt) break;
-            first += nt;
+        int64_t first = 0, next = 0;
+#pragma unroll
+        for (int i = 0; i < WINDQ_MAX_BATCH; ++i) {
+            if (listed[i] > 0 && w >= next) {
+                mi = i;
+                first = next;
+            }
+            next += listed[i];
         }
         const FitScoreMat& A = B.m[mi];
         const int64_t local = w - first;
@@ -1384,8 +1463,12 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const TileCoord tc = tile_coord_of_unit(A.g, u, t);
         const int32_t K = B.K, ncand = fit_score_ncand(K);
         double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
-        if (run == 0) sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));       // (a wait for memory: once a run)
-        fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);
+        if (run == 0) {       // (waits for memory: once a run)
+            sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
+            planned = CAN_PLAN && A.planned != 0 && chunk_heavy(A, (int64_t)((uint32_t)u % (uint32_t)A.g.n_chunks)) != 0;
+        }
+        if (CAN_PLAN && planned) fit_listed_tile(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
+        else fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);
         ++run;
         if (w + 1 < w_end && t + 1 < tpu) {
             __syncthreads();         // the next tile overwrites this one's LDS
@@ -1399,6 +1482,11 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         if (done != (uint32_t)tpu) continue;
         double* part = reinterpret_cast<double*>(smem);       // [FIN_PHASES][WINDQ_MAX_CLIP], then [WINDQ_MAX_CLIP]
         static_assert((FIN_PHASES + 1) * WINDQ_MAX_CLIP * sizeof(double) <= FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
+        static_assert((LISTED_SUMS + FS_THREADS) * sizeof(double) <= 64 * (32 * 2 + 16) + FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
+        if (CAN_PLAN && planned) {
+            fit_listed_end(A, u, unit, K, part);
+            continue;
+        }
         for (int i = threadIdx.x; i < FIN_PHASES * K; i += FS_THREADS) {
             const int phase = i / K, k = i - phase * K;
             double sum[1];
@@ -1442,10 +1530,7 @@ struct FitItem {
     size_t ws_bytes;
 };
 
-template <int MODE>
-static int launch_tiles_untimed(const FitScoreArgs& A, int32_t dtype, bool masked, size_t lds, dim3 grid, hipStream_t hs);
-
-// Profiling aid (windq_kernel_timer): while switched on, every launch of the main fit+score kernel is
+// Profiling aid (windq_kernel_timer): while switched on, the launches that score a call's tiles are
 // bracketed by a pair of HIP events on the launch stream.  Off by default; the only state the library keeps.
 namespace {
 struct KernelTimer {
@@ -1463,15 +1548,16 @@ void ktimer_drop_locked() {
 }
 }  // namespace
 
-template <int MODE>
-static int launch_tiles(const FitScoreArgs& A, int32_t dtype, bool masked, size_t lds, dim3 grid, hipStream_t hs) {
+// launches(): the launches in between; returns a WINDQ_* code.
+template <typename F>
+static int timed_launches(hipStream_t hs, const F& launches) {
     std::unique_lock<std::mutex> lock(g_ktimer.mu);
-    const bool timed = g_ktimer.on && MODE != FS_FEAT_ONLY;
+    const bool timed = g_ktimer.on;
     lock.unlock();
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed && (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)) return WINDQ_EHIP;
     if (timed && hipEventRecord(e0, hs) != hipSuccess) return WINDQ_EHIP;
-    const int st = launch_tiles_untimed<MODE>(A, dtype, masked, lds, grid, hs);
+    const int st = launches();
     if (timed) {
         if (hipEventRecord(e1, hs) != hipSuccess) return WINDQ_EHIP;
         lock.lock();
@@ -1481,7 +1567,7 @@ static int launch_tiles(const FitScoreArgs& A, int32_t dtype, bool masked, size_
 }
 
 template <int MODE>
-static int launch_tiles_untimed(const FitScoreArgs& A, int32_t dtype, bool masked, size_t lds, dim3 grid, hipStream_t hs) {
+static int launch_tiles(const FitScoreArgs& A, int32_t dtype, bool masked, size_t lds, dim3 grid, hipStream_t hs) {
     auto launch = [&](auto kernel) -> int {
         const int e = ensure_lds(reinterpret_cast<const void*>(kernel), lds);
         if (e != WINDQ_OK) return e;
@@ -1506,6 +1592,17 @@ static int launch_tiles_untimed(const FitScoreArgs& A, int32_t dtype, bool maske
     if (cut == FS_SPLIT) return by_input(std::integral_constant<int, CAN_CUT ? FS_SPLIT : FS_WHOLE>{});
     if (cut == FS_SERIAL) return by_input(std::integral_constant<int, CAN_CUT ? FS_SERIAL : FS_WHOLE>{});
     return by_input(std::integral_constant<int, FS_WHOLE>{});
+}
+
+// The heavy columns, and the units' plans for the others.
+static int launch_heavy(const FitScoreArgs& A, int32_t chunk_w, hipStream_t hs) {
+    const size_t lds = heavy_lds_bytes(chunk_w);
+    const int e = ensure_lds(reinterpret_cast<const void*>(&fit_heavy_kernel), lds);
+    if (e != WINDQ_OK) return e;
+    hipLaunchKernelGGL(fit_heavy_kernel, dim3((unsigned)A.heavy_start[A.n]), dim3(FS_THREADS), lds, hs, A);
+    if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
+    hipLaunchKernelGGL(fit_plan_kernel, dim3((unsigned)A.plan_start[A.n]), dim3(PLAN_THREADS), fit_plan_lds_bytes(A.K), hs, A);
+    return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
 }
 
 // feat: nullptr, or the filled feature batch of the same matrices: the main kernel then also makes the
@@ -1577,16 +1674,27 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         const float t = 7e-5f * (float)chunk_w * (float)M.g.R_u;
         M.tau = t < 1.0f ? 0.0f : t;
         A.unit_start[i] = units;
-        A.prep_start[i] = preps;
         tiles += M.g.n_tiles;
         units += M.g.U;
-        preps += (M.g.n_chunks + FS_PREP_CHUNKS - 1) / FS_PREP_CHUNKS + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
+    }
+    for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) A.unit_start[i] = units;
+    choose_cut(A, chunk_w, tiles);
+    int64_t plans = 0, heavies = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        FitScoreMat& M = A.m[i];
+        M.planned = M.cut == FS_WHOLE && by_plan(M.g, items[0].W->dtype, masked, K) ? 1 : 0;
+        A.plan_start[i] = plans;
+        A.heavy_start[i] = heavies;
+        A.prep_start[i] = preps;
+        plans += M.planned != 0 ? M.g.U : 0;
+        heavies += M.planned != 0 ? M.g.n_tiles : 0;
+        preps += prepare_groups(M) + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) {
-        A.unit_start[i] = units;
+        A.plan_start[i] = plans;
+        A.heavy_start[i] = heavies;
         A.prep_start[i] = preps;
     }
-    choose_cut(A, chunk_w, tiles);
     tiles = 0;
     for (int32_t i = 0; i < n; ++i) {
         A.tile_start[i] = tiles;
@@ -1602,11 +1710,11 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     const dim3 grid((unsigned)tiles);
     hipLaunchKernelGGL(fit_score_prepare_kernel, dim3((unsigned)preps), dim3(FS_THREADS), 0, hs, A);
     if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
-    if (feat != nullptr) {
-        st = launch_tiles<FS_SCORE_FEAT>(A, dtype, false, lds, grid, hs);
-    } else {
-        st = launch_tiles<FS_SCORE>(A, dtype, masked, lds, grid, hs);
-    }
+    st = timed_launches(hs, [&]() -> int {
+        const int e = plans > 0 ? launch_heavy(A, chunk_w, hs) : WINDQ_OK;
+        if (e != WINDQ_OK) return e;
+        return feat != nullptr ? launch_tiles<FS_SCORE_FEAT>(A, dtype, false, lds, grid, hs) : launch_tiles<FS_SCORE>(A, dtype, masked, lds, grid, hs);
+    });
     if (st != WINDQ_OK) return st;
     FitFinalBatch F;
     F.n = n;
@@ -1614,7 +1722,8 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     F.shares = A.shares;
     for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) F.unit_start[i] = A.unit_start[i];
     for (int32_t i = 0; i < WINDQ_MAX_BATCH; ++i)
-        F.m[i] = {A.m[i].partial, A.m[i].redo_count, A.m[i].redo_list, A.m[i].err, A.m[i].clip_idx, A.m[i].ref_energy, A.m[i].g.tiles_per_unit};
+        F.m[i] = {A.m[i].partial, A.m[i].redo_count, A.m[i].redo_list, A.m[i].err, A.m[i].clip_idx, A.m[i].ref_energy, A.m[i].g.tiles_per_unit,
+                  A.m[i].planned != 0 ? A.m[i].colsel : nullptr, chunk_w, (int32_t)A.m[i].g.n_chunks};
     if (feat != nullptr) {
         st = features_launch_rest(*feat, &F, hs);
         if (st != WINDQ_OK) return st;
@@ -1623,7 +1732,8 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
     }
     // the units that step listed: their 8-bit candidates on the exact route
-    const dim3 redo_grid((unsigned)(tiles < FS_REDO_GRID ? tiles : FS_REDO_GRID));
+    const int64_t redo_most = plans > 0 ? FS_REDO_GRID_PLANNED : FS_REDO_GRID;
+    const dim3 redo_grid((unsigned)(tiles < redo_most ? tiles : redo_most));
     auto launch_redo = [&](auto kernel) -> int {
         const int e = ensure_lds(reinterpret_cast<const void*>(kernel), lds);
         if (e != WINDQ_OK) return e;

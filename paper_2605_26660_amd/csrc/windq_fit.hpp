@@ -15,6 +15,9 @@ struct FitFinalMat {
     uint8_t* clip_idx;
     float* ref_energy;
     int64_t tiles_per_unit;
+    const float* colsel;   // the chunks' records, or null: no unit is scored by a plan
+    int32_t chunk_w;
+    int32_t n_chunks;
 };
 struct FitFinalBatch {
     int32_t n;
@@ -108,6 +111,91 @@ __device__ __forceinline__ uint32_t* fit_redo_done(double* unit_partial, int32_t
 }
 __device__ __forceinline__ uint32_t* fit_redo_sweeps(double* unit_partial, int32_t K) { return fit_redo_done(unit_partial, K) + 1; }
 
+// The sweep that ratio k belongs to.
+__device__ __forceinline__ uint32_t fit_sweep_of(int32_t K, int32_t shares, int32_t k) { return (uint32_t)(k + FS_KB * shares - K) % (uint32_t)shares; }
+
+// What is left to score of a unit whose heavy columns have been scored (windq_plan.hpp): a list of candidates, each with the number of
+// columns it goes on to.  In the noise slots of the unit's first tile, behind the two words above (such units have no noise).
+constexpr int PLAN_STEPS = 8;
+struct FitPlan {
+    uint32_t done, sweeps;
+    uint8_t low[PLAN_STEPS], high[PLAN_STEPS];      // candidates that go on to plan_columns(chunk_w, step) columns: 4, 3 and 2 bits; 8 bits
+    uint64_t scored[4];                             // those that take all (8, 4, 3, 2 bits): a bit per ratio
+    uint8_t list[4 * WINDQ_MAX_CLIP];               // (bit-width << 6) | ratio: the low ones, most columns first, then the 8-bit ones (4 K at most)
+};
+static_assert(sizeof(FitPlan) - 4 * WINDQ_MAX_CLIP + 4 * FS_PLAN_MIN_K <= 8 * FS_PLAN_MIN_K, "fits the noise slots");
+// In the noise slots of the unit's second tile: the shares of the chunk's columns (where the unit is the chunk's first, see windq_plan.hpp),
+// then, once the unit is listed, the least error of each bit-width so far and its ratio.
+struct FitListed {
+    float shares[PLAN_STEPS + 2];
+    double best[4];
+    int32_t at[4];
+};
+static_assert(sizeof(FitListed) <= 8 * FS_PLAN_MIN_K, "fits the noise slots");
+__device__ __forceinline__ FitListed* fit_listed(double* unit_partial, int32_t K) {
+    return reinterpret_cast<FitListed*>(unit_partial + fit_score_ncand(K) + fit_score_noise_slot(K));
+}
+__device__ __forceinline__ FitPlan* fit_plan(double* unit_partial, int32_t K) {
+    return reinterpret_cast<FitPlan*>(unit_partial + fit_score_noise_slot(K));
+}
+// A sum that is a bound: below zero, whatever it is.
+__device__ __forceinline__ double plan_bound(double v) { return -fmax(fabs(v), 1e-300); }
+// Columns (a multiple of 8) of a step: sixteenths of the chunk, the last one all of it.
+__device__ __forceinline__ int32_t plan_columns(int32_t chunk_w, int step) {
+    const int32_t n = (chunk_w * (int32_t)((0xFB754321u >> (4 * step)) & 15u) + (step == PLAN_STEPS - 1 ? chunk_w : 0)) >> 4;      // 1 2 3 4 5 7 11 16
+    return n < 8 ? 8 : n & ~7;
+}
+// The list, by a workgroup of at least 4 K threads (called by all of them), thread i with the step of candidate i (b * K + k), or a number below zero.
+// lds: PLAN_LIST_WORDS.  more: the scored candidates are added to those that are.
+constexpr int PLAN_LIST_WORDS = 2 * PLAN_STEPS * 4 + 2 * PLAN_STEPS;
+__device__ __forceinline__ void fit_plan_list(FitPlan* __restrict__ plan, uint64_t* __restrict__ lds, int step, int32_t K, int tid, bool more) {
+    const int wave = tid >> 6, lane = tid & 63;
+    const bool on = tid < 4 * K && step >= 0, high = tid < K;
+    uint64_t* __restrict__ total = lds + 2 * PLAN_STEPS * 4;
+    if (wave < 4) {
+#pragma unroll
+        for (int s = 0; s < PLAN_STEPS; ++s) {
+            const uint64_t lo = __builtin_amdgcn_ballot_w64(on && !high && step == s), hi = __builtin_amdgcn_ballot_w64(on && high && step == s);
+            if (lane == 0) {
+                lds[s * 4 + wave] = lo;
+                lds[(PLAN_STEPS + s) * 4 + wave] = hi;
+            }
+        }
+    }
+    __syncthreads();
+    if (tid < 2 * PLAN_STEPS) {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) n += __builtin_popcountll(lds[tid * 4 + w]);
+        total[tid] = (uint64_t)n;
+        (tid < PLAN_STEPS ? plan->low : plan->high)[tid & (PLAN_STEPS - 1)] = (uint8_t)n;
+    }
+    __syncthreads();
+    if (on) {
+        int at = __builtin_popcountll(lds[((high ? PLAN_STEPS : 0) + step) * 4 + wave] & ((1ull << lane) - 1ull));
+        for (int w = 0; w < wave; ++w) at += __builtin_popcountll(lds[((high ? PLAN_STEPS : 0) + step) * 4 + w]);
+#pragma unroll
+        for (int s = 0; s < PLAN_STEPS; ++s) {
+            if (high) at += (int)total[s];
+            if (s > step) at += (int)total[(high ? PLAN_STEPS : 0) + s];
+        }
+        const int b = tid / K;
+        plan->list[at] = (uint8_t)((b << 6) | (tid - b * K));
+    }
+    if (tid < 4) {          // bit-width tid: candidates tid K .. tid K + K - 1, out of the wavefronts' sets
+        uint64_t all = 0u;
+        const int s = PLAN_STEPS - 1, first = tid * K;
+        for (int w = 0; w < 4; ++w) {
+            const uint64_t set = lds[s * 4 + w] | lds[(PLAN_STEPS + s) * 4 + w];
+            const int shift = first - 64 * w;
+            all |= shift >= 64 || shift <= -64 ? 0ull : (shift >= 0 ? set >> shift : set << -shift);
+        }
+        all &= K < 64 ? (1ull << K) - 1ull : ~0ull;
+        plan->scored[tid] = more ? plan->scored[tid] | all : all;
+        if (more) total[tid] = all != 0u ? 1u << tid : 0u;
+    }
+}
+
 // Dynamic LDS of a workgroup that finalizes: [FIN_PHASES][ncand] phase sums, [ncand] totals.
 constexpr size_t fit_finalize_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES + 1) * (size_t)fit_score_ncand(K) * sizeof(double); }
 
@@ -125,6 +213,12 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     const int32_t ncand = fit_score_ncand(K);
     double* __restrict__ E = lds + FIN_PHASES * ncand;
     double* base = A.partial + (size_t)u * (size_t)tiles_per_unit * (size_t)ncand;
+    // (read ahead of the sums, which they wait for together; words of any kind where the unit is not planned)
+    const int tid = threadIdx.x;
+    static_assert(NT >= 4 * WINDQ_MAX_CLIP, "a candidate a thread");
+    const bool planned = A.colsel != nullptr &&
+                         heavy_columns(__float_as_int(A.colsel[(size_t)((uint32_t)u % (uint32_t)A.n_chunks) * (size_t)colsel_words(A.chunk_w) + A.chunk_w + FS_HMAX])) != 0;
+    const uint64_t scored = A.colsel != nullptr ? fit_plan(base, K)->scored[tid < 4 * K ? tid / K : 0] : 0u;
     constexpr int WAVES = NT / 64, NP = FIN_PHASES / WAVES;
     static_assert(NP * WAVES == FIN_PHASES, "a wavefront's phases");
     for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) {
@@ -137,7 +231,11 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     __syncthreads();
     for (int32_t cand = threadIdx.x; cand < ncand; cand += NT) E[cand] = fit_phases_total(lds, ncand, cand);
     __syncthreads();
-    const int tid = threadIdx.x;
+    if (planned) {           // what has not taken every column is a bound
+        if (tid < 4 * K && ((scored >> (tid % K)) & 1u) == 0u) E[tid] = plan_bound(E[tid]);
+        __syncthreads();
+    }
+    bool open = false;           // (a planned unit) a candidate is not proved to be worse
     if (tid < 4) {
         double best, bound;
         const int bk = fit_least(E + tid * K, K, &best, &bound);
@@ -145,11 +243,12 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
         A.clip_idx[u * 4 + tid] = (uint8_t)bk;
         // (tid 0: 8 bits) listed: too much noise, then every sweep is taken again; or a candidate that was left out is not
         // proved to be worse, then the sweeps of such candidates
-        const bool noisy = tid == 0 && E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best;
-        if (tid == 0 && (noisy || bound * (1.0 - BOUND_SLACK) <= best)) {
+        open = planned && !(bound * (1.0 - BOUND_SLACK) > best) && bound < INFINITY;
+        const bool noisy = tid == 0 && !planned && E[fit_score_noise_slot(K) + bk] * NOISE_C1 > best * best;
+        if (tid == 0 && !planned && (noisy || bound * (1.0 - BOUND_SLACK) <= best)) {
             uint32_t sweeps = 0u;
             for (int k = 0; k < K; ++k) {
-                const uint32_t v = (uint32_t)(k + FS_KB * B.shares - K) % (uint32_t)B.shares;
+                const uint32_t v = fit_sweep_of(K, B.shares, k);
                 if (noisy || (E[k] < 0.0 && -E[k] * (1.0 - BOUND_SLACK) <= best)) sweeps |= 1u << v;
             }
             *fit_redo_done(base, K) = 0u;
@@ -163,6 +262,30 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
         const double e = ((E[4 * K + j] + E[4 * K + 3 + j]) + E[4 * K + 6 + j]) + E[4 * K + 9 + j];
         if (j < 2) A.err[u * WINDQ_N_ERR + 4 + j] = (float)e;
         else if (A.ref_energy != nullptr) A.ref_energy[u] = (float)e;
+    }
+    if (!planned || __syncthreads_or(open ? 1 : 0) == 0) return;           // (the same for the whole workgroup)
+    // listed: the open candidates are scored on all columns
+    int step = -1;
+    if (tid < 4 * K) {
+        double best, bound;
+        fit_least(E + (tid / K) * K, K, &best, &bound);
+        if (E[tid] < 0.0 && !(-E[tid] * (1.0 - BOUND_SLACK) > best)) step = PLAN_STEPS - 1;
+    }
+    FitPlan* __restrict__ plan = fit_plan(base, K);
+    uint64_t* __restrict__ lists = reinterpret_cast<uint64_t*>(lds);         // (the phases' sums are done with)
+    fit_plan_list(plan, lists, step, K, tid, true);
+    __syncthreads();
+    if (tid < 4) {
+        double best, bound;
+        fit_listed(base, K)->at[tid] = fit_least(E + tid * K, K, &best, &bound);
+        fit_listed(base, K)->best[tid] = best;
+    }
+    if (tid == 0) {
+        plan->done = 0u;
+        const uint64_t* widths = lists + 2 * PLAN_STEPS * 4;
+        plan->sweeps = (uint32_t)(widths[0] | widths[1] | widths[2] | widths[3]);         // the bit-widths that have some
+        const uint32_t pos = atomicAdd(A.redo_count, 1u);
+        A.redo_list[pos] = (uint32_t)u;
     }
 }
 

@@ -24,6 +24,13 @@ __host__ __device__ inline int32_t fit_score_noise_slot(int32_t K) { return 4 * 
 // number (-1: every column takes the exact route) and sum s_c^4 / sum s_c^2 over the short route.
 constexpr int FS_HMAX = WINDQ_MAX_CHUNK / 8;   // most columns a chunk may send down the exact 8-bit route on their own
 inline __host__ __device__ int32_t colsel_words(int32_t chunk_w) { return chunk_w + FS_HMAX + 4; }   // 4-byte words per chunk
+// Where a chunk's units are scored heavy columns first (windq_plan.hpp) its record is of another kind: the activation scales with the
+// columns in the order of their weight; in the list's place a byte per column, its place in that order; and for the number of listed
+// columns -1 - (heavy columns).
+inline __host__ __device__ int32_t heavy_columns(int32_t listed) { return listed < -1 ? -1 - listed : 0; }
+constexpr int FS_PLAN_MAX_CHUNK = 256;          // places are bytes
+constexpr int FS_PLAN_MIN_K = 16;               // the unit's plan (FitPlan, windq_fit.hpp) lies in the K noise slots of its first tile
+static_assert(FS_PLAN_MAX_CHUNK <= FS_HMAX * 4, "the places lie where the list does");
 
 struct FitScoreLayout {
     size_t partial;      // [n_tiles][ncand] fp64
