@@ -169,6 +169,7 @@ struct FitScoreArgs {
     int32_t n;                                   // matrices in the launch
     int32_t K;
     int32_t shares;                              // sweeps the clip grid is dealt to, ceil(K / FS_KB) (see share_ratio)
+    int32_t lean;                                // nothing to prepare and nothing to score again (see lean_launch)
     float skip8_p;                               // clip ratio at which the tiles take the clipping error
     float skip8_q;                               // the grid's last ratio, squared
     float skip8_last;                            // most that the clipping error there can be of that at skip8_p, and a thousandth
@@ -227,10 +228,11 @@ __device__ __forceinline__ int32_t share_ratio(int32_t K, int32_t shares, int32_
 // sweeps by quarters: shorter ones, which the launch ends better with (1200 tiles in one piece and 512 in quarters, chunk 64, 20
 // ratios: a wavefront per sweep 119 us, so 115, with 128 in quarters 110 and 100; 512 in quarters alone 42.0 and 41.2).  Up to 256
 // tiles in quarters beside others: again a workgroup per sweep (3 beside 1278, chunk 32, 40 ratios, fp32: 70 us, two per tile 75).
+__host__ __device__ __forceinline__ bool in_small_quarters(int64_t n_tiles, int32_t chunk_w, int32_t shares) { return n_tiles <= (chunk_w < 64 && shares > 2 ? 64 : 256); }
 static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
     const int32_t waves = (A.shares + FS_WAVES - 1) / FS_WAVES;          // workgroups for a wavefront per sweep
     const bool few = A.shares <= 3;
-    const auto small = [&](const FitScoreMat& M) { return M.g.n_tiles <= (chunk_w < 64 && A.shares > 2 ? 64 : 256); };
+    const auto small = [&](const FitScoreMat& M) { return in_small_quarters(M.g.n_tiles, chunk_w, A.shares); };
     int64_t in_quarters = 0;                 // tiles
     for (int32_t i = 0; i < A.n; ++i) in_quarters += small(A.m[i]) ? A.m[i].g.n_tiles : 0;
     const bool mixed = 2 * (tiles - in_quarters) >= in_quarters;
@@ -250,6 +252,24 @@ static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
             M.parts = tiles <= 640 || waves < 2 ? waves : 2;
         }
     }
+}
+
+// Matrices this small take every column on the exact 8-bit route, whatever the launch (the matrix alone decides about bits): their sweeps wait
+// more than they issue.  In a launch of nothing but such matrices, and little of that, no 8-bit candidate is left out either: then no
+// unit can be listed, nothing has to be known of the columns beforehand, and the call goes without the launch that scores listed
+// units again and, where there are no counters of the features to clear, without the preparing one.  What the sweeps take longer (six instructions more a
+// weight, ratio and candidate that would have been left out) is less than a launch while a workgroup per sweep leaves the chip half
+// empty: features and fit of 512 x 512 fp32, chunk 64, 20 ratios 35.1 -> 32.1 us, of 256 x 256, 40 ratios 28.9 -> 25.3, of 1024 x 1024 at chunk 128 33.0 -> 30.5;
+// fit under a mask of 512 x 1024 28.4 -> 22.2.  (A call of one unit keeps the bound and the second pass: the tests of both use such calls.)
+constexpr int64_t LEAN_MOST = 65536;         // tiles times sweeps times columns
+static bool lean_launch(const FitScoreArgs& A, int32_t chunk_w) {
+    int64_t work = 0, units = 0;
+    for (int32_t i = 0; i < A.n; ++i) {
+        if (!in_small_quarters(A.m[i].g.n_tiles, chunk_w, A.shares)) return false;
+        work += A.m[i].g.n_tiles * A.shares * chunk_w;
+        units += A.m[i].g.U;
+    }
+    return work <= LEAN_MOST && units > 1;
 }
 
 // The 8-bit residual is ~1/500 of the range, so it is taken relative to an ANCHOR c: a grid
@@ -664,7 +684,9 @@ __device__ __forceinline__ bool by_quarters(int n, int32_t chunk_w) { return n *
 template <int DT, bool MASKED, int MODE, int CUT>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
                                                const int rot, const int part, const uint32_t sweeps, char* __restrict__ smem) {
-    const bool split = MODE == FS_ONLY8 ? by_quarters(__builtin_popcount(sweeps), A.g.chunk_w) : CUT == FS_SPLIT && A.cut == FS_SPLIT;
+    // (the second pass of a matrix in quarters takes quarters too: a launch that leaves nothing out has the same bits)
+    const bool split = MODE == FS_ONLY8 ? (A.cut != FS_WHOLE && in_small_quarters(A.g.n_tiles, A.g.chunk_w, B.shares)) || by_quarters(__builtin_popcount(sweeps), A.g.chunk_w)
+                                        : CUT == FS_SPLIT && A.cut == FS_SPLIT;
     const bool serial = CUT == FS_SERIAL && A.cut == FS_SERIAL;
     const bool once = CUT == FS_WHOLE || part == 0;
     constexpr bool ONLY8 = MODE == FS_ONLY8;
@@ -712,7 +734,9 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     int32_t heavy = 0;         // (nh below -1)
     float s2 = 0.0f;           // sum s_c^2 over the chunk
     float s4_over_s2 = 0.0f;   // sum s_c^4 / sum s_c^2 over the short route: scales the tile's noise term
-    if (SCORE && !ONLY8) {
+    if (SCORE && !ONLY8 && B.lean != 0) {
+        if (once && threadIdx.x == 0 && tc.u == 0 && tc.t == 0) *A.redo_count = 0u;
+    } else if (SCORE && !ONLY8) {
         const float* __restrict__ rec = A.colsel + (size_t)(tc.col0 / G) * (size_t)colsel_words(G);
         for (int32_t c = threadIdx.x; c < G + FS_HMAX; c += FS_THREADS) sshort[c] = rec[c];
         // (wave-uniform: parked in scalar registers across the hot loops)
@@ -1672,13 +1696,15 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         // deviation; what the rows really do is measured per unit, see NOISE_MAX).  Below
         // tau = 1 every column takes the exact route.
         const float t = 7e-5f * (float)chunk_w * (float)M.g.R_u;
-        M.tau = t < 1.0f ? 0.0f : t;
+        M.tau = t < 1.0f || in_small_quarters(M.g.n_tiles, chunk_w, A.shares) ? 0.0f : t;
         A.unit_start[i] = units;
         tiles += M.g.n_tiles;
         units += M.g.U;
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) A.unit_start[i] = units;
     choose_cut(A, chunk_w, tiles);
+    A.lean = lean_launch(A, chunk_w) ? 1 : 0;
+    if (A.lean != 0) A.skip8_p = 0.0f;          // (then nothing is left out)
     int64_t plans = 0, heavies = 0;
     for (int32_t i = 0; i < n; ++i) {
         FitScoreMat& M = A.m[i];
@@ -1708,8 +1734,10 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     const int32_t dtype = items[0].W->dtype;
     const size_t lds = fit_score_lds_bytes(dtype, chunk_w, masked);
     const dim3 grid((unsigned)tiles);
-    hipLaunchKernelGGL(fit_score_prepare_kernel, dim3((unsigned)preps), dim3(FS_THREADS), 0, hs, A);
-    if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
+    if (A.lean == 0 || feat != nullptr) {
+        hipLaunchKernelGGL(fit_score_prepare_kernel, dim3((unsigned)preps), dim3(FS_THREADS), 0, hs, A);
+        if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
+    }
     st = timed_launches(hs, [&]() -> int {
         const int e = plans > 0 ? launch_heavy(A, chunk_w, hs) : WINDQ_OK;
         if (e != WINDQ_OK) return e;
@@ -1731,6 +1759,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         hipLaunchKernelGGL(fit_score_finalize_kernel, dim3((unsigned)units), dim3(FIN_THREADS), fit_finalize_lds_bytes(K), hs, F);
         if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
     }
+    if (A.lean != 0) return WINDQ_OK;
     // the units that step listed: their 8-bit candidates on the exact route
     const int64_t redo_most = plans > 0 ? FS_REDO_GRID_PLANNED : FS_REDO_GRID;
     const dim3 redo_grid((unsigned)(tiles < redo_most ? tiles : redo_most));
@@ -1751,6 +1780,7 @@ int windq::features_launch_tiles(const FeatBatch& F, hipStream_t hs) {
     A.n = F.n;
     A.K = 1;
     A.shares = 0;
+    A.lean = 0;
     A.skip8_p = A.skip8_q = A.skip8_last = 0.0f;
     for (int k = 0; k < WINDQ_MAX_CLIP; ++k) A.skip8_f.p[k] = 0.0f;
     A.inv_G = 0.0;
