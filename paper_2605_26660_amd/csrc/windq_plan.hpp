@@ -18,8 +18,8 @@ namespace windq {
 // wavefront and tile at chunk 128, 20 ratios, two thirds of them in its sweeps) and the call has two launches more, which a
 // large chunk's sweeps pay for and a small one's do not.  Features and fit, in one piece and heavy columns first: 7B-shaped block, chunk 128,
 // 20 ratios 1290 us and 935; 13B-shaped 1982 and 1388; 11008 x 4096, 40 ratios, chunk 128 565 and 439, chunk 256 603 and 412, chunk 64 569 and
-// 494; 8192 x 8192, 20 ratios 442 and 340; 4096 x 4096 (2048 tiles) 134 and 133.  Not so: 2048 x 4096 (1024 tiles) 82 and 90; chunk 64, 20 ratios 327
-// and 404; chunk 96 130 and 135; units of 8 tiles 135 and 146 (the probed tiles tell too little: one unit in twenty is scored again);
+// 494; 8192 x 8192, 20 ratios 442 and 340; 4096 x 4096 (2048 tiles) 133 and 126.  Not so: 2048 x 4096 (1024 tiles) 82 and 90; chunk 64, 20 ratios 327
+// and 404; chunk 96 130 and 135; units of 8 tiles 135 and 146 (the probed tiles tell too little: one unit in twenty scored again);
 // fp32, whose tiles leave three workgroups a CU, 203 and 223; under a mask, which takes the largest products out and the columns' difference with them, 451 and 620.
 constexpr int64_t PLAN_MIN_TILES = 2048;
 constexpr int32_t PLAN_MIN_WORK = 2560;
@@ -30,10 +30,12 @@ constexpr int64_t PLAN_MAX_UNITS = 1 << 18;       // of a matrix: eight of them 
 // COST_TILE for its second load and the second set of parameters and sums.  A chunk is scored heavy columns first where that is less than in one piece.
 // (COST_LIGHT 3.8 or 5.5: a 7B-shaped block within 1 %; 2.6: 8 % slower, its light columns leave twice as many candidates.)
 constexpr float COST_HEAVY = 4.85f, COST_LIGHT = 4.8f, COST_TILE = 8000.0f;
-// Tiles that are asked for the light columns' part of the least errors too: one in four, in tall units one in eight, and not the first two,
-// whose noise slots are in use (a probed tile has it there: three sums, then the heavy columns' errors that they belong to).
+// Tiles that are asked for the light columns' part of the least errors too: about eight of a unit, and not the first two, whose noise
+// slots are in use (a probed tile has it there: three sums, then the heavy columns' errors that they belong to).  (Units of 16 tiles with four
+// probed: one in fifty scored again, 1024 x 8192 at chunk 64, 40 ratios 143 us; with seven, one in two hundred, 128; in one piece 134.)
 constexpr int PROBE_FIRST = 2;
-__host__ __device__ __forceinline__ int probe_every(int64_t tiles_per_unit) { return tiles_per_unit >= 64 ? 8 : 4; }
+__device__ __forceinline__ int probe_every(int64_t tiles_per_unit) { return tiles_per_unit >= 64 ? 8 : (tiles_per_unit >= 32 ? 4 : 2); }
+__device__ __forceinline__ bool probe_tile(int64_t t, int64_t tiles_per_unit) { return t >= PROBE_FIRST && (int)(t - PROBE_FIRST) % probe_every(tiles_per_unit) == 0; }
 constexpr int PREP_ROWS = 32;                     // sampled for the columns' weight
 
 static bool by_plan(const Geometry& g, int32_t dtype, bool masked, int32_t K) {
@@ -549,7 +551,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_heavy_kernel(const FitScore
     const float skip8_above = s2_rg2 * ((A.g.tiles_per_unit <= SKIP8_FEW_TILES ? SKIP8_MARGIN_FEW : SKIP8_MARGIN) / (12.0f * 65025.0f)) * B.skip8_q +
                               tile_clip * B.skip8_last;
     const bool anchored = __builtin_amdgcn_ballot_w64(!(mn <= 0.0f && mx >= 0.0f)) == 0;
-    const bool probe = (int)tc.t % probe_every(A.g.tiles_per_unit) == PROBE_FIRST;
+    const bool probe = probe_tile(tc.t, A.g.tiles_per_unit);
     double* __restrict__ etab = reinterpret_cast<double*>(gstat);         // (the ranges have been read)
     static_assert(FS_WAVES * TILE_ROWS * sizeof(float2) >= 4 * WINDQ_MAX_CLIP * sizeof(double), "a tile's sums in the place of the ranges");
     float* __restrict__ red = red_all + wave * 16 * HEAVY_NROW;
@@ -664,11 +666,11 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_heavy_kernel(const FitScore
 // ---- the plan
 // The light columns' part of an error is taken to be the heavy columns' times the ratio that the probed tiles show for the least errors
 // (at 8 bits, where residuals do not depend on the column: the ratio of the sums of s_c^2): PLAN_HIGH of that for the least error,
-// with PLAN_MARGIN on the whole; PLAN_LOW of that, dealt to the columns by their weight, for what is left out.  With these one unit in a hundred
-// of a 7B-shaped block is scored again; margins twice as wide save half of those and cost 4 % of the call.  (A ratio taken from the columns'
+// with PLAN_MARGIN on the whole; PLAN_LOW of that, dealt to the columns by their weight, for what is left out.  With these one unit in
+// three hundred of a 7B-shaped block is scored again; half the margins list three times as many, in the same time.  (A ratio taken from the columns'
 // weights alone is off by up to four times where a column of heavy-tailed weights is a light one: one unit in ten again.)
 constexpr int PLAN_THREADS = 1024;
-constexpr double PLAN_LOW = 0.8, PLAN_HIGH = 1.07, PLAN_MARGIN = 1.005;
+constexpr double PLAN_LOW = 0.8, PLAN_HIGH = 1.12, PLAN_MARGIN = 1.01;
 
 inline size_t fit_plan_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES + 1) * 4 * (size_t)K * sizeof(double) + PLAN_LIST_WORDS * sizeof(uint64_t); }
 
