@@ -762,6 +762,8 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
         float mn = INFINITY, mx = -INFINITY;
         double S1 = 0.0;
         int32_t nk = 0;
+        uint32_t pair_lo = 8u * FEAT_FINE_COARSE0, pair_hi = 8u * FEAT_FINE_COARSE0 + FEAT_FINE_PAIRS - 1;
+        asm volatile("" : "+v"(pair_lo), "+v"(pair_hi));        // kept in registers
         for (int32_t c = qc0; c < qc1; c += 8) {
             float w[8];
             read8<DT>(wr, c, w);
@@ -784,15 +786,15 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             if (FINE && once) {
                 // key = bits 16..30 of the pattern; its pair (key >> 1) is dword pair - 8 * FEAT_FINE_COARSE0
                 // of the histogram, clamped: everything below the resolved range lands in the first
-                // dword, everything above in the last.  Bit 16 picks the half.
+                // dword, everything above in the last.  Bit 16 picks the half.  (The clamp comes before the difference, which then is
+                // part of the address: five instructions a weight.)
                 if (valid) {
-                    char* __restrict__ lh = reinterpret_cast<char*>(lhist);
 #pragma unroll
                     for (int j = 0; j < 8; ++j) {
                         const uint32_t bits = __float_as_uint(w[j]);
-                        int32_t off = (int32_t)((bits >> 15) & 0xFFFCu) - 32 * FEAT_FINE_COARSE0;
-                        off = min(max(off, 0), 4 * (FEAT_FINE_PAIRS - 1));
-                        atomicAdd(reinterpret_cast<uint32_t*>(lh + off), max(bits & 0x10000u, 1u));
+                        uint32_t pair;
+                        asm("v_med3_u32 %0, %1, %2, %3" : "=v"(pair) : "v"((bits >> 17) & 0x3FFFu), "v"(pair_lo), "v"(pair_hi));
+                        atomicAdd(lhist + (int32_t)(pair - 8u * FEAT_FINE_COARSE0), max(bits & 0x10000u, 1u));
                     }
                 }
             } else if (FEAT && once) {
@@ -1046,14 +1048,13 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
             for (int j = 0; j < 8; ++j) {
                 const float sc = s8[j];
                 const float y = fma_clamp01(w[j], hginv, half);
-                const float qp = fmaf(y, two, M) - M;                    // q + 1
-                const float rt = fmaf(qp, ngam, w[j] + gam) * sc;        // s_c (w - q gamma)
-                acc3[0] = fmaf(rt, rt, acc3[0]);
-                const float aw = __uint_as_float(__float_as_uint(w[j]) & 0x7fffffffu);
-                const float rb = (aw + nalpha) * sc;                     // s_c (|w| - alpha)
-                acc3[1] = fmaf(rb, rb, acc3[1]);
                 const float w1 = w[j] * sc;
                 acc3[2] = fmaf(w1, w1, acc3[2]);
+                const float qp = fmaf(y, two, M) - M;                    // q + 1
+                const float rt = fmaf(fmaf(qp, ngam, gam), sc, w1);      // s_c (w - q gamma)
+                acc3[0] = fmaf(rt, rt, acc3[0]);
+                const float rb = (fabsf(w[j]) + nalpha) * sc;            // s_c (|w| - alpha)
+                acc3[1] = fmaf(rb, rb, acc3[1]);
             }
             if (bounds) {
 #pragma unroll

@@ -575,24 +575,29 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_heavy_kernel(const FitScore
             const float p = B.grid.p[k];
             const float flo = p * mn, fhi = p * mx, frg = fhi - flo;
             const float rinv = frg >= FLT_MIN ? __builtin_amdgcn_rcpf(frg) : 0.0f;
-            float d8 = 0.0f;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                // (the correctly rounded quotient, as in fit_score_tile)
-                float d = (float)((double)frg * (b == 0 ? 1.0 / 255.0 : (b == 1 ? 1.0 / 15.0 : (b == 2 ? 1.0 / 7.0 : 1.0 / 3.0))));
-                d = d >= FLT_MIN ? d : 0.0f;
-                if (b == 0) d8 = d;
-                P[i].nd[b] = pin_vgpr(-d);
-                acc[i][b] = 0.0f;
-            }
-            float q0 = 0.0f;
-            if (flo <= 0.0f && fhi >= 0.0f) q0 = __builtin_amdgcn_fmed3f(__builtin_rintf(-flo * rinv * 255.0f), 0.0f, 255.0f);
-            const float c = fmaf(q0, d8, flo);
+            // step: the correctly rounded quotient, as in fit_score_tile
+            const auto step = [&](double rq) -> float {
+                const float d = (float)((double)frg * rq);
+                return d >= FLT_MIN ? d : 0.0f;
+            };
+            P[i].nd[1] = pin_vgpr(-step(1.0 / 15.0));
+            P[i].nd[2] = pin_vgpr(-step(1.0 / 7.0));
+            P[i].nd[3] = pin_vgpr(-step(1.0 / 3.0));
             P[i].rinv = rinv;
-            P[i].h = pin_vgpr((anchored ? -flo : c - flo) * rinv);
-            P[i].nc = pin_vgpr(-c);
-            P[i].Mq = pin_vgpr(RNE_POS + q0);
+            P[i].h = pin_vgpr(-flo * rinv);
             P[i].nlo = pin_vgpr(-flo);
+            if (i >= s8) {             // the 8-bit candidate's anchor
+                const float d8 = step(1.0 / 255.0);
+                float q0 = 0.0f;
+                if (flo <= 0.0f && fhi >= 0.0f) q0 = __builtin_amdgcn_fmed3f(__builtin_rintf(-flo * rinv * 255.0f), 0.0f, 255.0f);
+                const float c = fmaf(q0, d8, flo);
+                P[i].nd[0] = pin_vgpr(-d8);
+                P[i].nc = pin_vgpr(-c);
+                P[i].Mq = pin_vgpr(RNE_POS + q0);
+                if (!anchored) P[i].h = pin_vgpr((c - flo) * rinv);
+            }
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[i][b] = 0.0f;
         }
         __builtin_amdgcn_s_setprio(0);
         const auto sweep = [&](auto anchored_t, auto s8_t) {
