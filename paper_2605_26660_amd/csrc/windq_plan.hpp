@@ -55,6 +55,44 @@ __device__ __forceinline__ float* chunk_shares(const FitScoreMat& A, int32_t K, 
 }
 static_assert(PLAN_MIN_ROWS > PROBE_FIRST * TILE_ROWS, "a second tile, and one that is probed");
 
+// Whether a matrix's scales are steep enough: (sum s)^2 <= STEEP G sum s^2 in at least three quarters of sixteen chunks spread over it (all, where it has
+// fewer).  Chunks in one piece and chunks heavy columns first do not mix well in a launch, and a matrix of which only a few chunks gain
+// is slower by the other kernels' time.  Two 4096 x 4096 and one 11008 x 4096, chunk 128, 20 ratios, us in one piece / by the chunks' costs alone / with
+// this rule: log-normal scales of sigma 0.3 485 / 544 / 495, 0.7 486 / 468 / 469, 1.0 488 / 416 / 417; sigma 0.3 with 2 % of them x5
+// 487 / 559 / 497, 0.1 % x30 489 / 537 / 497, 5 % x10 491 / 410 / 414; chunk 64, 40 ratios, sigma 0.7 929 / 854 / 853 (933 with STEEP 0.69).
+// What is left above one piece is the two further launches, which find nothing to do.
+constexpr int STEEP_SAMPLE = 16;
+constexpr float STEEP = 0.75f;
+__device__ __forceinline__ bool steep_matrix(const FitScoreMat& A) {
+    __shared__ int32_t steep[FS_WAVES];
+    constexpr int PER = STEEP_SAMPLE / FS_WAVES;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int32_t G = A.g.chunk_w, n = A.g.n_chunks < STEEP_SAMPLE ? (int32_t)A.g.n_chunks : STEEP_SAMPLE;
+    float s1[PER], s2[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int32_t at = i * FS_WAVES + wave;
+        const float* __restrict__ sc = A.s + ((int64_t)at * A.g.n_chunks / n) * G;
+        s1[i] = s2[i] = 0.0f;
+#pragma unroll
+        for (int32_t c = 0; c < FS_PLAN_MAX_CHUNK; c += 64) {
+            const float v = at < n && c < G ? sc[c + lane] : 0.0f;
+            s1[i] += v;
+            s2[i] = fmaf(v, v, s2[i]);
+        }
+    }
+    int32_t count = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const float t1 = wave_sum_f32(s1[i]), t2 = wave_sum_f32(s2[i]);
+        count += t1 * t1 < STEEP * (float)G * t2 ? 1 : 0;
+    }
+    if (lane == 0) steep[wave] = count;
+    __syncthreads();
+    return 4 * (steep[0] + steep[1] + steep[2] + steep[3]) >= 3 * n;
+}
+static_assert(FS_WAVES == 4, "steep_matrix adds four counts");
+
 // The record of chunk j, by a workgroup, a column a thread; false (and nothing written) where scoring in one piece is expected to cost
 // less.  A column's weight is s_c^2 times the root mean square of its weights, from a few rows: a column of large weights
 // has larger residuals, but not by as much (clipping, and the range it gives to all columns, see to that).
@@ -63,6 +101,7 @@ __device__ __forceinline__ bool prepare_planned(const FitScoreArgs& B, const Fit
     __shared__ float sorted[FS_PLAN_MAX_CHUNK], run[FS_PLAN_MAX_CHUNK / 8], upto[FS_PLAN_MAX_CHUNK / 8], ss_part[FS_WAVES];
     __shared__ int32_t heavy_sh;
     static_assert(FS_THREADS >= FS_PLAN_MAX_CHUNK, "a column a thread");
+    if (!steep_matrix(A)) return false;                                                     // (the same for every chunk)
     const int32_t G = A.g.chunk_w, c = threadIdx.x, runs = G >> 3;
     const bool in = c < G;
     const float sv = in ? A.s[j * G + c] : 0.0f;
