@@ -48,7 +48,7 @@
 //                8-bit candidates of the listed units again, exact route only, and finalizes
 //                them.  With nothing listed it ends at once.
 //   * large bf16 matrices are scored heavy columns first: a few columns carry most of every error, and what they add up to
-//     shows most candidates to lose (windq_plan.hpp; a 7B-shaped block 1250 -> 930 us);
+//     shows most candidates to lose (windq_plan.hpp; a 7B-shaped block 1250 -> 890 us);
 //   * lanes accumulate in fp32 over the chunk's columns only (<= 512 terms); rows are
 //     combined in fp64 in a fixed order (LDS transpose), tiles by the finalize kernel;
 //   * what depends on s alone (the column list, s_c of the other columns) is prepared once per

@@ -18,7 +18,7 @@ namespace windq {
 // wavefront and tile at chunk 128, 20 ratios, two thirds of them in its sweeps) and the call has two launches more, which a
 // large chunk's sweeps pay for and a small one's do not.  Features and fit, in one piece and heavy columns first: 7B-shaped block, chunk 128,
 // 20 ratios 1290 us and 935; 13B-shaped 1982 and 1388; 11008 x 4096, 40 ratios, chunk 128 565 and 439, chunk 256 603 and 412, chunk 64 569 and
-// 494; 8192 x 8192, 20 ratios 442 and 340; 4096 x 4096 (2048 tiles) 133 and 126.  Not so: 2048 x 4096 (1024 tiles) 82 and 90; chunk 64, 20 ratios 327
+// 494; 8192 x 8192, 20 ratios 442 and 340; 4096 x 4096 (2048 tiles) 133 and 126 (before the bands of tiles were turned: the 7B-shaped block 890 since).  Not so: 2048 x 4096 (1024 tiles) 82 and 90; chunk 64, 20 ratios 327
 // and 404; chunk 96 130 and 135; units of 8 tiles 135 and 146 (the probed tiles tell too little: one unit in twenty scored again);
 // fp32, whose tiles leave three workgroups a CU, 203 and 223; under a mask, which takes the largest products out and the columns' difference with them, 451 and 620.
 constexpr int64_t PLAN_MIN_TILES = 2048;
