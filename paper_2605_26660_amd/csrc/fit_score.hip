@@ -1433,7 +1433,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
         part = (int)((uint32_t)local / (uint32_t)A.g.n_tiles);
         local -= (int64_t)part * A.g.n_tiles;
     }
-    const TileCoord tc = tile_coord<true>(A.g, local);
+    const TileCoord tc = tile_coord(A.g, local, DT == WINDQ_BF16 && !MASKED && A.planned != 0);
     fit_score_tile<DT, MASKED, MODE, CUT>(B, A, tc, blockIdx.x & (FS_WAVES - 1), part, 0u, smem);
 }
 

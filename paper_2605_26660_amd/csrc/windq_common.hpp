@@ -78,17 +78,17 @@ struct TileCoord {
 // of rows: a band of 64 rows is contiguous in HBM row by row, and neighbouring
 // workgroups (which land on different XCDs round-robin) share DRAM pages, not L2 lines.
 // (A matrix has fewer than 2^31 tiles, checked on the host: the two divisions are 32-bit ones.)
-// With an even number of chunks the tiles of one chunk would come round on the same XCDs band after band; TURN starts every
-// band a chunk further on, for kernels whose tiles take longer in some chunks than in others.  (fit+score heavy columns first: 7B-shaped
+// With an even number of chunks the tiles of one chunk would come round on the same XCDs band after band; turn starts every
+// band a chunk further on, for matrices whose tiles take longer in some chunks than in others.  (fit+score heavy columns first: 7B-shaped
 // block 941 us and 894 so; three matrices of 32 chunks, of which one in ten is scored so, 595 and 546.  With an odd number of chunks
-// the bands shift by themselves.)
-template <bool TURN = false>
-__device__ __forceinline__ TileCoord tile_coord(const Geometry& g, int64_t tile) {
+// the bands shift by themselves.  Matrices whose tiles take equally long are better off without: 2048 x 4096 in units of 128 rows 83.5 us, turned
+// 85.3; 925 x 3072 fp32 under a mask 45.9 and 46.9.)
+__device__ __forceinline__ TileCoord tile_coord(const Geometry& g, int64_t tile, bool turn = false) {
     TileCoord tc;
     const uint32_t nc = (uint32_t)g.n_chunks, tpu = (uint32_t)g.tiles_per_unit;
     const uint32_t band32 = (uint32_t)tile / nc;     // band = rb * tiles_per_unit + t
     uint32_t j32 = (uint32_t)tile - band32 * nc;
-    if (TURN && nc >= 8 && nc % 2 == 0) {
+    if (turn && nc >= 8 && nc % 2 == 0) {
         j32 += band32 % 8;
         j32 -= j32 >= nc ? nc : 0;
     }

@@ -535,7 +535,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_heavy_kernel(const FitScore
     extern __shared__ char smem[];
     const int mi = batch_index(B.heavy_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
-    const TileCoord tc = tile_coord<true>(A.g, (int64_t)blockIdx.x - B.heavy_start[mi]);
+    const TileCoord tc = tile_coord(A.g, (int64_t)blockIdx.x - B.heavy_start[mi], true);
     const int32_t K = B.K, G = A.g.chunk_w;
     const int64_t j = tc.col0 / G;
     const int32_t heavy = chunk_heavy(A, j);
