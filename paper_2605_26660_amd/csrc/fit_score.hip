@@ -1448,22 +1448,30 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_kernel(const FitScore
 // to do in most.  The tiles' sums are stored and loaded past the L2s (device-scope atomic accesses), and a workgroup
 // waits for its stores before it adds its run to the unit's count of finished tiles: with a device-wide release and
 // acquire per tile instead, which write back and drop whole L2s, a matrix with all of its 108 units listed took 912 us.
-template <int DT, bool MASKED>
+// PLANS: a launch with a matrix that heavy columns first is open to.  The others have a kernel without that second way to score a tile (74 vector
+// registers for 96 and scratch memory), which reads the counters that there are, one after the other.
+template <int DT, bool MASKED, bool PLANS>
 __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const FitScoreArgs B) {
     extern __shared__ char smem[];
     __shared__ uint32_t done;
-    constexpr bool CAN_PLAN = DT == WINDQ_BF16 && !MASKED;
-    // (the tables are only indexed in unrolled loops: otherwise they would live in scratch memory)
-    int64_t listed[WINDQ_MAX_BATCH];
+    const auto listed_tiles = [&](int i) -> int64_t {
+        int64_t cnt = (int64_t)*B.m[i].redo_count;
+        cnt = cnt < B.m[i].g.U ? cnt : B.m[i].g.U;
+        return cnt * B.m[i].g.tiles_per_unit;
+    };
+    // (a table is only indexed in unrolled loops: otherwise it would live in scratch memory)
+    int64_t listed[WINDQ_MAX_BATCH], total = 0;
+    if constexpr (PLANS) {
 #pragma unroll
-    for (int i = 0; i < WINDQ_MAX_BATCH; ++i) {
-        const int at = i < B.n ? i : 0;
-        const int64_t cnt = (int64_t)*B.m[at].redo_count;
-        listed[i] = i < B.n ? (cnt < B.m[at].g.U ? cnt : B.m[at].g.U) * B.m[at].g.tiles_per_unit : 0;
+        for (int i = 0; i < WINDQ_MAX_BATCH; ++i) {
+            const int64_t here = listed_tiles(i < B.n ? i : 0);        // (all asked for at once)
+            listed[i] = i < B.n ? here : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < WINDQ_MAX_BATCH; ++i) total += listed[i];
+    } else {
+        for (int i = 0; i < B.n; ++i) total += listed_tiles(i);
     }
-    int64_t total = 0;
-#pragma unroll
-    for (int i = 0; i < WINDQ_MAX_BATCH; ++i) total += listed[i];
     const int64_t per = (total + gridDim.x - 1) / gridDim.x;
     const int64_t w_end = ((int64_t)blockIdx.x + 1) * per < total ? ((int64_t)blockIdx.x + 1) * per : total;
     uint32_t run = 0;                // tiles of the current unit that this workgroup has scored
@@ -1471,14 +1479,23 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
     bool planned = false;
     for (int64_t w = (int64_t)blockIdx.x * per; w < w_end; ++w) {
         int mi = 0;
-        int64_t first = 0, next = 0;
+        int64_t first = 0;
+        if constexpr (PLANS) {
+            int64_t next = 0;
 #pragma unroll
-        for (int i = 0; i < WINDQ_MAX_BATCH; ++i) {
-            if (listed[i] > 0 && w >= next) {
-                mi = i;
-                first = next;
+            for (int i = 0; i < WINDQ_MAX_BATCH; ++i) {
+                if (listed[i] > 0 && w >= next) {
+                    mi = i;
+                    first = next;
+                }
+                next += listed[i];
             }
-            next += listed[i];
+        } else {
+            for (; mi + 1 < B.n; ++mi) {
+                const int64_t nt = listed_tiles(mi);
+                if (w < first + nt) break;
+                first += nt;
+            }
         }
         const FitScoreMat& A = B.m[mi];
         const int64_t local = w - first;
@@ -1490,9 +1507,9 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
         if (run == 0) {       // (waits for memory: once a run)
             sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
-            planned = CAN_PLAN && A.planned != 0 && chunk_heavy(A, (int64_t)((uint32_t)u % (uint32_t)A.g.n_chunks)) != 0;
+            planned = PLANS && A.planned != 0 && chunk_heavy(A, (int64_t)((uint32_t)u % (uint32_t)A.g.n_chunks)) != 0;
         }
-        if (CAN_PLAN && planned) fit_listed_tile(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
+        if (PLANS && planned) fit_listed_tile(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
         else fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);
         ++run;
         if (w + 1 < w_end && t + 1 < tpu) {
@@ -1508,7 +1525,7 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         double* part = reinterpret_cast<double*>(smem);       // [FIN_PHASES][WINDQ_MAX_CLIP], then [WINDQ_MAX_CLIP]
         static_assert((FIN_PHASES + 1) * WINDQ_MAX_CLIP * sizeof(double) <= FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
         static_assert((LISTED_SUMS + FS_THREADS) * sizeof(double) <= 64 * (32 * 2 + 16) + FS_WAVES * 16 * fs_nrow(true) * 4 + FS_WAVES * TILE_ROWS * 16, "fits a tile's LDS");
-        if (CAN_PLAN && planned) {
+        if (PLANS && planned) {
             fit_listed_end(A, u, unit, K, part);
             continue;
         }
@@ -1770,9 +1787,9 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         hipLaunchKernelGGL(kernel, redo_grid, dim3(FS_THREADS), lds, hs, A);
         return hipPeekAtLastError() == hipSuccess ? WINDQ_OK : WINDQ_EHIP;
     };
-    if (dtype == WINDQ_BF16) st = masked ? launch_redo(&fit_score_redo_kernel<WINDQ_BF16, true>) : launch_redo(&fit_score_redo_kernel<WINDQ_BF16, false>);
-    else st = masked ? launch_redo(&fit_score_redo_kernel<WINDQ_F32, true>) : launch_redo(&fit_score_redo_kernel<WINDQ_F32, false>);
-    return st;
+    if (plans > 0) return launch_redo(&fit_score_redo_kernel<WINDQ_BF16, false, true>);
+    if (dtype == WINDQ_BF16) return masked ? launch_redo(&fit_score_redo_kernel<WINDQ_BF16, true, false>) : launch_redo(&fit_score_redo_kernel<WINDQ_BF16, false, false>);
+    return masked ? launch_redo(&fit_score_redo_kernel<WINDQ_F32, true, false>) : launch_redo(&fit_score_redo_kernel<WINDQ_F32, false, false>);
 }
 
 // The first pass of the unit features by itself (windq_unit_features): the same tile kernel, scoring nothing.
