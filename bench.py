@@ -36,30 +36,24 @@ def fit_score_flops_per_weight(k: int) -> float:
 
 def executed_work(wq, torch, mats, wss, G, unit_rows, K, fused):
     """(flops per weight, share of the (weight, candidate) pairs) that the last fit+score call with these workspaces scored: candidates that
-    are shown to lose are left out, on some columns or on all.  Read from what the call leaves in the workspaces (with the fused
-    call, behind the unit features' part): per 64-row tile 5 K + 12 doubles, the 8-bit candidates first, below zero where left out; and
-    for units that are scored heavy columns first the unit's plan, in the last K of its first tile's doubles, and the chunks' records behind the list of units."""
-    steps = [((G * t + (G if t == 15 else 0)) >> 4) for t in (1, 2, 3, 4, 5, 7, 11, 15)]
-    steps = torch.tensor([max(n & ~7, 8) for n in steps], dtype=torch.float64)
+    are shown to lose are left out, on some columns or on all.  Read from what the call leaves in the workspaces (workload.FitWorkspace): the tiles'
+    sums, the 8-bit candidates first, below zero where left out; and for units that are scored heavy columns first the plans and the chunks' records."""
+    from paper_2605_26660_amd import workload
+    steps = torch.tensor(workload.plan_columns(G), dtype=torch.float64)
     flops = pairs = total = 0.0
     for m, ws in zip(mats, wss):
         sp = m.spec
         dt = wq.WINDQ_BF16 if m.W.dtype == torch.bfloat16 else wq.WINDQ_F32
         at = wq.workspace_bytes(wq.CALL_UNIT_FEATURES, dt, sp.rows, sp.cols, G, unit_rows, 1) if fused else 0
-        tpu, nc = (m.R_u + 63) // 64, 5 * K + 12
-        size = m.U * tpu * nc * 8
-        sums = ws[at:at + size].view(torch.float64).view(m.U, tpu, nc)
-        out8 = (sums[:, :, :K] < 0).double().mean((1, 2)).cpu()
-        pos = at + (size + 255) // 256 * 256 + 256
-        pos += (4 * m.U + 255) // 256 * 256
-        words = G + 64 + 4
-        rec = ws[pos:pos + sp.cols // G * words * 4].view(torch.int32).view(sp.cols // G, words)[:, G + 64].cpu()
+        lay = workload.FitWorkspace(sp.rows, sp.cols, G, unit_rows, K, at)
+        out8 = (lay.sums(ws)[:, :, :K] < 0).double().mean((1, 2)).cpu()
+        rec = lay.listed_columns(ws)
         heavy = torch.where(rec < -1, -1 - rec, torch.zeros_like(rec)).double().repeat(m.U // rec.numel())
         f = 31.0 * K - 7.0 * K * out8
         q = 4.0 * K - K * out8
-        if K >= 16 and bool((heavy > 0).any()):
-            plan = ws[at:at + size].view(m.U, tpu, nc * 8)[:, 0, (4 * K + 12) * 8 + 8:(4 * K + 12) * 8 + 24].cpu().double()
-            on = (plan[:, :8] + plan[:, 8:]) * (steps[None, :] - heavy[:, None]).clamp(min=0)
+        if bool((heavy > 0).any()):
+            low, high = lay.plan_counts(ws)
+            on = (low + high).double() * (steps[None, :] - heavy[:, None]).clamp(min=0)
             f = torch.where(heavy > 0, (f * heavy + 10.0 * on.sum(1)) / G, f)
             q = torch.where(heavy > 0, (q * heavy + on.sum(1)) / G, q)
         w = float(sp.rows) * sp.cols

@@ -140,8 +140,9 @@ __device__ __forceinline__ FitPlan* fit_plan(double* unit_partial, int32_t K) {
 }
 // A sum that is a bound: below zero, whatever it is.
 __device__ __forceinline__ double plan_bound(double v) { return -fmax(fabs(v), 1e-300); }
-// Columns (a multiple of 8) of a step: sixteenths of the chunk, the last one all of it.
-__device__ __forceinline__ int32_t plan_columns(int32_t chunk_w, int step) {
+// Columns (a multiple of 8) of a step: sixteenths of the chunk, the last one all of it.  (workload.py reads plans and records out of workspaces
+// for the benchmark and the tests; tests/test_fit_workspace_layout.py holds it to these structures.)
+__host__ __device__ __forceinline__ int32_t plan_columns(int32_t chunk_w, int step) {
     const int32_t n = (chunk_w * (int32_t)((0xFB754321u >> (4 * step)) & 15u) + (step == PLAN_STEPS - 1 ? chunk_w : 0)) >> 4;      // 1 2 3 4 5 7 11 16
     return n < 8 ? 8 : n & ~7;
 }

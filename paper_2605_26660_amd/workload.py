@@ -47,6 +47,46 @@ CONFIGS = {
 }
 
 
+def plan_columns(chunk_w: int) -> list:
+    """Columns of each step of a unit's plan (fit+score heavy columns first): sixteenths of the chunk, the last one all of it."""
+    return [max((chunk_w * t >> 4) & ~7, 8) for t in (1, 2, 3, 4, 5, 7, 11, 16)]
+
+
+class FitWorkspace:
+    """What a fit+score call leaves in its workspace, as byte offsets; the library's own layout (windq_ws.hpp, windq_fit.hpp), which
+    tests/test_fit_workspace_layout.py holds this to.  at: where the fit's part begins (behind the unit features', in the fused calls)."""
+
+    def __init__(self, rows: int, cols: int, chunk_w: int, unit_rows: int, K: int, at: int = 0):
+        up = lambda x: (x + 255) // 256 * 256
+        self.U, R_u = wq.n_units(rows, cols, chunk_w, unit_rows)
+        self.tiles_per_unit, self.n_chunks, self.G, self.K = (R_u + 63) // 64, cols // chunk_w, chunk_w, K
+        self.n_sums = 5 * K + 12                       # doubles per tile: 4 K candidates, 12 more, K noise slots
+        self.noise_slot = 4 * K + 12
+        self.partial = at
+        self.redo_count = up(at + self.U * self.tiles_per_unit * self.n_sums * 8)
+        self.redo_list = self.redo_count + 256
+        self.colsel = up(self.redo_list + 4 * self.U)
+        self.record_words = chunk_w + 64 + 4           # per chunk: scales, list or places, count, two sums, one unused
+        self.count_word = chunk_w + 64                 # listed columns; below -1: -1 - (heavy columns)
+        self.plan = self.noise_slot * 8                # in a unit's first tile: the plan of a unit scored heavy columns first ...
+        self.plan_low, self.plan_high, self.plan_steps = self.plan + 8, self.plan + 16, 8     # ... its candidates per step
+
+    def sums(self, ws):
+        """[units][tiles][n_sums] fp64"""
+        return ws[self.partial:self.partial + self.U * self.tiles_per_unit * self.n_sums * 8].view(torch.float64).view(self.U, self.tiles_per_unit, self.n_sums)
+
+    def listed_columns(self, ws):
+        """[n_chunks] the records' counts of columns"""
+        n = self.n_chunks * self.record_words * 4
+        return ws[self.colsel:self.colsel + n].view(torch.int32).view(self.n_chunks, self.record_words)[:, self.count_word].cpu()
+
+    def plan_counts(self, ws):
+        """[units][plan_steps] candidates of each step, the low bit-widths' and the 8-bit ones (of units scored heavy columns first)"""
+        tile = self.n_sums * 8
+        first = ws[self.partial:self.partial + self.U * self.tiles_per_unit * tile].view(self.U, self.tiles_per_unit * tile)
+        return tuple(first[:, p:p + self.plan_steps].cpu().long() for p in (self.plan_low, self.plan_high))
+
+
 class Mat:
     """One weight matrix of the stack with every output buffer of the hot path."""
     __slots__ = ("spec", "W", "U", "R_u", "feat", "err", "clip_idx", "ref", "action", "action_d", "off", "off_d",

@@ -3,7 +3,7 @@ say which route was taken, and the results are those of the same columns in matr
 import pytest
 import torch
 
-from paper_2605_26660_amd import synth
+from paper_2605_26660_amd import synth, workload
 from test_gpu_heavy_first import both, same
 
 pytestmark = pytest.mark.gpu
@@ -24,7 +24,6 @@ def test_route_by_steep_chunks(windq, R, n_chunks, G, K, steep, taken):
     cg = synth.clip_grid(K)
     ws = torch.empty(windq.workspace_bytes(windq.CALL_FIT_SCORE, windq.WINDQ_BF16, R, G * n_chunks, G, 0, K), dtype=torch.uint8, device=DEV)
     windq.windq_fit_score_all_bits(W, s, G, 0, cg, ws=ws)
-    # behind the tiles' sums and the list of units: a record per chunk, its count of columns below -1 where heavy columns went first
-    at = (n_chunks * ((R + 63) // 64) * (5 * K + 12) * 8 + 255) // 256 * 256 + 256 + (4 * n_chunks + 255) // 256 * 256
-    records = ws[at:at + n_chunks * (G + 68) * 4].view(torch.int32).view(n_chunks, G + 68)[:, G + 64].cpu()
+    # a record per chunk, its count of columns below -1 where heavy columns went first
+    records = workload.FitWorkspace(R, G * n_chunks, G, 0, K).listed_columns(ws)
     assert int((records < -1).sum()) == (steep if taken else 0)
