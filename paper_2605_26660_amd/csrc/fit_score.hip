@@ -261,11 +261,16 @@ static void choose_cut(FitScoreArgs& A, int32_t chunk_w, int64_t tiles) {
 // weight, ratio and candidate that would have been left out) is less than a launch while a workgroup per sweep leaves the chip half
 // empty: features and fit of 512 x 512 fp32, chunk 64, 20 ratios 35.1 -> 32.1 us, of 256 x 256, 40 ratios 28.9 -> 25.3, of 1024 x 1024 at chunk 128 33.0 -> 30.5;
 // fit under a mask of 512 x 1024 28.4 -> 22.2.  (A call of one unit keeps the bound and the second pass: the tests of both use such calls.)
+// Matrices in quarters with more work than that can never be in such a launch and keep the short route (two instructions less a weight, ratio
+// and 8-bit candidate: 6080 x 256 at chunk 128, 40 ratios 57.4 us, 59.0 on the exact route).
 constexpr int64_t LEAN_MOST = 65536;         // tiles times sweeps times columns
+__host__ __device__ __forceinline__ bool may_be_lean(int64_t n_tiles, int32_t chunk_w, int32_t shares) {
+    return in_small_quarters(n_tiles, chunk_w, shares) && n_tiles * shares * chunk_w <= LEAN_MOST;
+}
 static bool lean_launch(const FitScoreArgs& A, int32_t chunk_w) {
     int64_t work = 0, units = 0;
     for (int32_t i = 0; i < A.n; ++i) {
-        if (!in_small_quarters(A.m[i].g.n_tiles, chunk_w, A.shares)) return false;
+        if (!may_be_lean(A.m[i].g.n_tiles, chunk_w, A.shares)) return false;
         work += A.m[i].g.n_tiles * A.shares * chunk_w;
         units += A.m[i].g.U;
     }
@@ -684,8 +689,8 @@ __device__ __forceinline__ bool by_quarters(int n, int32_t chunk_w) { return n *
 template <int DT, bool MASKED, int MODE, int CUT>
 __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitScoreMat& A, const TileCoord& tc,
                                                const int rot, const int part, const uint32_t sweeps, char* __restrict__ smem) {
-    // (the second pass of a matrix in quarters takes quarters too: a launch that leaves nothing out has the same bits)
-    const bool split = MODE == FS_ONLY8 ? (A.cut != FS_WHOLE && in_small_quarters(A.g.n_tiles, A.g.chunk_w, B.shares)) || by_quarters(__builtin_popcount(sweeps), A.g.chunk_w)
+    // (the second pass of a matrix that may be in a lean launch takes quarters too: such a launch has the same bits)
+    const bool split = MODE == FS_ONLY8 ? may_be_lean(A.g.n_tiles, A.g.chunk_w, B.shares) || by_quarters(__builtin_popcount(sweeps), A.g.chunk_w)
                                         : CUT == FS_SPLIT && A.cut == FS_SPLIT;
     const bool serial = CUT == FS_SERIAL && A.cut == FS_SERIAL;
     const bool once = CUT == FS_WHOLE || part == 0;
@@ -734,7 +739,7 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
     int32_t heavy = 0;         // (nh below -1)
     float s2 = 0.0f;           // sum s_c^2 over the chunk
     float s4_over_s2 = 0.0f;   // sum s_c^4 / sum s_c^2 over the short route: scales the tile's noise term
-    if (SCORE && !ONLY8 && B.lean != 0) {
+    if (SCORE && !ONLY8 && CUT != FS_WHOLE && B.lean != 0) {       // (a lean launch has its columns in quarters)
         if (once && threadIdx.x == 0 && tc.u == 0 && tc.t == 0) *A.redo_count = 0u;
     } else if (SCORE && !ONLY8) {
         const float* __restrict__ rec = A.colsel + (size_t)(tc.col0 / G) * (size_t)colsel_words(G);
@@ -1714,7 +1719,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         // deviation; what the rows really do is measured per unit, see NOISE_MAX).  Below
         // tau = 1 every column takes the exact route.
         const float t = 7e-5f * (float)chunk_w * (float)M.g.R_u;
-        M.tau = t < 1.0f || in_small_quarters(M.g.n_tiles, chunk_w, A.shares) ? 0.0f : t;
+        M.tau = t < 1.0f || may_be_lean(M.g.n_tiles, chunk_w, A.shares) ? 0.0f : t;
         A.unit_start[i] = units;
         tiles += M.g.n_tiles;
         units += M.g.U;

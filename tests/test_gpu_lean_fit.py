@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from oracle import windq_oracle as O
-from paper_2605_26660_amd import synth
+from paper_2605_26660_amd import synth, workload
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -38,5 +38,26 @@ def test_alone_and_beside_a_large_matrix(windq, R, C, G, unit_rows, K, dtype):
     g_err, g_clip = alone[0].double().cpu().numpy(), alone[1].cpu().numpy()
     bar = 1e-5 if min(R, unit_rows or R) >= 64 else 1e-4            # few rows: one weight may carry the error (include/windq.h)
     assert (np.abs(g_err - o_err) <= bar * o_err + 1e-30).all()
+    for u, b in zip(*np.nonzero(g_clip != o_clip)):
+        assert table[u, b, g_clip[u, b]] <= table[u, b].min() * (1 + 1e-9)
+
+
+@pytest.mark.parametrize("R,C,G,K,lean", [(4096, 256, 64, 20, True), (4096, 512, 128, 20, False), (2100, 256, 256, 33, True), (2100, 512, 256, 33, False)])
+def test_where_the_exact_route_ends(windq, R, C, G, K, lean):
+    """Matrices in quarters whose work is that of a lean launch at most take every column on the exact 8-bit route, larger ones the short route for
+    most of them; alone and in a batch the bits are the same on both sides, and within the bars."""
+    W = synth.weights_llm(R, C, seed=R + K, device=DEV)
+    s = torch.exp(torch.randn(C, generator=torch.Generator().manual_seed(R)))
+    big, sb = synth.weights_llm(R, 4 * C, seed=2, device=DEV), torch.exp(torch.randn(4 * C, generator=torch.Generator().manual_seed(3))).to(DEV)
+    cg = synth.clip_grid(K)
+    alone = windq.windq_fit_score_all_bits(W, s.to(DEV), G, 0, cg)
+    ws = [torch.empty(windq.workspace_bytes(windq.CALL_FIT_SCORE, windq.WINDQ_BF16, R, c, G, 0, K), dtype=torch.uint8, device=DEV) for c in (C, 4 * C)]
+    both = windq.windq_fit_score_all_bits_batch([W, big], [s.to(DEV), sb], G, 0, cg, wss=ws)
+    assert all(torch.equal(a, b) for a, b in zip(alone, both[0]))
+    listed = workload.FitWorkspace(R, C, G, 0, K).listed_columns(ws[0])
+    assert ((listed == -1) if lean else (listed >= 0)).all()
+    o_err, o_clip, o_ref, table = O.fit_score_all_bits(W.float().cpu().numpy(), s.numpy(), G, 0, cg.numpy())
+    g_err, g_clip = alone[0].double().cpu().numpy(), alone[1].cpu().numpy()
+    assert (np.abs(g_err - o_err) <= 1e-5 * o_err).all()
     for u, b in zip(*np.nonzero(g_clip != o_clip)):
         assert table[u, b, g_clip[u, b]] <= table[u, b].min() * (1 + 1e-9)
