@@ -1375,7 +1375,7 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
     const int mi = batch_index(B.prep_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
     const int64_t local = (int64_t)blockIdx.x - B.prep_start[mi];
-    const int64_t sel_groups = prepare_groups(A);
+    const int64_t sel_groups = B.lean != 0 ? 0 : prepare_groups(A);          // (a lean launch reads no selection, only the counters have to be cleared)
     if (local >= sel_groups) {
         const int64_t i = ((local - sel_groups) * FS_THREADS + (int64_t)threadIdx.x) * 4;
         if (i < A.fclear_words) *reinterpret_cast<uint4*>(A.fclear + i) = make_uint4(0u, 0u, 0u, 0u);
@@ -1737,7 +1737,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         A.prep_start[i] = preps;
         plans += M.planned != 0 ? M.g.U : 0;
         heavies += M.planned != 0 ? M.g.n_tiles : 0;
-        preps += prepare_groups(M) + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
+        preps += (A.lean != 0 ? 0 : prepare_groups(M)) + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) {
         A.plan_start[i] = plans;

@@ -61,3 +61,15 @@ def test_where_the_exact_route_ends(windq, R, C, G, K, lean):
     assert (np.abs(g_err - o_err) <= 1e-5 * o_err).all()
     for u, b in zip(*np.nonzero(g_clip != o_clip)):
         assert table[u, b, g_clip[u, b]] <= table[u, b].min() * (1 + 1e-9)
+
+
+def test_lean_call_with_features_makes_no_records(windq):
+    """Nothing of a lean launch reads the chunks' records: the kernel that clears the features' counters leaves them as they were."""
+    R, C, G, K = 512, 512, 64, 20
+    W = synth.weights_llm(R, C, seed=1, device=DEV)
+    s = torch.ones(C, device=DEV)
+    at = windq.workspace_bytes(windq.CALL_UNIT_FEATURES, windq.WINDQ_BF16, R, C, G, 0, 1)
+    ws = torch.full((windq.workspace_bytes(windq.CALL_FEATURES_FIT_SCORE, windq.WINDQ_BF16, R, C, G, 0, K),), 7, dtype=torch.uint8, device=DEV)
+    got = windq.windq_features_fit_score(W, s, G, 0, synth.clip_grid(K), ws=ws)
+    assert (workload.FitWorkspace(R, C, G, 0, K, at).listed_columns(ws) == 0x07070707).all()
+    assert all(torch.equal(a, b) for a, b in zip(got, windq.windq_features_fit_score(W, s, G, 0, synth.clip_grid(K))))
