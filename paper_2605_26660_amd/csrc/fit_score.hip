@@ -1511,8 +1511,8 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const int32_t K = B.K, ncand = fit_score_ncand(K);
         double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
         if (run == 0) {       // (waits for memory: once a run)
-            sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
             planned = PLANS && A.planned != 0 && chunk_heavy(A, (int64_t)((uint32_t)u % (uint32_t)A.g.n_chunks)) != 0;
+            if (!planned) sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
         }
         if (PLANS && planned) fit_listed_tile(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
         else fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);

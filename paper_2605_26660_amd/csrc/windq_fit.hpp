@@ -118,7 +118,7 @@ __device__ __forceinline__ uint32_t fit_sweep_of(int32_t K, int32_t shares, int3
 // columns it goes on to.  In the noise slots of the unit's first tile, behind the two words above (such units have no noise).
 constexpr int PLAN_STEPS = 8;
 struct FitPlan {
-    uint32_t done, sweeps;
+    uint32_t done, sweeps;                          // (sweeps: of the units that have no plan)
     uint8_t low[PLAN_STEPS], high[PLAN_STEPS];      // candidates that go on to plan_columns(chunk_w, step) columns: 4, 3 and 2 bits; 8 bits
     uint64_t scored[4];                             // those that take all (8, 4, 3, 2 bits): a bit per ratio
     uint8_t list[4 * WINDQ_MAX_CLIP];               // (bit-width << 6) | ratio: the low ones, most columns first, then the 8-bit ones (4 K at most)
@@ -147,9 +147,9 @@ __host__ __device__ __forceinline__ int32_t plan_columns(int32_t chunk_w, int st
     return n < 8 ? 8 : n & ~7;
 }
 // The list, by a workgroup of at least 4 K threads (called by all of them), thread i with the step of candidate i (b * K + k), or a number below zero.
-// lds: PLAN_LIST_WORDS.  more: the scored candidates are added to those that are.
+// lds: PLAN_LIST_WORDS.
 constexpr int PLAN_LIST_WORDS = 2 * PLAN_STEPS * 4 + 2 * PLAN_STEPS;
-__device__ __forceinline__ void fit_plan_list(FitPlan* __restrict__ plan, uint64_t* __restrict__ lds, int step, int32_t K, int tid, bool more) {
+__device__ __forceinline__ void fit_plan_list(FitPlan* __restrict__ plan, uint64_t* __restrict__ lds, int step, int32_t K, int tid) {
     const int wave = tid >> 6, lane = tid & 63;
     const bool on = tid < 4 * K && step >= 0, high = tid < K;
     uint64_t* __restrict__ total = lds + 2 * PLAN_STEPS * 4;
@@ -192,8 +192,7 @@ __device__ __forceinline__ void fit_plan_list(FitPlan* __restrict__ plan, uint64
             all |= shift >= 64 || shift <= -64 ? 0ull : (shift >= 0 ? set >> shift : set << -shift);
         }
         all &= K < 64 ? (1ull << K) - 1ull : ~0ull;
-        plan->scored[tid] = more ? plan->scored[tid] | all : all;
-        if (more) total[tid] = all != 0u ? 1u << tid : 0u;
+        plan->scored[tid] = all;
     }
 }
 
@@ -274,8 +273,7 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     }
     FitPlan* __restrict__ plan = fit_plan(base, K);
     uint64_t* __restrict__ lists = reinterpret_cast<uint64_t*>(lds);         // (the phases' sums are done with)
-    fit_plan_list(plan, lists, step, K, tid, true);
-    __syncthreads();
+    fit_plan_list(plan, lists, step, K, tid);
     if (tid < 4) {
         double best, bound;
         fit_listed(base, K)->at[tid] = fit_least(E + tid * K, K, &best, &bound);
@@ -283,8 +281,6 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     }
     if (tid == 0) {
         plan->done = 0u;
-        const uint64_t* widths = lists + 2 * PLAN_STEPS * 4;
-        plan->sweeps = (uint32_t)(widths[0] | widths[1] | widths[2] | widths[3]);         // the bit-widths that have some
         const uint32_t pos = atomicAdd(A.redo_count, 1u);
         A.redo_list[pos] = (uint32_t)u;
     }

@@ -779,7 +779,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void fit_plan_kernel(const FitScoreAr
         }
         if (e < 0.0) step = -1;         // an 8-bit candidate that a tile has left out stays a bound
     }
-    fit_plan_list(fit_plan(unit, K), lists, step, K, tid, false);
+    fit_plan_list(fit_plan(unit, K), lists, step, K, tid);
 }
 
 // A tile of a listed unit: its list (the open candidates, on all columns).  With few tiles the launch waits for memory most of the time: what the
