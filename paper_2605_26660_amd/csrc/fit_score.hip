@@ -1371,11 +1371,13 @@ __device__ __forceinline__ void fit_score_tile(const FitScoreArgs& B, const FitS
 //   exact route, one at a time; all others go down the short route, and their
 //   S4/S2 = sum s_c^4 / sum s_c^2 scales a tile's noise term.  It depends on s alone, so the
 //   chunk's tiles read it instead of deriving it again.
+// PLANS: a launch with a matrix that heavy columns first is open to.
+template <bool PLANS>
 __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const FitScoreArgs B) {
     const int mi = batch_index(B.prep_start, B.n, blockIdx.x);
     const FitScoreMat& A = B.m[mi];
     const int64_t local = (int64_t)blockIdx.x - B.prep_start[mi];
-    const int64_t sel_groups = B.lean != 0 ? 0 : prepare_groups(A);          // (a lean launch reads no selection, only the counters have to be cleared)
+    const int64_t sel_groups = PLANS ? prepare_groups(A) : (A.g.n_chunks + FS_PREP_CHUNKS - 1) / FS_PREP_CHUNKS;
     if (local >= sel_groups) {
         const int64_t i = ((local - sel_groups) * FS_THREADS + (int64_t)threadIdx.x) * 4;
         if (i < A.fclear_words) *reinterpret_cast<uint4*>(A.fclear + i) = make_uint4(0u, 0u, 0u, 0u);
@@ -1383,10 +1385,13 @@ __global__ __launch_bounds__(FS_THREADS) void fit_score_prepare_kernel(const Fit
         return;
     }
     if (local == 0 && threadIdx.x == 0) *A.redo_count = 0u;      // the list the finalize kernel fills
-    if (A.planned != 0) {           // a workgroup per chunk; where it makes no such record its first wavefront makes the other
-        if (prepare_planned(B, A, local) || threadIdx.x >= 64) return;
+    int64_t j = local * FS_PREP_CHUNKS + (int64_t)(threadIdx.x >> 6);
+    if constexpr (PLANS) {
+        if (A.planned != 0) {           // a workgroup per chunk; where it makes no such record its first wavefront makes the other
+            if (prepare_planned(B, A, local) || threadIdx.x >= 64) return;
+            j = local;
+        }
     }
-    const int64_t j = A.planned != 0 ? local : local * FS_PREP_CHUNKS + (int64_t)(threadIdx.x >> 6);
     if (j >= A.g.n_chunks) return;
     const int l = threadIdx.x & 63;
     const int32_t G = A.g.chunk_w;
@@ -1510,9 +1515,9 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
         const TileCoord tc = tile_coord_of_unit(A.g, u, t);
         const int32_t K = B.K, ncand = fit_score_ncand(K);
         double* unit = A.partial + (size_t)u * (size_t)tpu * (size_t)ncand;
-        if (run == 0) {       // (waits for memory: once a run)
+        if (run == 0) {       // (waits for memory: once a run, both words at once; a unit with a plan has no sweeps)
+            sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
             planned = PLANS && A.planned != 0 && chunk_heavy(A, (int64_t)((uint32_t)u % (uint32_t)A.g.n_chunks)) != 0;
-            if (!planned) sweeps = __builtin_amdgcn_readfirstlane(*fit_redo_sweeps(unit, K));
         }
         if (PLANS && planned) fit_listed_tile(B, A, tc, (int)(w & (FS_WAVES - 1)), smem);
         else fit_score_tile<DT, MASKED, FS_ONLY8, FS_WHOLE>(B, A, tc, (int)(w & (FS_WAVES - 1)), 0, sweeps, smem);
@@ -1737,7 +1742,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         A.prep_start[i] = preps;
         plans += M.planned != 0 ? M.g.U : 0;
         heavies += M.planned != 0 ? M.g.n_tiles : 0;
-        preps += (A.lean != 0 ? 0 : prepare_groups(M)) + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
+        preps += prepare_groups(M) + (M.fclear_words + FS_PREP_CLEAR - 1) / FS_PREP_CLEAR;
     }
     for (int32_t i = n; i <= WINDQ_MAX_BATCH; ++i) {
         A.plan_start[i] = plans;
@@ -1757,9 +1762,13 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     const int32_t dtype = items[0].W->dtype;
     const size_t lds = fit_score_lds_bytes(dtype, chunk_w, masked);
     const dim3 grid((unsigned)tiles);
-    if (A.lean == 0 || feat != nullptr) {
-        hipLaunchKernelGGL(fit_score_prepare_kernel, dim3((unsigned)preps), dim3(FS_THREADS), 0, hs, A);
+    if (A.lean == 0) {
+        if (plans > 0) hipLaunchKernelGGL(fit_score_prepare_kernel<true>, dim3((unsigned)preps), dim3(FS_THREADS), 0, hs, A);
+        else hipLaunchKernelGGL(fit_score_prepare_kernel<false>, dim3((unsigned)preps), dim3(FS_THREADS), 0, hs, A);
         if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
+    } else if (feat != nullptr) {          // (no column selection is read: only the counters have to be cleared)
+        st = features_launch_init(*feat, hs);
+        if (st != WINDQ_OK) return st;
     }
     st = timed_launches(hs, [&]() -> int {
         const int e = plans > 0 ? launch_heavy(A, chunk_w, hs) : WINDQ_OK;
