@@ -20,7 +20,7 @@ def test_route_by_steep_chunks(windq, R, n_chunks, G, K, steep, taken):
     s[torch.randperm(n_chunks, generator=g)[:steep]] = torch.exp(1.5 * torch.randn(G, generator=g))
     s = s.reshape(-1).to(DEV)
     whole, parts, _ = both(windq, W, s, G, K)
-    same(whole, parts)
+    same(whole, parts, W, s, G, synth.clip_grid(K))
     cg = synth.clip_grid(K)
     ws = torch.empty(windq.workspace_bytes(windq.CALL_FIT_SCORE, windq.WINDQ_BF16, R, G * n_chunks, G, 0, K), dtype=torch.uint8, device=DEV)
     windq.windq_fit_score_all_bits(W, s, G, 0, cg, ws=ws)
