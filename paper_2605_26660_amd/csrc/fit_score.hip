@@ -1561,9 +1561,10 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_score_redo_kernel(const Fit
 
 // The unit's last step by itself (with the unit features riding along, theirs does it: unit_features.hip).
 constexpr int FIN_THREADS = 1024;
+template <bool PLANS>
 __global__ __launch_bounds__(FIN_THREADS) void fit_score_finalize_kernel(const FitFinalBatch B) {
     extern __shared__ double fin_lds[];
-    fit_finalize_unit<FIN_THREADS>(B, blockIdx.x, fin_lds);
+    fit_finalize_unit<FIN_THREADS, PLANS>(B, blockIdx.x, fin_lds);
 }
 
 }  // namespace windq
@@ -1780,6 +1781,7 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
     F.n = n;
     F.K = K;
     F.shares = A.shares;
+    F.plans = plans > 0 ? 1 : 0;
     for (int32_t i = 0; i <= WINDQ_MAX_BATCH; ++i) F.unit_start[i] = A.unit_start[i];
     for (int32_t i = 0; i < WINDQ_MAX_BATCH; ++i)
         F.m[i] = {A.m[i].partial, A.m[i].redo_count, A.m[i].redo_list, A.m[i].err, A.m[i].clip_idx, A.m[i].ref_energy, A.m[i].g.tiles_per_unit,
@@ -1788,7 +1790,8 @@ static int fit_score_launch(const FitItem* items, int32_t n, int32_t chunk_w, in
         st = features_launch_rest(*feat, &F, hs);
         if (st != WINDQ_OK) return st;
     } else {
-        hipLaunchKernelGGL(fit_score_finalize_kernel, dim3((unsigned)units), dim3(FIN_THREADS), fit_finalize_lds_bytes(K), hs, F);
+        if (plans > 0) hipLaunchKernelGGL(fit_score_finalize_kernel<true>, dim3((unsigned)units), dim3(FIN_THREADS), fit_finalize_lds_bytes(K), hs, F);
+        else hipLaunchKernelGGL(fit_score_finalize_kernel<false>, dim3((unsigned)units), dim3(FIN_THREADS), fit_finalize_lds_bytes(K), hs, F);
         if (hipPeekAtLastError() != hipSuccess) return WINDQ_EHIP;
     }
     if (A.lean != 0) return WINDQ_OK;

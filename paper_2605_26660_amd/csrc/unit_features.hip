@@ -592,20 +592,20 @@ __device__ __forceinline__ void feat_small_f32_unit(const FeatBatch& B, const in
     feat_tail(A, u, in, (double)cnt, true, red, smax_sh);
 }
 
-// The features' last step, one workgroup per unit, and where fit+score is part of the call (FIT) its last step too, by
+// The features' last step, one workgroup per unit, and where fit+score is part of the call (FIT: 1, or 2 with units that are scored by a plan) its last step too, by
 // as many workgroups behind them: each is a chain of memory latencies that leaves the chip idle, and neither needs
 // the other.  PER = 0: the finish step after the passes; else units kept in registers.  The finish step uses the LDS that the launch
 // asks for, as the fit's step does: a workgroup does one or the other, and the two side by side (36 KB for bf16, 45 KB at 64
 // ratios) would pass the 64 KB that a workgroup gets without ensure_lds.  The units in registers have 8 KB of their own (a
 // pointer to it spills registers at PER = 12: 27.4 us for 26.0).
-template <int DT, int NT, int PER, bool FIT>
+template <int DT, int NT, int PER, int FIT>
 __global__ __launch_bounds__(NT) void feat_last_kernel(const FeatBatch B, const FitFinalBatch F) {
     extern __shared__ __align__(16) char last_lds[];
-    if (!FIT || (int64_t)blockIdx.x < B.units_total) {
+    if (FIT == 0 || (int64_t)blockIdx.x < B.units_total) {
         if constexpr (PER == 0) feat_finish_unit<DT>(B, blockIdx.x, last_lds);
         else feat_small_f32_unit<NT, PER>(B, blockIdx.x);
     } else {
-        fit_finalize_unit<NT>(F, (int64_t)blockIdx.x - B.units_total, reinterpret_cast<double*>(last_lds));
+        fit_finalize_unit<NT, FIT == 2>(F, (int64_t)blockIdx.x - B.units_total, reinterpret_cast<double*>(last_lds));
     }
 }
 
@@ -615,12 +615,14 @@ static void launch_last(const FeatBatch& B, const FitFinalBatch* fit, hipStream_
     constexpr size_t feat_lds = PER == 0 ? feat_finish_lds_bytes<DT>() : 0;
     static_assert(feat_lds <= 64 * 1024 && fit_finalize_lds_bytes(WINDQ_MAX_CLIP) <= 64 * 1024, "what a workgroup gets by default");
     const bool both = fit != nullptr && fits_launch(2 * B.units_total, NT);         // (2^21 units of fp32 in registers: a launch for each half)
-    if (!both) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, false>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
+    if (!both) hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, 0>), dim3(units), dim3(NT), feat_lds, hs, B, FitFinalBatch{});
     if (fit != nullptr) {
         const size_t fit_lds = fit_finalize_lds_bytes(fit->K);
         FeatBatch F = B;
         F.units_total = both ? B.units_total : 0;
-        hipLaunchKernelGGL((feat_last_kernel<DT, NT, PER, true>), dim3(both ? 2 * units : units), dim3(NT), feat_lds > fit_lds ? feat_lds : fit_lds, hs, F, *fit);
+        const auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(both ? 2 * units : units), dim3(NT), feat_lds > fit_lds ? feat_lds : fit_lds, hs, F, *fit); };
+        if (DT == WINDQ_BF16 && fit->plans != 0) launch(&feat_last_kernel<DT, NT, PER, DT == WINDQ_BF16 ? 2 : 1>);          // (plans are for bf16 alone)
+        else launch(&feat_last_kernel<DT, NT, PER, 1>);
     }
 }
 

@@ -23,6 +23,7 @@ struct FitFinalBatch {
     int32_t n;
     int32_t K;
     int32_t shares;        // sweeps the clip grid is dealt to: ratio k belongs to sweep (k - K) mod shares
+    int32_t plans;         // nonzero: some matrix may have units that are scored by a plan
     int64_t unit_start[WINDQ_MAX_BATCH + 1];
     FitFinalMat m[WINDQ_MAX_BATCH];
 };
@@ -202,8 +203,8 @@ constexpr size_t fit_finalize_lds_bytes(int32_t K) { return (size_t)(FIN_PHASES 
 // Per unit: add the tiles' partial errors in a fixed order, pick the clip index with the
 // least error for each uniform bit-width (ties to the largest index), emit fp32.  A unit whose 8-bit
 // error may hold too much of the short route's rounding noise, or one of whose left-out candidates is not
-// proved to be worse, is put on the list.  Called by all NT threads of a workgroup.
-template <int NT>
+// proved to be worse, is put on the list.  Called by all NT threads of a workgroup.  PLANS: a launch that may have units scored by a plan.
+template <int NT, bool PLANS>
 __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_t block, double* __restrict__ lds) {
     const int mi = batch_index(B.unit_start, B.n, block);
     const FitFinalMat& A = B.m[mi];
@@ -216,9 +217,9 @@ __device__ __forceinline__ void fit_finalize_unit(const FitFinalBatch& B, int64_
     // (read ahead of the sums, which they wait for together; words of any kind where the unit is not planned)
     const int tid = threadIdx.x;
     static_assert(NT >= 4 * WINDQ_MAX_CLIP, "a candidate a thread");
-    const bool planned = A.colsel != nullptr &&
+    const bool planned = PLANS && A.colsel != nullptr &&
                          heavy_columns(__float_as_int(A.colsel[(size_t)((uint32_t)u % (uint32_t)A.n_chunks) * (size_t)colsel_words(A.chunk_w) + A.chunk_w + FS_HMAX])) != 0;
-    const uint64_t scored = A.colsel != nullptr ? fit_plan(base, K)->scored[tid < 4 * K ? tid / K : 0] : 0u;
+    const uint64_t scored = PLANS && A.colsel != nullptr ? fit_plan(base, K)->scored[tid < 4 * K ? tid / K : 0] : 0u;
     constexpr int WAVES = NT / 64, NP = FIN_PHASES / WAVES;
     static_assert(NP * WAVES == FIN_PHASES, "a wavefront's phases");
     for (int32_t cand = threadIdx.x & 63; cand < ncand; cand += 64) {
