@@ -13,14 +13,38 @@
 
 namespace windq {
 
-// Which matrices: bf16, no mask, 2048 tiles or more, units of 16 tiles or more, chunks of 64, 128, 192 or 256 columns, and clip
-// ratios times columns 2560 or more.  The tiles are read and set up a second time (the heavy columns' kernel: 2500 vector instructions a
-// wavefront and tile at chunk 128, 20 ratios, two thirds of them in its sweeps) and the call has two launches more, which a
-// large chunk's sweeps pay for and a small one's do not.  Features and fit, in one piece and heavy columns first: 7B-shaped block, chunk 128,
-// 20 ratios 1290 us and 935; 13B-shaped 1982 and 1388; 11008 x 4096, 40 ratios, chunk 128 565 and 439, chunk 256 603 and 412, chunk 64 569 and
-// 494; 8192 x 8192, 20 ratios 442 and 340; 4096 x 4096 (2048 tiles) 133 and 126 (before the bands of tiles were turned: the 7B-shaped block 890 since).  Not so: 2048 x 4096 (1024 tiles) 82 and 90; chunk 64, 20 ratios 327
-// and 404; chunk 96 130 and 135; units of 8 tiles 135 and 146 (the probed tiles tell too little: one unit in twenty scored again);
-// fp32, whose tiles leave three workgroups a CU, 203 and 223; under a mask, which takes the largest products out and the columns' difference with them, 451 and 620.
+// Which matrices: bf16, no mask, 2048 tiles or more, units of 1024 rows (16 tiles) or more, chunks of 64, 128, 192 or 256 columns, and clip
+// ratios times columns 2560 or more.  The tiles are read and set up a second time (the heavy columns' kernel: 2948 vector instructions a
+// wavefront and tile at chunk 128, 20 ratios, two thirds of them in its sweeps) and the call has two launches more, which
+// large matrices and large chunks' sweeps pay for.  Features and fit of one matrix a call, us in one piece, then what heavy columns first
+// changes for scales that are (a) log-normal of sigma 1 with one column in a hundred 30 times larger, (b) log-normal of sigma 1, (c) of 0.7, and
+// (d) flat (0.3: scored in one piece all the same, the two launches, 8.6 us and 0.35 for a thousand tiles, find nothing to do):
+//                                                 tiles   us   (a)   (b)   (c)   (d) %
+//   chunk 128, 20 ratios   2816 x 4096             1408  103    +4   +13   +23    +9     not so
+//                          3584 x 4096             1792  115    +4    +9   +21    +8     not so
+//                          4096 x 4096             2048  131    -6    +1   +13    +7
+//                          5120 x 5120             3200  187   -13    -8    +1    +5
+//                          8192 x 4096             4096  228   -16   -11    +1    +4
+//                          8192 x 8192             8192  437   -31   -20    -7    +3
+//   chunk 64, 40 ratios    1024 x 6144             1536  104    +3   +26   +50    +9     not so
+//                          1024 x 8192             2048  131    -6    +2    +6    +7
+//                          2048 x 8192             4096  227   -16   -11    +1    +4
+//   chunk 256, 20 ratios   4096 x 4096             1024  150    +7   +15   +25    +6     not so
+//                          8192 x 8192             4096  493   -30   -17    -8    +3
+//   chunk 128, 20, in one call: four 4096 x 4096   8192  418   -25   -17    -6    +3
+//                               7B-shaped block   24704 1222   -29   -22   -10    +1
+//   chunk 64, 40, in one call: two 1024 x 8192     4096  230   -16   -11    -1    +4
+// So the line of 2048 tiles is where a matrix by itself breaks even on (a); in a batch, whose matrices share the launches, it gains on all but
+// flat scales from there.  (The matrix alone decides, so that a batch has the bits of its single calls: a line for single calls would be one for batches.)
+//   Fewer rows: 512 rows (8 tiles, of which 3 are probed) 512 x 32768 132 +6 -1 +11 +7; 768 x 24576 147 -9 -3 +9 +6: the line could lie at 768.
+//   Less work: chunk 128 with 16 ratios 4096 x 4096 129 -9 -3 +36 +7 and 8192 x 8192 433 -32 -23 +4 +3; 18 ratios 130 -7 0 +9 +7 and 435 -32 -21 -6
+// +3; chunk 64 with 30 ratios 4096 x 4096 193 -6 +3 +21 +5 and 8192 x 8192 655 -25 -13 +9 +2, with 20 ratios 456 -2 +8 +5 +4.  There scales like (c) leave
+// a quarter of the chunks in one piece by their cost, and chunks of both kinds side by side are the slowest: to let 16 to 19 ratios
+// in (which take longer than 20 on steep scales) the rule on steep scales would have to be stricter for less work.
+//   Other chunks: steep_matrix reads 64 scales at a time.  Chunk 96 (with a bound there) at 40 ratios, 4096 x 6144 319 -26 -18 -2 +3, at 20 ratios
+// 181 -9 -2 +22 +5; chunk 160, 20 ratios, 4096 x 7680 215 -16 -8 +4 +4.  Not open yet.
+//   Seen on the first version of these kernels only (half as many probed tiles): fp32, whose tiles leave three workgroups a CU, 203 -> 223 us; under a mask, which
+// takes the largest products out and the columns' difference with them, 451 -> 620 us, 296 of them for units scored again.
 constexpr int64_t PLAN_MIN_TILES = 2048;
 constexpr int32_t PLAN_MIN_WORK = 2560;
 constexpr int64_t PLAN_MIN_ROWS = 1024;
@@ -30,9 +54,10 @@ constexpr int64_t PLAN_MAX_UNITS = 1 << 18;       // of a matrix: eight of them 
 // COST_TILE for its second load and the second set of parameters and sums.  A chunk is scored heavy columns first where that is less than in one piece.
 // (COST_LIGHT 3.8 or 5.5: a 7B-shaped block within 1 %; 2.6: 8 % slower, its light columns leave twice as many candidates.)
 constexpr float COST_HEAVY = 4.85f, COST_LIGHT = 4.8f, COST_TILE = 8000.0f;
-// Tiles that are asked for the light columns' part of the least errors too: about eight of a unit, and not the first two, whose noise
-// slots are in use (a probed tile has it there: three sums, then the heavy columns' errors that they belong to).  (Units of 16 tiles with four
-// probed: one in fifty scored again, 1024 x 8192 at chunk 64, 40 ratios 143 us; with seven, one in two hundred, 128; in one piece 134.)
+// Tiles that are asked for the light columns' part of the least errors too: every second one of a unit of fewer than 32 tiles, every fourth below 64, every
+// eighth from there, and not the first two, whose noise slots are in use (a probed tile has it there: three sums, then the heavy columns' errors
+// that they belong to): 7 of 16 tiles, 15 of 31, 8 of 32, 8 of 64, 22 of 172.  (Units of 16 tiles with four probed: one in fifty scored again,
+// 1024 x 8192 at chunk 64, 40 ratios 143 us; with seven, one in four hundred, 124; in one piece 131.)
 constexpr int PROBE_FIRST = 2;
 __device__ __forceinline__ int probe_every(int64_t tiles_per_unit) { return tiles_per_unit >= 64 ? 8 : (tiles_per_unit >= 32 ? 4 : 2); }
 __device__ __forceinline__ bool probe_tile(int64_t t, int64_t tiles_per_unit) { return t >= PROBE_FIRST && (int)(t - PROBE_FIRST) % probe_every(tiles_per_unit) == 0; }
@@ -60,7 +85,10 @@ static_assert(PLAN_MIN_ROWS > PROBE_FIRST * TILE_ROWS, "a second tile, and one t
 // is slower by the other kernels' time.  Two 4096 x 4096 and one 11008 x 4096, chunk 128, 20 ratios, us in one piece / by the chunks' costs alone / with
 // this rule: log-normal scales of sigma 0.3 485 / 544 / 495, 0.7 486 / 468 / 469, 1.0 488 / 416 / 417; sigma 0.3 with 2 % of them x5
 // 487 / 559 / 497, 0.1 % x30 489 / 537 / 497, 5 % x10 491 / 410 / 414; chunk 64, 40 ratios, sigma 0.7 929 / 854 / 853 (933 with STEEP 0.69).
-// What is left above one piece is the two further launches, which find nothing to do.
+// What is left above one piece is the two further launches, which find nothing to do.  A stricter rule for small matrices gives single calls
+// with scales of sigma 0.7 some of their loss back (STEEP 0.5 below 3072 tiles: 4096 x 4096 +14 -> +7 % over one piece) and takes more from batches (a
+// 7B-shaped block -10 -> -6 %, two 1024 x 8192 with scales of sigma 1 -11 -> 0).  The weights are not looked at here: flat scales over columns of
+// very different weights are scored in one piece.
 constexpr int STEEP_SAMPLE = 16;
 constexpr float STEEP = 0.75f;
 __device__ __forceinline__ bool steep_matrix(const FitScoreMat& A) {
@@ -711,7 +739,8 @@ __global__ __launch_bounds__(FS_THREADS, 5) void fit_heavy_kernel(const FitScore
 // The light columns' part of an error is taken to be the heavy columns' times the ratio that the probed tiles show for the least errors
 // (at 8 bits, where residuals do not depend on the column: the ratio of the sums of s_c^2): PLAN_HIGH of that for the least error,
 // with PLAN_MARGIN on the whole; PLAN_LOW of that, dealt to the columns by their weight, for what is left out.  With these one unit in
-// three hundred of a 7B-shaped block is scored again; half the margins list three times as many, in the same time.  (A ratio taken from the columns'
+// five hundred of a 7B-shaped block is scored again (40 draws of scales as (a) above: 4096 x 4096 one in 320, 11008 x 4096 none of 1280, 4096 x 11008 one in
+// 570; 1024 x 8192 at chunk 64 one in 390; 8192 x 8192 at chunk 256 one in 53); half the margins list three times as many, in the same time.  (A ratio taken from the columns'
 // weights alone is off by up to four times where a column of heavy-tailed weights is a light one: one unit in ten again.)
 constexpr int PLAN_THREADS = 1024;
 constexpr double PLAN_LOW = 0.8, PLAN_HIGH = 1.12, PLAN_MARGIN = 1.01;
