@@ -48,6 +48,8 @@ def executed_work(wq, torch, mats, wss, G, unit_rows, K, fused):
         lay = workload.FitWorkspace(sp.rows, sp.cols, G, unit_rows, K, at)
         out8 = (lay.sums(ws)[:, :, :K] < 0).double().mean((1, 2)).cpu()
         rec = lay.listed_columns(ws)
+        if lay.U * lay.tiles_per_unit <= 256:          # (a call of small matrices may make no records, and no plans)
+            rec = torch.zeros_like(rec)
         heavy = torch.where(rec < -1, -1 - rec, torch.zeros_like(rec)).double().repeat(m.U // rec.numel())
         f = 31.0 * K - 7.0 * K * out8
         q = 4.0 * K - K * out8

@@ -73,3 +73,16 @@ def test_lean_call_with_features_makes_no_records(windq):
     got = windq.windq_features_fit_score(W, s, G, 0, synth.clip_grid(K), ws=ws)
     assert (workload.FitWorkspace(R, C, G, 0, K, at).listed_columns(ws) == 0x07070707).all()
     assert all(torch.equal(a, b) for a, b in zip(got, windq.windq_features_fit_score(W, s, G, 0, synth.clip_grid(K))))
+
+
+@pytest.mark.parametrize("K", [20, 64])
+def test_counted_work_of_a_lean_call(windq, K):
+    """The benchmark counts the work of such a call as all of the definition's, whatever the workspace held before."""
+    import bench
+    R, C, G = 512, 512, 64
+    mat = workload.Mat()
+    mat.spec, mat.W, (mat.U, mat.R_u) = synth.MatrixSpec("linear", R, C, "h"), synth.weights_llm(R, C, seed=1, device=DEV), windq.n_units(R, C, G, 0)
+    ws = torch.full((windq.workspace_bytes(windq.CALL_FEATURES_FIT_SCORE, windq.WINDQ_BF16, R, C, G, 0, K),), 0xEE, dtype=torch.uint8, device=DEV)
+    windq.windq_features_fit_score(mat.W, torch.ones(C, device=DEV), G, 0, synth.clip_grid(K), ws=ws)
+    flops, share = bench.executed_work(windq, torch, [mat], [ws], G, 0, K, True)
+    assert share == 1.0 and abs(flops - bench.fit_score_flops_per_weight(K)) < 1e-9
