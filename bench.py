@@ -13,6 +13,7 @@ units against the CPU oracle, and the oracle's own speed on the host cores.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import re
@@ -113,6 +114,7 @@ class CallTimer:
 
 def timed_steps(torch, stack, steps, warmup, per_matrix, fused=True):
     """W untimed steps, then K timed ones; only the dominant call carries events (for the roofline)."""
+    gc.collect()          # (otherwise a full collection, 35 ms of the host's time, falls into the timed steps or not by how many objects the imports have left)
     for _ in range(warmup):
         stack.run_step(per_matrix=per_matrix, fused=fused)
     torch.cuda.synchronize()
